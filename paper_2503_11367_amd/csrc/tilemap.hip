@@ -3,15 +3,13 @@
 // mask block is all zeros is the one the attention kernels skip.  Row sums give
 // the per-block workloads W_b that Alg. 1 balances.
 //
-// Integer ALU work.  One wavefront per tile pair, four k-tiles per workgroup
-// sharing the q-tile's words in LDS.  A k-tile is a handful of "runs" (maximal
-// stretches of keys with the same sample/span/modality fields: a text run, a
-// modality span); for one query row and one run the number of visible keys has
-// a closed form -- the whole run if it is the row's own span, the keys up to
-// the row's position (and inside its look-back window, if it has one for that
-// modality) if the row looks back at that modality in its sample, else none --
-// so every lane takes a few rows and walks the runs.  Exact for
-// any layout; a tile whose keys all differ degenerates to one run per key.
+// A k-tile is a handful of "runs" (maximal stretches of keys with the same
+// sample/span/modality fields: a text run, a modality span), a q-tile likewise, and
+// the visible pairs of two runs have a closed form; on small maps, and for tiles of
+// many short runs, a lane takes a query row and counts it against each run of keys
+// (the whole run if it is the row's own span, the keys up to the row's position and
+// inside its look-back window if the row looks back at that modality in its sample,
+// else none).  Exact for any layout.
 //
 // The same device code serves the attention kernels' private maps: there the q rows
 // are a rank's local rows (positions looked up through its block list) and the
@@ -51,7 +49,7 @@ int launch_tile_map(const uint64_t* d_bits, int64_t S, const int32_t* d_blocks, 
                        d_blocks, block, d_blocks ? S / block : (int64_t)0, n_rows, jobs);
     MM_LAUNCH_CHECK();
     if (d_rowpairs) {
-        hipLaunchKernelGGL(row_pairs_kernel, dim3(jobs.j[0].gy), dim3(256), 0, st, d_cnt, jobs.j[0].nk,
+        hipLaunchKernelGGL(row_pairs_kernel, dim3((unsigned)jobs.j[0].nq), dim3(256), 0, st, d_cnt, jobs.j[0].nk,
                            d_rowpairs);
         MM_LAUNCH_CHECK();
     }

@@ -9,7 +9,9 @@ namespace mm {
 
 constexpr int kTmThreads = 256;
 constexpr int kTmWaves = kTmThreads / kWave;
-constexpr int kTmQChunk = 256;     // q rows staged in LDS at a time
+constexpr int kTmGroup = 32;       // most q-tiles and most k-tiles of a workgroup
+constexpr int kTmRuns = 15;        // runs of a tile that are kept in LDS
+constexpr int kTmAhead = 4;        // tiles whose words a wavefront requests together
 
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -17,20 +19,56 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 }
 
 // One launch serves up to two maps of the same rows (the second map's workgroups follow
-// the first's in the one-dimensional grid).
-// kpw: k-tiles per wavefront (each wavefront walks kpw consecutive k-tiles, so that on
-// large maps the q-tile's words are staged once for 4*kpw tile pairs)
+// the first's in the one-dimensional grid).  A workgroup takes gq q-tiles x gk k-tiles (powers
+// of two, at most kTmGroup each).
 struct TileMapJob {
-    int32_t tq, tk, nk, kpw;
+    int32_t tq, tk, nq, nk, gq, gk;
     uint32_t gx, gy;                     // workgroups this map needs
     uint8_t* cls;
     uint32_t* cnt;
 };
 struct TileMapJobs { TileMapJob j[2]; };
 
+// A run: consecutive tokens of a tile that carry the same fields (x: the attend word of query
+// rows, the modality of keys) at consecutive positions.  A list of runs ends with an entry
+// whose `at` is the tile's length.
+struct TmRun { uint32_t ss, x, pos, at; };
+
+// the value held by the next lower lane; lane 0 gets `first`
+__device__ __forceinline__ uint32_t lane_below(uint32_t v, uint32_t first) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
+}
+
+// Pairs (row, key) with key position <= row position for n rows and m keys at consecutive
+// positions, summed row by row from prefix(x) = sum of min(t, m) over t = 1..x: the first row
+// looks at d = row position - first key position + 1 keys.  Modulo 2^32 throughout (a tile
+// has at most 2^31 pairs).
+__device__ __forceinline__ uint32_t prefix_pairs(int32_t x, uint32_t m) {
+    if (x <= 0) return 0u;
+    const uint32_t y = min((uint32_t)x, m);
+    const uint32_t tri = (y & 1u) ? ((y + 1u) >> 1) * y : (y >> 1) * (y + 1u);
+    return tri + ((uint32_t)x - y) * m;
+}
+__device__ __forceinline__ uint32_t pairs_upto(int32_t d, int32_t n, uint32_t m) {
+    return prefix_pairs(d + n - 1, m) - prefix_pairs(d - 1, m);
+}
+
 // Workgroup `wg_index` (of tile_map_workgroups(jobs)) of the map(s); kTmThreads threads.
 // `blocks` may be a caller's unchecked list: an entry outside [0, n_seq_blocks) counts
 // as block 0, exactly as validate_blocks_body rewrites it.
+//
+// A layout is a handful of runs, so a tile is one to three of them, and the pairs of a run of
+// rows and a run of keys have a closed form: all of them inside one span, a (clamped) triangle
+// where the rows look back at the keys, minus a second triangle for a look-back window.  The
+// workgroup's wavefronts cut its q-tiles and k-tiles into runs once (every word of the group is
+// requested before the first is used), then each lane counts one tile pair.  Bound by the
+// latency of the words and the integer work per run pair; the group's shape trades words read
+// per pair, (gq + gk) / (gq gk) tiles, against workgroups in flight.  Measured per launch:
+// 1024 x 1024 tiles of 128 x 128 302 -> 25 us, 512 x 512 88 -> 13 us against counting every
+// row of a tile against every run of keys.
+// Counted that way still, one wavefront per pair and a row per lane: tiles of more than kTmRuns
+// runs (spans of a few tokens), sequences whose positions do not fit 30 bits, and maps of up to
+// 4096 pairs (a pair per wavefront; cutting tiles into runs first made these 1.2 us slower).
 __device__ __forceinline__ void
 tile_map_body(uint32_t wg_index, const uint64_t* __restrict__ bits,
               const int32_t* __restrict__ blocks, int32_t block, int64_t n_seq_blocks, int64_t n_rows,
@@ -39,82 +77,199 @@ tile_map_body(uint32_t wg_index, const uint64_t* __restrict__ bits,
     const bool second = wg_index >= n_first;                 // workgroup-uniform
     const TileMapJob& J = jobs.j[second ? 1 : 0];
     const uint32_t wg = wg_index - (second ? n_first : 0u);
-    const uint32_t wg_x = wg % J.gx, wg_y = wg / J.gx;       // k-tile group, q-tile
-    const int32_t tq = J.tq, tk = J.tk, nk = J.nk, kpw = J.kpw;
-    uint8_t* __restrict__ cls = J.cls;
-    uint32_t* __restrict__ cnt = J.cnt;
-    __shared__ uint32_t q_ss[kTmQChunk];
-    __shared__ uint32_t q_att[kTmQChunk];
-    __shared__ int64_t q_pos[kTmQChunk];
+    const int32_t tq = J.tq, tk = J.tk, nq = J.nq, nk = J.nk;
+    const int gq = J.gq, gk = J.gk, log_gk = __ffs(gk) - 1;      // gk is a power of two
+    const int32_t i0 = (int32_t)(wg / J.gx) * gq, j0 = (int32_t)(wg % J.gx) * gk;
+    __shared__ TmRun runs[2 * kTmGroup][kTmRuns + 1];        // q-tiles, then k-tiles
+    __shared__ int32_t n_runs[2 * kTmGroup];
 
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    const int64_t i = wg_y;
-    const int64_t r0 = i * tq;
-    const int64_t rows = min((int64_t)tq, n_rows - r0);      // ragged last q-tile
-    // words of the q rows c0 .. c0+n-1 of the tile into LDS (all threads; two barriers)
-    auto stage_rows = [&](int64_t c0, int n) {
-        __syncthreads();
-        if ((int)threadIdx.x < n) {
-            int64_t p = row_pos_checked(blocks, block, n_seq_blocks, r0 + c0 + threadIdx.x);
-            uint64_t w = bits[p];
-            q_pos[threadIdx.x] = p;
-            q_ss[threadIdx.x] = word_ss(w);
-            q_att[threadIdx.x] = word_att(w);
-        }
-        __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const bool small = gq * gk == kTmWaves;                  // workgroup-uniform
+    const bool by_runs = !small && (int64_t)nk * tk <= ((int64_t)1 << 30);      // positions fit 30 bits
+
+    // rows of q-tile i (the last one may be ragged)
+    auto rows_of = [&](int32_t i) -> int64_t { return min((int64_t)tq, n_rows - (int64_t)i * tq); };
+    auto pos_of = [&](int64_t r) -> int64_t {
+        if (!blocks) return r;
+        const uint32_t b = (uint32_t)r / (uint32_t)block;    // a share has fewer than 2^31 rows
+        int64_t g = blocks[b];
+        if (g < 0 || g >= n_seq_blocks) g = 0;
+        return g * block + ((uint32_t)r - b * (uint32_t)block);
     };
-    const bool single = rows <= kTmQChunk;                   // workgroup-uniform
-    if (single) stage_rows(0, (int)rows);
-
-    for (int jj = 0; jj < kpw; ++jj) {
-        const int64_t j = ((int64_t)wg_x * kTmWaves + wave) * kpw + jj;
-        const bool wave_active = j < nk;
-        const int64_t k0 = j * tk;
-        uint32_t part = 0;
-        for (int64_t c0 = 0; c0 < rows; c0 += kTmQChunk) {
-            const int n = (int)min((int64_t)kTmQChunk, rows - c0);
-            if (!single) stage_rows(c0, n);
-            if (!wave_active) continue;
-
-            for (int kc = 0; kc < tk; kc += kWave) {
-                // run starts among this chunk's keys: a key whose fields differ from its
-                // predecessor's (the first key of the chunk always starts one)
-                const int n_keys = min(kWave, tk - kc);
-                const uint64_t wk = lane < n_keys ? bits[k0 + kc + lane] : 0;
-                const uint32_t ss_k = word_ss(wk), mod_k = word_mod(wk);
-                const uint32_t ss_p = __shfl_up(ss_k, 1), mod_p = __shfl_up(mod_k, 1);
-                const bool starts = lane < n_keys && (lane == 0 || ss_k != ss_p || mod_k != mod_p);
-                uint64_t m = __ballot(starts);
-                while (m) {
-                    const int a = __ffsll((unsigned long long)m) - 1;
-                    m &= m - 1;
-                    const int b = m ? __ffsll((unsigned long long)m) - 1 : n_keys;   // the run is keys a..b-1
-                    const uint32_t ss_r = __shfl(ss_k, a), mod_r = __shfl(mod_k, a);
-                    const int64_t first = k0 + kc + a;
-                    const int64_t len = b - a;
-                    for (int r = lane; r < n; r += kWave) {
-                        const uint32_t ss_q = q_ss[r], att = q_att[r];
-                        const bool same_span = (ss_q & 0xFFFFu) != 0 && ss_q == ss_r;
-                        const bool back = (ss_q >> 16) == (ss_r >> 16) && ((att >> mod_r) & 1u);
-                        // keys of the run at or before the row's position ...
-                        const int64_t upto = max((int64_t)0, min(q_pos[r] - first + 1, len));
-                        // ... minus those a look-back window over the row's own modality cuts off
-                        const uint32_t win = att_window(att);
-                        const bool windowed = win != 0 && mod_r == att_modality(att);
-                        const int64_t cut = windowed ? max((int64_t)0, min(q_pos[r] - win + 1 - first, len)) : 0;
-                        part += (uint32_t)(same_span ? len : (back ? upto - cut : 0));
+    // tile `slot` of the group (q-tiles first): its length (0: past the end of the map), and the
+    // position of its element e
+    auto length_of = [&](int slot) -> int32_t {
+        if (slot < gq) return i0 + slot < nq ? (int32_t)rows_of(i0 + slot) : 0;
+        return slot < gq + gk && j0 + slot - gq < nk ? tk : 0;
+    };
+    auto element = [&](int slot, int32_t e) -> uint32_t {
+        return slot < gq ? (uint32_t)pos_of((int64_t)(i0 + slot) * tq + e)
+                         : (uint32_t)(j0 + slot - gq) * (uint32_t)tk + (uint32_t)e;
+    };
+    // 64 elements at0 .. of a tile (n of them valid) appended to its list of runs; (p_ss, p_x,
+    // p_pos): the last element of the 64 before
+    auto append = [&](int slot, int32_t at0, int32_t n, uint64_t w, uint32_t pos, int32_t& count, uint32_t& p_ss,
+                      uint32_t& p_x, uint32_t& p_pos) {
+        const uint32_t ss = word_ss(w), x = slot < gq ? word_att(w) : word_mod(w);
+        // (all lanes exchange before any lane decides)
+        const uint32_t b_ss = lane_below(ss, p_ss), b_x = lane_below(x, p_x), b_pos = lane_below(pos, p_pos);
+        const bool same = ss == b_ss && x == b_x && pos == b_pos + 1u;
+        const bool starts = lane < n && (!same || (lane == 0 && at0 == 0));
+        const uint64_t m = __ballot(starts);
+        const int32_t idx = count + __popcll(m & ((1ull << lane) - 1));
+        if (starts && idx < kTmRuns) runs[slot][idx] = TmRun{ss, x, pos, (uint32_t)(at0 + lane)};
+        count += __popcll(m);
+        p_ss = (uint32_t)__builtin_amdgcn_readlane((int)ss, 63);
+        p_x = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+        p_pos = (uint32_t)__builtin_amdgcn_readlane((int)pos, 63);
+    };
+    auto finish = [&](int slot, int32_t len, int32_t count) {
+        if (lane == 0) {
+            n_runs[slot] = count;
+            if (count <= kTmRuns) runs[slot][count].at = (uint32_t)len;
+        }
+    };
+    if (by_runs && max(tq, tk) <= 2 * kWave) {
+        // tiles of one or two words per lane, the words of kTmAhead tiles in flight together
+        for (int s0 = wave; s0 < gq + gk; s0 += kTmWaves * kTmAhead) {
+            uint64_t w[kTmAhead][2];
+            uint32_t pos[kTmAhead][2];
+#pragma unroll
+            for (int s = 0; s < kTmAhead; ++s) {
+                const int slot = s0 + kTmWaves * s;
+                const int32_t len = length_of(slot);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    pos[s][c] = 0u;
+                    w[s][c] = 0u;
+                    if (c * kWave + lane < len) {
+                        pos[s][c] = element(slot, c * kWave + lane);
+                        w[s][c] = bits[pos[s][c]];
                     }
                 }
             }
+#pragma unroll
+            for (int s = 0; s < kTmAhead; ++s) {
+                const int slot = s0 + kTmWaves * s;
+                const int32_t len = length_of(slot);
+                if (len == 0) continue;                      // wave-uniform
+                int32_t count = 0;
+                uint32_t p_ss = 0u, p_x = 0u, p_pos = 0u;
+                append(slot, 0, len, w[s][0], pos[s][0], count, p_ss, p_x, p_pos);
+                if (len > kWave) append(slot, kWave, len - kWave, w[s][1], pos[s][1], count, p_ss, p_x, p_pos);
+                finish(slot, len, count);
+            }
         }
-        const uint32_t total = wave_sum(part);
-        if (wave_active && lane == 0) {
-            const uint32_t full = (uint32_t)rows * (uint32_t)tk;
-            if (cnt) cnt[i * nk + j] = total;
-            if (cls)
-                cls[i * nk + j] = total == 0 ? MMATTN_TILE_EMPTY
-                                  : (total == full ? MMATTN_TILE_FULL : MMATTN_TILE_PARTIAL);
+    } else if (by_runs) {
+        for (int slot = wave; slot < gq + gk; slot += kTmWaves) {
+            const int32_t len = length_of(slot);
+            if (len == 0) continue;
+            int32_t count = 0;
+            uint32_t p_ss = 0u, p_x = 0u, p_pos = 0u;
+            for (int32_t at = 0; at < len; at += kWave) {
+                const uint32_t pos = at + lane < len ? element(slot, at + lane) : 0u;
+                append(slot, at, len - at, at + lane < len ? bits[pos] : 0u, pos, count, p_ss, p_x, p_pos);
+            }
+            finish(slot, len, count);
+        }
+    }
+    if (by_runs) __syncthreads();
+
+    // the pair's count and class
+    auto put = [&](int32_t i, int32_t j, uint32_t total) {
+        const uint32_t full = (uint32_t)rows_of(i) * (uint32_t)tk;
+        if (J.cnt) J.cnt[(int64_t)i * nk + j] = total;
+        if (J.cls)
+            J.cls[(int64_t)i * nk + j] = total == 0 ? MMATTN_TILE_EMPTY
+                                         : (total == full ? MMATTN_TILE_FULL : MMATTN_TILE_PARTIAL);
+    };
+    for (int p0 = 0; p0 < gq * gk; p0 += kTmThreads) {
+        const int pair = p0 + threadIdx.x;
+        const int qi = pair >> log_gk, ki = pair & (gk - 1);
+        const bool mine = pair < gq * gk && i0 + qi < nq && j0 + ki < nk;
+        const bool few = mine && by_runs && n_runs[qi] <= kTmRuns && n_runs[gq + ki] <= kTmRuns;
+        if (few) {
+            const TmRun* qr = runs[qi];
+            const int nqr = n_runs[qi], nkr = n_runs[gq + ki];
+            uint32_t total = 0;
+            for (int a = 0; a < nqr; ++a) {
+                const TmRun A = qr[a];
+                const int32_t n = (int32_t)(qr[a + 1].at - A.at);
+                const int32_t win = (int32_t)att_window(A.x);
+                const uint32_t mod = att_modality(A.x);
+                const TmRun* kr = runs[gq + ki];
+                TmRun B = kr[0];
+                for (int b = 0; b < nkr; ++b) {
+                    const TmRun next = kr[b + 1];
+                    const uint32_t m = next.at - B.at;
+                    if ((A.ss & 0xFFFFu) != 0u && A.ss == B.ss) {
+                        total += (uint32_t)n * m;
+                    } else if ((A.ss >> 16) == (B.ss >> 16) && ((A.x >> B.x) & 1u)) {
+                        const int32_t d = (int32_t)(A.pos - B.pos) + 1;
+                        total += pairs_upto(d, n, m);
+                        if (win != 0 && B.x == mod) total -= pairs_upto(d - win, n, m);
+                    }
+                    B = next;
+                }
+            }
+            put(i0 + qi, j0 + ki, total);
+        }
+
+        // the other pairs, one after the other, by the whole wavefront
+        uint64_t left = __ballot(mine && !few);
+        if (small) left = j0 + wave < nk ? 1u : 0u;          // a pair per wavefront
+        while (left) {
+            const int p = small ? wave : p0 + wave * kWave + __ffsll((unsigned long long)left) - 1;
+            left &= left - 1;
+            const int32_t i = i0 + (p >> log_gk), j = j0 + (p & (gk - 1));
+            const int64_t rows = rows_of(i), k0 = (int64_t)j * tk;
+            uint32_t part = 0;
+            // (the first 64 keys' words, and the next row's, are requested ahead of their use)
+            const uint64_t wk0 = lane < tk ? bits[k0 + lane] : 0;
+            int64_t q_next = 0;
+            uint64_t w_next = 0;
+            auto fetch_row = [&](int64_t r) {
+                if (r < rows) {
+                    q_next = pos_of((int64_t)i * tq + r);
+                    w_next = bits[q_next];
+                }
+            };
+            fetch_row(lane);
+            for (int64_t r = 0; r < rows; r += kWave) {
+                const bool row_ok = r + lane < rows;
+                const int64_t q = q_next;
+                const uint32_t ss_q = word_ss(w_next), att = word_att(w_next);
+                fetch_row(r + kWave + lane);
+                const uint32_t win = att_window(att), own = att_modality(att);
+                for (int kc = 0; kc < tk; kc += kWave) {
+                    // run starts among these keys: a key whose fields differ from its predecessor's
+                    const int n_keys = min(kWave, tk - kc);
+                    const uint64_t wk = kc == 0 ? wk0 : (lane < n_keys ? bits[k0 + kc + lane] : 0);
+                    const uint32_t ss_k = word_ss(wk), mod_k = word_mod(wk);
+                    const uint32_t b_ss = lane_below(ss_k, 0u), b_mod = lane_below(mod_k, 0u);
+                    const bool starts = lane < n_keys && (lane == 0 || ss_k != b_ss || mod_k != b_mod);
+                    uint64_t m = __ballot(starts);
+                    while (m) {
+                        const int a = __ffsll((unsigned long long)m) - 1;
+                        m &= m - 1;
+                        const int b = m ? __ffsll((unsigned long long)m) - 1 : n_keys;   // the run is keys a..b-1
+                        const uint32_t ss_r = (uint32_t)__builtin_amdgcn_readlane((int)ss_k, a);
+                        const uint32_t mod_r = (uint32_t)__builtin_amdgcn_readlane((int)mod_k, a);
+                        const int64_t first = k0 + kc + a, len = b - a;
+                        const bool same_span = (ss_q & 0xFFFFu) != 0 && ss_q == ss_r;
+                        const bool back = (ss_q >> 16) == (ss_r >> 16) && ((att >> mod_r) & 1u);
+                        // keys of the run at or before the row's position, minus those a look-back
+                        // window over the row's own modality cuts off
+                        const int64_t upto = max((int64_t)0, min(q - first + 1, len));
+                        const bool windowed = win != 0 && mod_r == own;
+                        const int64_t cut = windowed ? max((int64_t)0, min(q - (int64_t)win + 1 - first, len)) : 0;
+                        if (row_ok) part += (uint32_t)(same_span ? len : (back ? upto - cut : 0));
+                    }
+                }
+            }
+            const uint32_t total = wave_sum(part);
+            if (lane == 0) put(i, j, total);
         }
     }
 }
@@ -143,12 +298,16 @@ inline TileMapJob tile_map_job(int64_t S, int64_t n_rows, int32_t tq, int32_t tk
                                uint32_t* d_cnt) {
     const int64_t nq = (n_rows + tq - 1) / tq;
     const int32_t nk = (int32_t)(S / tk);
-    // k-tiles per wavefront: one while the map has few tile pairs, up to 8 once there are
-    // enough pairs for a thousand workgroups anyway
-    const int64_t kpw64 = nq * nk / (kTmWaves * 1024);
-    const int32_t kpw = (int32_t)std::max<int64_t>(1, std::min<int64_t>(8, kpw64));
-    const int32_t per_wg = kTmWaves * kpw;
-    return TileMapJob{tq, tk, nk, kpw, (uint32_t)((nk + per_wg - 1) / per_wg), (uint32_t)nq, d_cls, d_cnt};
+    // one q-tile x four k-tiles (a pair per wavefront, should the runs not serve) while the map
+    // has few pairs, more pairs per workgroup once about a thousand workgroups remain
+    int32_t gq = 1, gk = kTmWaves;
+    auto groups = [&]() { return ((nq + gq - 1) / gq) * (((int64_t)nk + gk - 1) / gk); };
+    while (groups() > 1024 && gq * gk < kTmGroup * kTmGroup) {
+        int32_t& g = (gq <= gk && gq < nq) || gk == kTmGroup ? gq : gk;
+        g *= 2;
+    }
+    return TileMapJob{tq, tk, (int32_t)nq, nk, gq, gk, (uint32_t)((nk + gk - 1) / gk),
+                      (uint32_t)((nq + gq - 1) / gq), d_cls, d_cnt};
 }
 
 inline uint32_t tile_map_workgroups(const TileMapJobs& jobs, int n_maps) {

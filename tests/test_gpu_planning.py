@@ -146,6 +146,19 @@ def test_tile_map_many_short_runs():
         check_tile_map(lay, tile[0], tile[1], use_c=False)
 
 
+@pytest.mark.parametrize("tile", [(16, 16), (64, 64), (128, 64), (48, 80), (80, 240), (256, 16), (16, 640)])
+@pytest.mark.parametrize("kind", ["short spans", "window", "packed", "denied"])
+def test_tile_map_large_maps(tile, kind):
+    """Maps of more than 4096 tile pairs, where tiles are cut into runs: tiles of more runs than
+    are kept (spans of 1-3 tokens), of one, two and many words per lane, groups of tiles that
+    end past the map's edge, windows and deny masks."""
+    S = 15360
+    lay = {"short spans": lambda: wl.layout_short_spans(7, S), "window": lambda: wl.layout_lambda([9000, 6360], 70, 1000),
+           "packed": lambda: wl.layout_packed(8, S=S, n_samples=12, span_lo=5, span_hi=900),
+           "denied": lambda: wl.layout_random(9, S=S, n_samples=5, max_spans=30, noncausal_prob=0.3, deny_prob=0.5)}[kind]()
+    check_tile_map(lay, tile[0], tile[1], use_c=True)
+
+
 def layouts_window():
     """Look-back windows: attention sinks plus a sliding window (the lambda
     pattern of section 5.5) in one sample and packed, window shorter and longer
