@@ -4,24 +4,37 @@
 // the greedy loop is inherently serial and the inputs are at most a few
 // thousand blocks.
 //
-//   phase 1  every thread ranks its blocks by counting the blocks that precede
-//            them in the visiting order (a total order, so ranks are a
-//            permutation); the workloads are staged in LDS when they fit;
-//   phase 2  wavefront 0 runs the greedy loop.  Up to 64 ranks (SLOTS == 1): the
-//            lanes hold the ranks sorted by (load, rank), the block goes to lane
-//            0's rank and one ballot re-inserts its grown key.  More ranks: lane
-//            l keeps the loads of ranks l, l+64, ... in registers (SLOTS of
-//            them, a template parameter chosen from P) and its own local
-//            minimum; a wave-level lexicographic min picks the receiving rank;
-//   phase 3  per-rank CSR lists in ascending block index by counting, for each
-//            block, the earlier blocks of the same rank.
+//   phase 1  the visiting order: up to 64 blocks by counting, for each, those that
+//            precede it, more by a bitonic sort of (W, index) keys, in registers up
+//            to 1024 blocks, else in LDS;
+//   phase 2  wavefront 0 runs the greedy loop over the ranks held SORTED by (load,
+//            rank), SLOTS per lane: a block goes to the first, whose grown key is
+//            re-inserted by one minimum and one maximum per key (see greedy_sorted);
+//   phase 3  per-rank CSR lists in ascending block index: every wavefront takes a
+//            stretch of blocks, finds equal ranks among 64 of them by ballots and
+//            counts with a histogram of its own.
+//
+// Bound by the latency of the loop, one block after the other.  Measured, 8 ranks:
+// 512 blocks 126 -> 23 us, 1024 blocks 259 -> 38 us against a loop that found a
+// block's place by a ballot and scalar arithmetic, an order counted over all pairs
+// of blocks (34 us of the 259) and lists counted the same way.
+// Workloads too large for the sorted keys (a sum of 2^42 to 2^46 pairs and more, by
+// the number of ranks) are ordered by counting and assigned by wave-wide minima.
 #include "common.h"
 
 namespace mm {
 
 constexpr int kBalThreads = 1024;
+constexpr int kBalWaves = kBalThreads / kWave;
 constexpr int kBalSlots = MMATTN_MAX_RANKS / kWave;   // most ranks per lane
-constexpr int kBalLdsW = 8192;                        // workloads staged in LDS up to this many blocks
+constexpr int kBalCounted = 64;                       // up to this many blocks the order is counted
+constexpr int kBalIndexBits = 14;                     // block index in a sort key
+static_assert(MMATTN_MAX_BLOCKS == 1 << kBalIndexBits, "a sort key holds any block index");
+// LDS, in 64-bit words: sort keys; up to kBalLdsRob blocks also their ranks; histograms
+// (over the keys, which are done with by then, when there are more blocks)
+constexpr int kBalLdsRob = 8192;
+constexpr int kBalRobAt = kBalLdsRob, kBalHistAt = kBalLdsRob + 4096;
+static_assert((MMATTN_MAX_BLOCKS - kBalHistAt) * 8 >= kBalWaves * MMATTN_MAX_RANKS * 2, "histograms fit");
 
 struct MinKey { uint64_t load; uint32_t rank; };
 
@@ -60,10 +73,270 @@ __device__ __forceinline__ MinKey wave_min(MinKey k) {
     return r;
 }
 
-// the value held by the next higher lane (wavefront shift left by one; lane 63 keeps
-// its own, which the caller never uses)
-__device__ __forceinline__ uint32_t lane_above(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x130 /* wave_shl:1 */, 0xf, 0xf, false);
+// A block on its way through the kernel is an entry of 64 bits in LDS: W << 14 | complement of
+// the index while the blocks are sorted; for 32-bit keys then the workload as the loop
+// subtracts it (high word) and the complement (low word); after the loop the high word is the
+// low word of the key that the block's rank had.
+constexpr uint32_t kIndexMask = MMATTN_MAX_BLOCKS - 1;
+
+// Keys of the greedy loop: the complement of (load << bits | rank), so that the least loaded
+// rank's key is the largest, 0 stands for an absent rank, and a load grows by a subtraction.
+// Loads count from a base that moves up with the smallest load.
+struct Key32 {
+    typedef uint32_t T;
+    static constexpr bool kRebase = true;
+    static constexpr int kLanes = kWave;               // lanes that hold keys
+    __device__ static __forceinline__ T of(uint32_t v) { return ~v; }
+    __device__ static __forceinline__ uint64_t value(T k) { return ~k; }
+    __device__ static __forceinline__ uint32_t low(T k) { return k; }
+    __device__ static __forceinline__ T step(uint64_t entry, int) { return (uint32_t)(entry >> 32); }
+    __device__ static __forceinline__ T most(T a, T b) { return max(a, b); }
+    __device__ static __forceinline__ T least(T a, T b) { return min(a, b); }
+    // the value of a lane in all lanes that hold keys
+    template <int LANE>
+    __device__ static __forceinline__ T everywhere(T v) {
+        return (uint32_t)__builtin_amdgcn_readlane((int)v, LANE);
+    }
+    // the value held by the next higher lane (wavefront shift left by one); the last lane gets 0
+    __device__ static __forceinline__ T above(T v) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130 /* wave_shl:1 */, 0xf, 0xf, true);
+    }
+};
+// the same for at most 16 ranks: the first row of 16 lanes holds their keys, and there a
+// lane's value reaches the others without a detour through a scalar register
+struct Key32Row : Key32 {
+    static constexpr int kLanes = 16;
+    template <int LANE>
+    __device__ static __forceinline__ T everywhere(T v) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + LANE /* row_newbcast */, 0xf, 0xf, true);
+    }
+    __device__ static __forceinline__ T above(T v) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x101 /* row_shl:1 */, 0xf, 0xf, true);
+    }
+};
+// the same in the 52 fraction bits of doubles from 2^52 on, integers that a double holds exactly
+struct Key52 {
+    typedef double T;
+    static constexpr bool kRebase = false;
+    static constexpr int kLanes = kWave;
+    __device__ static __forceinline__ T of(uint32_t v) {
+        return __builtin_bit_cast(double, 0x433FFFFF00000000ull | (uint32_t)~v);
+    }
+    __device__ static __forceinline__ uint64_t value(T k) {
+        return ~__builtin_bit_cast(uint64_t, k) & ((1ull << 52) - 1);
+    }
+    __device__ static __forceinline__ uint32_t low(T k) { return (uint32_t)__builtin_bit_cast(uint64_t, k); }
+    __device__ static __forceinline__ T step(uint64_t entry, int bits) {
+        return (double)(entry >> kBalIndexBits << bits);
+    }
+    __device__ static __forceinline__ T most(T a, T b) { return fmax(a, b); }
+    __device__ static __forceinline__ T least(T a, T b) { return fmin(a, b); }
+    template <class F>
+    __device__ static __forceinline__ T words(T v, F&& f) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        return __builtin_bit_cast(double, ((uint64_t)f((uint32_t)(b >> 32)) << 32) | f((uint32_t)b));
+    }
+    template <int LANE>
+    __device__ static __forceinline__ T everywhere(T v) {
+        return words(v, [](uint32_t x) { return Key32::everywhere<LANE>(x); });
+    }
+    __device__ static __forceinline__ T above(T v) {
+        return words(v, [](uint32_t x) { return Key32::above(x); });
+    }
+};
+
+// The greedy loop.  Keys are sorted over (lane, slot).  A block goes to the first key's rank;
+// with x the first key less the workload, every place then holds max(next key, min(own key,
+// x)): the keys above x move down one place, x takes the place behind them.  One wavefront.
+// Every lane also holds the first key, `head`: the next one is max(second key, x).  Bound by
+// the chain from step to step and by the instructions that one wavefront can issue (one in
+// about five cycles), so the workloads come from LDS two to a read, kSteps steps ahead, and
+// all else is left to the other wavefronts.  Measured per block: 185 ns with ballots and scalar
+// arithmetic; now 27 to 30 ns with at most 16 ranks, 35 ns with 64 (a crossing from vector to
+// scalar registers in every step), 46 ns with doubles (their minimum and maximum issue slowly),
+// 94 ns with 1024 ranks.
+constexpr int kSteps = 8;
+template <class K, int SLOTS>
+__device__ __forceinline__ void greedy_sorted(uint64_t* entries, int32_t nB, int32_t P, int bits, int rebase_mask,
+                                              int lane, uint64_t* __restrict__ load) {
+    typedef typename K::T T;
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    const uint32_t mask = (1u << bits) - 1u;
+    T key[SLOTS];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        const int r = lane * SLOTS + s;
+        key[s] = r < P ? K::of((uint32_t)r) : T(0);
+    }
+    T head = K::template everywhere<0>(key[0]);
+    T second = K::template everywhere<1 / SLOTS>(key[1 % SLOTS]);
+    uint64_t base = 0;
+    u64x2 ahead[kSteps / 2];
+    auto fetch = [&](int t) {
+#pragma unroll
+        for (int v = 0; v < kSteps / 2; ++v) ahead[v] = *(const u64x2*)&entries[t + 2 * v];
+    };
+    fetch(0);
+    // entries past the last block (up to a whole number of steps) are 0 and leave the keys as they are
+    for (int t = 0; t < nB; t += kSteps) {
+        T w[kSteps];
+#pragma unroll
+        for (int v = 0; v < kSteps; ++v) w[v] = K::step(ahead[v / 2][v % 2], bits);
+        if (t + kSteps < nB) fetch(t + kSteps);
+        if (K::kRebase && (t & rebase_mask) == 0) {
+            // the smallest load becomes the base
+            const uint64_t least = K::value(head) >> bits;
+            const T by = (T)(least << bits);
+            base += least;
+            head += by;
+            second += second != T(0) ? by : T(0);
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s) key[s] += key[s] != T(0) ? by : T(0);
+        }
+        uint32_t got[kSteps];
+#pragma unroll
+        for (int v = 0; v < kSteps; ++v) {
+            got[v] = K::low(head);
+            const T x = head - w[v];
+            head = K::most(second, x);
+            const T above = K::above(key[0]);
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s)
+                key[s] = K::most(s + 1 < SLOTS ? key[s + 1] : above, K::least(key[s], x));
+            second = K::template everywhere<1 / SLOTS>(key[1 % SLOTS]);
+        }
+        // (the same value from every lane)
+#pragma unroll
+        for (int v = 0; v < kSteps; ++v) ((uint32_t*)entries)[2 * (t + v) + 1] = got[v];
+    }
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+        if (lane * SLOTS + s < P) {
+            const uint64_t v = K::value(key[s]);
+            load[v & mask] = base + (v >> bits);
+        }
+}
+
+// the same for workloads of any size: lane l keeps the loads of ranks l, l+64, ... and its
+// local minimum, a wave-wide lexicographic minimum picks the receiving rank
+template <int SLOTS>
+__device__ __forceinline__ void greedy_wide(const uint64_t* __restrict__ W, const int32_t* __restrict__ order,
+                                            int32_t nB, int32_t P, int lane, int32_t* __restrict__ rank_of_block,
+                                            uint64_t* __restrict__ load) {
+    uint64_t mine[SLOTS];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) mine[s] = 0;
+    MinKey local;                       // this lane's least-loaded rank
+    local.load = lane < P ? 0 : ~0ull;
+    local.rank = lane < P ? (uint32_t)lane : 0xFFFFFFFFu;
+    for (int t0 = 0; t0 < nB; t0 += kWave) {
+        const int t = t0 + lane;
+        const int32_t my_b = t < nB ? order[t] : 0;
+        const uint64_t my_w = t < nB ? W[my_b] : 0;
+        const int n = min(kWave, nB - t0);
+        for (int u = 0; u < n; ++u) {
+            const int32_t b = __builtin_amdgcn_readlane(my_b, u);
+            const uint32_t wlo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_w, u);
+            const uint32_t whi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_w >> 32), u);
+            const uint64_t w = ((uint64_t)whi << 32) | wlo;
+            const uint32_t g = wave_min(local).rank;
+            if ((int)(g & (kWave - 1)) == lane) {
+                const int slot = g / kWave;
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s)
+                    if (s == slot) mine[s] += w;
+                // recompute the lane's local minimum over its ranks
+                local.load = ~0ull;
+                local.rank = 0xFFFFFFFFu;
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) {
+                    const uint32_t r = (uint32_t)(lane + s * kWave);
+                    if ((int)r < P) {
+                        MinKey cand{mine[s], r};
+                        if (key_less(cand, local)) local = cand;
+                    }
+                }
+                rank_of_block[b] = (int32_t)g;
+            }
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        const int r = lane + s * kWave;
+        if (r < P) load[r] = mine[s];
+    }
+}
+
+// n2 keys (a power of two, >= 128) into descending order.  A wavefront's compare-exchanges
+// over distances up to 64 stay inside 128 consecutive keys of its own: the workgroup
+// meets only around the longer ones.
+__device__ __forceinline__ void sort_descending(uint64_t* keys, int n2) {
+    bool far = true;                                   // the keys were just written by others
+    for (int k = 2; k <= n2; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            if (far || j > kWave) __syncthreads();
+            else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            far = j > kWave;
+            for (int t = threadIdx.x; t < n2 / 2; t += kBalThreads) {
+                const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
+                const uint64_t a = keys[i], b = keys[i + j];
+                if ((a < b) == ((i & k) == 0)) {
+                    keys[i] = b;
+                    keys[i + j] = a;
+                }
+            }
+        }
+    __syncthreads();
+}
+
+// the key of lane ^ J
+template <int J>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t v) {
+    auto one = [](uint32_t x) -> uint32_t {
+        if (J == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1 /* quad_perm 1,0,3,2 */, 0xf, 0xf, true);
+        if (J == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E /* quad_perm 2,3,0,1 */, 0xf, 0xf, true);
+        if (J < 32) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, 0x1F | (J << 10));
+        return (uint32_t)__shfl_xor((int)x, 32);
+    };
+    return ((uint64_t)one((uint32_t)(v >> 32)) << 32) | one((uint32_t)v);
+}
+// one compare-exchange over distance J inside the wavefronts, of the merge into runs of k
+template <int J>
+__device__ __forceinline__ void exchange(uint64_t& mine, int tid, int k) {
+    const uint64_t other = lane_xor<J>(mine);
+    // the lower place of a pair keeps the larger key in a descending run
+    const bool larger = ((tid & J) == 0) == ((tid & k) == 0);
+    mine = (mine > other) == larger ? mine : other;
+}
+// the same for at most kBalThreads keys, one per thread in registers: distances below 64 by
+// exchanges between lanes (about 110 cycles each; 480 through LDS)
+__device__ __forceinline__ void sort_descending_regs(uint64_t* keys, int n2) {
+    const int tid = threadIdx.x;
+    const bool active = tid < n2;                      // whole wavefronts: n2 is a multiple of 64
+    uint64_t mine = active ? keys[tid] : 0;
+    for (int k = 2; k <= n2; k <<= 1) {
+        for (int j = k >> 1; j >= kWave; j >>= 1) {
+            __syncthreads();
+            if (active) keys[tid] = mine;
+            __syncthreads();
+            if (active) {
+                const uint64_t other = keys[tid ^ j];
+                const bool larger = ((tid & j) == 0) == ((tid & k) == 0);
+                mine = (mine > other) == larger ? mine : other;
+            }
+        }
+        if (active) {
+            if (k > 32) exchange<32>(mine, tid, k);
+            if (k > 16) exchange<16>(mine, tid, k);
+            if (k > 8) exchange<8>(mine, tid, k);
+            if (k > 4) exchange<4>(mine, tid, k);
+            if (k > 2) exchange<2>(mine, tid, k);
+            exchange<1>(mine, tid, k);
+        }
+    }
+    __syncthreads();
+    if (active) keys[tid] = mine;
+    __syncthreads();
 }
 
 template <int SLOTS>
@@ -71,162 +344,185 @@ __global__ void __launch_bounds__(kBalThreads)
 balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
                int32_t* __restrict__ rank_of_block, uint64_t* __restrict__ load,
                int32_t* __restrict__ rank_off, int32_t* __restrict__ rank_blocks) {
-    __shared__ __attribute__((aligned(16))) uint16_t rob[MMATTN_MAX_BLOCKS];
-    __shared__ int32_t count[MMATTN_MAX_RANKS + 1];
-    __shared__ __attribute__((aligned(16))) uint64_t w_lds[kBalLdsW];
-    const int tid = threadIdx.x;
+    __shared__ __attribute__((aligned(16))) uint64_t lds[MMATTN_MAX_BLOCKS];
+    __shared__ uint64_t sum_s[kBalWaves], max_s[kBalWaves];
+    __shared__ int32_t scan_s[kBalWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    uint64_t* keys = lds;
+    uint16_t* rob = (uint16_t*)(lds + kBalRobAt);
+    uint16_t* hist = (uint16_t*)(lds + kBalHistAt);    // [wave][rank]
 
-    // phase 1: visiting order, kept in rank_blocks until phase 3 overwrites it
-    int32_t* order = rank_blocks;
-    const bool staged = nB <= kBalLdsW;                // workgroup-uniform
-    if (staged) {
-        for (int b = tid; b < nB; b += kBalThreads) w_lds[b] = W[b];
-        __syncthreads();
+    // sum and largest workload; small ones go to LDS as sort keys on the way
+    uint64_t sum = 0, most = 0;
+    int n2 = 2 * kWave;
+    while (n2 < nB) n2 <<= 1;
+    for (int b = tid; b < n2; b += kBalThreads) {
+        const uint64_t w = b < nB ? W[b] : 0;
+        sum += w;
+        most = max(most, w);
+        keys[b] = b < nB ? (w << kBalIndexBits) | (uint64_t)(MMATTN_MAX_BLOCKS - 1 - b) : 0;
+        if (P == 1 && b < nB) {                        // a single rank receives every block
+            rank_of_block[b] = 0;
+            rank_blocks[b] = b;
+        }
     }
-    const uint64_t* Wp = staged ? w_lds : W;           // phase 2 reads the workloads through this
-    for (int b = tid; b < nB; b += kBalThreads) {
-        int pos = 0;
-        if (staged) {
-            const uint64_t wb = w_lds[b];
-            typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
-            const u64x2* w2 = (const u64x2*)w_lds;     // two workloads per LDS read
-            const int pairs = nB >> 1;
+    for (int off = 32; off > 0; off >>= 1) {
+        sum += __shfl_xor(sum, off);
+        most = max(most, (uint64_t)__shfl_xor(most, off));
+    }
+    if (lane == 0) { sum_s[wave] = sum; max_s[wave] = most; }
+    __syncthreads();
+    sum = 0; most = 0;
+    for (int w = 0; w < kBalWaves; ++w) { sum += sum_s[w]; most = max(most, max_s[w]); }
+    if (P == 1) {                                      // workgroup-uniform
+        if (tid == 0) {
+            load[0] = sum;
+            rank_off[0] = 0;
+            rank_off[1] = nB;
+        }
+        return;
+    }
+    // How large keys get.  Loads differ by at most the largest workload at any time, and among
+    // the n blocks between two moves of the base the smallest load grows by at most one
+    // workload per P blocks: 32-bit keys hold 2 + (n - 1) / P workloads and the rank.
+    // Doubles hold the sum of all (the largest first: a sum of workloads below 2^46 cannot have
+    // wrapped).
+    const int bits = 32 - __clz(P - 1);                // P >= 2
+    auto fits32_for = [&](int n) {
+        return most < (1ull << 31) && (2 + (n - 1) / P) * most < (1ull << (32 - bits)) - 1;
+    };
+    const bool fits = most < (1ull << 46) && sum < (1ull << (52 - bits));
+    const bool fits32 = fits && fits32_for(kSteps);
+    const bool rob_lds = fits && nB <= kBalLdsRob;     // workgroup-uniform, like the branches below
+
+    if (fits) {
+        if (nB <= kBalCounted) {
+            // every block's place; the keys are distinct
+            uint64_t mine = 0;
+            int pos = 0;
+            if (tid < nB) {
+                mine = keys[tid];
+                typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+                const u64x2* k2 = (const u64x2*)keys;  // two keys per LDS read, zeros past the last
 #pragma unroll 4
-            for (int c2 = 0; c2 < pairs; ++c2) {
-                const u64x2 wc = w2[c2];
-                pos += (wc.x > wb || (wc.x == wb && 2 * c2 < b)) ? 1 : 0;
-                pos += (wc.y > wb || (wc.y == wb && 2 * c2 + 1 < b)) ? 1 : 0;
+                for (int c = 0; c < (nB + 1) / 2; ++c) {
+                    const u64x2 kc = k2[c];
+                    pos += (kc.x > mine ? 1 : 0) + (kc.y > mine ? 1 : 0);
+                }
             }
-            if (nB & 1) {
-                const uint64_t wc = w_lds[nB - 1];
-                pos += (wc > wb || (wc == wb && nB - 1 < b)) ? 1 : 0;
-            }
+            __syncthreads();
+            if (tid < nB) keys[pos] = mine;
+            __syncthreads();
+        } else if (nB <= kBalThreads) {
+            sort_descending_regs(keys, n2);
         } else {
+            sort_descending(keys, n2);
+        }
+        if (fits32) {
+            for (int t = tid; t < nB; t += kBalThreads) {
+                const uint64_t e = keys[t];
+                keys[t] = (e >> kBalIndexBits << (32 + bits)) | (e & kIndexMask);
+            }
+            __syncthreads();
+        }
+        if (wave == 0) {
+            // one move of the base per 64 blocks where 32 bits allow it
+            const int rebase_mask = fits32_for(64) ? 63 : kSteps - 1;
+            if (SLOTS == 1 && fits32 && P <= Key32Row::kLanes) {
+                if (lane < Key32Row::kLanes)
+                    greedy_sorted<Key32Row, SLOTS>(keys, nB, P, bits, rebase_mask, lane, load);
+            } else if (fits32) {
+                greedy_sorted<Key32, SLOTS>(keys, nB, P, bits, rebase_mask, lane, load);
+            } else {
+                greedy_sorted<Key52, SLOTS>(keys, nB, P, bits, rebase_mask, lane, load);
+            }
+        }
+        __syncthreads();
+        for (int t = tid; t < nB; t += kBalThreads) {
+            const uint64_t e = keys[t];
+            const int b = (int)(kIndexMask - ((uint32_t)e & kIndexMask));
+            const int g = (int)(~(uint32_t)(e >> 32) & ((1u << bits) - 1u));
+            rank_of_block[b] = g;
+            if (rob_lds) rob[b] = (uint16_t)g;
+        }
+    } else {
+        int32_t* order = rank_blocks;                  // until phase 3 overwrites it
+        for (int b = tid; b < nB; b += kBalThreads) {
             const uint64_t wb = W[b];
+            int pos = 0;
             for (int c = 0; c < nB; ++c) {
                 const uint64_t wc = W[c];
                 pos += (wc > wb || (wc == wb && c < b)) ? 1 : 0;
             }
+            order[pos] = b;
         }
-        order[pos] = b;
-    }
-    for (int g = tid; g <= P; g += kBalThreads) count[g] = 0;
-    __syncthreads();
-
-    // phase 2: greedy assignment by wavefront 0
-    if (SLOTS == 1 && P == 1 && tid < kWave) {
-        // a single rank receives every block
-        uint64_t sum = 0;
-        for (int b = tid; b < nB; b += kWave) {
-            rank_of_block[b] = 0;
-            rob[b] = 0;
-            sum += Wp[b];
-        }
-        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-        if (tid == 0) load[0] = sum;
-    } else if (SLOTS == 1 && tid < kWave) {
-        // At most one rank per lane: the lanes hold the ranks SORTED by (load, rank), lane 0
-        // the least loaded.  A block goes to lane 0's rank; its new key is re-inserted at
-        // the position given by how many other keys are smaller (one ballot), the keys
-        // before that position move down one lane.  All per-block decisions are scalar.
-        const int lane = tid;
-        uint32_t lo = lane < P ? 0u : 0xFFFFFFFFu, hi = lo;          // load; lanes >= P: +inf
-        uint32_t rk = lane < P ? (uint32_t)lane : 0xFFFFFFFFu;
-        for (int t0 = 0; t0 < nB; t0 += kWave) {
-            const int t = t0 + lane;
-            const int32_t my_b = t < nB ? order[t] : 0;
-            const uint64_t my_w = t < nB ? Wp[my_b] : 0;
-            const int n = min(kWave, nB - t0);
-            for (int u = 0; u < n; ++u) {
-                const int32_t b = __builtin_amdgcn_readlane(my_b, u);
-                const uint64_t w = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_w >> 32), u) << 32) |
-                                   (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_w, u);
-                const uint32_t g = (uint32_t)__builtin_amdgcn_readlane((int)rk, 0);
-                const uint64_t grown = (((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, 0) << 32) |
-                                        (uint32_t)__builtin_amdgcn_readlane((int)lo, 0)) + w;
-                const uint64_t mine = ((uint64_t)hi << 32) | lo;
-                const bool less = lane > 0 && (mine < grown || (mine == grown && rk < g));
-                const int at = __popcll(__ballot(less));              // new lane of rank g
-                // lanes below `at` take their upper neighbour's key, lane `at` the grown one
-                const uint32_t lo_up = lane_above(lo), hi_up = lane_above(hi), rk_up = lane_above(rk);
-                if (lane < at) { lo = lo_up; hi = hi_up; rk = rk_up; }
-                else if (lane == at) { lo = (uint32_t)grown; hi = (uint32_t)(grown >> 32); rk = g; }
-                if (lane == 0) {
-                    rank_of_block[b] = (int32_t)g;
-                    rob[b] = (uint16_t)g;
-                }
-            }
-        }
-        if (lane < P) load[rk] = ((uint64_t)hi << 32) | lo;
-    } else if (tid < kWave) {
-        const int lane = tid;
-        uint64_t mine[SLOTS];
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s) mine[s] = 0;
-        MinKey local;                       // this lane's least-loaded rank
-        local.load = lane < P ? 0 : ~0ull;
-        local.rank = lane < P ? (uint32_t)lane : 0xFFFFFFFFu;
-        for (int t0 = 0; t0 < nB; t0 += kWave) {
-            const int t = t0 + lane;
-            const int32_t my_b = t < nB ? order[t] : 0;
-            const uint64_t my_w = t < nB ? Wp[my_b] : 0;
-            const int n = min(kWave, nB - t0);
-            for (int u = 0; u < n; ++u) {
-                const int32_t b = __builtin_amdgcn_readlane(my_b, u);
-                const uint32_t wlo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_w, u);
-                const uint32_t whi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_w >> 32), u);
-                const uint64_t w = ((uint64_t)whi << 32) | wlo;
-                const uint32_t g = wave_min(local).rank;
-                if ((int)(g & (kWave - 1)) == lane) {
-                    const int slot = g / kWave;
-#pragma unroll
-                    for (int s = 0; s < SLOTS; ++s)
-                        if (s == slot) mine[s] += w;
-                    // recompute the lane's local minimum over its ranks
-                    local.load = ~0ull;
-                    local.rank = 0xFFFFFFFFu;
-#pragma unroll
-                    for (int s = 0; s < SLOTS; ++s) {
-                        const uint32_t r = (uint32_t)(lane + s * kWave);
-                        if ((int)r < P) {
-                            MinKey cand{mine[s], r};
-                            if (key_less(cand, local)) local = cand;
-                        }
-                    }
-                    rank_of_block[b] = (int32_t)g;
-                    rob[b] = (uint16_t)g;
-                }
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            const int r = lane + s * kWave;
-            if (r < P) load[r] = mine[s];
-        }
+        __syncthreads();
+        if (wave == 0) greedy_wide<SLOTS>(W, order, nB, P, lane, rank_of_block, load);
     }
     __syncthreads();
 
-    // phase 3: CSR lists, ascending block index inside each rank
-    for (int b = tid; b < nB; b += kBalThreads) atomicAdd(&count[rob[b] + 1], 1);
+    // phase 3.  Wavefront `wave` takes blocks first .. last-1
+    const int per = ((nB + kBalThreads - 1) / kBalThreads) * kWave;
+    const int first = wave * per, last = min(nB, first + per);
+    uint16_t* my_hist = hist + wave * P;
+    for (int i = tid; i < kBalWaves * P; i += kBalThreads) hist[i] = 0;
     __syncthreads();
-    if (tid == 0)
-        for (int g = 0; g < P; ++g) count[g + 1] += count[g];
-    __syncthreads();
-    for (int g = tid; g <= P; g += kBalThreads) rank_off[g] = count[g];
-    for (int b = tid; b < nB; b += kBalThreads) {
-        const uint16_t g = rob[b];
-        int before = 0;
-        typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
-        const u16x8* rob8 = (const u16x8*)rob;         // eight ranks per LDS read
-        const int octets = b >> 3;
-#pragma unroll 2
-        for (int c8 = 0; c8 < octets; ++c8) {
-            const u16x8 r = rob8[c8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) before += r[u] == g ? 1 : 0;
+    // the lanes of this wavefront whose block has the same rank
+    auto peers = [&](int g, bool ok) -> uint64_t {
+        uint64_t m = __ballot(ok);
+        for (int bit = 0; bit < bits; ++bit) {
+            const uint64_t set = __ballot((g >> bit) & 1);
+            m &= (g >> bit) & 1 ? set : ~set;
         }
-        for (int c = octets << 3; c < b; ++c) before += rob[c] == g ? 1 : 0;
-        rank_blocks[count[g] + before] = b;
+        return m;
+    };
+    auto rank_at = [&](int b) -> int { return b < last ? (rob_lds ? (int)rob[b] : rank_of_block[b]) : 0; };
+    const uint64_t below = (1ull << lane) - 1;
+    for (int b = first + lane; b - lane < last; b += kWave) {
+        const int g = rank_at(b);
+        const uint64_t m = peers(g, b < last);
+        if (b < last && (m & below) == 0) my_hist[g] += (uint16_t)__popcll(m);     // one lane per rank
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    __syncthreads();
+    // counts of a rank over the wavefronts -> first list entries of (wavefront, rank)
+    int total = 0, before[kBalWaves];
+    if (tid < P) {
+#pragma unroll
+        for (int w = 0; w < kBalWaves; ++w) before[w] = hist[w * P + tid];
+#pragma unroll
+        for (int w = 0; w < kBalWaves; ++w) {
+            const int c = before[w];
+            before[w] = total;
+            total += c;
+        }
+    }
+    int inc = total;                                   // inclusive scan over the ranks
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int up = __shfl_up(inc, off);
+        if (lane >= off) inc += up;
+    }
+    if (P > kWave) {                                   // workgroup-uniform
+        if (lane == kWave - 1) scan_s[wave] = inc;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) inc += scan_s[w];
+    }
+    if (tid < P) {
+        rank_off[tid + 1] = inc;
+#pragma unroll
+        for (int w = 0; w < kBalWaves; ++w) hist[w * P + tid] = (uint16_t)(inc - total + before[w]);
+    }
+    if (tid == 0) rank_off[0] = 0;
+    __syncthreads();
+    for (int b = first + lane; b - lane < last; b += kWave) {
+        const int g = rank_at(b);
+        const uint64_t m = peers(g, b < last);
+        if (b < last) rank_blocks[my_hist[g] + __popcll(m & below)] = b;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (b < last && (m & below) == 0) my_hist[g] += (uint16_t)__popcll(m);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
 

@@ -241,6 +241,20 @@ def test_balance_random(seed):
     check_balance(rng.integers(0, hi, size=nB).tolist(), P)
 
 
+@pytest.mark.parametrize("nB,P", [(64, 2), (65, 16), (128, 17), (1000, 3), (1024, 64), (1025, 15), (2049, 65), (700, 256),
+                                  (600, 257), (8192, 8), (8193, 63), (16384, 5)])
+def test_balance_key_widths(nB, P):
+    """Largest workloads on either side of where the loop's keys get wider: 32 bits with the
+    base moved every 64 or every 8 blocks, doubles, any 64-bit workload."""
+    rng = np.random.default_rng(nB + P)
+    bits = (P - 1).bit_length()
+    limit = lambda n: ((1 << (32 - bits)) - 2) // (2 + (n - 1) // P)
+    for most in (3, limit(64), limit(64) + 1, limit(8), limit(8) + 1, (1 << (52 - bits)) // nB, 1 << 50):
+        W = rng.integers(most // 2, most + 1, size=nB)
+        W[rng.integers(0, nB, size=nB // 2)] = most          # many ties, at the top
+        check_balance(W.tolist(), P)
+
+
 @pytest.mark.parametrize("c", [1, 2, 3, 4, 5])
 def test_balance_workloads_end_to_end(c):
     """encode -> tile map -> balance, all on the GPU, against the oracle chain."""
