@@ -127,10 +127,16 @@ struct FwdSmem {
     alignas(256) uint64_t kw[NST][kFwdBN];                // mask words of a PARTIAL tile's keys, by ring stage
 };
 
-// HPW query heads per workgroup (4 wavefronts each), NST LDS stages; one workgroup per
-// CU at D = 128 (LDS), so HPW wavefronts per SIMD.
+// HPW query heads per workgroup (4 wavefronts each), NST LDS stages.  At D = 128 one workgroup
+// per CU (LDS), so HPW wavefronts per SIMD.  At D = 64 a tile has half the matrix instructions
+// under the same exponentials, so the vector work is the bound and more wavefronts per SIMD
+// help: one head per workgroup with three stages (50 KiB) and at most 168 registers puts three
+// workgroups on a CU.  Measured there (whole calls): 8192 tokens, 32 / 8 heads 341 us with two
+// heads per workgroup, 316 us so; 32768 tokens with a 4096 window, 16 heads 695 us with 205
+// registers (two workgroups per CU), 618 us so.
+constexpr int fwd_heads_per_wg(int D, int rep) { return D == 128 && rep % 2 == 0 ? 2 : 1; }
 template <int D, int HPW, int NST>
-__global__ void __launch_bounds__(256 * HPW, HPW)
+__global__ void __launch_bounds__(256 * HPW, D == 64 ? 3 : HPW)
 fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
            const ushort_t* __restrict__ V, const uint64_t* __restrict__ bits,
            const int32_t* __restrict__ blocks, int32_t block, int64_t n_loc, int64_t S,
@@ -686,7 +692,11 @@ static FwdLayout fwd_layout(int64_t S, int64_t n_loc, int32_t n_blocks, int32_t 
     const int32_t Hq_run = Hq / Hkv * Hkv_run;
     L.nq = (int32_t)((n_loc + kFwdBM - 1) / kFwdBM);
     L.nk = (int32_t)(S / kFwdBN);
-    L.split = list_split(L.nq, L.nk, Hq_run / ((Hq / Hkv) % 2 == 0 ? 2 : 1));
+    const int32_t rep = Hq / Hkv;
+    L.split = list_split(L.nq, L.nk, Hq_run / fwd_heads_per_wg(D, rep));
+    // the partial results have room for the slices that pairs of heads would be cut into at
+    // either head dim (never fewer)
+    const FwdSplit room = list_split(L.nq, L.nk, Hq_run / (rep % 2 == 0 ? 2 : 1));
     size_t off = 0;
     L.err = off;          off += 256;
     L.clean_blocks = off; off += align_up((size_t)n_blocks * 4, 256);
@@ -695,7 +705,7 @@ static FwdLayout fwd_layout(int64_t S, int64_t n_loc, int32_t n_blocks, int32_t 
     L.klist = off;        off += align_up((size_t)L.nq * L.nk * 4, 256);
     L.qorder = off;       off += align_up((size_t)L.nq * 4, 256);
     L.knorm = off;        off += align_up((size_t)Hkv * kNormChunks * 4, 256);
-    const size_t prow = L.split.cmax > 1 ? (size_t)L.split.cmax * L.nq * kFwdBM * Hq_run : 0;
+    const size_t prow = room.cmax > 1 ? (size_t)room.cmax * L.nq * kFwdBM * Hq_run : 0;
     L.opart = off;        off += align_up(prow * D * 4, 256);
     L.mlpart = off;       off += align_up(prow * 8, 256);
     L.total = off;
@@ -778,11 +788,11 @@ int launch_fwd(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st)
     plan.klist = (uint32_t*)(base + L.klist);
     plan.qorder = (int32_t*)(base + L.qorder);
     plan.csz = err + kFlagInts;
-    plan.groups = a.Hq / a.Hkv * a.kv_count / (a.Hq / a.Hkv % 2 == 0 ? 2 : 1);
+    const int32_t rep = a.Hq / a.Hkv;
+    const int32_t hpw = fwd_heads_per_wg(a.D, rep);
+    plan.groups = rep * a.kv_count / hpw;
 
     const float scale_log2 = a.scale * kLog2e;
-    const int32_t rep = a.Hq / a.Hkv;
-    const bool pair = rep % 2 == 0;                // two heads of a KV group per workgroup
     // largest key norms of the window's heads (data, not plan: every call)
     float* knorm = (float*)(base + L.knorm) + (int64_t)a.kv_begin * kNormChunks;
     const ushort_t* kw = (const ushort_t*)a.k + (int64_t)a.kv_begin * a.D;
@@ -810,11 +820,10 @@ int launch_fwd(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st)
     }
     stage_begin(MMATTN_STAGE_FWD, st);
     if (a.D == 128) {
-        if (pair) launch_fwd_kernel<128, 2, 4>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
-        else      launch_fwd_kernel<128, 1, 3>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
+        if (hpw == 2) launch_fwd_kernel<128, 2, 4>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
+        else          launch_fwd_kernel<128, 1, 3>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
     } else {
-        if (pair) launch_fwd_kernel<64, 2, 4>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
-        else      launch_fwd_kernel<64, 1, 3>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
+        launch_fwd_kernel<64, 1, 3>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
     }
     if (L.split.cmax > 1) {
         const int32_t Hq_run = rep * a.kv_count;
