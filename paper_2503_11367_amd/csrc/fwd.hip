@@ -16,7 +16,7 @@
 //   O^T += V^T P^T (A = V fragment read from the row-major V tile with the LDS
 //                  transpose read ds_read_b64_tr_b16).
 // K/V tiles go HBM/L2 -> LDS directly (global_load_lds_dwordx4, no registers)
-// through a ring of NST stages: the transfers of the next tiles overlap the
+// through a ring of NST stages (of a tile, or of half a tile): the transfers of the next tiles overlap the
 // math of the current one and there is one workgroup barrier per tile.
 // The loop is a software pipeline over half tiles (32 keys): while the
 // probabilities of one half tile are exponentiated and multiplied into O, the
@@ -120,23 +120,33 @@ fwd_prologue_kernel(const FwdPrologue p) {
     }
 }
 
-template <int D, int NST>
+// BN: keys per ring stage
+template <int D, int NST, int BN>
 struct FwdSmem {
-    alignas(1024) unsigned char k[NST][kFwdBN * D * 2];   // rotated tiles, see SwzTile
-    alignas(1024) unsigned char v[NST][kFwdBN * D * 2];
-    alignas(256) uint64_t kw[NST][kFwdBN];                // mask words of a PARTIAL tile's keys, by ring stage
+    alignas(1024) unsigned char k[NST][BN * D * 2];       // rotated tiles, see SwzTile
+    alignas(1024) unsigned char v[NST][BN * D * 2];
+    alignas(256) uint64_t kw[NST][BN];                    // mask words of a PARTIAL tile's keys, by ring stage
 };
 
-// HPW query heads per workgroup (4 wavefronts each), NST LDS stages.  At D = 128 one workgroup
-// per CU (LDS), so HPW wavefronts per SIMD.  At D = 64 a tile has half the matrix instructions
+// HPW query heads per workgroup (4 wavefronts each), NST LDS stages of a k-tile, or of half a
+// one (HALF).  At D = 128 two heads that read the same keys share a workgroup of eight
+// wavefronts and a ring of four tiles (130 KiB, one workgroup per CU).  An odd number of query
+// heads per KV head leaves one head per workgroup of four: its ring is four half tiles (65 KiB),
+// so that two workgroups, each with barriers of its own, put the same two wavefronts on a
+// SIMD.  Measured there (whole calls) against a ring of three tiles, one workgroup per CU: 8192
+// tokens, 32 / 32 heads 757 -> 646 us, 24 / 8 heads 530 -> 450 us; used for pairs of heads too it
+// is 4 % (8192 tokens) to 6 % (32768) slower than their shared ring, since every head then
+// transfers its own tiles.  A workgroup of 256 rows of one head, sharing a ring of four tiles,
+// was 1 % to 3 % faster on long samples and 27 % slower on a packed share.
+// At D = 64 a tile has half the matrix instructions
 // under the same exponentials, so the vector work is the bound and more wavefronts per SIMD
 // help: one head per workgroup with three stages (50 KiB) and at most 168 registers puts three
 // workgroups on a CU.  Measured there (whole calls): 8192 tokens, 32 / 8 heads 341 us with two
 // heads per workgroup, 316 us so; 32768 tokens with a 4096 window, 16 heads 695 us with 205
 // registers (two workgroups per CU), 618 us so.
 constexpr int fwd_heads_per_wg(int D, int rep) { return D == 128 && rep % 2 == 0 ? 2 : 1; }
-template <int D, int HPW, int NST>
-__global__ void __launch_bounds__(256 * HPW, D == 64 ? 3 : HPW)
+template <int D, int HPW, int NST, bool HALF>
+__global__ void __launch_bounds__(256 * HPW, D == 64 ? 3 : 2)
 fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
            const ushort_t* __restrict__ V, const uint64_t* __restrict__ bits,
            const int32_t* __restrict__ blocks, int32_t block, int64_t n_loc, int64_t S,
@@ -153,10 +163,11 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
     using KT = SwzTile<D, 1>;             // K: 16-byte row fragments
     using VT = SwzTile<D, 4>;             // V: transpose reads
     constexpr int RB = D * 2;
-    constexpr int kStageBytes = kFwdBN * RB;
+    constexpr int BN = HALF ? kFwdBN / 2 : kFwdBN;   // keys per ring stage
+    constexpr int kStageBytes = BN * RB;
     constexpr int NI = kStageBytes / 1024 / NW;      // 1 KiB transfers per wave per tensor
     static_assert(NI >= 1, "tile too small for this many wavefronts");
-    __shared__ FwdSmem<D, NST> sm;
+    __shared__ FwdSmem<D, NST, BN> sm;
     // The loads that find the work item form a chain (error flag, q-tile of this rank,
     // its list length, the list, the tiles); the independent ones are issued together and
     // the early exits are taken after the row's own loads have been issued, so that a
@@ -265,6 +276,19 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
         if ((entry & kPartialFlag) && wave < 2)
             dma4(bits + k0, (uint32_t)(wave * 256 + lane * 4), lds_kw + stage * (8 * kFwdBN) + wave * 256);
     };
+    // HALF: one half tile (32 keys) of K, with the mask words of its keys, or of V
+    auto issue_k = [&](uint32_t entry, int half, int stage) {
+        const int64_t k0 = (int64_t)(entry & ~kPartialFlag) * kFwdBN + half * 32;
+        const ushort_t* kt = K + k0 * Hkv_s * D;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) dma16(kt, gk[i], lds_k + stage * kStageBytes + i * 1024);
+        if ((entry & kPartialFlag) && wave == 0) dma4(bits + k0, (uint32_t)(lane * 4), lds_kw + stage * (8 * BN));
+    };
+    auto issue_v = [&](uint32_t entry, int half, int stage) {
+        const ushort_t* vt = V + ((int64_t)(entry & ~kPartialFlag) * kFwdBN + half * 32) * Hkv_s * D;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) dma16(vt, gv[i], lds_v + stage * kStageBytes + i * 1024);
+    };
 
     // ---- LDS read offsets (bytes) ---------------------------------------------------
     // (LDS byte addresses inside stage 0; stage, half tile and key-row offsets are
@@ -347,7 +371,8 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
         for (int r = 0; r < 16; ++r) s[r] *= scale_log2;
     };
     // (the query-side parts of the predicate, window included, are per-lane constants here)
-    // `kw_off`: byte offset of the tile's mask words in sm.kw (its ring stage)
+    // `kw_off`: byte offset of the tile's mask words in sm.kw (its ring stage; of the tile's first
+    // key there even where only its second half is staged)
     typedef const uint64_t __attribute__((address_space(3))) * lds_u8;
     auto mask_scores = [&](uint32_t entry, int kw_off, int kb, floatx16& s) __attribute__((always_inline)) {
         if (__builtin_expect((entry & kPartialFlag) != 0u, 0)) {   // workgroup-uniform; FULL tiles fall through
@@ -507,6 +532,88 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
         else wait_vmcnt<0>();
     };
 
+    // HALF: the walk with a ring of four half-tile stages for K and one for V.  While step u
+    // forms the scores of half tile u+1 and multiplies the probabilities of half tile u into O,
+    // K of u+1, u+2 and V of u are resident; K of u+4 goes where K of u was, V of u+3 where V of
+    // u-1 was, so a K transfer has two steps to land and a V transfer three.
+    auto walk_half = [&](auto TRACK_) __attribute__((always_inline)) {
+        constexpr bool TRACK = decltype(TRACK_)::value;
+        uint32_t e0 = 0u, e1 = 0u;             // list entries of tiles j and j+1
+        floatx16 s_a, s_b;
+        bf16x8 kf[NKF];
+        if (n_active > 0) {
+            e0 = entry_at(0);
+            issue_k(e0, 0, 0);
+            issue_k(e0, 1, 1);
+            issue_v(e0, 0, 0);
+            if (n_active > 1) {
+                e1 = entry_at(1);
+                issue_k(e1, 0, 2);
+                issue_v(e0, 1, 1);
+                issue_k(e1, 1, 3);
+                issue_v(e1, 0, 2);
+                wait_vmcnt<3 * NI>();
+            } else {
+                issue_v(e0, 1, 1);
+                wait_vmcnt<0>();
+            }
+            __syncthreads();
+            scores(0, s_a);
+            mask_scores(e0, 0, 0, s_a);
+            if (TRACK) {
+                float m_loc = -INFINITY;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) m_loc = fmaxf(m_loc, s_a[r]);
+                new_max(pair_max(m_loc), s_a);
+            }
+#pragma unroll
+            for (int i = 0; i < NKF; ++i) kf[i] = read_k(kStageBytes, i);
+        }
+        // tile j, whose halves lie in stages st and st+1 (st = 0 or 2)
+        auto tile = [&](auto STEADY_, int j, int st) __attribute__((always_inline)) {
+            constexpr bool STEADY = decltype(STEADY_)::value;     // tile j+2 exists
+            const bool more = STEADY || j + 1 < n_active, ahead = STEADY || j + 2 < n_active;
+            const int st1 = st + 1, st2 = (st + 2) & 3, st3 = (st + 3) & 3;
+            // the transfers that may still be in flight: V of u+1, K of u+3, V of u+2
+            if (STEADY) wait_vmcnt<3 * NI>();
+            else wait_vmcnt<0>();
+            __syncthreads();
+            uint32_t fresh = 0u;
+            if (ahead) {
+                if (((j + 2) & 63) == 0) {
+                    const int i = j + 2 + lane;
+                    list_chunk = i < n_active ? klist[i] : 0u;
+                    wait_vmcnt<0>();       // awaited here so that no wait is needed after the branch
+                }
+                fresh = entry_at(j + 2);
+                issue_k(fresh, 0, st);
+            }
+            if (more) issue_v(e1, 1, st3);
+            step(TRACK_, st1 * kStageBytes, s_b, s_a, st * kStageBytes, st2 * kStageBytes, kf, e0,
+                 st1 * (8 * BN) - 256, 1, true);
+            if (STEADY) wait_vmcnt<3 * NI>();
+            else wait_vmcnt<0>();
+            __syncthreads();
+            if (ahead) {
+                issue_k(fresh, 1, st1);
+                issue_v(fresh, 0, st);
+            }
+            step(TRACK_, st2 * kStageBytes, s_a, s_b, st1 * kStageBytes, st3 * kStageBytes, kf,
+                 more ? e1 : 0u, st2 * (8 * BN), 0, more);
+            e0 = e1;
+            e1 = fresh;
+        };
+        int j0 = 0;
+        for (; j0 + 4 <= n_active; j0 += 2) {
+            tile(std::true_type{}, j0, 0);
+            tile(std::true_type{}, j0 + 1, 2);
+        }
+        for (; j0 < n_active; j0 += 2) {
+            tile(std::false_type{}, j0, 0);
+            if (j0 + 1 < n_active) tile(std::false_type{}, j0 + 1, 2);
+        }
+    };
+
     // the whole walk over the active tiles, once with and once without maximum tracking
     auto walk = [&](auto TRACK_) __attribute__((always_inline)) {
         constexpr bool TRACK = decltype(TRACK_)::value;
@@ -588,8 +695,13 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
             }
         }
     };
-    if (tracked) walk(std::true_type{});
-    else walk(std::false_type{});
+    if constexpr (HALF) {
+        if (tracked) walk_half(std::true_type{});
+        else walk_half(std::false_type{});
+    } else {
+        if (tracked) walk(std::true_type{});
+        else walk(std::false_type{});
+    }
 #undef MM_SLOT_END
     // ---- epilogue -----------------------------------------------------------------
     const float l_tot = l_run + __shfl_xor(l_run, 32);
@@ -725,7 +837,7 @@ size_t fwd_heads_workspace(int64_t S, int64_t n_loc, int32_t Hq, int32_t Hkv, in
     return most;
 }
 
-template <int D, int HPW, int NST>
+template <int D, int HPW, int NST, bool HALF>
 static void launch_fwd_kernel(const AttnArgs& a, int64_t n_loc, int32_t nq, float scale_log2,
                               const int32_t* clean, const TilePlan& plan, const FwdSplit& split,
                               const int32_t* err, const float* knorm, void* o, float* lse, float* opart,
@@ -733,7 +845,7 @@ static void launch_fwd_kernel(const AttnArgs& a, int64_t n_loc, int32_t nq, floa
     const int32_t rep = a.Hq / a.Hkv, Hq_run = rep * a.kv_count;
     const int64_t qo = (int64_t)a.kv_begin * rep * a.D, ko = (int64_t)a.kv_begin * a.D;
     const unsigned grid = (unsigned)((int64_t)nq * Hq_run / HPW * split.cmax);
-    hipLaunchKernelGGL((fwd_kernel<D, HPW, NST>), dim3(grid), dim3(256 * HPW), 0, st,
+    hipLaunchKernelGGL((fwd_kernel<D, HPW, NST, HALF>), dim3(grid), dim3(256 * HPW), 0, st,
                        (const ushort_t*)a.q + qo, (const ushort_t*)a.k + ko, (const ushort_t*)a.v + ko,
                        a.bits, clean, a.block, n_loc, a.S, Hq_run, a.kv_count, a.Hq, a.Hkv, scale_log2,
                        plan, split, err, knorm, (ushort_t*)o + qo, lse + (int64_t)a.kv_begin * rep * n_loc,
@@ -820,10 +932,10 @@ int launch_fwd(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st)
     }
     stage_begin(MMATTN_STAGE_FWD, st);
     if (a.D == 128) {
-        if (hpw == 2) launch_fwd_kernel<128, 2, 4>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
-        else          launch_fwd_kernel<128, 1, 3>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
+        if (hpw == 2) launch_fwd_kernel<128, 2, 4, false>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
+        else          launch_fwd_kernel<128, 1, 4, true>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
     } else {
-        launch_fwd_kernel<64, 1, 3>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
+        launch_fwd_kernel<64, 1, 3, false>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
     }
     if (L.split.cmax > 1) {
         const int32_t Hq_run = rep * a.kv_count;

@@ -58,6 +58,30 @@ def run_case(lay, blocks, block, Hq, Hkv, D, seed, heads=None, rows_sample=None)
     return o, lse, t
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(1, 1, 128), (3, 1, 128), (2, 1, 64), (1, 1, 64)])
+@pytest.mark.parametrize("sharp", [1.0, 20.0])
+def test_one_head_per_workgroup_list_lengths(Hq, Hkv, D, sharp):
+    """Heads without a partner in their workgroup: a block that sees 1, 2, ... 16 key tiles
+    (lists up to 8 tiles stay whole, longer ones are cut), with and without tracking of the
+    running maximum (a sharp softmax needs it), ragged 64-row shares."""
+    lay = wl.Layout(1024, [(130, 60, 1), (500, 200, 2)], [0, 1024])
+    f, bits = fields(lay), gpu_bits(lay)
+    t = make_tensors(88, 64, 1024, Hq, Hkv, D)
+    Q, K, V = f64(t["q_bits"]), f64(t["k_bits"]), f64(t["v_bits"])
+    scale = sharp / np.sqrt(D)
+    for b in range(16):
+        o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, torch.tensor([b], dtype=torch.int32, device=DEV), 64, scale=scale)
+        oo, ll = oa.forward(Q, K, V, oa.rows_of_blocks([b], 64), f[0], f[1], f[2], modality=f[3], attend=f[4], scale=scale)
+        assert max_abs(bf16_to_f64(o), oo) < TOL_MAX and rel_l2(bf16_to_f64(o), oo) < TOL_L2, b
+        assert max_abs(lse.cpu().numpy().astype(np.float64), ll) < TOL_LSE, b
+
+
+def test_one_head_per_workgroup_long_lists():
+    """The same heads with lists of up to 130 tiles in one piece (fetched 64 entries at a time)."""
+    run_case(wl.layout_random(89, S=8320, max_spans=3), [1, 9, 17, 21, 25, 31, 32, 40, 47, 50, 55, 58, 60, 61, 63, 64], 128,
+             Hq=32, Hkv=32, D=128, seed=89, heads=[0, 31])
+
+
 def test_shared_question_and_block_causal():
     """Two patterns named in section 5.5: answers that see the question and
     themselves only (spans without the bidirectional term), and blocks that are
