@@ -62,15 +62,27 @@ key_norm_body(int chunk, int g, const ushort_t* __restrict__ K, int64_t S, int32
     __shared__ float wmax[4];
     const int64_t per = S / kNormChunks, k0 = chunk * per;
     const int sub = threadIdx.x % TPK, kk = threadIdx.x / TPK;
+    // kAhead keys per thread in flight: with one, the pass was bound by the latency of its
+    // loads (4 of 8 heads of 32768 keys: 18 -> 10 us)
+    constexpr int kAhead = 8;
     float best = 0.f;
-    for (int64_t k = kk; k < per; k += KPP) {
-        const bf16x8 x = __builtin_bit_cast(bf16x8, *(const u32x4*)(K + ((k0 + k) * Hkv_s + g) * (int64_t)D + sub * 8));
-        float a = 0.f;
+    for (int64_t k = kk; k < per; k += kAhead * KPP) {
+        u32x4 raw[kAhead];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) a += (float)x[u] * (float)x[u];
+        for (int i = 0; i < kAhead; ++i) {
+            raw[i] = u32x4{0u, 0u, 0u, 0u};
+            if (k + i * KPP < per) raw[i] = *(const u32x4*)(K + ((k0 + k + i * KPP) * Hkv_s + g) * (int64_t)D + sub * 8);
+        }
 #pragma unroll
-        for (int off = TPK / 2; off > 0; off >>= 1) a += __shfl_xor(a, off);
-        best = fmaxf(best, a);                            // a NaN norm is dropped here and caught by the row bound
+        for (int i = 0; i < kAhead; ++i) {
+            const bf16x8 x = __builtin_bit_cast(bf16x8, raw[i]);
+            float a = 0.f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) a += (float)x[u] * (float)x[u];
+#pragma unroll
+            for (int off = TPK / 2; off > 0; off >>= 1) a += __shfl_xor(a, off);
+            best = fmaxf(best, a);                        // a NaN norm is dropped here and caught by the row bound
+        }
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) best = fmaxf(best, __shfl_xor(best, off));
