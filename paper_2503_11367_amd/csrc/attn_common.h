@@ -201,7 +201,11 @@ struct FwdSplit {
 // length would need for about 1024 workgroups.  The slice length itself is chosen on the device from the
 // actual list lengths (slice_length below) and is never shorter than csz.
 // `groups`: workgroups per q-tile (head groups).
-inline FwdSplit list_split(int32_t nq, int32_t nk, int32_t groups) {
+//
+// list_room: what the partial buffers are sized for; list_split: what is launched, fewer where
+// slice_length cannot cut that far (slices of at least four tiles, lists of at most eight never)
+// and none at all, nor an aggregation launch (4 us), when no list can be cut.
+inline FwdSplit list_room(int32_t nq, int32_t nk, int32_t groups) {
     const int64_t items = (int64_t)nq * groups;
     int64_t cmax = 1;
     if (items < 512) {
@@ -215,6 +219,16 @@ inline FwdSplit list_split(int32_t nq, int32_t nk, int32_t groups) {
     sp.cmax = (nk + sp.csz - 1) / sp.csz;                     // no empty trailing slices
     return sp;
 }
+constexpr int32_t kWholeList = 8, kShortSlice = 4;
+inline FwdSplit list_split(int32_t nq, int32_t nk, int32_t groups) {
+    FwdSplit sp = list_room(nq, nk, groups);
+    const int32_t most = nk <= kWholeList ? 1 : (nk + kShortSlice - 1) / kShortSlice;
+    if (sp.cmax > most) {
+        sp.csz = (nk + most - 1) / most;
+        sp.cmax = (nk + sp.csz - 1) / sp.csz;
+    }
+    return sp;
+}
 // Slice length from the lists themselves (total entries, longest list, non-empty
 // lists; `groups` workgroups walk every list).
 //   Lists of about equal length: a quarter of one CU's share of all entries, i.e. about
@@ -222,7 +236,10 @@ inline FwdSplit list_split(int32_t nq, int32_t nk, int32_t groups) {
 //   Uneven lists: the slices that finish last cost about one slice of time, while every
 //   slice costs a fixed amount of bandwidth for its partial result (worth about 1/32 of
 //   a tile's time across the chip); c + W/(32 c) is smallest at c = sqrt(W/32).
-// At least 8 tiles, at most the whole list.
+// At least 8 tiles, at most the whole list.  When there are fewer than three tiles per CU, at
+// least 4, for then most CUs have nothing to do: half of 1920 tokens with 6 heads (480 tiles)
+// 28 -> 22 us in the forward, 34 -> 28 us in the dQ pass.  With four tiles per CU (4096 tokens, a
+// rank of four, 8 heads) the longer sums of the aggregation already cost more, 59 -> 65 us.
 __host__ __device__ inline int32_t slice_length(int64_t total, int32_t longest, int32_t lists,
                                                 int32_t groups, int32_t nk) {
     const int64_t work = total * groups;
@@ -232,7 +249,8 @@ __host__ __device__ inline int32_t slice_length(int64_t total, int32_t longest, 
     } else {
         c = (int64_t)__builtin_sqrtf((float)work / 32.0f) + 1;
     }
-    if (c < 8) c = 8;
+    const int32_t least = longest > kWholeList && work < 3 * 256 ? kShortSlice : kWholeList;
+    if (c < least) c = least;
     if (c > nk) c = nk;
     return (int32_t)c;
 }

@@ -820,7 +820,7 @@ static FwdLayout fwd_layout(int64_t S, int64_t n_loc, int32_t n_blocks, int32_t 
     L.split = list_split(L.nq, L.nk, Hq_run / fwd_heads_per_wg(D, rep));
     // the partial results have room for the slices that pairs of heads would be cut into at
     // either head dim (never fewer)
-    const FwdSplit room = list_split(L.nq, L.nk, Hq_run / (rep % 2 == 0 ? 2 : 1));
+    const FwdSplit room = list_room(L.nq, L.nk, Hq_run / (rep % 2 == 0 ? 2 : 1));
     size_t off = 0;
     L.err = off;          off += 256;
     L.clean_blocks = off; off += align_up((size_t)n_blocks * 4, 256);
