@@ -1206,8 +1206,16 @@ dq_combine_kernel(TilePlan plan, FwdSplit split, int64_t n_loc, int64_t n_pad, i
     const int nchunk = max(1, (kc_total + csz - 1) / csz);
     if (nchunk == 1) return;              // written by dq_kernel itself
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < nchunk; ++c)
-        acc += *(const floatx4*)(dQpart + (((int64_t)c * n_pad + row) * Hq + h) * D + d0);
+    constexpr int kBatch = 8;             // slices whose loads are in flight together
+    for (int c0 = 0; c0 < nchunk; c0 += kBatch) {
+        floatx4 part[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            part[u] = c0 + u < nchunk ? *(const floatx4*)(dQpart + (((int64_t)(c0 + u) * n_pad + row) * Hq + h) * D + d0)
+                                      : floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) acc += part[u];
+    }
     bf16x4 out;
 #pragma unroll
     for (int u = 0; u < 4; ++u) out[u] = (__bf16)acc[u];

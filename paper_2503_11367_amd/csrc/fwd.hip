@@ -776,21 +776,41 @@ fwd_combine_kernel(TilePlan plan, FwdSplit split, int64_t n_loc, int32_t Hq, int
     const int nchunk = max(1, (kc_total + csz - 1) / csz);
     if (nchunk == 1) return;              // written by the attention kernel itself
     const int64_t rows = (int64_t)plan.nq * kFwdBM;
+    // the slices' shifts and row sums, then their outputs, kBatch slices' loads in flight together
+    // (one after the other each costs a round trip to memory: eight query tiles of 4 heads in 16
+    // slices 11.8 -> 6.3 us)
+    constexpr int kBatch = 8;
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    auto fetch_ml = [&](int c0, floatx2 (&ml)[kBatch]) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            ml[u] = c0 + u < nchunk ? *(const floatx2*)(MLpart + (((int64_t)(c0 + u) * rows + row) * Hq + h) * 2)
+                                    : floatx2{0.f, 0.f};
+    };
     float m = -INFINITY;
-    for (int c = 0; c < nchunk; ++c) {
-        const float* ml = MLpart + (((int64_t)c * rows + row) * Hq + h) * 2;
-        if (ml[1] > 0.f) m = fmaxf(m, ml[0]);
+    floatx2 ml[kBatch];
+    for (int c0 = 0; c0 < nchunk; c0 += kBatch) {
+        fetch_ml(c0, ml);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            if (ml[u][1] > 0.f) m = fmaxf(m, ml[u][0]);
     }
     floatx4 num = {0.f, 0.f, 0.f, 0.f};
     float den = 0.f;
-    for (int c = 0; c < nchunk; ++c) {
-        const int64_t pr = ((int64_t)c * rows + row) * Hq + h;
-        const float lc = MLpart[pr * 2 + 1];
-        if (!(lc > 0.f)) continue;
-        const float w = __builtin_amdgcn_exp2f(MLpart[pr * 2] - m);
-        const floatx4 oc = *(const floatx4*)(Opart + pr * D + d0);
-        num += oc * w;
-        den += lc * w;
+    for (int c0 = 0; c0 < nchunk; c0 += kBatch) {
+        floatx4 oc[kBatch];
+        if (nchunk > kBatch) fetch_ml(c0, ml);           // else they are still here
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            if (c0 + u < nchunk) oc[u] = *(const floatx4*)(Opart + (((int64_t)(c0 + u) * rows + row) * Hq + h) * D + d0);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const float lc = ml[u][1];
+            if (!(lc > 0.f)) continue;                   // also past the last slice
+            const float w = __builtin_amdgcn_exp2f(ml[u][0] - m);
+            num += oc[u] * w;
+            den += lc * w;
+        }
     }
     const float inv = den > 0.f ? 1.f / den : 0.f;
     bf16x4 out;
