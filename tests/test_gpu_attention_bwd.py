@@ -132,6 +132,15 @@ def test_tiny_every_rank_share():
     run_case(w.layout, list(range(8)), w.N_B, w.Hq, w.Hkv, w.D, seed=10)
 
 
+def test_more_key_lists_than_one_ranking_pass():
+    """2064 key tiles (the ranking takes 2048 at a time) of which a handful have work: samples of
+    64 tokens, blocks spread over the sequence."""
+    S = 2064 * 128
+    lay = wl.Layout(S, [(64 * 70 + 5, 30, 1)], list(range(0, S + 1, 64)))
+    assert len(lay.sample_off) - 1 <= 65535
+    run_case(lay, [S // 64 - 1, 70, 2048], 64, Hq=1, Hkv=1, D=64, seed=98)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("seed", range(4))
 def test_random_layouts(seed, D):
