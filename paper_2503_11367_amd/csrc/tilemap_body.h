@@ -225,27 +225,29 @@ tile_map_body(uint32_t wg_index, const uint64_t* __restrict__ bits,
             const int32_t i = i0 + (p >> log_gk), j = j0 + (p & (gk - 1));
             const int64_t rows = rows_of(i), k0 = (int64_t)j * tk;
             uint32_t part = 0;
-            // (the first 64 keys' words, and the next row's, are requested ahead of their use)
-            const uint64_t wk0 = lane < tk ? bits[k0 + lane] : 0;
-            int64_t q_next = 0;
-            uint64_t w_next = 0;
-            auto fetch_row = [&](int64_t r) {
-                if (r < rows) {
-                    q_next = pos_of((int64_t)i * tq + r);
-                    w_next = bits[q_next];
+            // up to 256 rows at a time in registers, their words in flight together; the next 64
+            // keys' words are requested ahead of their use
+            constexpr int kRows = 4;
+            for (int64_t r0 = 0; r0 < rows; r0 += kRows * kWave) {
+                int64_t q[kRows];
+                uint64_t wq[kRows];
+                const int n_r = (int)min((int64_t)kRows, (rows - r0 + kWave - 1) / kWave);
+#pragma unroll
+                for (int u = 0; u < kRows; ++u) {
+                    q[u] = 0;
+                    wq[u] = 0;                               // (a word of zeros sees nothing)
+                    const int64_t r = r0 + u * kWave + lane;
+                    if (u < n_r && r < rows) {
+                        q[u] = pos_of((int64_t)i * tq + r);
+                        wq[u] = bits[q[u]];
+                    }
                 }
-            };
-            fetch_row(lane);
-            for (int64_t r = 0; r < rows; r += kWave) {
-                const bool row_ok = r + lane < rows;
-                const int64_t q = q_next;
-                const uint32_t ss_q = word_ss(w_next), att = word_att(w_next);
-                fetch_row(r + kWave + lane);
-                const uint32_t win = att_window(att), own = att_modality(att);
+                uint64_t wk_next = lane < tk ? bits[k0 + lane] : 0;
                 for (int kc = 0; kc < tk; kc += kWave) {
                     // run starts among these keys: a key whose fields differ from its predecessor's
                     const int n_keys = min(kWave, tk - kc);
-                    const uint64_t wk = kc == 0 ? wk0 : (lane < n_keys ? bits[k0 + kc + lane] : 0);
+                    const uint64_t wk = wk_next;
+                    if (kc + kWave < tk) wk_next = kc + kWave + lane < tk ? bits[k0 + kc + kWave + lane] : 0;
                     const uint32_t ss_k = word_ss(wk), mod_k = word_mod(wk);
                     const uint32_t b_ss = lane_below(ss_k, 0u), b_mod = lane_below(mod_k, 0u);
                     const bool starts = lane < n_keys && (lane == 0 || ss_k != b_ss || mod_k != b_mod);
@@ -257,14 +259,20 @@ tile_map_body(uint32_t wg_index, const uint64_t* __restrict__ bits,
                         const uint32_t ss_r = (uint32_t)__builtin_amdgcn_readlane((int)ss_k, a);
                         const uint32_t mod_r = (uint32_t)__builtin_amdgcn_readlane((int)mod_k, a);
                         const int64_t first = k0 + kc + a, len = b - a;
-                        const bool same_span = (ss_q & 0xFFFFu) != 0 && ss_q == ss_r;
-                        const bool back = (ss_q >> 16) == (ss_r >> 16) && ((att >> mod_r) & 1u);
-                        // keys of the run at or before the row's position, minus those a look-back
-                        // window over the row's own modality cuts off
-                        const int64_t upto = max((int64_t)0, min(q - first + 1, len));
-                        const bool windowed = win != 0 && mod_r == own;
-                        const int64_t cut = windowed ? max((int64_t)0, min(q - (int64_t)win + 1 - first, len)) : 0;
-                        if (row_ok) part += (uint32_t)(same_span ? len : (back ? upto - cut : 0));
+#pragma unroll
+                        for (int u = 0; u < kRows; ++u) {
+                            if (u >= n_r) continue;          // wave-uniform
+                            const uint32_t ss_q = word_ss(wq[u]), att = word_att(wq[u]);
+                            const bool same_span = (ss_q & 0xFFFFu) != 0 && ss_q == ss_r;
+                            const bool back = (ss_q >> 16) == (ss_r >> 16) && ((att >> mod_r) & 1u);
+                            // keys of the run at or before the row's position, minus those a look-back
+                            // window over the row's own modality cuts off
+                            const int64_t upto = max((int64_t)0, min(q[u] - first + 1, len));
+                            const uint32_t win = att_window(att);
+                            const bool windowed = win != 0 && mod_r == att_modality(att);
+                            const int64_t cut = windowed ? max((int64_t)0, min(q[u] - (int64_t)win + 1 - first, len)) : 0;
+                            part += (uint32_t)(same_span ? len : (back ? upto - cut : 0));
+                        }
                     }
                 }
             }
