@@ -278,7 +278,6 @@ constexpr int kSliceLen = 0, kSlicedTiles = 1, kExtraUsed = 2, kSliceInts = 4;
 // The kFlagInts int32 words at `err` (cleared by validate_blocks_body) are the error flag and
 // spare words; the word after them holds the slice length chosen by the list builder.
 int launch_compact_rows(const TilePlan& p, hipStream_t st);
-int launch_compact_cols(const TilePlanT& p, hipStream_t st);
 int launch_compact_both(const TilePlan& pa, const TilePlanT& pb, hipStream_t st);
 
 }  // namespace mm
