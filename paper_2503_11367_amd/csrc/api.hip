@@ -212,11 +212,14 @@ int mmattn_fwd_staged(const void* q_loc, const void* k_src, const void* v_src, v
         if (ok(hipEventCreateWithFlags(&arrived[i], hipEventDisableTiming)))
             ok(hipEventRecord(arrived[i], cs));
     }
+    // the plan needs neither keys nor values: it is built while the first window arrives (32768
+    // keys, two windows of four heads: 2011 -> 2001 us against building it behind the first wait)
+    AttnArgs a{q_loc, k_stage, v_stage, bits, blocks, n_blocks, block, S, Hq, Hkv, D, scale, 0, heads_per_stage, 1};
+    if (rc == MMATTN_OK && n_blocks > 0) rc = launch_fwd_plan(a, ws, st);
     for (int i = 0; i < n_stage && rc == MMATTN_OK; ++i) {
         if (!ok(hipStreamWaitEvent(st, arrived[i], 0))) break;
         if (n_blocks == 0) continue;
-        AttnArgs a{q_loc, k_stage, v_stage, bits, blocks, n_blocks, block, S, Hq, Hkv, D, scale,
-                   i * heads_per_stage, heads_per_stage, i > 0};
+        a.kv_begin = i * heads_per_stage;
         rc = launch_fwd(a, o_loc, lse, ws, st);
     }
     // on an error part-way, `stream` still has to wait for whatever the copy stream was given

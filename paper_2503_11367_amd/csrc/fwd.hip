@@ -917,50 +917,78 @@ int launch_fwd_static(const AttnArgs& a, void* o, float* lse, hipStream_t st) {
     return launch_fwd(a, o, lse, ptr, st);
 }
 
+// Where a call's scratch lies in `ws`, and the plan in it
+struct FwdScratch {
+    FwdLayout L;
+    TilePlan plan;
+    int32_t *err, *clean;
+    float *knorm, *opart, *mlpart;
+};
+static FwdScratch fwd_scratch(const AttnArgs& a, void* ws) {
+    const int64_t n_loc = (int64_t)a.n_blocks * a.block;
+    FwdScratch s;
+    s.L = fwd_layout(a.S, n_loc, (int32_t)(n_loc / 16 + 1), a.Hq, a.Hkv, a.D, a.kv_count);
+    char* base = (char*)ws;
+    s.err = (int32_t*)(base + s.L.err);
+    s.clean = (int32_t*)(base + s.L.clean_blocks);
+    // largest key norms of the window's heads (data, not plan: every call)
+    s.knorm = (float*)(base + s.L.knorm) + (int64_t)a.kv_begin * kNormChunks;
+    s.opart = (float*)(base + s.L.opart);
+    s.mlpart = (float*)(base + s.L.mlpart);
+    TilePlan& plan = s.plan;
+    plan.nq = s.L.nq; plan.nk = s.L.nk; plan.tq = kFwdBM; plan.tk = kFwdBN;
+    plan.cls = (uint8_t*)(base + s.L.cls);
+    plan.kcount = (int32_t*)(base + s.L.kcount);
+    plan.klist = (uint32_t*)(base + s.L.klist);
+    plan.qorder = (int32_t*)(base + s.L.qorder);
+    plan.csz = s.err + kFlagInts;
+    const int32_t rep = a.Hq / a.Hkv;
+    plan.groups = rep * a.kv_count / fwd_heads_per_wg(a.D, rep);
+    return s;
+}
+
+// the plan of the share, and the key norms of `norm_heads` KV heads from a.kv_begin on
+static int launch_fwd_prologue(const AttnArgs& a, const FwdScratch& s, int32_t norm_heads, hipStream_t st) {
+    const int64_t n_loc = (int64_t)a.n_blocks * a.block;
+    FwdPrologue p;
+    p.maps.j[0] = p.maps.j[1] = tile_map_job(a.S, n_loc, kFwdBM, kFwdBN, s.plan.cls, nullptr);
+    p.n_map_wgs = tile_map_workgroups(p.maps, 1);
+    p.bits = a.bits; p.blocks = a.blocks; p.n_blocks = a.n_blocks; p.block = a.block;
+    p.n_seq_blocks = a.S / a.block; p.n_rows = n_loc;
+    p.clean = s.clean; p.err = s.err;
+    p.K = (const ushort_t*)a.k + (int64_t)a.kv_begin * a.D; p.S = a.S; p.Hkv_s = a.Hkv; p.knorm = s.knorm;
+    const unsigned grid = p.n_map_wgs + 1u + (unsigned)(kNormChunks * norm_heads);
+    if (a.D == 128) hipLaunchKernelGGL(fwd_prologue_kernel<128>, dim3(grid), dim3(256), 0, st, p);
+    else            hipLaunchKernelGGL(fwd_prologue_kernel<64>, dim3(grid), dim3(256), 0, st, p);
+    MM_LAUNCH_CHECK();
+    return launch_compact_rows(s.plan, st);
+}
+
+int launch_fwd_plan(const AttnArgs& a, void* ws, hipStream_t st) {
+    return launch_fwd_prologue(a, fwd_scratch(a, ws), 0, st);
+}
+
 int launch_fwd(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st) {
     const int64_t n_loc = (int64_t)a.n_blocks * a.block;
-    const FwdLayout L = fwd_layout(a.S, n_loc, (int32_t)(n_loc / 16 + 1), a.Hq, a.Hkv, a.D, a.kv_count);
-    float* opart = (float*)((char*)ws + L.opart);
-    float* mlpart = (float*)((char*)ws + L.mlpart);
-    char* base = (char*)ws;
-    int32_t* err = (int32_t*)(base + L.err);
-    int32_t* clean = (int32_t*)(base + L.clean_blocks);
-    TilePlan plan;
-    plan.nq = L.nq; plan.nk = L.nk; plan.tq = kFwdBM; plan.tk = kFwdBN;
-    plan.cls = (uint8_t*)(base + L.cls);
-    plan.kcount = (int32_t*)(base + L.kcount);
-    plan.klist = (uint32_t*)(base + L.klist);
-    plan.qorder = (int32_t*)(base + L.qorder);
-    plan.csz = err + kFlagInts;
+    const FwdScratch s = fwd_scratch(a, ws);
+    const FwdLayout& L = s.L;
+    const TilePlan& plan = s.plan;
+    const int32_t *err = s.err, *clean = s.clean;
+    const float* knorm = s.knorm;
+    float *opart = s.opart, *mlpart = s.mlpart;
     const int32_t rep = a.Hq / a.Hkv;
     const int32_t hpw = fwd_heads_per_wg(a.D, rep);
-    plan.groups = rep * a.kv_count / hpw;
-
     const float scale_log2 = a.scale * kLog2e;
-    // largest key norms of the window's heads (data, not plan: every call)
-    float* knorm = (float*)(base + L.knorm) + (int64_t)a.kv_begin * kNormChunks;
-    const ushort_t* kw = (const ushort_t*)a.k + (int64_t)a.kv_begin * a.D;
     if (!a.plan_ready) {
-        FwdPrologue p;
-        p.maps.j[0] = p.maps.j[1] = tile_map_job(a.S, n_loc, kFwdBM, kFwdBN, plan.cls, nullptr);
-        p.n_map_wgs = tile_map_workgroups(p.maps, 1);
-        p.bits = a.bits; p.blocks = a.blocks; p.n_blocks = a.n_blocks; p.block = a.block;
-        p.n_seq_blocks = a.S / a.block; p.n_rows = n_loc;
-        p.clean = clean; p.err = err;
-        p.K = kw; p.S = a.S; p.Hkv_s = a.Hkv; p.knorm = knorm;
-        const unsigned grid = p.n_map_wgs + 1u + (unsigned)(kNormChunks * a.kv_count);
-        if (a.D == 128) hipLaunchKernelGGL(fwd_prologue_kernel<128>, dim3(grid), dim3(256), 0, st, p);
-        else            hipLaunchKernelGGL(fwd_prologue_kernel<64>, dim3(grid), dim3(256), 0, st, p);
-        MM_LAUNCH_CHECK();
-        const int rc = launch_compact_rows(plan, st);
+        const int rc = launch_fwd_prologue(a, s, a.kv_count, st);
         if (rc) return rc;
     } else {
+        const ushort_t* kw = (const ushort_t*)a.k + (int64_t)a.kv_begin * a.D;
+        const dim3 grid(kNormChunks, (unsigned)a.kv_count);
         if (a.D == 128)
-            hipLaunchKernelGGL(key_norm_kernel<128>, dim3(kNormChunks, (unsigned)a.kv_count), dim3(256), 0, st, kw,
-                               a.S, a.Hkv, knorm);
+            hipLaunchKernelGGL(key_norm_kernel<128>, grid, dim3(256), 0, st, kw, a.S, a.Hkv, s.knorm);
         else
-            hipLaunchKernelGGL(key_norm_kernel<64>, dim3(kNormChunks, (unsigned)a.kv_count), dim3(256), 0, st, kw,
-                               a.S, a.Hkv, knorm);
+            hipLaunchKernelGGL(key_norm_kernel<64>, grid, dim3(256), 0, st, kw, a.S, a.Hkv, s.knorm);
     }
     stage_begin(MMATTN_STAGE_FWD, st);
     if (a.D == 128) {
