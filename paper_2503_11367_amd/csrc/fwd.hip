@@ -156,7 +156,16 @@ struct FwdSmem {
 // workgroups on a CU.  Measured there (whole calls): 8192 tokens, 32 / 8 heads 341 us with two
 // heads per workgroup, 316 us so; 32768 tokens with a 4096 window, 16 heads 695 us with 205
 // registers (two workgroups per CU), 618 us so.
-constexpr int fwd_heads_per_wg(int D, int rep) { return D == 128 && rep % 2 == 0 ? 2 : 1; }
+// Pairs of heads also part ways in shares of fewer than kFwdPairItems (q-tile, pair) work items:
+// those do not fill the chip with whole lists, and twice as many smaller workgroups need fewer
+// slices and partial results.  Measured, pairs / single heads: 4096 tokens, 16 / 8 heads (256
+// pairs) 138 / 106 us, a rank of four of 8192 tokens, 32 / 8 heads (256) 203 / 181 us, a rank of 32
+// of 32768 (128) 366 / 338 us, 1920 tokens, 8 / 2 heads (60) 46 / 47 us; with whole lists 4096
+// tokens, 32 / 8 heads (512) 144 / 151 us, a rank of two of 8192 (512) 275 / 285 us.
+constexpr int64_t kFwdPairItems = 512;
+static int32_t fwd_heads_per_wg(int32_t D, int32_t rep, int32_t nq, int32_t Hq_run) {
+    return D == 128 && rep % 2 == 0 && (int64_t)nq * Hq_run / 2 >= kFwdPairItems ? 2 : 1;
+}
 template <int D, int HPW, int NST, bool HALF>
 __global__ void __launch_bounds__(256 * HPW, D == 64 ? 3 : 2)
 fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
@@ -837,9 +846,9 @@ static FwdLayout fwd_layout(int64_t S, int64_t n_loc, int32_t n_blocks, int32_t 
     L.nq = (int32_t)((n_loc + kFwdBM - 1) / kFwdBM);
     L.nk = (int32_t)(S / kFwdBN);
     const int32_t rep = Hq / Hkv;
-    L.split = list_split(L.nq, L.nk, Hq_run / fwd_heads_per_wg(D, rep));
-    // the partial results have room for the slices that pairs of heads would be cut into at
-    // either head dim (never fewer)
+    L.split = list_split(L.nq, L.nk, Hq_run / fwd_heads_per_wg(D, rep, L.nq, Hq_run));
+    // the partial results have room for the slices that pairs of heads would be cut into (never
+    // fewer)
     const FwdSplit room = list_room(L.nq, L.nk, Hq_run / (rep % 2 == 0 ? 2 : 1));
     size_t off = 0;
     L.err = off;          off += 256;
@@ -921,6 +930,7 @@ int launch_fwd_static(const AttnArgs& a, void* o, float* lse, hipStream_t st) {
 struct FwdScratch {
     FwdLayout L;
     TilePlan plan;
+    int32_t hpw;                          // query heads per workgroup
     int32_t *err, *clean;
     float *knorm, *opart, *mlpart;
 };
@@ -943,7 +953,8 @@ static FwdScratch fwd_scratch(const AttnArgs& a, void* ws) {
     plan.qorder = (int32_t*)(base + s.L.qorder);
     plan.csz = s.err + kFlagInts;
     const int32_t rep = a.Hq / a.Hkv;
-    plan.groups = rep * a.kv_count / fwd_heads_per_wg(a.D, rep);
+    s.hpw = fwd_heads_per_wg(a.D, rep, plan.nq, rep * a.kv_count);
+    plan.groups = rep * a.kv_count / s.hpw;
     return s;
 }
 
@@ -977,7 +988,6 @@ int launch_fwd(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st)
     const float* knorm = s.knorm;
     float *opart = s.opart, *mlpart = s.mlpart;
     const int32_t rep = a.Hq / a.Hkv;
-    const int32_t hpw = fwd_heads_per_wg(a.D, rep);
     const float scale_log2 = a.scale * kLog2e;
     if (!a.plan_ready) {
         const int rc = launch_fwd_prologue(a, s, a.kv_count, st);
@@ -992,8 +1002,8 @@ int launch_fwd(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st)
     }
     stage_begin(MMATTN_STAGE_FWD, st);
     if (a.D == 128) {
-        if (hpw == 2) launch_fwd_kernel<128, 2, 4, false>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
-        else          launch_fwd_kernel<128, 1, 4, true>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
+        if (s.hpw == 2) launch_fwd_kernel<128, 2, 4, false>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
+        else            launch_fwd_kernel<128, 1, 4, true>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
     } else {
         launch_fwd_kernel<64, 1, 3, false>(a, n_loc, L.nq, scale_log2, clean, plan, L.split, err, knorm, o, lse, opart, mlpart, st);
     }
