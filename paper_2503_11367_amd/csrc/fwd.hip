@@ -20,9 +20,9 @@
 // math of the current one and there is one workgroup barrier per tile.
 // The loop is a software pipeline over half tiles (32 keys): while the
 // probabilities of one half tile are exponentiated and multiplied into O, the
-// scores of the next one are already being formed.  Registers (about 230 per
-// lane) and LDS (the ring) allow one workgroup of 8 wavefronts per CU, two
-// wavefronts per SIMD, so latencies are covered inside the wave: operand
+// scores of the next one are already being formed.  Registers (about 210 per
+// lane at D = 128) and LDS (the ring) allow two wavefronts per SIMD (three at D =
+// 64; see fwd_heads_per_wg for the workgroup shapes), so latencies are covered inside the wave: operand
 // fragments are requested four MFMAs ahead and the instruction order is pinned
 // slot by slot (see `step`).
 // FULL tiles skip the predicate; PARTIAL tiles evaluate it per element from the
