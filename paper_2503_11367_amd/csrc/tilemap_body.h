@@ -86,7 +86,8 @@ tile_map_body(uint32_t wg_index, const uint64_t* __restrict__ bits,
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const bool small = gq * gk == kTmWaves;                  // workgroup-uniform
-    const bool by_runs = !small && (int64_t)nk * tk <= ((int64_t)1 << 30);      // positions fit 30 bits
+    const bool narrow = (int64_t)nk * tk <= ((int64_t)1 << 30);      // positions fit 30 bits
+    const bool by_runs = !small && narrow;
 
     // rows of q-tile i (the last one may be ragged)
     auto rows_of = [&](int32_t i) -> int64_t { return min((int64_t)tq, n_rows - (int64_t)i * tq); };
@@ -184,7 +185,93 @@ tile_map_body(uint32_t wg_index, const uint64_t* __restrict__ bits,
             J.cls[(int64_t)i * nk + j] = total == 0 ? MMATTN_TILE_EMPTY
                                          : (total == full ? MMATTN_TILE_FULL : MMATTN_TILE_PARTIAL);
     };
-    for (int p0 = 0; p0 < gq * gk; p0 += kTmThreads) {
+    // The pairs first + bit of `left`, one after the other by the whole wavefront, row by row: up to 256 rows in registers, kept while the q-tile stays the same, their words in
+    // flight together; the next 64 keys' words are requested ahead of their use.  T holds a
+    // position.  Bound by the instructions per (64 rows, run of keys): positions in 32 bits where they
+    // fit, the window's only where a row has one.  Measured on spans of 1 to 3 tokens, 32768 of
+    // them in all, against a wavefront per pair with its rows in LDS: tiles of 128 x 128 476 -> 367
+    // us, 256 x 256 528 -> 284, 16 x 16 2185 -> 774 (these by runs), 64 x 64 515 -> 586.
+    auto by_rows = [&](auto zero, uint64_t left, int first) {
+        typedef decltype(zero) T;
+        constexpr int kRows = 4;
+        T q[kRows];
+        uint32_t ss_q[kRows], att[kRows];
+        bool spans[kRows], windows = false;
+        int32_t have = -1;                                   // the q-tile whose rows are in registers
+        while (left) {
+            const int p = first + __ffsll((unsigned long long)left) - 1;
+            left &= left - 1;
+            const int32_t i = i0 + (p >> log_gk), j = j0 + (p & (gk - 1));
+            const int64_t rows = rows_of(i), k0 = (int64_t)j * tk;
+            uint32_t part = 0;
+            for (int64_t r0 = 0; r0 < rows; r0 += kRows * kWave) {
+                const int n_r = (int)min((int64_t)kRows, (rows - r0 + kWave - 1) / kWave);
+                uint64_t wk_next = lane < tk ? bits[k0 + lane] : 0;
+                if (have != i || rows > kRows * kWave) {     // wave-uniform
+                    have = i;
+                    uint64_t w[kRows];
+#pragma unroll
+                    for (int u = 0; u < kRows; ++u) {
+                        q[u] = 0;
+                        w[u] = 0;                            // (a word of zeros sees nothing)
+                        const int64_t r = r0 + u * kWave + lane;
+                        if (u < n_r && r < rows) {
+                            const int64_t pos = pos_of((int64_t)i * tq + r);
+                            q[u] = (T)pos;
+                            w[u] = bits[pos];
+                        }
+                    }
+                    bool any = false;
+#pragma unroll
+                    for (int u = 0; u < kRows; ++u) {
+                        ss_q[u] = word_ss(w[u]);
+                        att[u] = word_att(w[u]);
+                        spans[u] = (ss_q[u] & 0xFFFFu) != 0u;
+                        any = any || att_window(att[u]) != 0u;
+                    }
+                    windows = __any(any);
+                }
+                for (int kc = 0; kc < tk; kc += kWave) {
+                    // run starts among these keys: a key whose fields differ from its predecessor's
+                    const int n_keys = min(kWave, tk - kc);
+                    const uint64_t wk = wk_next;
+                    if (kc + kWave < tk) wk_next = kc + kWave + lane < tk ? bits[k0 + kc + kWave + lane] : 0;
+                    const uint32_t ss_k = word_ss(wk), mod_k = word_mod(wk);
+                    const uint32_t b_ss = lane_below(ss_k, 0u), b_mod = lane_below(mod_k, 0u);
+                    const bool starts = lane < n_keys && (lane == 0 || ss_k != b_ss || mod_k != b_mod);
+                    uint64_t m = __ballot(starts);
+                    while (m) {
+                        const int a = __ffsll((unsigned long long)m) - 1;
+                        m &= m - 1;
+                        const int b = m ? __ffsll((unsigned long long)m) - 1 : n_keys;   // the run is keys a..b-1
+                        const uint32_t ss_r = (uint32_t)__builtin_amdgcn_readlane((int)ss_k, a);
+                        const uint32_t mod_r = (uint32_t)__builtin_amdgcn_readlane((int)mod_k, a);
+                        const T before = (T)(k0 + kc + a - 1), len = (T)(b - a);
+#pragma unroll
+                        for (int u = 0; u < kRows; ++u) {
+                            if (u >= n_r) continue;          // wave-uniform
+                            const bool same_span = spans[u] && ss_q[u] == ss_r;
+                            const bool back = (ss_q[u] >> 16) == (ss_r >> 16) && ((att[u] >> mod_r) & 1u);
+                            // keys of the run at or before the row's position, minus those a look-back
+                            // window over the row's own modality cuts off
+                            T seen = max(T(0), min((T)(q[u] - before), len));
+                            if (windows) {                   // wave-uniform
+                                const T win = (T)att_window(att[u]);
+                                const T cut = max(T(0), min((T)(q[u] - win - before), len));
+                                if (win != 0 && mod_r == att_modality(att[u])) seen -= cut;
+                            }
+                            part += (uint32_t)(same_span ? len : (back ? seen : T(0)));
+                        }
+                    }
+                }
+            }
+            const uint32_t total = wave_sum(part);
+            if (lane == 0) put(i, j, total);
+        }
+    };
+    __shared__ uint64_t left_s[kTmGroup * kTmGroup / kWave];     // pairs that the runs do not serve
+    uint64_t any_left = 0;
+    for (int p0 = 0; !small && p0 < gq * gk; p0 += kTmThreads) {
         const int pair = p0 + threadIdx.x;
         const int qi = pair >> log_gk, ki = pair & (gk - 1);
         const bool mine = pair < gq * gk && i0 + qi < nq && j0 + ki < nk;
@@ -216,70 +303,22 @@ tile_map_body(uint32_t wg_index, const uint64_t* __restrict__ bits,
             put(i0 + qi, j0 + ki, total);
         }
 
-        // the other pairs, one after the other, by the whole wavefront
-        uint64_t left = __ballot(mine && !few);
-        if (small) left = j0 + wave < nk ? 1u : 0u;          // a pair per wavefront
-        while (left) {
-            const int p = small ? wave : p0 + wave * kWave + __ffsll((unsigned long long)left) - 1;
-            left &= left - 1;
-            const int32_t i = i0 + (p >> log_gk), j = j0 + (p & (gk - 1));
-            const int64_t rows = rows_of(i), k0 = (int64_t)j * tk;
-            uint32_t part = 0;
-            // up to 256 rows at a time in registers, their words in flight together; the next 64
-            // keys' words are requested ahead of their use
-            constexpr int kRows = 4;
-            for (int64_t r0 = 0; r0 < rows; r0 += kRows * kWave) {
-                int64_t q[kRows];
-                uint64_t wq[kRows];
-                const int n_r = (int)min((int64_t)kRows, (rows - r0 + kWave - 1) / kWave);
-#pragma unroll
-                for (int u = 0; u < kRows; ++u) {
-                    q[u] = 0;
-                    wq[u] = 0;                               // (a word of zeros sees nothing)
-                    const int64_t r = r0 + u * kWave + lane;
-                    if (u < n_r && r < rows) {
-                        q[u] = pos_of((int64_t)i * tq + r);
-                        wq[u] = bits[q[u]];
-                    }
-                }
-                uint64_t wk_next = lane < tk ? bits[k0 + lane] : 0;
-                for (int kc = 0; kc < tk; kc += kWave) {
-                    // run starts among these keys: a key whose fields differ from its predecessor's
-                    const int n_keys = min(kWave, tk - kc);
-                    const uint64_t wk = wk_next;
-                    if (kc + kWave < tk) wk_next = kc + kWave + lane < tk ? bits[k0 + kc + kWave + lane] : 0;
-                    const uint32_t ss_k = word_ss(wk), mod_k = word_mod(wk);
-                    const uint32_t b_ss = lane_below(ss_k, 0u), b_mod = lane_below(mod_k, 0u);
-                    const bool starts = lane < n_keys && (lane == 0 || ss_k != b_ss || mod_k != b_mod);
-                    uint64_t m = __ballot(starts);
-                    while (m) {
-                        const int a = __ffsll((unsigned long long)m) - 1;
-                        m &= m - 1;
-                        const int b = m ? __ffsll((unsigned long long)m) - 1 : n_keys;   // the run is keys a..b-1
-                        const uint32_t ss_r = (uint32_t)__builtin_amdgcn_readlane((int)ss_k, a);
-                        const uint32_t mod_r = (uint32_t)__builtin_amdgcn_readlane((int)mod_k, a);
-                        const int64_t first = k0 + kc + a, len = b - a;
-#pragma unroll
-                        for (int u = 0; u < kRows; ++u) {
-                            if (u >= n_r) continue;          // wave-uniform
-                            const uint32_t ss_q = word_ss(wq[u]), att = word_att(wq[u]);
-                            const bool same_span = (ss_q & 0xFFFFu) != 0 && ss_q == ss_r;
-                            const bool back = (ss_q >> 16) == (ss_r >> 16) && ((att >> mod_r) & 1u);
-                            // keys of the run at or before the row's position, minus those a look-back
-                            // window over the row's own modality cuts off
-                            const int64_t upto = max((int64_t)0, min(q[u] - first + 1, len));
-                            const uint32_t win = att_window(att);
-                            const bool windowed = win != 0 && mod_r == att_modality(att);
-                            const int64_t cut = windowed ? max((int64_t)0, min(q[u] - (int64_t)win + 1 - first, len)) : 0;
-                            part += (uint32_t)(same_span ? len : (back ? upto - cut : 0));
-                        }
-                    }
-                }
-            }
-            const uint32_t total = wave_sum(part);
-            if (lane == 0) put(i, j, total);
-        }
+        // the other pairs
+        const uint64_t left = __ballot(mine && !few);
+        if (lane == 0) left_s[p0 / kWave + wave] = left;
+        any_left |= left;
     }
+    // by whole wavefronts, every fourth pair to each
+    auto count_rows = [&](uint64_t left, int first) {
+        if (narrow) by_rows(int32_t(0), left, first);
+        else by_rows(int64_t(0), left, first);
+    };
+    if (small) {
+        count_rows(j0 + wave < nk ? 1u : 0u, wave);
+        return;
+    }
+    if (!__syncthreads_or(any_left != 0)) return;            // the usual case
+    for (int m = 0; m * kWave < gq * gk; ++m) count_rows(left_s[m] & (0x1111111111111111ull << wave), m * kWave);
 }
 
 // ---- block list ------------------------------------------------------------
