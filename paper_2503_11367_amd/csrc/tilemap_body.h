@@ -185,8 +185,9 @@ tile_map_body(uint32_t wg_index, const uint64_t* __restrict__ bits,
             J.cls[(int64_t)i * nk + j] = total == 0 ? MMATTN_TILE_EMPTY
                                          : (total == full ? MMATTN_TILE_FULL : MMATTN_TILE_PARTIAL);
     };
-    // The pairs first + bit of `left`, one after the other by the whole wavefront, row by row: up to 256 rows in registers, kept while the q-tile stays the same, their words in
-    // flight together; the next 64 keys' words are requested ahead of their use.  T holds a
+    // The pairs first + bit of `left`, one after the other by the whole wavefront, row by row: up
+    // to 256 rows in registers, kept while the q-tile stays the same, their words in flight
+    // together; the next 64 keys' words are requested ahead of their use.  T holds a
     // position.  Bound by the instructions per (64 rows, run of keys): positions in 32 bits where they
     // fit, the window's only where a row has one.  Measured on spans of 1 to 3 tokens, 32768 of
     // them in all, against a wavefront per pair with its rows in LDS: tiles of 128 x 128 476 -> 367
