@@ -236,9 +236,11 @@ int mmattn_fwd_heads(const void* q_loc, const void* k, const void* v, const uint
  *                     same buffers as k_src, v_src: then nothing is copied)
  *   copy_stream       a HIP stream other than `stream`, default priority
  *   ws                mmattn_workspace_size(MMATTN_OP_FWD_HEADS, ...) bytes
+ * Everything enqueued before this call on either stream has completed before any of
+ * its work reads or writes the caller's buffers.
  * When the call returns, all work has been enqueued; `stream` has been made to
  * wait for every copy, so later work on `stream` may reuse all buffers.
- * Creates and destroys up to Hkv/heads_per_stage + 1 HIP events (no device
+ * Creates and destroys up to Hkv/heads_per_stage + 2 HIP events (no device
  * memory).  Hkv % heads_per_stage == 0, at most MMATTN_MAX_STAGES windows. */
 #define MMATTN_MAX_STAGES 64
 int mmattn_fwd_staged(const void* q_loc, const void* k_src, const void* v_src,

@@ -194,13 +194,18 @@ int mmattn_fwd_staged(const void* q_loc, const void* k_src, const void* v_src, v
     hipStream_t cs = (hipStream_t)copy_stream, st = (hipStream_t)stream;
     const int n_stage = Hkv / heads_per_stage;
     const size_t pitch = (size_t)Hkv * D * 2, width = (size_t)heads_per_stage * D * 2;
-    hipEvent_t ready = nullptr, arrived[MMATTN_MAX_STAGES] = {};
+    hipEvent_t ready = nullptr, behind = nullptr, arrived[MMATTN_MAX_STAGES] = {};
     if (n_stage > MMATTN_MAX_STAGES) return MMATTN_ERR_UNSUPPORTED;
     rc = MMATTN_OK;
     auto ok = [&](hipError_t e) { if (e != hipSuccess && rc == MMATTN_OK) rc = MMATTN_ERR_HIP; return e == hipSuccess; };
     // the copy stream starts once the inputs and the staging buffers are free on `stream`
     if (ok(hipEventCreateWithFlags(&ready, hipEventDisableTiming)) && ok(hipEventRecord(ready, st)))
         ok(hipStreamWaitEvent(cs, ready, 0));
+    // the plan reads bits and blocks and writes ws, which the caller may have left to earlier work
+    // on the copy stream (recorded behind the wait, so that a capture of `stream` takes it in)
+    if (rc == MMATTN_OK && n_blocks > 0 &&
+        ok(hipEventCreateWithFlags(&behind, hipEventDisableTiming)) && ok(hipEventRecord(behind, cs)))
+        ok(hipStreamWaitEvent(st, behind, 0));
     for (int i = 0; i < n_stage && rc == MMATTN_OK; ++i) {
         const size_t off = (size_t)i * width;
         if (k_src != k_stage)                   // already in place: nothing to move
@@ -213,7 +218,7 @@ int mmattn_fwd_staged(const void* q_loc, const void* k_src, const void* v_src, v
             ok(hipEventRecord(arrived[i], cs));
     }
     // the plan needs neither keys nor values: it is built while the first window arrives (32768
-    // keys, two windows of four heads: 2011 -> 2001 us against building it behind the first wait)
+    // keys, two windows of four heads: 1999 -> 1993 us against building it behind the first wait)
     AttnArgs a{q_loc, k_stage, v_stage, bits, blocks, n_blocks, block, S, Hq, Hkv, D, scale, 0, heads_per_stage, 1};
     if (rc == MMATTN_OK && n_blocks > 0) rc = launch_fwd_plan(a, ws, st);
     for (int i = 0; i < n_stage && rc == MMATTN_OK; ++i) {
@@ -228,6 +233,7 @@ int mmattn_fwd_staged(const void* q_loc, const void* k_src, const void* v_src, v
             if (arrived[i]) (void)hipStreamWaitEvent(st, arrived[i], 0);
     // destroying a recorded event is deferred by the runtime until it has completed
     if (ready) (void)hipEventDestroy(ready);
+    if (behind) (void)hipEventDestroy(behind);
     for (int i = 0; i < n_stage; ++i)
         if (arrived[i]) (void)hipEventDestroy(arrived[i]);
     return rc;

@@ -76,6 +76,31 @@ def test_staged_entry_point(Hq, Hkv, D, hps):
         ks.fill_(float("nan")); vs.fill_(float("nan"))
 
 
+def test_staged_inputs_written_on_the_copy_stream():
+    """Mask words and block list that earlier work on the copy stream writes, behind some
+    milliseconds of other work: the plan waits for them."""
+    Hq, Hkv, D = 8, 4, 128
+    lay = wl.layout_random(152, S=1024, n_samples=2, max_spans=5)
+    blocks = [3, 14, 6, 9]
+    t = make_tensors(412, len(blocks) * 64, lay.S, Hq, Hkv, D)
+    bits_late = gpu_bits(lay)
+    bl_late = torch.tensor(blocks, dtype=torch.int32, device=DEV)
+    bits, bl = torch.zeros_like(bits_late), torch.zeros_like(bl_late)
+    ks, vs = torch.empty_like(t["k"]), torch.empty_like(t["v"])
+    a = torch.randn(4096, 4096, device=DEV)
+    copy = torch.cuda.Stream()
+    copy.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(copy):
+        for _ in range(8):
+            a = a @ a
+            a = a / a.norm()
+        bits.copy_(bits_late)
+        bl.copy_(bl_late)
+    o, lse = mb.fwd_staged(t["q"], t["k"], t["v"], ks, vs, bits, bl, 64, 1, copy)
+    torch.cuda.synchronize()
+    check(o, lse, *oracle_fwd(lay, blocks, 64, t, Hq, Hkv))
+
+
 def test_staged_in_place():
     """k_stage / v_stage may be the source buffers themselves: no copies, same result."""
     lay = wl.layout_random(151, S=512, n_samples=1, max_spans=3)
