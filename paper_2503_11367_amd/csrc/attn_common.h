@@ -173,8 +173,9 @@ constexpr float kLn2 = 0.6931471805599453f;
 //   klist[nq][nk], kcount[nq]  active k-tiles of each q-tile, ascending;
 //                            entry = k-tile index | (PARTIAL ? kPartialFlag : 0)
 //   qorder[nq]               q-tiles by kcount descending (longest first)
-//   csz[1]                   slice length the list builder suggests for cutting the
-//                            lists into slices (see list_split), from the actual lengths
+//   csz[2]                   slice length the list builder suggests for cutting the
+//                            lists into slices (see list_split), from the actual lengths;
+//                            length of the longest list
 constexpr uint32_t kPartialFlag = 0x80000000u;
 
 struct TilePlan {
@@ -201,6 +202,7 @@ struct FwdSplit {
 // length would need for about 1024 workgroups.  The slice length itself is chosen on the device from the
 // actual list lengths (slice_length below) and is never shorter than csz.
 // `groups`: workgroups per q-tile (head groups).
+constexpr int32_t kFewItems = 512;
 //
 // list_room: what the partial buffers are sized for; list_split: what is launched, fewer where
 // slice_length cannot cut that far (slices of at least four tiles, lists of at most eight never)
@@ -208,7 +210,7 @@ struct FwdSplit {
 inline FwdSplit list_room(int32_t nq, int32_t nk, int32_t groups) {
     const int64_t items = (int64_t)nq * groups;
     int64_t cmax = 1;
-    if (items < 512) {
+    if (items < kFewItems) {
         cmax = (nk >= 512 ? 4 : 2) * ((1024 + items - 1) / items);
         const int64_t most = nk / 2 > 1 ? nk / 2 : 1;         // at least two tiles per slice
         if (cmax > most) cmax = most;
@@ -240,11 +242,22 @@ inline FwdSplit list_split(int32_t nq, int32_t nk, int32_t groups) {
 // least 4, for then most CUs have nothing to do: half of 1920 tokens with 6 heads (480 tiles)
 // 28 -> 22 us in the forward, 34 -> 28 us in the dQ pass.  With four tiles per CU (4096 tokens, a
 // rank of four, 8 heads) the longer sums of the aggregation already cost more, 59 -> 65 us.
+//   512 work items or more (see fwd_split_groups) give every CU two from the outset: they are
+//   cut only where some lists outlast the rest.  Whole stay lists about as long as each other;
+//   and, where none has more than twice the mean, lists of up to 32 tiles, or of up to 128 when
+//   one of them spans the sequence (one sample: a causal triangle), for there partial results
+//   cost more than the wait.  Whole / cut in us, head_dim 128: 4096 tokens, 16 / 4 heads, one
+//   sample 99 / 114; 8192, 12 / 3 heads, one sample 221 / 255; 16384, 8 / 2 heads, one sample
+//   337 / 317; 16384, 4 / 2 heads, four samples 424 / 267, three samples 290 / 216.
+constexpr int32_t kShortLists = 32, kTriangleLists = 128;
 __host__ __device__ inline int32_t slice_length(int64_t total, int32_t longest, int32_t lists,
                                                 int32_t groups, int32_t nk) {
     const int64_t work = total * groups;
     int64_t c;
-    if ((int64_t)longest * lists * 4 <= total * 5) {          // longest <= 1.25 x mean
+    const bool equal = (int64_t)longest * lists * 4 <= total * 5;       // longest <= 1.25 x mean
+    const bool brief = longest <= kShortLists || (longest <= kTriangleLists && longest * 4 >= nk * 3);
+    if (lists * groups >= kFewItems && (equal || (brief && (int64_t)longest * lists <= total * 2))) return nk;
+    if (equal) {
         c = (work + 1023) / 1024;
     } else {
         c = (int64_t)__builtin_sqrtf((float)work / 32.0f) + 1;

@@ -166,6 +166,14 @@ constexpr int64_t kFwdPairItems = 512;
 static int32_t fwd_heads_per_wg(int32_t D, int32_t rep, int32_t nq, int32_t Hq_run) {
     return D == 128 && rep % 2 == 0 && (int64_t)nq * Hq_run / 2 >= kFwdPairItems ? 2 : 1;
 }
+// Workgroups per q-tile that the cutting of lists counts with.  512 to 1023 single heads of even
+// groups may be cut like the 256 to 511 pairs that they would be: whole lists alone leave CUs to
+// the longest of uneven lists (four samples in 16384 tokens, 4 / 2 heads: 267 us, 424 uncut; the
+// pairs 288).  Fewer than 512 are cut by their own number.
+static int32_t fwd_split_groups(int32_t D, int32_t rep, int32_t nq, int32_t Hq_run) {
+    const bool halve = rep % 2 == 0 && (int64_t)nq * Hq_run >= kFewItems;
+    return halve ? Hq_run / 2 : Hq_run / fwd_heads_per_wg(D, rep, nq, Hq_run);
+}
 template <int D, int HPW, int NST, bool HALF>
 __global__ void __launch_bounds__(256 * HPW, D == 64 ? 3 : 2)
 fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
@@ -194,7 +202,7 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
     // the early exits are taken after the row's own loads have been issued, so that a
     // work item starts after three round trips instead of six.
     const int err_flag = *err;
-    const int csz_dev = *plan.csz;
+    const int csz_dev = plan.csz[0], longest = plan.csz[1];
 
     // ---- work decode: KV heads are pinned to XCDs (workgroups are dealt
     // round-robin to the 8 XCDs) so that one head's K/V stays in one L2 --------
@@ -202,6 +210,7 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
     int tile_rank, h0;                    // h0: first of the HPW heads of this workgroup
     const int items = gridDim.x / split.cmax;
     const int chunk = blockIdx.x / items; // which slice of the q-tile's k-tile list (0 when not split)
+    if (chunk > 0 && csz_dev >= longest) return;      // no list is cut
     {
         const int bid = blockIdx.x - chunk * items;
         if (Hkv % 8 == 0) {
@@ -772,7 +781,7 @@ fwd_combine_kernel(TilePlan plan, FwdSplit split, int64_t n_loc, int32_t Hq, int
                    const int32_t* __restrict__ err, const float* __restrict__ Opart,
                    const float* __restrict__ MLpart, ushort_t* __restrict__ O,
                    float* __restrict__ LSE) {
-    if (*err) return;
+    if (*err || plan.csz[0] >= plan.csz[1]) return;      // no list is cut
     const int dq4 = D / 4;
     const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t rh = gid / dq4;
@@ -846,7 +855,7 @@ static FwdLayout fwd_layout(int64_t S, int64_t n_loc, int32_t n_blocks, int32_t 
     L.nq = (int32_t)((n_loc + kFwdBM - 1) / kFwdBM);
     L.nk = (int32_t)(S / kFwdBN);
     const int32_t rep = Hq / Hkv;
-    L.split = list_split(L.nq, L.nk, Hq_run / fwd_heads_per_wg(D, rep, L.nq, Hq_run));
+    L.split = list_split(L.nq, L.nk, fwd_split_groups(D, rep, L.nq, Hq_run));
     // the partial results have room for the slices that pairs of heads would be cut into (never
     // fewer)
     const FwdSplit room = list_room(L.nq, L.nk, Hq_run / (rep % 2 == 0 ? 2 : 1));

@@ -193,7 +193,7 @@ struct RankJob {
 };
 struct RankJobs { RankJob j[2]; };
 
-// the slice length of row lists
+// the slice length of row lists and the longest list
 __device__ void slice_rows(const int32_t* __restrict__ count, int32_t n_lines, int32_t n_items, int32_t groups,
                            int32_t* __restrict__ csz_out) {
     constexpr int kWaves = kRankThreads / kWave;
@@ -217,7 +217,8 @@ __device__ void slice_rows(const int32_t* __restrict__ count, int32_t n_lines, i
     __syncthreads();
     if (tid != 0) return;
     for (int w = 1; w < kWaves; ++w) { total += tot_s[w]; longest = max(longest, max_s[w]); lists += num_s[w]; }
-    *csz_out = slice_length(total, longest, lists, groups, n_items);
+    csz_out[0] = slice_length(total, longest, lists, groups, n_items);
+    csz_out[1] = longest;
 }
 
 // One launch serves up to two sets of lines (the second set's workgroups follow the first's).

@@ -82,6 +82,23 @@ def test_one_head_per_workgroup_long_lists():
              Hq=32, Hkv=32, D=128, seed=89, heads=[0, 31])
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_single_heads_of_even_groups(D):
+    """512 to 1023 (q-tile, head) work items of even groups: lists that are cut because some are
+    much longer than the rest (packed samples) or long and uneven (one sample of 8448 tokens),
+    lists that stay whole (all about equal, or short)."""
+    sample = lambda n: np.sort(np.random.default_rng(n).choice(n, size=160, replace=False))
+    for lay, Hq, Hkv, seed in ((wl.Layout(4096, [(200, 300, 1)], [0, 2900, 3100, 3400, 4096]), 16, 4, 90),
+                               (wl.layout_random(91, S=8448, max_spans=3), 8, 2, 91),
+                               (wl.layout_lambda([4096], 64, 512), 16, 8, 92),
+                               (wl.layout_random(93, S=2048, n_samples=1), 32, 4, 93)):
+        run_case(lay, list(range(lay.S // 128)), 128, Hq, Hkv, D, seed, heads=[0, Hq - 1], rows_sample=sample(lay.S))
+    # a ragged, unsorted share: 31 blocks of 240 rows are 58.1 q-tiles
+    lay = wl.layout_random(94, S=9600, n_samples=2, max_spans=5, deny_prob=0.4)
+    blocks = np.random.default_rng(94).permutation(40)[:31].tolist()
+    run_case(lay, blocks, 240, 12, 6, D, 94, heads=[1, 11], rows_sample=sample(31 * 240))
+
+
 def test_shared_question_and_block_causal():
     """Two patterns named in section 5.5: answers that see the question and
     themselves only (spans without the bidirectional term), and blocks that are
