@@ -1,7 +1,7 @@
 // mmattn_balance: Alg. 1 of the paper (section 3.2.1) in its LPT reading --
 // blocks visited by (W descending, index ascending), each given to the rank
 // with (load ascending, rank ascending).  Integer-only; one workgroup, because
-// the greedy loop is inherently serial and the inputs are at most a few
+// a block goes where the loads before it say, and the inputs are at most a few
 // thousand blocks.
 //
 //   phase 1  the visiting order: up to 64 blocks by counting, for each, those that
@@ -14,27 +14,31 @@
 //            stretch of blocks, finds equal ranks among 64 of them by ballots and
 //            counts with a histogram of its own.
 //
-// Bound by the latency of the loop, one block after the other.  Measured, 8 ranks:
-// 512 blocks 126 -> 23 us, 1024 blocks 259 -> 38 us against a loop that found a
+// Bound by the latency of the loop, which takes the blocks one by one.  Measured, 8 ranks:
+// 512 blocks 126 -> 21 us, 1024 blocks 259 -> 38 us against a loop that found a
 // block's place by a ballot and scalar arithmetic, an order counted over all pairs
 // of blocks (34 us of the 259) and lists counted the same way.
-// Workloads too large for the sorted keys (a sum of 2^42 to 2^46 pairs and more, by
-// the number of ranks) are ordered by counting and assigned by wave-wide minima.
+// Up to 64 blocks are the work of a single wavefront, which meets no other at barriers: 8
+// blocks over 4 ranks 5.4 us with sixteen, 3.4 so.  Eight or fewer, or no more than there are
+// ranks, it keeps in registers (few_blocks): 1 block 3.8 -> 1.9 us, 64 blocks over 64 ranks
+// 8.5 -> 8.2 us.
+// A workload of 2^46, or a sum of 2^(52 - ceil(log2 P)), does not fit the sorted keys: then the
+// order is counted and the loop is the one with ballots (greedy_wide).
 #include "common.h"
 
 namespace mm {
 
-constexpr int kBalThreads = 1024;
-constexpr int kBalWaves = kBalThreads / kWave;
+constexpr int kBalThreads = 1024;                     // workgroup; a single wavefront up to kBalCounted blocks
 constexpr int kBalSlots = MMATTN_MAX_RANKS / kWave;   // most ranks per lane
 constexpr int kBalCounted = 64;                       // up to this many blocks the order is counted
+constexpr int kBalFew = 8;                            // up to this many blocks stay in registers
 constexpr int kBalIndexBits = 14;                     // block index in a sort key
 static_assert(MMATTN_MAX_BLOCKS == 1 << kBalIndexBits, "a sort key holds any block index");
 // LDS, in 64-bit words: sort keys; up to kBalLdsRob blocks also their ranks; histograms
 // (over the keys, which are done with by then, when there are more blocks)
 constexpr int kBalLdsRob = 8192;
 constexpr int kBalRobAt = kBalLdsRob, kBalHistAt = kBalLdsRob + 4096;
-static_assert((MMATTN_MAX_BLOCKS - kBalHistAt) * 8 >= kBalWaves * MMATTN_MAX_RANKS * 2, "histograms fit");
+static_assert((MMATTN_MAX_BLOCKS - kBalHistAt) * 8 >= kBalThreads / kWave * MMATTN_MAX_RANKS * 2, "histograms fit");
 
 struct MinKey { uint64_t load; uint32_t rank; };
 
@@ -58,6 +62,20 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
     MM_MIN_DPP(0x143, 0xc);                 // row_bcast:31 into rows 2 and 3
 #undef MM_MIN_DPP
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// the same for a 64-bit sum or maximum, left in lane 63 (0 is the identity of both)
+template <class F>
+__device__ __forceinline__ uint64_t lane63_reduce(uint64_t v, F&& f) {
+#define MM_RED_DPP(ctrl, rows)                                                                                  v = f(v, ((uint64_t)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), ctrl, rows, 0xf, false) << 32) |                  (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, ctrl, rows, 0xf, false))
+    MM_RED_DPP(0x111, 0xf);
+    MM_RED_DPP(0x112, 0xf);
+    MM_RED_DPP(0x114, 0xf);
+    MM_RED_DPP(0x118, 0xf);
+    MM_RED_DPP(0x142, 0xa);
+    MM_RED_DPP(0x143, 0xc);
+#undef MM_RED_DPP
+    return v;
 }
 
 // lexicographic minimum of (load, rank) over the wavefront: three 32-bit minima,
@@ -217,12 +235,100 @@ __device__ __forceinline__ void greedy_sorted(uint64_t* entries, int32_t nB, int
         }
 }
 
-// the same for workloads of any size: lane l keeps the loads of ranks l, l+64, ... and its
-// local minimum, a wave-wide lexicographic minimum picks the receiving rank
+// the value of lane `u`, wave-uniform
+__device__ __forceinline__ uint64_t lane_value(uint64_t v, int u) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), u) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, u);
+}
+
+// Up to 64 ranks with loads of any size, held by the lanes SORTED by (load, rank): a block goes
+// to lane 0's rank, whose grown key is re-inserted behind the smaller ones (one ballot).
+struct Ballots {
+    uint32_t lo, hi, rk;                               // load; lanes >= P: +inf
+    __device__ __forceinline__ Ballots(int32_t P, int lane)
+        : lo(lane < P ? 0u : 0xFFFFFFFFu), hi(lo), rk(lane < P ? (uint32_t)lane : 0xFFFFFFFFu) {}
+    __device__ __forceinline__ uint32_t give(uint64_t w, int lane) {
+        const uint64_t mine = ((uint64_t)hi << 32) | lo;
+        const uint32_t g = (uint32_t)__builtin_amdgcn_readlane((int)rk, 0);
+        const uint64_t grown = lane_value(mine, 0) + w;
+        const bool less = lane > 0 && (mine < grown || (mine == grown && rk < g));
+        const int at = __popcll(__ballot(less));       // new lane of rank g
+        // lanes below `at` take their upper neighbour's key, lane `at` the grown one
+        const uint32_t lo_up = Key32::above(lo), hi_up = Key32::above(hi), rk_up = Key32::above(rk);
+        if (lane < at) { lo = lo_up; hi = hi_up; rk = rk_up; }
+        else if (lane == at) { lo = (uint32_t)grown; hi = (uint32_t)(grown >> 32); rk = g; }
+        return g;
+    }
+    __device__ __forceinline__ void loads(int32_t P, int lane, uint64_t* __restrict__ load) const {
+        if (lane < P) load[rk] = ((uint64_t)hi << 32) | lo;
+    }
+};
+
+// At most 64 blocks, one per lane of a wavefront, workloads of any size.  No more blocks than
+// ranks: the block at place t of the visiting order finds rank t empty, and those without work
+// all go to the first rank that the others leave.
+__device__ void few_blocks(const uint64_t* __restrict__ W, int32_t nB, int32_t P, int lane,
+                           int32_t* __restrict__ rank_of_block, uint64_t* __restrict__ load,
+                           int32_t* __restrict__ rank_off, int32_t* __restrict__ rank_blocks) {
+    const uint64_t w = lane < nB ? W[lane] : 0;
+    int pos = lane < nB ? 0 : lane;                    // place in the visiting order
+    for (int c = 0; c < nB; ++c) {
+        const uint64_t wc = lane_value(w, c);
+        if (lane < nB) pos += (wc > w || (wc == w && c < lane)) ? 1 : 0;
+    }
+    // lane t: workload and block at place t
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_permute(pos * 4, (int)(uint32_t)(w >> 32));
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_permute(pos * 4, (int)(uint32_t)w);
+    const uint64_t w_at = ((uint64_t)hi << 32) | lo;
+    int g = 0;
+    if (nB <= P) {
+        g = min(pos, (int)__popcll(__ballot(w != 0)));
+        for (int r = lane; r < P; r += kWave) load[r] = r < nB ? w_at : 0;
+    } else {
+        const int b_at = __builtin_amdgcn_ds_permute(pos * 4, lane);
+        Ballots ranks(P, lane);
+        for (int t = 0; t < nB; ++t) {
+            const int got = (int)ranks.give(lane_value(w_at, t), lane);
+            if (lane == __builtin_amdgcn_readlane(b_at, t)) g = got;
+        }
+        ranks.loads(P, lane, load);
+    }
+    int before = 0, upto = 0;                          // list entries ahead of this block; of ranks <= lane
+    for (int c = 0; c < nB; ++c) {
+        const int gc = __builtin_amdgcn_readlane(g, c);
+        before += (gc < g || (gc == g && c < lane)) ? 1 : 0;
+        upto += gc <= lane ? 1 : 0;
+    }
+    if (lane < nB) {
+        rank_of_block[lane] = g;
+        rank_blocks[before] = lane;
+    }
+    for (int r = lane; r < P; r += kWave) rank_off[r + 1] = r < kWave ? upto : nB;
+    if (lane == 0) rank_off[0] = 0;
+}
+
+// The greedy loop for workloads of any size, W[] in LDS.  More than 64 ranks: lane l keeps the loads of ranks l, l+64, ... and its local
+// minimum, a wave-wide lexicographic minimum picks the receiving rank.  Measured, 8 ranks, 1024
+// blocks (whole kernel): 264 us with ballots, 288 with minima.
 template <int SLOTS>
-__device__ __forceinline__ void greedy_wide(const uint64_t* __restrict__ W, const int32_t* __restrict__ order,
+__device__ __forceinline__ void greedy_wide(const uint64_t* W, const int32_t* __restrict__ order,
                                             int32_t nB, int32_t P, int lane, int32_t* __restrict__ rank_of_block,
                                             uint64_t* __restrict__ load) {
+    if (SLOTS == 1) {
+        Ballots ranks(P, lane);
+        for (int t0 = 0; t0 < nB; t0 += kWave) {
+            const int t = t0 + lane;
+            const int32_t my_b = t < nB ? order[t] : 0;
+            const uint64_t my_w = t < nB ? W[my_b] : 0;
+            const int n = min(kWave, nB - t0);
+            for (int u = 0; u < n; ++u) {
+                const uint32_t g = ranks.give(lane_value(my_w, u), lane);
+                if (lane == 0) rank_of_block[__builtin_amdgcn_readlane(my_b, u)] = (int32_t)g;
+            }
+        }
+        ranks.loads(P, lane, load);
+        return;
+    }
     uint64_t mine[SLOTS];
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) mine[s] = 0;
@@ -339,25 +445,33 @@ __device__ __forceinline__ void sort_descending_regs(uint64_t* keys, int n2) {
     __syncthreads();
 }
 
-template <int SLOTS>
-__global__ void __launch_bounds__(kBalThreads)
+template <int SLOTS, int THREADS>
+__global__ void __launch_bounds__(THREADS)
 balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
                int32_t* __restrict__ rank_of_block, uint64_t* __restrict__ load,
                int32_t* __restrict__ rank_off, int32_t* __restrict__ rank_blocks) {
-    __shared__ __attribute__((aligned(16))) uint64_t lds[MMATTN_MAX_BLOCKS];
-    __shared__ uint64_t sum_s[kBalWaves], max_s[kBalWaves];
-    __shared__ int32_t scan_s[kBalWaves];
+    constexpr int kWaves = THREADS / kWave;
+    constexpr bool kOne = kWaves == 1;                 // at most kBalCounted blocks
+    constexpr int kLds = kOne ? 4 * kWave : MMATTN_MAX_BLOCKS;
+    constexpr int kRobAt = kOne ? 2 * kWave : kBalRobAt, kHistAt = kOne ? 3 * kWave : kBalHistAt;
+    __shared__ __attribute__((aligned(16))) uint64_t lds[kLds];
+    __shared__ uint64_t sum_s[kWaves], max_s[kWaves];
+    __shared__ int32_t scan_s[kWaves];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     uint64_t* keys = lds;
-    uint16_t* rob = (uint16_t*)(lds + kBalRobAt);
-    uint16_t* hist = (uint16_t*)(lds + kBalHistAt);    // [wave][rank]
+    uint16_t* rob = (uint16_t*)(lds + kRobAt);
+    uint16_t* hist = (uint16_t*)(lds + kHistAt);    // [wave][rank]
 
+    if (kOne && P > 1 && (nB <= P || nB <= kBalFew)) {
+        few_blocks(W, nB, P, lane, rank_of_block, load, rank_off, rank_blocks);
+        return;
+    }
     // sum and largest workload; small ones go to LDS as sort keys on the way
     uint64_t sum = 0, most = 0;
     int n2 = 2 * kWave;
     while (n2 < nB) n2 <<= 1;
-    for (int b = tid; b < n2; b += kBalThreads) {
+    for (int b = tid; b < n2; b += THREADS) {
         const uint64_t w = b < nB ? W[b] : 0;
         sum += w;
         most = max(most, w);
@@ -367,14 +481,12 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
             rank_blocks[b] = b;
         }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        sum += __shfl_xor(sum, off);
-        most = max(most, (uint64_t)__shfl_xor(most, off));
-    }
-    if (lane == 0) { sum_s[wave] = sum; max_s[wave] = most; }
+    sum = lane63_reduce(sum, [](uint64_t a, uint64_t b) { return a + b; });
+    most = lane63_reduce(most, [](uint64_t a, uint64_t b) { return max(a, b); });
+    if (lane == kWave - 1) { sum_s[wave] = sum; max_s[wave] = most; }
     __syncthreads();
     sum = 0; most = 0;
-    for (int w = 0; w < kBalWaves; ++w) { sum += sum_s[w]; most = max(most, max_s[w]); }
+    for (int w = 0; w < kWaves; ++w) { sum += sum_s[w]; most = max(most, max_s[w]); }
     if (P == 1) {                                      // workgroup-uniform
         if (tid == 0) {
             load[0] = sum;
@@ -397,7 +509,7 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
     const bool rob_lds = fits && nB <= kBalLdsRob;     // workgroup-uniform, like the branches below
 
     if (fits) {
-        if (nB <= kBalCounted) {
+        if constexpr (kOne) {
             // every block's place; the keys are distinct
             uint64_t mine = 0;
             int pos = 0;
@@ -414,13 +526,13 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
             __syncthreads();
             if (tid < nB) keys[pos] = mine;
             __syncthreads();
-        } else if (nB <= kBalThreads) {
+        } else if (nB <= THREADS) {
             sort_descending_regs(keys, n2);
         } else {
             sort_descending(keys, n2);
         }
         if (fits32) {
-            for (int t = tid; t < nB; t += kBalThreads) {
+            for (int t = tid; t < nB; t += THREADS) {
                 const uint64_t e = keys[t];
                 keys[t] = (e >> kBalIndexBits << (32 + bits)) | (e & kIndexMask);
             }
@@ -439,34 +551,51 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
             }
         }
         __syncthreads();
-        for (int t = tid; t < nB; t += kBalThreads) {
+        for (int t = tid; t < nB; t += THREADS) {
             const uint64_t e = keys[t];
             const int b = (int)(kIndexMask - ((uint32_t)e & kIndexMask));
             const int g = (int)(~(uint32_t)(e >> 32) & ((1u << bits) - 1u));
             rank_of_block[b] = g;
             if (rob_lds) rob[b] = (uint16_t)g;
         }
+    } else if (kOne) {
+        few_blocks(W, nB, P, lane, rank_of_block, load, rank_off, rank_blocks);
+        return;
     } else {
         int32_t* order = rank_blocks;                  // until phase 3 overwrites it
-        for (int b = tid; b < nB; b += kBalThreads) {
-            const uint64_t wb = W[b];
+        __syncthreads();                               // (the keys are in LDS until here)
+        for (int b = tid; b < nB + (nB & 1); b += THREADS) lds[b] = b < nB ? W[b] : 0;
+        __syncthreads();
+        for (int b = tid; b < nB; b += THREADS) {
+            const uint64_t wb = lds[b];
+            typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+            const u64x2* w2 = (const u64x2*)lds;       // two workloads per LDS read; a last zero never precedes
             int pos = 0;
-            for (int c = 0; c < nB; ++c) {
-                const uint64_t wc = W[c];
-                pos += (wc > wb || (wc == wb && c < b)) ? 1 : 0;
+#pragma unroll 4
+            for (int c2 = 0; c2 < (nB + 1) / 2; ++c2) {
+                const u64x2 wc = w2[c2];
+                pos += (wc.x > wb || (wc.x == wb && 2 * c2 < b)) ? 1 : 0;
+                pos += (wc.y > wb || (wc.y == wb && 2 * c2 + 1 < b)) ? 1 : 0;
             }
             order[pos] = b;
         }
         __syncthreads();
-        if (wave == 0) greedy_wide<SLOTS>(W, order, nB, P, lane, rank_of_block, load);
+        if (SLOTS > 1 && nB <= P) {                    // as in few_blocks (P is at most the number of threads)
+            const uint64_t w = tid < nB ? lds[order[tid]] : 0;
+            const int busy = __syncthreads_count(w != 0);
+            if (tid < nB) rank_of_block[order[tid]] = min(tid, busy);
+            if (tid < P) load[tid] = w;
+        } else if (wave == 0) {
+            greedy_wide<SLOTS>(lds, order, nB, P, lane, rank_of_block, load);
+        }
     }
     __syncthreads();
 
     // phase 3.  Wavefront `wave` takes blocks first .. last-1
-    const int per = ((nB + kBalThreads - 1) / kBalThreads) * kWave;
+    const int per = ((nB + THREADS - 1) / THREADS) * kWave;
     const int first = wave * per, last = min(nB, first + per);
     uint16_t* my_hist = hist + wave * P;
-    for (int i = tid; i < kBalWaves * P; i += kBalThreads) hist[i] = 0;
+    for (int i = tid; i < kWaves * P; i += THREADS) hist[i] = 0;
     __syncthreads();
     // the lanes of this wavefront whose block has the same rank
     auto peers = [&](int g, bool ok) -> uint64_t {
@@ -487,12 +616,12 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
     }
     __syncthreads();
     // counts of a rank over the wavefronts -> first list entries of (wavefront, rank)
-    int total = 0, before[kBalWaves];
+    int total = 0, before[kWaves];
     if (tid < P) {
 #pragma unroll
-        for (int w = 0; w < kBalWaves; ++w) before[w] = hist[w * P + tid];
+        for (int w = 0; w < kWaves; ++w) before[w] = hist[w * P + tid];
 #pragma unroll
-        for (int w = 0; w < kBalWaves; ++w) {
+        for (int w = 0; w < kWaves; ++w) {
             const int c = before[w];
             before[w] = total;
             total += c;
@@ -512,7 +641,7 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
     if (tid < P) {
         rank_off[tid + 1] = inc;
 #pragma unroll
-        for (int w = 0; w < kBalWaves; ++w) hist[w * P + tid] = (uint16_t)(inc - total + before[w]);
+        for (int w = 0; w < kWaves; ++w) hist[w * P + tid] = (uint16_t)(inc - total + before[w]);
     }
     if (tid == 0) rank_off[0] = 0;
     __syncthreads();
@@ -529,14 +658,17 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
 int launch_balance(const uint64_t* d_W, int32_t nB, int32_t P, int32_t* d_rank_of_block,
                    uint64_t* d_load, int32_t* d_rank_off, int32_t* d_rank_blocks, hipStream_t st) {
     // registers per lane for the rank loads: the smallest instantiation that holds P ranks
-    if (P <= kWave)
-        hipLaunchKernelGGL(balance_kernel<1>, dim3(1), dim3(kBalThreads), 0, st, d_W, nB, P,
+    if (nB <= kBalCounted)
+        hipLaunchKernelGGL((balance_kernel<1, kWave>), dim3(1), dim3(kWave), 0, st, d_W, nB, P,
+                           d_rank_of_block, d_load, d_rank_off, d_rank_blocks);
+    else if (P <= kWave)
+        hipLaunchKernelGGL((balance_kernel<1, kBalThreads>), dim3(1), dim3(kBalThreads), 0, st, d_W, nB, P,
                            d_rank_of_block, d_load, d_rank_off, d_rank_blocks);
     else if (P <= 4 * kWave)
-        hipLaunchKernelGGL(balance_kernel<4>, dim3(1), dim3(kBalThreads), 0, st, d_W, nB, P,
+        hipLaunchKernelGGL((balance_kernel<4, kBalThreads>), dim3(1), dim3(kBalThreads), 0, st, d_W, nB, P,
                            d_rank_of_block, d_load, d_rank_off, d_rank_blocks);
     else
-        hipLaunchKernelGGL(balance_kernel<kBalSlots>, dim3(1), dim3(kBalThreads), 0, st, d_W, nB, P,
+        hipLaunchKernelGGL((balance_kernel<kBalSlots, kBalThreads>), dim3(1), dim3(kBalThreads), 0, st, d_W, nB, P,
                            d_rank_of_block, d_load, d_rank_off, d_rank_blocks);
     MM_LAUNCH_CHECK();
     return MMATTN_OK;

@@ -255,6 +255,20 @@ def test_balance_key_widths(nB, P):
         check_balance(W.tolist(), P)
 
 
+@pytest.mark.parametrize("nB", [1, 2, 7, 8, 9, 16, 33, 63, 64, 65, 100])
+def test_balance_few_blocks(nB):
+    """Up to 64 blocks on one wavefront: fewer blocks than ranks, as many, more; blocks without
+    work; workloads of any size.  And 65 and 100 blocks of workloads too large for sorted keys."""
+    rng = np.random.default_rng(nB)
+    for P in (1, 2, 3, 8, nB - 1, nB, nB + 1, 63, 64, 65, 100, 129, 1024):
+        if P < 1:
+            continue
+        for hi in (1, 3, 2 ** 20, 2 ** 40, 2 ** 57):
+            check_balance(rng.integers(0, hi, size=nB).tolist(), P)
+    check_balance([2 ** 63] + [0] * (nB - 1), nB + 2)
+    check_balance([0] * nB, max(1, nB // 2))
+
+
 @pytest.mark.parametrize("c", [1, 2, 3, 4, 5])
 def test_balance_workloads_end_to_end(c):
     """encode -> tile map -> balance, all on the GPU, against the oracle chain."""
