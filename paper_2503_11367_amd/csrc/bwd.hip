@@ -144,12 +144,13 @@ struct BwdPrologue {
     int32_t* err;
     BwdPrepArgs prep;
 };
-template <int D>
+template <int D, bool RUNS>
 __global__ void __launch_bounds__(256)
 bwd_prologue_kernel(const BwdPrologue p) {
     static_assert(kTmThreads == 256, "one workgroup shape for all three jobs");
+    constexpr int kMapCode = kTmRows1 | kTmRows2;                       // q-tiles of 128 and of 64 rows
     if (blockIdx.x < p.n_map_wgs) {
-        tile_map_body(blockIdx.x, p.prep.bits, p.prep.blocks, p.prep.block, p.prep.n_seq_blocks,
+        tile_map_body<kMapCode | (RUNS ? kTmByRuns | kTmBeside : 0)>(blockIdx.x, p.prep.bits, p.prep.blocks, p.prep.block, p.prep.n_seq_blocks,
                       p.prep.n_loc, p.maps);
     } else if (blockIdx.x == p.n_map_wgs) {
         validate_blocks_body(p.prep.blocks, p.n_blocks, p.prep.n_seq_blocks, p.clean, p.err);
@@ -1366,7 +1367,8 @@ static int launch_bwd_d(const AttnArgs& a, const void* o, const float* lse, cons
                              ld, ldk, info, qh, doh};
         const int64_t threads = dq_first ? 0 : L.n_pad * a.Hq * (D / 8);
         const unsigned grid = p.n_map_wgs + 1u + (unsigned)((threads + 255) / 256);
-        hipLaunchKernelGGL(bwd_prologue_kernel<D>, dim3(grid), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((tile_map_by_runs(p.maps) ? bwd_prologue_kernel<D, true> : bwd_prologue_kernel<D, false>),
+                           dim3(grid), dim3(256), 0, st, p);
         MM_LAUNCH_CHECK();
     }
     int rc = launch_compact_both(pa, pb, st);

@@ -118,12 +118,13 @@ struct FwdPrologue {
     int32_t Hkv_s;
     float* knorm;
 };
-template <int D>
+template <int D, bool RUNS>
 __global__ void __launch_bounds__(256)
 fwd_prologue_kernel(const FwdPrologue p) {
     static_assert(kTmThreads == 256, "one workgroup shape for all three jobs");
+    constexpr int kMapCode = kTmRows2;                       // q-tiles of 128 rows
     if (blockIdx.x < p.n_map_wgs) {
-        tile_map_body(blockIdx.x, p.bits, p.blocks, p.block, p.n_seq_blocks, p.n_rows, p.maps);
+        tile_map_body<kMapCode | (RUNS ? kTmByRuns | kTmBeside : 0)>(blockIdx.x, p.bits, p.blocks, p.block, p.n_seq_blocks, p.n_rows, p.maps);
     } else if (blockIdx.x == p.n_map_wgs) {
         validate_blocks_body(p.blocks, p.n_blocks, p.n_seq_blocks, p.clean, p.err);
     } else {
@@ -978,8 +979,10 @@ static int launch_fwd_prologue(const AttnArgs& a, const FwdScratch& s, int32_t n
     p.clean = s.clean; p.err = s.err;
     p.K = (const ushort_t*)a.k + (int64_t)a.kv_begin * a.D; p.S = a.S; p.Hkv_s = a.Hkv; p.knorm = s.knorm;
     const unsigned grid = p.n_map_wgs + 1u + (unsigned)(kNormChunks * norm_heads);
-    if (a.D == 128) hipLaunchKernelGGL(fwd_prologue_kernel<128>, dim3(grid), dim3(256), 0, st, p);
-    else            hipLaunchKernelGGL(fwd_prologue_kernel<64>, dim3(grid), dim3(256), 0, st, p);
+    const bool runs = tile_map_by_runs(p.maps);
+    hipLaunchKernelGGL(a.D == 128 ? (runs ? fwd_prologue_kernel<128, true> : fwd_prologue_kernel<128, false>)
+                                  : (runs ? fwd_prologue_kernel<64, true> : fwd_prologue_kernel<64, false>),
+                       dim3(grid), dim3(256), 0, st, p);
     MM_LAUNCH_CHECK();
     return launch_compact_rows(s.plan, st);
 }

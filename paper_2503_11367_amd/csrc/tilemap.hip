@@ -18,10 +18,11 @@
 
 namespace mm {
 
+template <int CODE>
 __global__ void __launch_bounds__(kTmThreads)
 tile_map_kernel(const uint64_t* __restrict__ bits, const int32_t* __restrict__ blocks, int32_t block,
                 int64_t n_seq_blocks, int64_t n_rows, const TileMapJobs jobs) {
-    tile_map_body(blockIdx.x, bits, blocks, block, n_seq_blocks, n_rows, jobs);
+    tile_map_body<CODE>(blockIdx.x, bits, blocks, block, n_seq_blocks, n_rows, jobs);
 }
 
 __global__ void __launch_bounds__(256)
@@ -45,8 +46,13 @@ int launch_tile_map(const uint64_t* d_bits, int64_t S, const int32_t* d_blocks, 
     if (n_rows <= 0) return MMATTN_OK;
     TileMapJobs jobs;
     jobs.j[0] = jobs.j[1] = tile_map_job(S, n_rows, tq, tk, d_cls, d_cnt);
-    hipLaunchKernelGGL(tile_map_kernel, dim3(jobs.j[0].gx * jobs.j[0].gy), dim3(kTmThreads), 0, st, d_bits,
-                       d_blocks, block, d_blocks ? S / block : (int64_t)0, n_rows, jobs);
+    const bool runs = tile_map_by_runs(jobs);
+    const auto kernel = S > kTmNarrow    ? tile_map_kernel<kTmWide>
+                        : tq <= kWave     ? (runs ? tile_map_kernel<kTmByRuns | kTmRows1> : tile_map_kernel<kTmRows1>)
+                        : tq <= 2 * kWave ? (runs ? tile_map_kernel<kTmByRuns | kTmRows2> : tile_map_kernel<kTmRows2>)
+                                          : (runs ? tile_map_kernel<kTmByRuns | kTmRows4> : tile_map_kernel<kTmRows4>);
+    hipLaunchKernelGGL(kernel, dim3(jobs.j[0].gx * jobs.j[0].gy), dim3(kTmThreads), 0, st, d_bits, d_blocks, block,
+                       d_blocks ? S / block : (int64_t)0, n_rows, jobs);
     MM_LAUNCH_CHECK();
     if (d_rowpairs) {
         hipLaunchKernelGGL(row_pairs_kernel, dim3((unsigned)jobs.j[0].nq), dim3(256), 0, st, d_cnt, jobs.j[0].nk,

@@ -159,6 +159,67 @@ def test_tile_map_large_maps(tile, kind):
     check_tile_map(lay, tile[0], tile[1], use_c=True)
 
 
+def layout_medium_spans(seed, S):
+    """Spans of 4 to 12 tokens with 0 to 7 text tokens between them: 10 to 30 runs per tile of 64
+    to 128 tokens, on either side of how many are kept."""
+    rng, spans, pos = np.random.default_rng(seed), [], 1
+    while pos + 40 < S:
+        spans.append((pos, int(rng.integers(4, 13)), 1 + len(spans) % 3))
+        pos += spans[-1][1] + int(rng.integers(0, 8))
+    return wl.Layout(S, spans, [0, S])
+
+
+@pytest.mark.parametrize("tile", [(640, 16), (320, 48), (32, 32), (24, 40), (64, 128), (128, 128), (16, 16)])
+@pytest.mark.parametrize("kind", ["short spans", "medium spans", "window"])
+def test_tile_map_many_runs_in_large_maps(tile, kind):
+    """Tiles of more runs than have a closed form, by rows: more than 256 rows per tile (fetched
+    anew for every pair), two tiles of at most 32 rows together; several threads per pair in
+    groups of few pairs; workloads of every kind in one map (the last third is plain text)."""
+    S = 15360
+    lay = {"short spans": lambda: wl.layout_short_spans(21, S), "medium spans": lambda: layout_medium_spans(22, S),
+           "window": lambda: wl.layout_lambda([9000, 6360], 70, 1000)}[kind]()
+    if kind != "window":
+        keep = [j for j, s in enumerate(lay.spans) if s[0] + s[1] <= 2 * S // 3]
+        lay = wl.Layout(S, [lay.spans[j] for j in keep], lay.sample_off, deny=[lay.deny[j] for j in keep],
+                        window=[5 * (j % 3 == 0) for j in keep])
+    check_tile_map(lay, tile[0], tile[1], use_c=True)
+
+
+def test_tile_map_positions_beyond_30_bits():
+    """A share's rows near the end of 2^30 + 2^20 tokens (the library's own map of a share; the
+    public one would count all rows): positions are 64-bit there."""
+    import ctypes
+    from oracle import mask as om
+    S, T, tk, block = (1 << 30) + (1 << 20), 8192, 8192, 128
+    # the last T tokens: spans with deny masks and windows, two samples; all before: text of sample 0
+    lay = wl.Layout(T, [(300, 700, 1), (2000, 130, 2), (5100, 900, 1)], [0, 5000, T], deny=[0, 1, 2], window=[90, 0, 400])
+    tail = torch.from_numpy(oracle_bits(lay).view(np.int64)).to(DEV)
+    bits = torch.empty(S, dtype=torch.int64, device=DEV)
+    bits[:S - T] = tail[0]
+    bits[S - T:] = tail
+    blocks = torch.tensor([(S - T) // block + b for b in (63, 2, 16, 40, 8)], dtype=torch.int32, device=DEV)
+    rows = np.concatenate([np.arange(128) + 128 * b for b in (63, 2, 16, 40, 8)])
+    n_q, n_k = 3, S // tk                                    # q-tiles of 256 rows, the last one ragged
+    cls = torch.full((n_q, n_k), 9, dtype=torch.uint8, device=DEV)
+    cnt = torch.full((n_q, n_k), -1, dtype=torch.int32, device=DEV)
+    f = mb.lib()._ZN2mm15launch_tile_mapEPKmlPKiiliiPhPjPmP12ihipStream_t
+    f.restype = ctypes.c_int
+    vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+    f.argtypes = [vp, i64, vp, i32, i64, i32, i32, vp, vp, vp, vp]
+    assert f(bits.data_ptr(), S, blocks.data_ptr(), block, len(rows), 256, tk, cls.data_ptr(), cnt.data_ptr(), 0,
+             torch.cuda.current_stream().cuda_stream) == 0
+    fl = fields(lay)
+    seen = om.visible(rows, np.arange(T), fl[0], fl[1], fl[2], fl[3], fl[4], windows(lay)).sum(axis=1)
+    before = np.where((fl[0][rows] == 0) & fl[2][rows].astype(bool) & (fl[4][rows] & 1 == 1), tk, 0)     # text of sample 0
+    for i in range(n_q):
+        r = slice(256 * i, min(256 * (i + 1), len(rows)))
+        n = r.stop - r.start
+        c = cnt[i].cpu().numpy().view(np.uint32)
+        assert (c[:-1] == before[r].sum()).all() and c[-1] == seen[r].sum()
+        k = cls[i].cpu().numpy()
+        assert (k[:-1] == (0 if before[r].sum() == 0 else 1 if before[r].sum() == n * tk else 2)).all()
+
+
 def layouts_window():
     """Look-back windows: attention sinks plus a sliding window (the lambda
     pattern of section 5.5) in one sample and packed, window shorter and longer
