@@ -188,10 +188,11 @@ int mmattn_fwd(const void* q_loc, const void* k, const void* v, const uint64_t* 
  *   - the device that `stream` belongs to must be the current device;
  *   - shares needing more scratch than that (mmattn_workspace_size(
  *     MMATTN_OP_FWD, ...) says how much) give MMATTN_ERR_WORKSPACE; nothing is
- *     launched then.  Shares with at least 512 (128-row tile, head pair) work
- *     items need about 5 bytes per (128-row tile, 64-key tile) pair, 1.3 MiB at
- *     131072 keys x 16384 rows; smaller shares are cut into list slices whose
- *     fp32 partial results can take far more (up to 64 x the size of O in fp32);
+ *     launched then.  Shares with at least 512 work items (a 128-row tile of a pair
+ *     of heads; of one head where Hq/Hkv is odd) and shares of sequences of up to
+ *     512 keys need about 5 bytes per (128-row tile, 64-key tile) pair, 1.3 MiB at
+ *     131072 keys x 16384 rows; others are cut into list slices whose fp32 partial
+ *     results can take far more (up to 64 x the size of O in fp32);
  *   - all calls on one GPU share the one array: calls that overlap on a GPU
  *     (different streams, different threads) race and must be ordered by the
  *     caller.  The status word of the block-index check lives in that array and

@@ -14,6 +14,7 @@
 // contraction indices in the order [0..3, 8..11, 4..7, 12..15] (kPerm16), so a
 // lane's 8 values are 16 contiguous bytes.
 #pragma once
+#include <algorithm>
 #include "common.h"
 
 namespace mm {
@@ -201,30 +202,21 @@ struct FwdSplit {
 // slices are workgroups that exit at once, about 4 us per thousand) what lists of full
 // length would need for about 1024 workgroups.  The slice length itself is chosen on the device from the
 // actual list lengths (slice_length below) and is never shorter than csz.
-// `groups`: workgroups per q-tile (head groups).
-constexpr int32_t kFewItems = 512;
-//
-// list_room: what the partial buffers are sized for; list_split: what is launched, fewer where
-// slice_length cannot cut that far (slices of at least four tiles, lists of at most eight never)
-// and none at all, nor an aggregation launch (4 us), when no list can be cut.
-inline FwdSplit list_room(int32_t nq, int32_t nk, int32_t groups) {
+// `groups`: workgroups per q-tile (head groups).  No more slices than slice_length can cut (slices
+// of at least four tiles; no list is cut when the longest has at most eight) and none at all, nor
+// an aggregation launch (4 us) or partial buffers, when no list can be cut.
+constexpr int32_t kFewItems = 512, kWholeList = 8, kShortSlice = 4;
+inline FwdSplit list_split(int32_t nq, int32_t nk, int32_t groups) {
     const int64_t items = (int64_t)nq * groups;
     int64_t cmax = 1;
-    if (items < kFewItems) {
+    if (items < kFewItems && nk > kWholeList) {
         cmax = (nk >= 512 ? 4 : 2) * ((1024 + items - 1) / items);
-        const int64_t most = nk / 2 > 1 ? nk / 2 : 1;         // at least two tiles per slice
-        if (cmax > most) cmax = most;
-        if (cmax > 64) cmax = 64;
+        cmax = std::min<int64_t>({cmax, 64, nk / 2});         // at least two tiles per slice
     }
     FwdSplit sp;
     sp.csz = (int32_t)((nk + cmax - 1) / cmax);
     sp.cmax = (nk + sp.csz - 1) / sp.csz;                     // no empty trailing slices
-    return sp;
-}
-constexpr int32_t kWholeList = 8, kShortSlice = 4;
-inline FwdSplit list_split(int32_t nq, int32_t nk, int32_t groups) {
-    FwdSplit sp = list_room(nq, nk, groups);
-    const int32_t most = nk <= kWholeList ? 1 : (nk + kShortSlice - 1) / kShortSlice;
+    const int32_t most = (nk + kShortSlice - 1) / kShortSlice;
     if (sp.cmax > most) {
         sp.csz = (nk + most - 1) / most;
         sp.cmax = (nk + sp.csz - 1) / sp.csz;

@@ -1286,8 +1286,7 @@ static BwdLayout bwd_layout(int64_t S, int64_t n_loc, int32_t n_blocks, int32_t 
                          (size_t)L.n_extra * L.ch.cmax;
     L.pool = take(slots * 2 * kKvBN * Hkv * D * 4);
     L.split = list_split(L.nq_a, L.nk_a, Hq);          // dq_kernel: one workgroup per (q-tile, head)
-    const int32_t room = list_room(L.nq_a, L.nk_a, Hq).cmax;
-    L.dq_part = take(room > 1 ? (size_t)room * L.n_pad * Hq * D * 4 : 0);
+    L.dq_part = take(L.split.cmax > 1 ? (size_t)L.split.cmax * L.n_pad * Hq * D * 4 : 0);
     L.total = off;
     return L;
 }

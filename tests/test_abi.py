@@ -153,3 +153,21 @@ def test_workspace_size_monotone():
     assert 0 < a < b
     assert mb.workspace_size(mb.OP_TILE_MAP, 8192, 0, 0) == 0
     assert mb.workspace_size(mb.OP_ENCODE, 8192, 4, 1) >= 4 * 24 + 16
+
+
+@pytest.mark.parametrize("S,n_blocks,Hq,Hkv,D", [(512, 4, 8, 8, 128), (512, 1, 64, 8, 64), (256, 2, 16, 2, 128),
+                                                 (8192, 64, 16, 16, 128), (4096, 32, 32, 8, 128), (4096, 32, 32, 8, 64)])
+def test_no_partial_buffers_where_no_list_is_cut(S, n_blocks, Hq, Hkv, D):
+    """Up to eight key tiles, or 512 work items or more (pairs of heads, where they are even):
+    no list is cut, so the workspaces hold no partial results."""
+    tiles, out_fp32 = n_blocks * (S // 64), n_blocks * 128 * Hq * D * 4
+    plan = 5 * tiles + 256 * 16 + Hkv * 64 * 4 + 8 * n_blocks * 128       # lists, norms, tables, alignment
+    assert mb.workspace_size(mb.OP_FWD, S, n_blocks, 128, Hq, Hkv, D) <= plan
+    if S <= 512:
+        # the backward's copies of Q and dO (bf16) and its rows' constants; its pool of dK, dV partials
+        # belongs to the pass over keys
+        pool = (S // 128) * (Hq // Hkv) * 2 * 128 * Hkv * D * 4
+        rows = 2 * out_fp32 // 2 + 4 * n_blocks * 128 * (4 * Hq + 3)
+        assert mb.workspace_size(mb.OP_BWD, S, n_blocks, 128, Hq, Hkv, D) <= rows + pool + plan + 4 * tiles + 256 * 16
+    # one that is cut has room for slices of at least four tiles
+    assert mb.workspace_size(mb.OP_FWD, 2048, 2, 128, 2, 1, 128) >= 8 * 256 * 2 * (128 + 2) * 4

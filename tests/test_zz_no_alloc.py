@@ -10,8 +10,8 @@ FAKE = 0x1000          # non-null, aligned, never dereferenced on an error path
 
 
 def test_too_large_share_is_rejected_on_the_host():
-    # two q-tiles of 8 heads against 8192 keys are cut into 64 list slices whose fp32 partial
-    # results need 67 MiB: more than the static array holds
+    # two q-tiles of 8 heads against 8192 keys are cut into 32 list slices whose fp32 partial
+    # results need 32.5 MiB: more than the static array holds
     S, nb, block, Hq, Hkv, D = 8192, 2, 128, 8, 8, 128
     assert mb.workspace_size(mb.OP_FWD, S, nb, block, Hq, Hkv, D) > mb.STATIC_SCRATCH_BYTES
     rc = mb.lib().mmattn_fwd_static(FAKE, FAKE, FAKE, FAKE, FAKE, nb, block, S, Hq, Hkv, D, 0.1, mb.BF16,
@@ -36,7 +36,7 @@ def test_two_calls_in_a_row_match_the_workspace_entry_point():
     cases = [
         # 16 q-tiles x 32 head pairs: lists not cut, the scratch holds the plan only
         (wl.layout_random(30, S=2048, n_samples=1, max_spans=3), list(range(16)), 128, 64, 16, 128, 300),
-        # few work items: every q-tile's list is cut into slices, 16 MiB of partial results in the scratch
+        # few work items: every q-tile's list may be cut into slices, 8 MiB of partial results in the scratch
         (wl.layout_random(31, S=1024, n_samples=2, max_spans=5), list(range(8)), 128, 4, 2, 128, 301),
         # smaller share, other head shape, unsorted block list; its slices land on the leftovers
         (wl.layout_random(32, S=1024, n_samples=1, max_spans=3), [5, 1, 6], 128, 2, 1, 64, 302),
