@@ -85,12 +85,15 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+# The handle of a device's current stream without a Stream object, which costs 3 us per call (a
+# plan of a short sequence pays that three times out of 58 us); None where this torch lacks it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        # the handle itself where CUDA is up: a Stream object costs 3 us per call, which a plan of
-        # a short sequence pays three times out of 58 us
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 

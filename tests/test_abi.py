@@ -171,3 +171,20 @@ def test_no_partial_buffers_where_no_list_is_cut(S, n_blocks, Hq, Hkv, D):
         assert mb.workspace_size(mb.OP_BWD, S, n_blocks, 128, Hq, Hkv, D) <= rows + pool + plan + 4 * tiles + 256 * 16
     # one that is cut has room for slices of at least four tiles
     assert mb.workspace_size(mb.OP_FWD, 2048, 2, 128, 2, 1, 128) >= 8 * 256 * 2 * (128 + 2) * 4
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """A torch without the raw-handle function: the Stream object's handle is used; likewise
+    before CUDA is initialised, and for a stream given as an object or a handle."""
+    class Stream:
+        cuda_stream = 77
+    monkeypatch.setattr(mb.torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(mb.torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(mb.torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(mb, "_raw_stream", None)
+    assert mb._stream(None) == 77
+    monkeypatch.setattr(mb, "_raw_stream", lambda device: 100 + device)
+    assert mb._stream(None) == 103
+    monkeypatch.setattr(mb.torch.cuda, "is_initialized", lambda: False)
+    assert mb._stream(None) == 77
+    assert mb._stream(Stream) == 77 and mb._stream(5) == 5
