@@ -82,6 +82,40 @@ def test_one_head_per_workgroup_long_lists():
              Hq=32, Hkv=32, D=128, seed=89, heads=[0, 31])
 
 
+def pairs_of_heads(n_loc, Hq, Hkv):
+    """Whether the share is one that puts two heads into a workgroup (head_dim 128)."""
+    return Hq // Hkv % 2 == 0 and -(-n_loc // 128) * Hq // 2 >= 512
+
+
+@pytest.mark.parametrize("kind", ["lambda", "denied", "short spans", "windowed spans", "noncausal"])
+def test_pairs_of_heads(kind):
+    """Shares of 512 pairs of heads and more, which share a workgroup: ragged last q-tiles,
+    unsorted blocks of 48, 80 and 240 rows, KV heads that are no multiple of the XCDs, windows,
+    deny masks, element-by-element masking, rows that see nothing but their span."""
+    lay, block, Hq, Hkv, n = {
+        "lambda": (wl.layout_lambda([1200, 720], 4, 300), 80, 96, 12, 18),
+        "denied": (wl.layout_random(101, S=1920, n_samples=2, max_spans=6, noncausal_prob=0.2, deny_prob=0.8), 48, 96, 6, 29),
+        "short spans": (wl.layout_short_spans(102, 2048), 128, 64, 32, 16),
+        "windowed spans": (wl.layout_random(103, S=1024, n_samples=2, max_spans=6), 64, 128, 4, 16),
+        "noncausal": (wl.layout_random(104, S=1920, n_samples=3, max_spans=5, noncausal_prob=0.7), 240, 72, 36, 8)}[kind]
+    if kind == "windowed spans":
+        lay.window = [37 * (j + 1) for j in range(len(lay.spans))]
+    blocks = np.random.default_rng(105).permutation(lay.S // block)[:n].tolist()
+    assert pairs_of_heads(n * block, Hq, Hkv)
+    run_case(lay, blocks, block, Hq, Hkv, 128, seed=106, heads=[0, Hq // 2 - 1, Hq - 1])
+
+
+def test_pairs_of_heads_bad_block_index_is_contained():
+    lay = wl.Layout(1024, [], [0, 1024])
+    t = make_tensors(107, 1024, 1024, 128, 4, 128)
+    bl = torch.tensor([1, 2, 3, 9, 4, 5, 6, 7], dtype=torch.int32, device=DEV)
+    assert pairs_of_heads(1024, 128, 4)
+    o, lse = torch.full_like(t["q"], 7.0), torch.full((128, 1024), 7.0, dtype=torch.float32, device=DEV)
+    mb.fwd(t["q"], t["k"], t["v"], gpu_bits(lay), bl, 128, out=(o, lse))
+    torch.cuda.synchronize()
+    assert (o.float() == 7.0).all() and (lse == 7.0).all()
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_single_heads_of_even_groups(D):
     """512 to 1023 (q-tile, head) work items of even groups: lists that are cut because some are
@@ -171,7 +205,7 @@ def test_block_size_not_a_power_of_two(block):
 def test_few_work_items_split_into_list_slices():
     """Shares with few (q-tile, head) work items cut every q-tile's k-tile list
     into slices run by separate workgroups and aggregate the partial results:
-    4096 keys, 2 head pairs -> 16 slices of 4 tiles, ragged at the diagonal."""
+    4096 keys, 11 q-tiles of 4 heads -> up to 16 slices, ragged at the diagonal."""
     lay = wl.layout_random(91, S=4096, n_samples=2, noncausal_prob=0.0)
     run_case(lay, list(range(0, 32, 3)), 128, Hq=4, Hkv=2, D=128, seed=51)
     run_case(lay, [31, 2, 17], 128, Hq=2, Hkv=2, D=64, seed=52)

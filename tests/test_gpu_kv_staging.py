@@ -145,6 +145,38 @@ def test_window_touches_only_its_heads():
     check(o, lse, o_ref, lse_ref)
 
 
+@pytest.mark.parametrize("order", [[(0, 4), (4, 1), (5, 2), (7, 1)], [(7, 1), (0, 4), (4, 1), (5, 2)], "staged"])
+def test_windows_share_a_plan_across_kernels(order):
+    """4096 rows of 64 / 8 heads: windows of four KV heads put pairs of heads into a workgroup and
+    walk whole lists, windows of one and two run single heads and cut them; each reuses the plan
+    that another left, whatever slice length that chose.  `staged`: two windows of four."""
+    Hq, Hkv, D, S = 64, 8, 128, 4096
+    lay = wl.layout_packed(153, S=S, n_samples=4, span_lo=40, span_hi=300)
+    blocks = np.random.default_rng(153).permutation(S // 64).tolist()
+    t = make_tensors(413, S, S, Hq, Hkv, D)
+    bits = gpu_bits(lay)
+    bl = torch.tensor(blocks, dtype=torch.int32, device=DEV)
+    if order == "staged":
+        o, lse = mb.fwd_staged(t["q"], t["k"], t["v"], torch.empty_like(t["k"]), torch.empty_like(t["v"]), bits, bl, 64, 4,
+                               torch.cuda.Stream())
+        order = [(0, 4), (4, 4)]
+    else:
+        ws = torch.empty(mb.workspace_size(mb.OP_FWD_HEADS, S, len(blocks), 64, Hq, Hkv, D), dtype=torch.uint8, device=DEV)
+        o, lse = torch.full_like(t["q"], 7.0), torch.full((Hq, S), 7.0, dtype=torch.float32, device=DEV)
+        for n, (g0, c) in enumerate(order):
+            mb.fwd_heads(t["q"], t["k"], t["v"], bits, bl, 64, g0, c, plan_ready=n > 0, out=(o, lse), ws=ws)
+    torch.cuda.synchronize()
+    f = fields(lay)
+    rows = oa.rows_of_blocks(blocks, 64)
+    sel = np.sort(np.random.default_rng(6).choice(S, size=160, replace=False))
+    Q, K, V = f64(t["q_bits"]), f64(t["k_bits"]), f64(t["v_bits"])
+    for g0, c in order:
+        for g, h in ((g0, 8 * g0), (g0 + c - 1, 8 * (g0 + c) - 1)):
+            o_ref, lse_ref = oa.forward(Q[sel][:, h:h + 1], K[:, g:g + 1], V[:, g:g + 1], rows[sel], f[0], f[1], f[2],
+                                        modality=f[3], attend=f[4])
+            check(o[sel][:, h:h + 1], lse[h:h + 1][:, sel], o_ref, lse_ref)
+
+
 def test_workload2_pipelined_sampled():
     """The 8k workload in the configuration bench.py times: whole sequence,
     one KV head per stage; sampled rows and heads against the oracle."""
