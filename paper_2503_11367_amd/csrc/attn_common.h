@@ -230,9 +230,9 @@ inline FwdSplit list_split(int32_t nq, int32_t nk, int32_t groups) {
 //   Uneven lists: the slices that finish last cost about one slice of time, while every
 //   slice costs a fixed amount of bandwidth for its partial result (worth about 1/32 of
 //   a tile's time across the chip); c + W/(32 c) is smallest at c = sqrt(W/32).
-// At least 8 tiles, at most the whole list.  When there are fewer than three tiles per CU, at
-// least 4, for then most CUs have nothing to do: half of 1920 tokens with 6 heads (480 tiles)
-// 28 -> 22 us in the forward, 34 -> 28 us in the dQ pass.  With four tiles per CU (4096 tokens, a
+// At least 8 tiles, at most the whole list.  When there are fewer than three tiles per CU, and
+// the longest list has more than eight, at least 4, for then most CUs have nothing to do: half of
+// 1920 tokens with 6 heads (540 tiles) 28 -> 22 us in the forward, 34 -> 28 us in the dQ pass.  With four tiles per CU (4096 tokens, a
 // rank of four, 8 heads) the longer sums of the aggregation already cost more, 59 -> 65 us.
 //   512 work items or more (see fwd_split_groups) give every CU two from the outset: they are
 //   cut only where some lists outlast the rest.  Whole stay lists about as long as each other;

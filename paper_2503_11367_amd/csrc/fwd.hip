@@ -17,7 +17,8 @@
 //                  transpose read ds_read_b64_tr_b16).
 // K/V tiles go HBM/L2 -> LDS directly (global_load_lds_dwordx4, no registers)
 // through a ring of NST stages (of a tile, or of half a tile): the transfers of the next tiles overlap the
-// math of the current one and there is one workgroup barrier per tile.
+// math of the current one and there is one workgroup barrier per stage (a tile; two per
+// tile where the stages are half tiles).
 // The loop is a software pipeline over half tiles (32 keys): while the
 // probabilities of one half tile are exponentiated and multiplied into O, the
 // scores of the next one are already being formed.  Registers (about 210 per
@@ -147,22 +148,23 @@ struct FwdSmem {
 // heads per KV head leaves one head per workgroup of four: its ring is four half tiles (65 KiB),
 // so that two workgroups, each with barriers of its own, put the same two wavefronts on a
 // SIMD.  Measured there (whole calls) against a ring of three tiles, one workgroup per CU: 8192
-// tokens, 32 / 32 heads 757 -> 646 us, 24 / 8 heads 530 -> 450 us; used for pairs of heads too it
+// tokens, 32 / 32 heads 655 -> 561 us, 24 / 8 heads 502 -> 426 us; used for pairs of heads too it
 // is 4 % (8192 tokens) to 6 % (32768) slower than their shared ring, since every head then
 // transfers its own tiles.  A workgroup of 256 rows of one head, sharing a ring of four tiles,
 // was 1 % to 3 % faster on long samples and 27 % slower on a packed share.
 // At D = 64 a tile has half the matrix instructions
 // under the same exponentials, so the vector work is the bound and more wavefronts per SIMD
 // help: one head per workgroup with three stages (50 KiB) and at most 168 registers puts three
-// workgroups on a CU.  Measured there (whole calls): 8192 tokens, 32 / 8 heads 341 us with two
-// heads per workgroup, 316 us so; 32768 tokens with a 4096 window, 16 heads 695 us with 205
-// registers (two workgroups per CU), 618 us so.
+// workgroups on a CU.  Measured there (whole calls): 8192 tokens, 32 / 8 heads 322 us with two
+// heads per workgroup, 310 us so; 32768 tokens with a 4096 window, 16 heads 657 us with 205
+// registers (two workgroups per CU), 564 us so.
 // Pairs of heads also part ways in shares of fewer than kFwdPairItems (q-tile, pair) work items:
 // those do not fill the chip with whole lists, and twice as many smaller workgroups need fewer
 // slices and partial results.  Measured, pairs / single heads: 4096 tokens, 16 / 8 heads (256
-// pairs) 138 / 106 us, a rank of four of 8192 tokens, 32 / 8 heads (256) 203 / 181 us, a rank of 32
-// of 32768 (128) 366 / 338 us, 1920 tokens, 8 / 2 heads (60) 46 / 47 us; with whole lists 4096
-// tokens, 32 / 8 heads (512) 144 / 151 us, a rank of two of 8192 (512) 275 / 285 us.
+// pairs) 145 / 112 us, a rank of four of 8192 tokens, 32 / 8 heads (256) 215 / 182 us, a rank of 32
+// of 32768 (128) 396 / 354 us, 1920 tokens, 8 / 2 heads (60) 47 / 40 us (the pairs with the lists,
+// slices and tile maps of that time); with whole lists 4096 tokens, 32 / 8 heads (512) 144 / 151
+// us, a rank of two of 8192 (512) 275 / 285 us.
 constexpr int64_t kFwdPairItems = 512;
 static int32_t fwd_heads_per_wg(int32_t D, int32_t rep, int32_t nq, int32_t Hq_run) {
     return D == 128 && rep % 2 == 0 && (int64_t)nq * Hq_run / 2 >= kFwdPairItems ? 2 : 1;

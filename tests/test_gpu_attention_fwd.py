@@ -62,7 +62,7 @@ def run_case(lay, blocks, block, Hq, Hkv, D, seed, heads=None, rows_sample=None)
 @pytest.mark.parametrize("sharp", [1.0, 20.0])
 def test_one_head_per_workgroup_list_lengths(Hq, Hkv, D, sharp):
     """Heads without a partner in their workgroup: a block that sees 1, 2, ... 16 key tiles
-    (lists up to 8 tiles stay whole, longer ones are cut), with and without tracking of the
+    (a longest list of up to 8 tiles stays whole, longer ones are cut), with and without tracking of the
     running maximum (a sharp softmax needs it), ragged 64-row shares."""
     lay = wl.Layout(1024, [(130, 60, 1), (500, 200, 2)], [0, 1024])
     f, bits = fields(lay), gpu_bits(lay)
