@@ -60,3 +60,21 @@ def test_two_calls_in_a_row_match_the_workspace_entry_point():
     for t, bits, bl, block, ref, out in results:
         assert torch.equal(out[0].view(torch.int16), ref[0].view(torch.int16))
         assert torch.equal(out[1].view(torch.int32), ref[1].view(torch.int32))
+
+
+@pytest.mark.gpu
+def test_share_without_partial_results_fits_whatever_its_heads():
+    """512 keys, 64 heads: no list is cut, so the scratch holds the plan only."""
+    import torch
+    from paper_2503_11367_amd import workloads as wl
+    from gpu_util import DEV, gpu_bits, make_tensors
+
+    lay = wl.layout_random(33, S=512, n_samples=2, max_spans=4)
+    t = make_tensors(303, 512, 512, 64, 8, 128)
+    bits, bl = gpu_bits(lay), torch.arange(4, dtype=torch.int32, device=DEV)
+    assert mb.workspace_size(mb.OP_FWD, 512, 4, 128, 64, 8, 128) < 1 << 16
+    ref = mb.fwd(t["q"], t["k"], t["v"], bits, bl, 128)
+    out = torch.full_like(t["q"], float("nan")), torch.full((64, 512), float("nan"), dtype=torch.float32, device=DEV)
+    mb.fwd_static(t["q"], t["k"], t["v"], bits, bl, 128, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], ref[0]) and torch.equal(out[1], ref[1])
