@@ -274,7 +274,10 @@ rank_lines_kernel(const RankJobs jobs) {
 // kSmallLines lines of at most kSmallItems items, four lines per wavefront with all their
 // classes in flight together.  Bound by latency and by what a launch costs.  Measured (the two
 // kernels together / this one): one list of 8 items 3.9 us / 2.6 us, 8 to 15 lists of up to 30
-// items 5.6 us / 4.2 us; 64 lists of 128 items, in four such rounds, 9.7 us / 14.8 us.
+// items 5.6 us / 4.2 us; 64 lists of 128 items, in four such rounds, 9.7 us / 14.8 us.  The line
+// lies where neither is ahead any more: whole forward calls with 4 lists of 256 items 32.4 / 30.8
+// us, 8 lists 36.2 / 35.4, 12 lists 44.4 / 44.6, 16 lists 48.0 / 48.6 (backward, two sets of 16
+// lists of 16 and 32 items, 53.0 / 52.2).
 constexpr int kSmallLines = 16, kSmallItems = 256;
 struct ListJob { CompactJob c; RankJob r; };
 struct ListJobs { ListJob j[2]; };
