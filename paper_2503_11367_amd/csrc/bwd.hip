@@ -1356,6 +1356,7 @@ static int launch_bwd_d(const AttnArgs& a, const void* o, const float* lse, cons
     const float scale_log2 = a.scale * kLog2e;
     {
         BwdPrologue p;
+        static_assert(kDqBM == 2 * kWave && kKvBM == kWave, "rows that the prologue's map code is for");
         p.maps.j[0] = tile_map_job(a.S, n_loc, kDqBM, kDqBN, pa.cls, nullptr);
         p.maps.j[1] = tile_map_job(a.S, n_loc, kKvBM, kKvBN, pb.cls, nullptr);
         p.n_map_wgs = tile_map_workgroups(p.maps, 2);

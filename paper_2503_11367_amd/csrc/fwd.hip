@@ -973,6 +973,7 @@ static FwdScratch fwd_scratch(const AttnArgs& a, void* ws) {
 static int launch_fwd_prologue(const AttnArgs& a, const FwdScratch& s, int32_t norm_heads, hipStream_t st) {
     const int64_t n_loc = (int64_t)a.n_blocks * a.block;
     FwdPrologue p;
+    static_assert(kFwdBM == 2 * kWave, "rows that the prologue's map code is for");
     p.maps.j[0] = p.maps.j[1] = tile_map_job(a.S, n_loc, kFwdBM, kFwdBN, s.plan.cls, nullptr);
     p.n_map_wgs = tile_map_workgroups(p.maps, 1);
     p.bits = a.bits; p.blocks = a.blocks; p.n_blocks = a.n_blocks; p.block = a.block;
