@@ -139,7 +139,7 @@ int mmattn_fwd(const void* q_loc, const void* k, const void* v, const uint64_t* 
     const size_t need = fwd_workspace(S, (int64_t)n_blocks * block, Hq, Hkv, D);
     if (!ws || !aligned(ws, 256) || ws_bytes < need) return MMATTN_ERR_WORKSPACE;
     AttnArgs a{q_loc, k, v, bits, blocks, n_blocks, block, S, Hq, Hkv, D, scale, 0, Hkv, 0};
-    return launch_fwd(a, o_loc, lse, ws, (hipStream_t)stream);
+    return launch_fwd_whole(a, o_loc, lse, ws, (hipStream_t)stream);
 }
 
 int mmattn_fwd_static(const void* q_loc, const void* k, const void* v, const uint64_t* bits,

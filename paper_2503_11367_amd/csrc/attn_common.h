@@ -165,6 +165,11 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// how far (in powers of two) the running row maximum may drift from the shift that
+// the probabilities are taken relative to before the shift follows it; inside
+// this band probabilities stay within 2^+-kShiftSlack, harmless in fp32/bf16
+constexpr float kShiftSlack = 64.0f;
+
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 

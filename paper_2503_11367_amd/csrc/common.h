@@ -162,6 +162,8 @@ size_t fwd_workspace(int64_t S, int64_t n_loc, int32_t Hq, int32_t Hkv, int32_t 
 size_t fwd_heads_workspace(int64_t S, int64_t n_loc, int32_t Hq, int32_t Hkv, int32_t D);
 size_t bwd_workspace(int64_t S, int64_t n_loc, int32_t Hq, int32_t Hkv, int32_t D);
 int launch_fwd(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st);
+// the whole share in one call: leaves no plan, so that small ones may do without
+int launch_fwd_whole(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st);
 // the plan alone, which needs neither q, k nor v; launch_fwd with plan_ready runs on it
 int launch_fwd_plan(const AttnArgs& a, void* ws, hipStream_t st);
 int launch_fwd_static(const AttnArgs& a, void* o, float* lse, hipStream_t st);

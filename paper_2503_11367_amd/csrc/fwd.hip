@@ -32,15 +32,12 @@
 #include <type_traits>
 #include "attn_common.h"
 #include "tilemap_body.h"
+#include "small.h"
 
 namespace mm {
 
 constexpr int kFwdBM = 128;     // query rows per q-tile
 constexpr int kFwdBN = 64;      // keys per k-tile
-// how far (in powers of two) the running row maximum may drift from the shift that
-// the probabilities are taken relative to before the shift follows it; inside
-// this band probabilities stay within 2^+-kShiftSlack, harmless in fp32/bf16
-constexpr float kShiftSlack = 64.0f;
 
 // A bound on the scores of a wavefront's rows: |s| <= |q| |k| scale log2(e) (Cauchy-Schwarz)
 // with the largest key norm of the KV head.  When it stays below kScoreBound for all 32
@@ -934,7 +931,7 @@ int launch_fwd_static(const AttnArgs& a, void* o, float* lse, hipStream_t st) {
     // nothing in the scratch has to start at zero: every call rebuilds the status word, the
     // block list and the plan before reading them, and reads back only the partial results
     // its own workgroups wrote
-    return launch_fwd(a, o, lse, ptr, st);
+    return launch_fwd_whole(a, o, lse, ptr, st);
 }
 
 // Where a call's scratch lies in `ws`, and the plan in it
@@ -1032,6 +1029,10 @@ int launch_fwd(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st)
     stage_end(MMATTN_STAGE_FWD, st);
     MM_LAUNCH_CHECK();
     return MMATTN_OK;
+}
+
+int launch_fwd_whole(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st) {
+    return small_fwd_wanted(a) ? launch_fwd_small(a, o, lse, (int32_t*)ws, st) : launch_fwd(a, o, lse, ws, st);
 }
 
 }  // namespace mm

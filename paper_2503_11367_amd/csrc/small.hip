@@ -1,0 +1,489 @@
+// Attention forward of small shares in ONE launch: no plan, no lists in memory, no partial results.
+//
+// The general path (fwd.hip) spends three or four dependent launches on a call; on a share of a few
+// hundred rows these, and the walk of one workgroup over its whole list of key tiles, are the
+// call's time.  Here a workgroup owns 32 query rows of one head, finds out by itself which units of 32
+// keys it has to visit, and its wavefronts take those units in turn, each with a ring of its own in
+// LDS and no barrier between them; at the end their partial results are added up in LDS in a fixed
+// order.
+//
+//   check     every workgroup reads the whole block list into LDS and checks it (as
+//             validate_blocks_body does for the general path); the first one leaves the status word
+//   classify  64 words per wavefront and step.  A unit of equal fields is compared as a whole, a
+//             lane per unit, with the runs of the workgroup's rows; a mixed one run by run, a lane
+//             per row: unit EMPTY, FULL or PARTIAL
+//   walk      unit i of the active ones belongs to wavefront i mod NW
+//   combine   through LDS, in the order of the wavefronts
+//
+// Bound by latency: block list, mask words, first tiles, one after the other, then a unit or two
+// per wavefront, about 1 us each; on larger shares by the transfers, for 32 rows of one head use a
+// unit where the general path's 128 or 256 do.  Measured, whole calls back to back: 512 tokens, one
+// head, 128 rows 16.9 -> 8.4 us; 1920 tokens, 960 rows, 6 / 2 heads (head_dim 128) 32 -> 15 us; 4096 tokens, 1024
+// rows, 8 / 2 heads 44 -> 24 us (128), 27 -> 14 us (64).  Over 1100 shapes of up to 16384 tokens the calls
+// that come here take 0.55 of the general path's time on the mean; the slowest is 3 % behind.
+#include "attn_common.h"
+#include "tilemap_body.h"
+#include "small.h"
+
+namespace mm {
+
+constexpr int kUnit = 32;              // rows and keys of a unit
+
+// the wavefront's own LDS reads are done (a transfer may overwrite what they read)
+__device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// at most N of the wavefront's transfers are on their way; nothing that reads LDS moves above
+template <int N>
+__device__ __forceinline__ void wait_landed() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// A unit's tokens where they carry equal fields at consecutive positions (x: the attend word of rows,
+// the modality of keys); else x is kSmallMixed | the unit's class
+struct SmallRun { uint32_t ss, x; };
+constexpr uint32_t kSmallMixed = 0x100u;   // neither an attend word nor a modality has this bit
+// What the two kernels' workgroups share in LDS beside their rings
+struct SmallPlanLds {
+    int32_t blk[kSmallBlocks];
+    SmallRun run[kSmallUnits];
+    uint16_t list[kSmallUnits];        // active units, ascending; PARTIAL ones with kSmallPartial
+};
+constexpr uint32_t kSmallPartial = 0x8000u;
+
+struct SmallShare {
+    const uint64_t* __restrict__ bits;
+    const int32_t* __restrict__ blocks;
+    int32_t n_blocks, block;
+    int32_t S, n_loc;
+    int32_t* __restrict__ err;
+    // position of local row r (< n_loc)
+    __device__ __forceinline__ int32_t pos(const int32_t* blk, int32_t r) const {
+        const uint32_t b = (uint32_t)r / (uint32_t)block;
+        return blk[b] * block + (int32_t)((uint32_t)r - b * (uint32_t)block);
+    }
+};
+
+// Block list into LDS; false when an entry is out of range (workgroup-uniform)
+template <int NT>
+__device__ __forceinline__ bool small_check(const SmallShare& sh, int32_t* blk) {
+    const int32_t n_seq = sh.S / sh.block;
+    int bad = 0;
+    for (int i = threadIdx.x; i < sh.n_blocks; i += NT) {
+        int32_t b = sh.blocks[i];
+        if (b < 0 || b >= n_seq) {
+            bad = 1;
+            b = 0;
+        }
+        blk[i] = b;
+    }
+    bad = __syncthreads_or(bad);
+    if (blockIdx.x == 0 && threadIdx.x < kFlagInts) sh.err[threadIdx.x] = threadIdx.x == 0 ? bad : 0;
+    return !bad;
+}
+
+// Any / all pairs of n_q rows at positions q0 .. and n_k keys at positions k0 .. visible, all rows and
+// all keys of equal fields
+__device__ __forceinline__ void small_pairs(uint32_t ss_q, uint32_t att, int32_t q0, int32_t n_q, uint32_t ss_k,
+                                            uint32_t mod, int32_t k0, int32_t n_k, bool& any, bool& all) {
+    const bool same_span = (ss_q & 0xFFFFu) != 0u && ss_q == ss_k;
+    const bool back = (ss_q >> 16) == (ss_k >> 16) && ((att >> mod) & 1u);
+    const int32_t win = mod == att_modality(att) ? (int32_t)att_window(att) : 0;
+    const int32_t reach = win != 0 ? win - 1 : 0x7FFFFFFF;
+    const int32_t least = q0 - (k0 + n_k - 1), most = q0 + n_q - 1 - k0;      // look-back distances
+    any = any || same_span || (back && most >= 0 && least <= reach);
+    all = all && (same_span || (back && least >= 0 && most <= reach));
+}
+
+__device__ __forceinline__ uint32_t unit_class(bool any, bool all) {
+    return !any ? MMATTN_TILE_EMPTY : (all ? MMATTN_TILE_FULL : MMATTN_TILE_PARTIAL);
+}
+
+// The active ones of `n` units into lds.list, by all wavefronts; returns how many.  A lane has a unit;
+// sees(unit, run, any, all) compares it with the workgroup's own tokens.
+template <int NW, class F>
+__device__ __forceinline__ int small_list(SmallPlanLds& lds, int n, int wave, int lane, F&& sees) {
+    __syncthreads();
+    int count = 0;
+    for (int u0 = 0; u0 < n; u0 += kWave) {
+        const int u = u0 + lane;
+        uint32_t c = MMATTN_TILE_EMPTY;
+        if (u < n) {
+            const SmallRun r = lds.run[u];
+            bool any = false, all = true;
+            sees(u, r, any, all);
+            c = r.x & kSmallMixed ? r.x & 3u : unit_class(any, all);
+        }
+        const uint64_t m = __ballot(c != MMATTN_TILE_EMPTY);
+        const int at = count + __popcll(m & ((1ull << lane) - 1));
+        if (c != MMATTN_TILE_EMPTY && at % NW == wave)
+            lds.list[at] = (uint16_t)((uint32_t)u | (c == MMATTN_TILE_PARTIAL ? kSmallPartial : 0u));
+        count += __popcll(m);
+    }
+    __syncthreads();
+    return count;
+}
+
+constexpr int kSmallAhead = 4;         // steps whose words a wavefront requests together
+
+// The classes of the mixed units among the two of a step, run by run: `m` the first tokens of all
+// runs, `valid` tokens in all; seen(run's first token, its length, some, every) for the workgroup.
+template <class F>
+__device__ __forceinline__ void small_mixed(SmallPlanLds& lds, int step, uint64_t m, int valid, bool mixed0, bool mixed1,
+                                            int lane, F&& seen) {
+    if (!mixed0) m &= ~0xFFFFFFFFull;
+    if (!mixed1) m &= 0xFFFFFFFFull;
+    bool any[2] = {false, false}, all[2] = {valid >= kUnit, valid >= kWave};
+    while (m) {
+        const int at = __ffsll((unsigned long long)m) - 1;
+        m &= m - 1;
+        const int len = (m ? __ffsll((unsigned long long)m) - 1 : (at < kUnit ? min(valid, kUnit) : valid)) - at;
+        bool some, every;
+        seen(at, len, some, every);
+        if (at < kUnit) { any[0] = any[0] || some; all[0] = all[0] && every; }
+        else { any[1] = any[1] || some; all[1] = all[1] && every; }
+    }
+    if (lane == 0 && mixed0) lds.run[2 * step].x = kSmallMixed | unit_class(any[0], all[0]);
+    if (lane == 0 && mixed1) lds.run[2 * step + 1].x = kSmallMixed | unit_class(any[1], all[1]);
+}
+
+// The key units that the 32 rows of a workgroup see: lane li holds a row (both half-waves the same).
+// `first`: words of the wavefront's first kSmallAhead steps.
+template <int NW>
+__device__ __forceinline__ int small_keys_of_rows(const SmallShare& sh, SmallPlanLds& lds, uint64_t (&first)[kSmallAhead],
+                                                  bool row_ok, uint32_t q_ss, uint32_t q_att, int32_t q_pos, int wave,
+                                                  int lane) {
+    const int steps = sh.S / kWave;
+    uint64_t w[kSmallAhead];
+#pragma unroll
+    for (int a = 0; a < kSmallAhead; ++a) w[a] = first[a];
+    for (int s0 = wave; s0 < steps; s0 += NW * kSmallAhead) {
+#pragma unroll
+        for (int a = 0; a < kSmallAhead; ++a) {
+            const int step = s0 + a * NW;
+            if (step >= steps) break;                          // wave-uniform
+            const uint32_t ss_k = word_ss(w[a]), mod_k = word_mod(w[a]);
+            const uint32_t b_ss = lane_below(ss_k, 0u), b_mod = lane_below(mod_k, 0u);
+            const uint64_t m = __ballot((lane & (kUnit - 1)) == 0 || ss_k != b_ss || mod_k != b_mod);
+            if ((lane & (kUnit - 1)) == 0) lds.run[2 * step + (lane >> 5)] = SmallRun{ss_k, mod_k};
+            if (m != 0x100000001ull)
+                small_mixed(lds, step, m, kWave, (uint32_t)m != 1u, (uint32_t)(m >> 32) != 1u, lane,
+                            [&](int at, int len, bool& some, bool& every) {
+                    const KeyRange r = visible_range(q_ss, q_att, q_pos, (uint32_t)__builtin_amdgcn_readlane((int)ss_k, at),
+                                                     (uint32_t)__builtin_amdgcn_readlane((int)mod_k, at), step * kWave + at, len);
+                    some = __any(row_ok && r.lo < (uint32_t)kWave);
+                    every = __all(!row_ok || r.all_of(len));
+                });
+        }
+#pragma unroll
+        for (int a = 0; a < kSmallAhead; ++a) {
+            const int step = s0 + (kSmallAhead + a) * NW;
+            if (step < steps) w[a] = sh.bits[step * kWave + lane];
+        }
+    }
+    // the rows' own runs
+    const uint32_t b_ss = lane_below(q_ss, 0u), b_att = lane_below(q_att, 0u), b_pos = lane_below((uint32_t)q_pos, 0u);
+    const uint32_t ok = (uint32_t)__ballot(row_ok);            // the first ones
+    const uint32_t starts = (uint32_t)__ballot(lane == 0 || q_ss != b_ss || q_att != b_att || (uint32_t)q_pos != b_pos + 1u) & ok;
+    return small_list<NW>(lds, sh.S / kUnit, wave, lane, [&](int u, const SmallRun& k, bool& any, bool& all) {
+        for (uint32_t m = starts; m != 0u;) {
+            const int at = __ffs(m) - 1;
+            m &= m - 1u;
+            const int end = m ? __ffs(m) - 1 : __popc(ok);
+            small_pairs((uint32_t)__builtin_amdgcn_readlane((int)q_ss, at), (uint32_t)__builtin_amdgcn_readlane((int)q_att, at),
+                        __builtin_amdgcn_readlane(q_pos, at), end - at, k.ss, k.x & 0xFu, u * kUnit, kUnit, any, all);
+        }
+    });
+}
+
+// A unit's 32 rows of a tensor in LDS (SwzTile MODE 0: row fragments and transpose reads)
+template <int D>
+struct SmallTile {
+    static constexpr int NDS = D / 16, NDB = D / 32, RB = D * 2;
+    static constexpr int kBytes = kUnit * RB, NI = kBytes / 1024;      // 1 KiB transfers
+    using T = SwzTile<D, 0>;
+    static constexpr int PER = 16 * T::RPS, NV = PER / 8;
+    uint32_t row[NDS], tr[NDB][NV];                                   // byte offsets of fragments
+    // byte offset of what this lane fetches: transfer i takes rows that are 64 / CPR * 4 beyond those
+    // of transfer i - 4, in the same rotation
+    uint32_t src[4];
+    int64_t src_step;
+    __device__ __forceinline__ void init(int lane, int64_t row_stride) {
+        RowFragAddr<T, D> fr;
+        TrFragAddr<T, D> ft;
+        fr.init(lane);
+        ft.init(lane);
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) row[ds] = (uint32_t)fr.off[ds];
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) tr[db][v] = (uint32_t)ft.off[db][v];
+        static_assert(NI == 4 || NI == 8, "four rotations");
+#pragma unroll
+        for (int i = 0; i < 4; ++i) src[i] = source(lane, i, row_stride, kUnit - 1);
+        src_step = 16 * T::RPS * row_stride;
+    }
+    // where transfer i of a unit at `unit` starts (wave-uniform) for the lane offsets src[i % 4]
+    __device__ __forceinline__ const char* from(const void* unit, int i) const {
+        return (const char*)unit + (i / 4) * src_step;
+    }
+    // the same for a unit whose rows past `last` do not exist (that row's data in their place)
+    __device__ __forceinline__ static uint32_t source(int lane, int i, int64_t row_stride, int last) {
+        int r, c;
+        T::src_of(4 * i + (lane >> 4), lane & 15, r, c);
+        return (uint32_t)(min(r, last) * row_stride + c * 16);
+    }
+    __device__ __forceinline__ bf16x8 read_row(uint32_t tile, int ds) const {
+        return __builtin_bit_cast(bf16x8, *(lds_u4)(uintptr_t)(tile + row[ds]));
+    }
+    // rows ks*16 .. of the tile (in the order of a C tile fed back), columns db*32 ..
+    __device__ __forceinline__ bf16x8 read_tr(uint32_t tile, int ks, int db) const {
+        const int r_lo = ks * 16, r_hi = ks * 16 + 8;
+        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(
+            tile + tr[db][(r_lo % PER) / 8] + (uint32_t)((r_lo / PER) * PER * RB)));
+        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(
+            tile + tr[db][(r_hi % PER) / 8] + (uint32_t)((r_hi / PER) * PER * RB)));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+};
+
+// Scores of a unit's keys (their words at `kw` in LDS, the first key k0) against this lane's row:
+// -inf where the row does not see the key
+__device__ __forceinline__ void mask_keys(floatx16& s, uint32_t kw, int32_t k0, uint32_t q_ss, uint32_t q_att,
+                                          int32_t q_pos, int lane) {
+    typedef const uint64_t __attribute__((address_space(3))) * lds_u8;
+    const uint32_t li = lane & 31, hh = lane >> 5;
+    const uint64_t wk = *(lds_u8)(uintptr_t)(kw + li * 8u);
+    const uint32_t ss_k = word_ss(wk), mod_k = word_mod(wk);
+    const uint32_t ss0 = __builtin_amdgcn_readfirstlane(ss_k), mod0 = __builtin_amdgcn_readfirstlane(mod_k);
+    if (__all(ss_k == ss0 && mod_k == mod0)) {                 // one run (wave-uniform)
+        const KeyRange r = visible_range(q_ss, q_att, q_pos, ss0, mod0, k0, kUnit);
+        if (__all(r.all_of(kUnit))) return;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (!r.sees(4u * hh + (uint32_t)(8 * q4 + j))) s[q4 * 4 + j] = -INFINITY;
+        return;
+    }
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t kl = 8u * q4 + 4u * hh + j;
+            const uint64_t w = *(lds_u8)(uintptr_t)(kw + kl * 8u);
+            if (!visible(q_ss, q_att, q_pos, word_ss(w), word_mod(w), k0 + (int32_t)kl)) s[q4 * 4 + j] = -INFINITY;
+        }
+}
+
+// max over the two half-waves (lanes l and l^32 hold the same row)
+__device__ __forceinline__ float halves_max(float x) {
+    float a = x, b = x;
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+    return fmaxf(a, b);
+}
+
+// ---------------------------------------------------------------- forward ----
+// (row unit, head); NW wavefronts, two per SIMD.  One stage per tensor and wavefront: the next
+// unit's K is requested once this one's scores are formed, its V once O is updated.
+template <int D, int NW>
+struct SmallFwdLds {
+    alignas(1024) unsigned char ring[NW][2 * SmallTile<D>::kBytes];    // K, V; then the wavefront's O
+    alignas(256) uint64_t kw[NW][kUnit];
+    float ml[NW][kUnit][2];
+    SmallPlanLds plan;
+};
+
+template <int D, int NW>
+__global__ void __launch_bounds__(64 * NW, 2)
+fwd_small_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K, const ushort_t* __restrict__ V,
+                 const SmallShare sh, int32_t Hq, int32_t rep, int32_t Hq_s, int32_t Hkv_s, float scale_log2,
+                 ushort_t* __restrict__ O, float* __restrict__ LSE) {
+    using Tile = SmallTile<D>;
+    constexpr int NDS = Tile::NDS, NDB = Tile::NDB, NI = Tile::NI;
+    __shared__ SmallFwdLds<D, NW> sm;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, hh = lane >> 5;
+    // the last rows, which under causal masks see the most keys, first
+    const int n_rb = (sh.n_loc + kUnit - 1) / kUnit;
+    const int rb = n_rb - 1 - (int)blockIdx.x / Hq, h = (int)blockIdx.x % Hq, g = h / rep;
+    const int row = rb * kUnit + li;
+    const bool row_ok = row < sh.n_loc;
+
+    bf16x8 qf[NDS];
+    uint64_t first[kSmallAhead];
+#pragma unroll
+    for (int a = 0; a < kSmallAhead; ++a) {
+        first[a] = 0;
+        if ((wave + a * NW) * kWave < sh.S) first[a] = sh.bits[(wave + a * NW) * kWave + lane];
+    }
+#pragma unroll
+    for (int ds = 0; ds < NDS; ++ds) qf[ds] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+    if (row_ok) {
+        const ushort_t* qp = Q + ((int64_t)row * Hq_s + h) * D + hh * 8;
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) qf[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + ds * 16));
+    }
+    if (!small_check<64 * NW>(sh, sm.plan.blk)) return;
+    int32_t q_pos = 0;
+    uint32_t q_ss = 0, q_att = 0;
+    if (row_ok) {
+        q_pos = sh.pos(sm.plan.blk, row);
+        const uint64_t w = sh.bits[q_pos];
+        q_ss = word_ss(w);
+        q_att = word_att(w);
+    }
+    Tile t;
+    t.init(lane, (int64_t)Hkv_s * D * 2);
+    const int n = small_keys_of_rows<NW>(sh, sm.plan, first, row_ok, q_ss, q_att, q_pos, wave, lane);
+
+    const uint32_t k_tile = lds_addr_of(sm.ring[wave]), v_tile = k_tile + Tile::kBytes, kw = lds_addr_of(sm.kw[wave]);
+    auto entry_at = [&](int i) -> uint32_t { return __builtin_amdgcn_readfirstlane((uint32_t)sm.plan.list[i]); };
+    auto issue_k = [&](uint32_t e) {                           // with the words of the unit's keys: NI + 1 transfers
+        const int64_t k0 = (int64_t)(e & ~kSmallPartial) * kUnit;
+        dma4(sh.bits + k0, (uint32_t)(lane * 4), kw);
+        const ushort_t* src = K + (k0 * Hkv_s + g) * D;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) dma16(t.from(src, i), t.src[i % 4], k_tile + i * 1024);
+    };
+    auto issue_v = [&](uint32_t e) {
+        const ushort_t* src = V + ((int64_t)(e & ~kSmallPartial) * kUnit * Hkv_s + g) * D;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) dma16(t.from(src, i), t.src[i % 4], v_tile + i * 1024);
+    };
+    floatx16 o[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+    // the shift starts at 0 and follows the running maximum only when the two drift far apart (see
+    // the general forward kernel)
+    float m_run = 0.f, m_true = -INFINITY, l_run = 0.f;
+    uint32_t e = wave < n ? entry_at(wave) : 0u;
+    wait_landed<0>();                                          // the loads so far: none is left for the loop
+    if (wave < n) {
+        issue_k(e);
+        issue_v(e);
+    }
+    for (int i = wave; i < n; i += NW) {
+        const bool more = i + NW < n;
+        const uint32_t e_next = more ? entry_at(i + NW) : 0u;
+        wait_landed<NI>();                                     // K and its words
+        floatx16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) s = mfma32(t.read_row(k_tile, ds), qf[ds], s);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] *= scale_log2;
+        if (e & kSmallPartial) mask_keys(s, kw, (int32_t)((e & ~kSmallPartial) * kUnit), q_ss, q_att, q_pos, lane);
+        if (more) {
+            wait_lds_reads();
+            issue_k(e_next);
+        }
+        float m_loc = s[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) m_loc = fmaxf(m_loc, s[r]);
+        m_true = fmaxf(m_true, halves_max(m_loc));
+        const bool move = m_true != -INFINITY && fabsf(m_true - m_run) > kShiftSlack;
+        if (__any(move)) {
+            const float m_new = move ? m_true : m_run;
+            const float alpha = __builtin_amdgcn_exp2f(fminf(m_run - m_new, 126.f));
+            l_run *= alpha;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+            m_run = m_new;
+        }
+        bf16x8 pf[2];
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+            const bf16x2 p2 = {(__bf16)__builtin_amdgcn_exp2f(s[r] - m_run), (__bf16)__builtin_amdgcn_exp2f(s[r + 1] - m_run)};
+            pf[r >> 3][r & 7] = p2[0];
+            pf[r >> 3][(r & 7) + 1] = p2[1];
+            // (the rounded probabilities, which the product below sees)
+            l_run = __builtin_amdgcn_fdot2_f32_bf16(p2, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, l_run, false);
+        }
+        if (more) wait_landed<NI + 1>();                       // V
+        else wait_landed<0>();
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) o[db] = mfma32(t.read_tr(v_tile, ks, db), pf[ks], o[db]);
+        if (more) {
+            wait_lds_reads();
+            issue_v(e_next);
+        }
+        e = e_next;
+    }
+
+    // ---- combine: register quads of O by lane, the wavefront's own ring --------------
+    l_run += __shfl_xor(l_run, 32);
+    constexpr int kQuads = 4 * NDB;                            // of 4 head-dim values per lane
+    static_assert(kQuads * 1024 <= 2 * Tile::kBytes, "O fits the ring");
+    wait_lds_reads();
+#pragma unroll
+    for (int q = 0; q < kQuads; ++q)
+        *(floatx4*)(sm.ring[wave] + q * 1024 + lane * 16) =
+            floatx4{o[q / 4][(q & 3) * 4], o[q / 4][(q & 3) * 4 + 1], o[q / 4][(q & 3) * 4 + 2], o[q / 4][(q & 3) * 4 + 3]};
+    if (hh == 0) {
+        sm.ml[wave][li][0] = m_run;
+        sm.ml[wave][li][1] = l_run;
+    }
+    __syncthreads();
+    float m = -INFINITY, den = 0.f, wt[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+        if (sm.ml[w][li][1] != 0.f) m = fmaxf(m, sm.ml[w][li][0]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float l = sm.ml[w][li][1];
+        wt[w] = l != 0.f ? __builtin_amdgcn_exp2f(sm.ml[w][li][0] - m) : 0.f;
+        den += l != 0.f ? l * wt[w] : 0.f;
+    }
+    if (!row_ok) return;
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+    ushort_t* op = O + ((int64_t)row * Hq_s + h) * D + 4 * hh;
+#pragma unroll
+    for (int q0 = 0; q0 < kQuads; q0 += NW) {
+        const int q = q0 + wave;
+        if (kQuads % NW != 0 && q >= kQuads) break;
+        floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const floatx4 part = *(const floatx4*)(sm.ring[w] + q * 1024 + lane * 16);
+            if (wt[w] != 0.f) sum += part * wt[w];             // (a wavefront without work left no sum)
+        }
+        bf16x4 out;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) out[u] = (__bf16)(sum[u] * inv);
+        *(u32x2*)(op + (q / 4) * 32 + (q & 3) * 8) = __builtin_bit_cast(u32x2, out);
+    }
+    if (wave == 0 && hh == 0)
+        LSE[(int64_t)h * sh.n_loc + row] = den > 0.f ? (m + __builtin_amdgcn_logf(den)) * kLn2 : -INFINITY;
+}
+
+// ---------------------------------------------------------------- host -------
+static SmallShare small_share(const AttnArgs& a, int32_t* err) {
+    return SmallShare{a.bits, a.blocks, a.n_blocks, a.block, (int32_t)a.S, a.n_blocks * a.block, err};
+}
+
+int launch_fwd_small(const AttnArgs& a, void* o, float* lse, int32_t* err, hipStream_t st) {
+    const int32_t rep = a.Hq / a.Hkv, Hq_run = rep * a.kv_count, n_loc = a.n_blocks * a.block;
+    const int64_t qo = (int64_t)a.kv_begin * rep * a.D, ko = (int64_t)a.kv_begin * a.D;
+    const dim3 grid((unsigned)((n_loc + kUnit - 1) / kUnit * Hq_run));
+    stage_begin(MMATTN_STAGE_FWD, st);
+    const bool four = small_fwd_four(a);
+    hipLaunchKernelGGL((a.D == 128 ? (four ? fwd_small_kernel<128, 4> : fwd_small_kernel<128, 8>)
+                                   : (four ? fwd_small_kernel<64, 4> : fwd_small_kernel<64, 8>)),
+                       grid, dim3(four ? 256 : 512), 0, st,
+                       (const ushort_t*)a.q + qo, (const ushort_t*)a.k + ko, (const ushort_t*)a.v + ko, small_share(a, err),
+                       Hq_run, rep, a.Hq, a.Hkv, a.scale * kLog2e, (ushort_t*)o + qo,
+                       lse + (int64_t)a.kv_begin * rep * n_loc);
+    stage_end(MMATTN_STAGE_FWD, st);
+    MM_LAUNCH_CHECK();
+    return MMATTN_OK;
+}
+
+}  // namespace mm

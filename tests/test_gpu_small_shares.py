@@ -1,0 +1,92 @@
+"""GPU parity of the single-launch kernels for small shares (csrc/small.hip) at the sizes where they
+can go wrong: one 16-row block, units of 32 rows that straddle blocks, mixed units, every number
+of wavefronts with and without work, both sides of the lines between the kernels.  The forward is
+compared with the oracle and with mmattn_fwd_heads, which takes the general path whatever the
+size: the same rounded probabilities, other orders of fp32 sums, so that O differs by a flipped last
+bit of bf16 here and there (2^-8 of the value; 1e-3 in relative L2 is a flip in one value of 15)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention as oa
+from paper_2503_11367_amd import binding as mb
+from paper_2503_11367_amd import workloads as wl
+
+from gpu_util import DEV, bf16_to_f64, f64, fields, gpu_bits, make_tensors, max_abs, rel_l2, windows
+
+pytestmark = pytest.mark.gpu
+
+
+def windowed(seed, S):
+    lay = wl.layout_random(seed, S=S, n_samples=2, max_spans=6, deny_prob=0.4)
+    lay.window = [37 * (j + 1) for j in range(len(lay.spans))]
+    return lay
+
+
+def spread(n, take, seed=0):
+    return np.random.default_rng(seed).permutation(n)[:take].tolist()
+
+
+# (layout, blocks, block, Hq, Hkv, D)
+CASES = {
+    "one block of 16 rows": (wl.Layout(128, [(20, 50, 1)], [0, 128]), [5], 16, 1, 1, 64),
+    "all of 128 tokens": (wl.Layout(128, [], [0, 100, 128]), [0], 128, 3, 1, 128),
+    "more workgroups than CUs at 128 tokens": (wl.Layout(128, [], [0, 128]), [1, 0], 64, 96, 12, 64),
+    "units of two runs": (wl.layout_random(201, S=640, n_samples=2, max_spans=4), spread(40, 23), 16, 4, 2, 128),
+    "mixed units everywhere": (wl.layout_short_spans(202, 1024), spread(8, 5), 128, 2, 1, 64),
+    "windows": (windowed(203, 1024), spread(64, 33), 16, 6, 2, 128),
+    "sinks": (wl.layout_lambda([1200, 720], 4, 300), spread(40, 21), 48, 2, 2, 64),
+    "rows that see only their span": (wl.layout_random(204, S=896, n_samples=3, max_spans=6, noncausal_prob=0.7), spread(7, 6), 128, 2, 1, 128),
+    "long list": (wl.Layout(4096, [(100, 700, 1)], [0, 4096]), [255, 17, 130, 40], 16, 32, 8, 128),
+    "eight wavefronts, last size": (wl.layout_random(205, S=2048, n_samples=1), spread(16, 8), 128, 8, 2, 64),
+    "four wavefronts, first size": (wl.layout_random(206, S=2048, n_samples=1), spread(128, 65), 16, 8, 4, 128),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_forward(name):
+    lay, blocks, block, Hq, Hkv, D = CASES[name]
+    f = fields(lay)
+    n_loc = len(blocks) * block
+    t = make_tensors(200, n_loc, lay.S, Hq, Hkv, D)
+    bits, bl = gpu_bits(lay), torch.tensor(blocks, dtype=torch.int32, device=DEV)
+    o, lse = torch.full_like(t["q"], 7.0), torch.full((Hq, n_loc), 7.0, dtype=torch.float32, device=DEV)
+    mb.fwd(t["q"], t["k"], t["v"], bits, bl, block, out=(o, lse))
+    heads = sorted({0, Hq // 2, Hq - 1})
+    for h in heads:
+        g = h // (Hq // Hkv)
+        oo, ll = oa.forward(f64(t["q_bits"])[:, h:h + 1], f64(t["k_bits"])[:, g:g + 1], f64(t["v_bits"])[:, g:g + 1],
+                            oa.rows_of_blocks(blocks, block), f[0], f[1], f[2], modality=f[3], attend=f[4], window=windows(lay))
+        got, l = bf16_to_f64(o)[:, h:h + 1], lse[h:h + 1].cpu().numpy().astype(np.float64)
+        assert max_abs(got, oo) < 2e-2 and rel_l2(got, oo) < 5e-3, h
+        fin = np.isfinite(ll)
+        assert np.array_equal(np.isneginf(l), ~fin) and max_abs(l[fin], ll[fin]) < 4.5e-3, h
+    ws = torch.empty(mb.workspace_size(mb.OP_FWD_HEADS, lay.S, len(blocks), block, Hq, Hkv, D), dtype=torch.uint8, device=DEV)
+    o2, lse2 = torch.full_like(o, 3.0), torch.full_like(lse, 3.0)
+    mb.fwd_heads(t["q"], t["k"], t["v"], bits, bl, block, 0, Hkv, False, (o2, lse2), ws)
+    assert rel_l2(bf16_to_f64(o), bf16_to_f64(o2)) < 1e-3
+    fin = torch.isfinite(lse2)
+    assert torch.equal(torch.isneginf(lse), ~fin) and float((lse - lse2)[fin].abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_forward_contains_nan_and_bad_blocks(D):
+    """A key of NaN makes the rows that see it NaN (their LSE -inf), as in the general path, and no
+    others; a block index out of range leaves the outputs and raises the status word."""
+    lay = wl.Layout(512, [(100, 60, 1)], [0, 300, 512])
+    t = make_tensors(207, 512, 512, 2, 1, D)
+    bits, bl = gpu_bits(lay), torch.arange(8, dtype=torch.int32, device=DEV)
+    t["k"][250] = float("nan")
+    o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, bl, 64)
+    sees = torch.zeros(512, dtype=torch.bool, device=DEV)
+    sees[250:300] = True
+    assert torch.equal(torch.isnan(o).all(dim=2), sees[:, None].expand(-1, 2)) and not torch.isnan(o[~sees]).any()
+    assert torch.isneginf(lse[:, sees]).all() and torch.isfinite(lse[:, ~sees]).all()
+    bl[3] = 8
+    ws = torch.zeros(mb.workspace_size(mb.OP_FWD, 512, 8, 64, 2, 1, D), dtype=torch.uint8, device=DEV)
+    out = torch.full_like(o, 7.0), torch.full_like(lse, 7.0)
+    mb.fwd(t["q"], t["k"], t["v"], bits, bl, 64, ws=ws, out=out)
+    assert (out[0] == 7.0).all() and (out[1] == 7.0).all() and int(ws[:4].view(torch.int32)) != 0
+    bl[3] = 3
+    mb.fwd(t["q"], t["k"], t["v"], bits, bl, 64, ws=ws, out=out)
+    assert not (out[0] == 7.0).all() and int(ws[:4].view(torch.int32)) == 0
