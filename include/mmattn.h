@@ -276,7 +276,8 @@ int mmattn_bwd(const void* q_loc, const void* k, const void* v, const uint64_t* 
  * include the aggregation launch when lists are split; DKV_REDUCE is the
  * partial-sum launch after the dK/dV kernel, recorded only when it runs; a
  * complete pair for DKV travels with the kernel's dispatch instead and carries
- * the kernel's own begin and end times).  Pass
+ * the kernel's own begin and end times; where a small share's whole backward is one
+ * kernel, DKV and DQ both enclose it).  Pass
  * nulls to clear.  stage: MMATTN_STAGE_*.  The only process-wide state in the library;
  * not thread-safe.  Returns MMATTN_ERR_SHAPE for an unknown stage. */
 enum { MMATTN_STAGE_FWD = 0, MMATTN_STAGE_DKV = 1, MMATTN_STAGE_DQ = 2, MMATTN_STAGE_DKV_REDUCE = 3,

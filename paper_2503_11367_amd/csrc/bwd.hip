@@ -34,6 +34,7 @@
 #include <type_traits>
 #include "attn_common.h"
 #include "tilemap_body.h"
+#include "small.h"
 #include <hip/hip_ext.h>
 
 namespace mm {
@@ -1430,6 +1431,7 @@ static int launch_bwd_d(const AttnArgs& a, const void* o, const float* lse, cons
 
 int launch_bwd(const AttnArgs& a, const void* o, const float* lse, const void* d_o, void* dq,
                void* dk, void* dv, void* ws, hipStream_t st) {
+    if (small_bwd_wanted(a)) return launch_bwd_small(a, o, lse, d_o, dq, dk, dv, (int32_t*)ws, st);
     if (a.D == 128) return launch_bwd_d<128>(a, o, lse, d_o, dq, dk, dv, ws, st);
     return launch_bwd_d<64>(a, o, lse, d_o, dq, dk, dv, ws, st);
 }

@@ -27,7 +27,19 @@ inline bool small_fwd_wanted(const AttnArgs& a) {
 // eight), and where there is hardly a unit for each of eight (256 tokens 7.0 / 7.5 us).
 inline bool small_fwd_four(const AttnArgs& a) { return small_fwd_wgs(a) > 256 || a.S <= 256; }
 
+// Backward (workgroups: 32 keys of a KV head for dK, as many for dV, 32 rows of a head for dQ): up to
+// about three rounds of one workgroup per CU, and no dK / dV workgroup with more than 24 units per
+// wavefront.  Beyond either the general path, whose tiles are shared by 128 keys, is level or ahead (2048
+// tokens, 1024 rows, 32 / 8 heads: 157 us both at head_dim 128, 100 here and 92 there at 64; 2048 rows,
+// 8 / 1 heads, sinks and a window, 64 units per wavefront: 161 and 107 us).
+inline bool small_bwd_wanted(const AttnArgs& a) {
+    const int64_t rows = small_row_units(a), wgs = 2 * (a.S / 32) * a.Hkv + rows * a.Hq;
+    return small_fits(a) && a.S <= 4096 && wgs <= 768 && rows * (a.Hq / a.Hkv) <= 192;
+}
+
 // `err`: the call's status word and its spare words (kFlagInts)
 int launch_fwd_small(const AttnArgs& a, void* o, float* lse, int32_t* err, hipStream_t st);
+int launch_bwd_small(const AttnArgs& a, const void* o, const float* lse, const void* d_o, void* dq, void* dk, void* dv,
+                     int32_t* err, hipStream_t st);
 
 }  // namespace mm

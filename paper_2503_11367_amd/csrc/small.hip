@@ -1,26 +1,28 @@
-// Attention forward of small shares in ONE launch: no plan, no lists in memory, no partial results.
+// Attention forward and backward of small shares, each in ONE launch: no plan, no lists in memory, no
+// partial results.
 //
-// The general path (fwd.hip) spends three or four dependent launches on a call; on a share of a few
-// hundred rows these, and the walk of one workgroup over its whole list of key tiles, are the
-// call's time.  Here a workgroup owns 32 query rows of one head, finds out by itself which units of 32
-// keys it has to visit, and its wavefronts take those units in turn, each with a ring of its own in
-// LDS and no barrier between them; at the end their partial results are added up in LDS in a fixed
-// order.
+// The general path (fwd.hip, bwd.hip) spends three to seven dependent launches on a call; on a share of
+// a few hundred rows these, and the walk of one workgroup over its whole list of tiles, are the
+// call's time.  Here a workgroup owns 32 query rows of one head (forward, dQ) or 32 keys of one KV head
+// (dK, dV), finds out by itself which units of 32 keys or rows it has to visit, and its wavefronts
+// take those units in turn, each with a ring of its own in LDS and no barrier between them; at the
+// end their partial results are added up in LDS in a fixed order.
 //
 //   check     every workgroup reads the whole block list into LDS and checks it (as
 //             validate_blocks_body does for the general path); the first one leaves the status word
 //   classify  64 words per wavefront and step.  A unit of equal fields is compared as a whole, a
-//             lane per unit, with the runs of the workgroup's rows; a mixed one run by run, a lane
-//             per row: unit EMPTY, FULL or PARTIAL
+//             lane per unit, with the runs of the workgroup's own tokens; a mixed one run by run, a
+//             lane per own token: unit EMPTY, FULL or PARTIAL
 //   walk      unit i of the active ones belongs to wavefront i mod NW
 //   combine   through LDS, in the order of the wavefronts
 //
 // Bound by latency: block list, mask words, first tiles, one after the other, then a unit or two
 // per wavefront, about 1 us each; on larger shares by the transfers, for 32 rows of one head use a
 // unit where the general path's 128 or 256 do.  Measured, whole calls back to back: 512 tokens, one
-// head, 128 rows 16.9 -> 8.4 us; 1920 tokens, 960 rows, 6 / 2 heads (head_dim 128) 32 -> 15 us; 4096 tokens, 1024
-// rows, 8 / 2 heads 44 -> 24 us (128), 27 -> 14 us (64).  Over 1100 shapes of up to 16384 tokens the calls
-// that come here take 0.55 of the general path's time on the mean; the slowest is 3 % behind.
+// head, 128 rows 16.9 -> 8.3 us forward, 27.9 -> 9.2 us backward; 1920 tokens, 960 rows, 6 / 2 heads (head_dim
+// 128) 32 -> 15 and 74 -> 37 us; 4096 tokens, 1024 rows, 8 / 2 heads 44 -> 24 and 93 -> 61 us (128), 27 -> 14
+// and 69 -> 47 us (64).  Over 2000 shapes of up to 16384 tokens the calls that come here take about half
+// of the general path's time on the mean; the slowest is 3 % behind.
 #include "attn_common.h"
 #include "tilemap_body.h"
 #include "small.h"
@@ -45,6 +47,7 @@ constexpr uint32_t kSmallMixed = 0x100u;   // neither an attend word nor a modal
 struct SmallPlanLds {
     int32_t blk[kSmallBlocks];
     SmallRun run[kSmallUnits];
+    int32_t pos[kSmallUnits];          // position of a row unit's first row
     uint16_t list[kSmallUnits];        // active units, ascending; PARTIAL ones with kSmallPartial
 };
 constexpr uint32_t kSmallPartial = 0x8000u;
@@ -192,6 +195,74 @@ __device__ __forceinline__ int small_keys_of_rows(const SmallShare& sh, SmallPla
                         __builtin_amdgcn_readlane(q_pos, at), end - at, k.ss, k.x & 0xFu, u * kUnit, kUnit, any, all);
         }
     });
+}
+
+// The row units that see the 32 keys of a workgroup: lane li holds a key.  A ragged last unit is mixed
+// and at best PARTIAL (its rows past the share are masked).
+template <int NW>
+__device__ __forceinline__ int small_rows_of_keys(const SmallShare& sh, SmallPlanLds& lds, uint32_t k_ss, uint32_t k_mod,
+                                                  int32_t key, int wave, int lane) {
+    const int n_units = (sh.n_loc + kUnit - 1) / kUnit, steps = (n_units + 1) / 2;
+    for (int s0 = wave; s0 < steps; s0 += NW * kSmallAhead) {
+        uint64_t w[kSmallAhead];
+        int32_t pos[kSmallAhead];
+#pragma unroll
+        for (int a = 0; a < kSmallAhead; ++a) {
+            const int32_t r = (s0 + a * NW) * kWave + lane;
+            w[a] = 0;
+            pos[a] = 0;
+            if (r < sh.n_loc) {
+                pos[a] = sh.pos(lds.blk, r);
+                w[a] = sh.bits[pos[a]];
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < kSmallAhead; ++a) {
+            const int step = s0 + a * NW;
+            if (step >= steps) break;                          // wave-uniform
+            const int valid = min(kWave, sh.n_loc - step * kWave);
+            const uint32_t ss_q = word_ss(w[a]), att_q = word_att(w[a]);
+            const uint32_t b_ss = lane_below(ss_q, 0u), b_att = lane_below(att_q, 0u), b_pos = lane_below((uint32_t)pos[a], 0u);
+            const uint64_t m = __ballot(lane < valid && ((lane & (kUnit - 1)) == 0 || ss_q != b_ss || att_q != b_att ||
+                                                         (uint32_t)pos[a] != b_pos + 1u));
+            const int u = 2 * step + (lane >> 5);
+            if ((lane & (kUnit - 1)) == 0 && u < n_units) {
+                lds.run[u] = SmallRun{ss_q, att_q};
+                lds.pos[u] = pos[a];
+            }
+            if (m != 0x100000001ull || valid < kWave)
+                small_mixed(lds, step, m, valid, (uint32_t)m != 1u || valid < kUnit,
+                            valid > kUnit && ((uint32_t)(m >> 32) != 1u || valid < kWave), lane,
+                            [&](int at, int len, bool& some, bool& every) {
+                    const KeyRange r = visible_rows((uint32_t)__builtin_amdgcn_readlane((int)ss_q, at),
+                                                    (uint32_t)__builtin_amdgcn_readlane((int)att_q, at),
+                                                    __builtin_amdgcn_readlane(pos[a], at), k_ss, k_mod, key, len);
+                    some = __any(r.lo < (uint32_t)kWave);
+                    every = __all(r.all_of(len));
+                });
+        }
+    }
+    // the keys' own runs (their positions are consecutive)
+    const uint32_t b_ss = lane_below(k_ss, 0u), b_mod = lane_below(k_mod, 0u);
+    const uint32_t starts = (uint32_t)__ballot(lane == 0 || k_ss != b_ss || k_mod != b_mod);
+    const int32_t key0 = __builtin_amdgcn_readfirstlane(key);
+    return small_list<NW>(lds, n_units, wave, lane, [&](int u, const SmallRun& q, bool& any, bool& all) {
+        const int32_t q0 = lds.pos[u];
+        for (uint32_t m = starts; m != 0u;) {
+            const int at = __ffs(m) - 1;
+            m &= m - 1u;
+            const int end = m ? __ffs(m) - 1 : kUnit;
+            small_pairs(q.ss, q.x, q0, kUnit, (uint32_t)__builtin_amdgcn_readlane((int)k_ss, at),
+                        (uint32_t)__builtin_amdgcn_readlane((int)k_mod, at), key0 + at, end - at, any, all);
+        }
+    });
+}
+
+// the lane's index, computed here: what rare code derives from it is not kept in registers meanwhile
+__device__ __forceinline__ int lane_afresh() {
+    uint32_t zero = 0u;
+    asm volatile("" : "+v"(zero));
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
 }
 
 // A unit's 32 rows of a tensor in LDS (SwzTile MODE 0: row fragments and transpose reads)
@@ -464,6 +535,442 @@ fwd_small_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
         LSE[(int64_t)h * sh.n_loc + row] = den > 0.f ? (m + __builtin_amdgcn_logf(den)) * kLn2 : -INFINITY;
 }
 
+// ---------------------------------------------------------------- backward ---
+// One launch for the three gradients, whose workgroups need nothing from each other: dK and dV (32
+// keys of a KV head against every row of its query heads), dQ (32 rows of a head).  Apart they form
+// S three times and dP twice (8 products where the general path has 7), but no wavefront holds two
+// accumulators, so that two of them fit a SIMD and each has fewer units to go through.  A dK
+// wavefront forms Delta of its unit's rows from O, which it fetches beside the tiles in the same
+// order of lanes.  One stage per tensor and wavefront, requested anew as soon as it has been read.
+template <int D, int NW>
+struct SmallBwdLds {
+    alignas(1024) unsigned char ring[NW][2 * SmallTile<D>::kBytes];     // K, V or Q, dO; then the sums
+    alignas(256) uint64_t kw[NW][kUnit];                                // dQ: words of the unit's keys
+    alignas(256) float lse[NW][kWave];                                  // dK, dV: of the unit's rows (twice)
+    alignas(256) float delta[NW][kUnit];                                // dK
+    alignas(256) unsigned char key_frags[D / 16][1024];                 // dK: the keys as operand of S, by lane
+    alignas(256) uint32_t info[NW][3][kUnit];                           // dK, dV: mask inputs of the unit's rows
+    SmallPlanLds plan;
+};
+struct SmallBwdArgs {
+    const ushort_t *Q, *K, *V, *O, *dO;
+    const float* lse;
+    SmallShare sh;
+    int32_t Hq, Hkv;
+    float scale, scale_log2;
+    ushort_t *dQ, *dK, *dV;
+};
+
+// The wavefronts' accumulators, added up in their order through their rings, times `scale`, as bf16:
+// this lane's row of the result starts at `out` (4 consecutive values per register quad).
+template <int D, int NW>
+__device__ __forceinline__ void small_store_sum(SmallBwdLds<D, NW>& sm, const floatx16 (&acc)[D / 32], float scale,
+                                                bool row_ok, ushort_t* out, int wave, int lane) {
+    constexpr int kQuads = D / 8;
+    static_assert(kQuads * 1024 <= 2 * SmallTile<D>::kBytes, "the sums fit the ring");
+    wait_lds_reads();
+#pragma unroll
+    for (int q = 0; q < kQuads; ++q) {
+        floatx4 v;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = acc[q / 4][(q & 3) * 4 + u];
+        *(floatx4*)(sm.ring[wave] + q * 1024 + lane * 16) = v;
+    }
+    __syncthreads();
+    if (!row_ok) return;
+#pragma unroll
+    for (int q0 = 0; q0 < kQuads; q0 += NW) {
+        const int q = q0 + wave;
+        floatx4 sum = *(const floatx4*)(sm.ring[0] + q * 1024 + lane * 16);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += *(const floatx4*)(sm.ring[w] + q * 1024 + lane * 16);
+        bf16x4 o;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[u] = (__bf16)(sum[u] * scale);
+        *(u32x2*)(out + (q / 4) * 32 + (q & 3) * 8) = __builtin_bit_cast(u32x2, o);
+    }
+}
+
+template <int D, int NW>
+__device__ __forceinline__ void small_dq(SmallBwdLds<D, NW>& sm, const SmallBwdArgs& p, int wg) {
+    using Tile = SmallTile<D>;
+    constexpr int NDS = Tile::NDS, NDB = Tile::NDB, NI = Tile::NI;
+    const SmallShare& sh = p.sh;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, hh = lane >> 5;
+    const int n_rb = (sh.n_loc + kUnit - 1) / kUnit;
+    const int rb = n_rb - 1 - wg / p.Hq, h = wg % p.Hq, g = h / (p.Hq / p.Hkv);
+    const int row = rb * kUnit + li;
+    const bool row_ok = row < sh.n_loc;
+
+    uint64_t first[kSmallAhead];
+#pragma unroll
+    for (int a = 0; a < kSmallAhead; ++a) {
+        first[a] = 0;
+        if ((wave + a * NW) * kWave < sh.S) first[a] = sh.bits[(wave + a * NW) * kWave + lane];
+    }
+    bf16x8 qf[NDS], dof[NDS];
+    float lse2 = INFINITY, delta = 0.f;                        // +inf: every probability is 0
+#pragma unroll
+    for (int ds = 0; ds < NDS; ++ds) {
+        qf[ds] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+        dof[ds] = qf[ds];
+    }
+    if (row_ok) {
+        const int64_t off = ((int64_t)row * p.Hq + h) * D + hh * 8;
+        bf16x8 of[NDS];
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) {
+            qf[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(p.Q + off + ds * 16));
+            dof[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(p.dO + off + ds * 16));
+            of[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(p.O + off + ds * 16));
+        }
+        const float l2 = p.lse[(int64_t)h * sh.n_loc + row] * kLog2e;
+        lse2 = l2 == -INFINITY ? INFINITY : l2;                // a row that sees no key
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) delta += (float)of[ds][u] * (float)dof[ds][u];
+    }
+    delta += __shfl_xor(delta, 32);
+    if (!small_check<64 * NW>(sh, sm.plan.blk)) return;
+    int32_t q_pos = 0;
+    uint32_t q_ss = 0, q_att = 0;
+    if (row_ok) {
+        q_pos = sh.pos(sm.plan.blk, row);
+        const uint64_t w = sh.bits[q_pos];
+        q_ss = word_ss(w);
+        q_att = word_att(w);
+    }
+    Tile t;
+    t.init(lane, (int64_t)p.Hkv * D * 2);
+    const int n = small_keys_of_rows<NW>(sh, sm.plan, first, row_ok, q_ss, q_att, q_pos, wave, lane);
+
+    const uint32_t k_tile = lds_addr_of(sm.ring[wave]), v_tile = k_tile + Tile::kBytes, kw = lds_addr_of(sm.kw[wave]);
+    auto entry_at = [&](int i) -> uint32_t { return __builtin_amdgcn_readfirstlane((uint32_t)sm.plan.list[i]); };
+    auto issue_v = [&](uint32_t e) {
+        const ushort_t* src = p.V + ((int64_t)(e & ~kSmallPartial) * kUnit * p.Hkv + g) * D;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) dma16(t.from(src, i), t.src[i % 4], v_tile + i * 1024);
+    };
+    auto issue_k = [&](uint32_t e) {                           // with the words of the unit's keys: NI + 1 transfers
+        const int64_t k0 = (int64_t)(e & ~kSmallPartial) * kUnit;
+        dma4(sh.bits + k0, (uint32_t)(lane * 4), kw);
+        const ushort_t* src = p.K + (k0 * p.Hkv + g) * D;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) dma16(t.from(src, i), t.src[i % 4], k_tile + i * 1024);
+    };
+    floatx16 dq[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dq[db][r] = 0.f;
+    uint32_t e = wave < n ? entry_at(wave) : 0u;
+    wait_landed<0>();                                          // the loads so far: none is left for the loop
+    if (wave < n) {
+        issue_v(e);
+        issue_k(e);
+    }
+    for (int i = wave; i < n; i += NW) {
+        const bool more = i + NW < n;
+        const uint32_t e_next = more ? entry_at(i + NW) : 0u;
+        floatx16 s, dp;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
+        wait_landed<NI + 1>();                                 // V
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) dp = mfma32(t.read_row(v_tile, ds), dof[ds], dp);
+        wait_lds_reads();
+        if (more) {
+            issue_v(e_next);
+            wait_landed<NI>();                                 // K
+        } else {
+            wait_landed<0>();
+        }
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) s = mfma32(t.read_row(k_tile, ds), qf[ds], s);
+        if (e & kSmallPartial) mask_keys(s, kw, (int32_t)((e & ~kSmallPartial) * kUnit), q_ss, q_att, q_pos, lane);
+        bf16x8 dsf[2];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float pr = __builtin_amdgcn_exp2f(s[r] * p.scale_log2 - lse2);
+            dsf[r >> 3][r & 7] = (__bf16)(pr * (dp[r] - delta));
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) dq[db] = mfma32(t.read_tr(k_tile, ks, db), dsf[ks], dq[db]);
+        if (more) {
+            wait_lds_reads();
+            issue_k(e_next);
+        }
+        e = e_next;
+    }
+    small_store_sum<D, NW>(sm, dq, p.scale, row_ok, p.dQ + ((int64_t)row * p.Hq + h) * D + 4 * hh, wave, lane);
+}
+
+// sum over the 16 lanes of a row, in all of them
+__device__ __forceinline__ float row16_sum(float x) {
+#define MM_ROR(n) x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + n, 0xf, 0xf, false))
+    MM_ROR(8);
+    MM_ROR(4);
+    MM_ROR(2);
+    MM_ROR(1);
+#undef MM_ROR
+    return x;
+}
+
+// dK (KR) or dV of 32 keys of KV head g: units are 32 rows of one of its query heads
+template <int D, int NW, bool KR>
+__device__ __forceinline__ void small_dkv(SmallBwdLds<D, NW>& sm, const SmallBwdArgs& p, int wg) {
+    using Tile = SmallTile<D>;
+    constexpr int NDS = Tile::NDS, NDB = Tile::NDB, NI = Tile::NI;
+    const SmallShare& sh = p.sh;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, hh = lane >> 5;
+    const int rep = p.Hq / p.Hkv, kb = wg / p.Hkv, g = wg % p.Hkv;
+    const int key = kb * kUnit + li;
+
+    // resident operands: the keys for S, in dK the values for dP.  (Both in registers, dK at D = 128
+    // would spill: there the keys are read from LDS, a fragment per product.)
+    bf16x8 res[NDS];
+    const uint64_t k_word = sh.bits[key];
+    {
+        const int64_t off = ((int64_t)key * p.Hkv + g) * D + hh * 8;
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds)
+            res[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)((KR ? p.V : p.K) + off + ds * 16));
+        static_assert(NDS <= NW, "a fragment per wavefront");
+        if (KR && wave < NDS)
+            *(u32x4*)(sm.key_frags[wave] + lane * 16) = *(const u32x4*)(p.K + off + wave * 16);
+    }
+    if (!small_check<64 * NW>(sh, sm.plan.blk)) return;
+    const uint32_t k_ss = word_ss(k_word), k_mod = word_mod(k_word);
+    const int n_list = small_rows_of_keys<NW>(sh, sm.plan, k_ss, k_mod, key, wave, lane);
+    const int n = n_list * rep;                                // item: (head of the group, entry of the list)
+
+    Tile t;
+    const int64_t row_bytes = (int64_t)p.Hq * D * 2;
+    t.init(lane, row_bytes);
+    const uint32_t q_tile = lds_addr_of(sm.ring[wave]), d_tile = q_tile + Tile::kBytes, lse_at = lds_addr_of(sm.lse[wave]);
+    const int n_units = (sh.n_loc + kUnit - 1) / kUnit, last_row = (sh.n_loc - 1) % kUnit;
+
+    u32x4 of[NI];                                              // O of the unit, in the order of the transfers
+    uint64_t row_word = 0;                                     // PARTIAL unit: this lane's row
+    int32_t row_at = 0;
+    // a ragged unit's missing rows are fetched as its last one and masked
+    auto fetch = [&](const ushort_t* src, uint32_t e, uint32_t tile) {
+        if ((int)(e & ~kSmallPartial) == n_units - 1 && last_row != kUnit - 1) {       // wave-uniform
+            const int l = lane_afresh();
+#pragma unroll
+            for (int i = 0; i < NI; ++i) dma16(src, Tile::source(l, i, row_bytes, last_row), tile + i * 1024);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) dma16(t.from(src, i), t.src[i % 4], tile + i * 1024);
+        }
+    };
+    auto offset = [&](uint32_t e, int h) -> int64_t { return ((int64_t)(e & ~kSmallPartial) * kUnit * p.Hq + h) * D; };
+    auto issue_q = [&](uint32_t e, int h) {                    // with LSE: NI + 1 transfers
+        const int u0 = (int)(e & ~kSmallPartial) * kUnit, last = min(kUnit - 1, sh.n_loc - 1 - u0);
+        if (e & kSmallPartial) {
+            row_word = 0;                                      // (sees nothing)
+            if (li <= last) {
+                row_at = sh.pos(sm.plan.blk, u0 + li);
+                row_word = sh.bits[row_at];
+            }
+        }
+        dma4(p.lse + (int64_t)h * sh.n_loc + u0, (uint32_t)(min(li, last) * 4), lse_at);
+        fetch(p.Q + offset(e, h), e, q_tile);
+    };
+    auto issue_d = [&](uint32_t e, int h) {
+        if (KR) {
+            const char* src = (const char*)(p.O + offset(e, h));
+            if ((int)(e & ~kSmallPartial) == n_units - 1 && last_row != kUnit - 1) {
+                const int l = lane_afresh();
+#pragma unroll
+                for (int i = 0; i < NI; ++i) of[i] = *(const u32x4*)(src + Tile::source(l, i, row_bytes, last_row));
+            } else {
+#pragma unroll
+                for (int i = 0; i < NI; ++i) of[i] = *(const u32x4*)(t.from(src, i) + t.src[i % 4]);
+            }
+        }
+        fetch(p.dO + offset(e, h), e, d_tile);
+    };
+    floatx16 acc[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+
+    // items wave, wave + NW, ...: the list's entries once per head of the group
+    int idx = wave, hj = 0;
+    auto entry = [&]() -> uint32_t {
+        while (idx >= n_list) { idx -= n_list; ++hj; }
+        const uint32_t e = __builtin_amdgcn_readfirstlane((uint32_t)sm.plan.list[idx]);
+        idx += NW;
+        return e;
+    };
+    uint32_t e = 0;
+    wait_landed<0>();                                          // the loads so far
+    if (wave < n) {
+        e = entry();
+        if (KR) {
+            issue_d(e, g * rep + hj);
+            issue_q(e, g * rep + hj);
+        } else {
+            issue_q(e, g * rep + hj);
+            issue_d(e, g * rep + hj);
+        }
+    }
+    typedef const floatx4 __attribute__((address_space(3))) * lds_f4;
+    const uint32_t info = lds_addr_of(sm.info[wave][0]) + hh * 16;
+    const float to_start = -1.0f / p.scale;
+    for (int i = wave; i < n; i += NW) {
+        const bool more = i + NW < n;
+        uint32_t e_next = 0;
+        if (more) e_next = entry();
+        const int h_next = g * rep + hj;
+        floatx16 x, dp;                                        // S - LSE/scale, dP
+        if (KR) {
+            wait_landed<NI + 1>();                             // O and dO
+#pragma unroll
+            for (int r = 0; r < 16; ++r) dp[r] = 0.f;
+#pragma unroll
+            for (int ds = 0; ds < NDS; ++ds) dp = mfma32(t.read_row(d_tile, ds), res[ds], dp);
+            wait_landed<0>();                                  // Q and LSE
+        } else {
+            wait_landed<NI>();
+        }
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const floatx4 l = *(lds_f4)(uintptr_t)(lse_at + hh * 16 + q4 * 32);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[q4 * 4 + j] = l[j] * to_start;
+        }
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds)
+            x = mfma32(t.read_row(q_tile, ds),
+                       KR ? __builtin_bit_cast(bf16x8, *(const u32x4*)(sm.key_frags[ds] + lane * 16)) : res[ds], x);
+        if (KR) {
+            // Delta of the unit's rows: O times dO, both as the transfers deliver them (lane, step): the
+            // 16 lanes of a super-row hold one row (D = 128) or two
+            float mine = 0.f;
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                const u32x4 dov = *(lds_u4)(uintptr_t)(d_tile + j * 1024 + lane * 16);
+                float a = 0.f;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t o2 = of[j][u], d2 = dov[u];
+                    a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, o2), __builtin_bit_cast(bf16x2, d2), a, false);
+                }
+                if (Tile::T::RPS == 1) {
+                    a = row16_sum(a);
+                    mine = (lane & 15) == j ? a : mine;
+                } else {
+                    int r, c;
+                    Tile::T::src_of(4 * j + (lane >> 4), lane & 15, r, c);
+                    const float even = row16_sum((r & 1) ? 0.f : a), odd = row16_sum((r & 1) ? a : 0.f);
+                    mine = (lane & 15) == 2 * j ? even : ((lane & 15) == 2 * j + 1 ? odd : mine);
+                }
+            }
+            // lane l of 16 holds row 4 l + lane / 16 (D = 128), or 8 (l / 2) + 2 (lane / 16) + l % 2
+            const int l16 = lane & 15, q16 = lane >> 4;
+            if (l16 < 8) sm.delta[wave][Tile::T::RPS == 1 ? 4 * l16 + q16 : 8 * (l16 >> 1) + 2 * q16 + (l16 & 1)] = mine;
+        }
+        if (e & kSmallPartial) {
+            const uint32_t ss_r = word_ss(row_word), att_r = word_att(row_word), pos_r = (uint32_t)row_at;
+            const uint32_t ss0 = __builtin_amdgcn_readfirstlane(ss_r), att0 = __builtin_amdgcn_readfirstlane(att_r);
+            const uint32_t pos0 = __builtin_amdgcn_readfirstlane(pos_r);
+            if (__all(ss_r == ss0 && att_r == att0 && pos_r == pos0 + (uint32_t)li)) {   // one run of rows
+                const KeyRange r = visible_rows(ss0, att0, (int32_t)pos0, k_ss, k_mod, key, kUnit);
+                if (!__all(r.all_of(kUnit))) {
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (!r.sees(4u * hh + (uint32_t)(8 * q4 + j))) x[q4 * 4 + j] = -INFINITY;
+                }
+            } else {
+                sm.info[wave][0][li] = ss_r;
+                sm.info[wave][1][li] = att_r;
+                sm.info[wave][2][li] = pos_r;
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const u32x4 ss = *(lds_u4)(uintptr_t)(info + q4 * 32), ca = *(lds_u4)(uintptr_t)(info + 4 * kUnit + q4 * 32);
+                    const u32x4 ps = *(lds_u4)(uintptr_t)(info + 8 * kUnit + q4 * 32);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (!visible(ss[j], ca[j], (int64_t)ps[j], k_ss, k_mod, key)) x[q4 * 4 + j] = -INFINITY;
+                }
+            }
+        }
+        if (KR) {
+            floatx4 dl[4];
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) dl[q4] = *(lds_f4)(uintptr_t)(lds_addr_of(sm.delta[wave]) + hh * 16 + q4 * 32);
+            wait_lds_reads();                                  // of dO, among others
+            if (more) issue_d(e_next, h_next);
+            bf16x8 dsf[2];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float pr = __builtin_amdgcn_exp2f(x[r] * p.scale_log2);
+                dsf[r >> 3][r & 7] = (__bf16)(pr * (dp[r] - dl[r >> 2][r & 3]));
+            }
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) acc[db] = mfma32(t.read_tr(q_tile, ks, db), dsf[ks], acc[db]);
+            if (more) {
+                wait_lds_reads();
+                issue_q(e_next, h_next);
+            }
+        } else {
+            wait_lds_reads();
+            if (more) issue_q(e_next, h_next);
+            bf16x8 pf[2];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) pf[r >> 3][r & 7] = (__bf16)__builtin_amdgcn_exp2f(x[r] * p.scale_log2);
+            if (more) wait_landed<NI + 1>();                   // dO
+            else wait_landed<0>();
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) acc[db] = mfma32(t.read_tr(d_tile, ks, db), pf[ks], acc[db]);
+            if (more) {
+                wait_lds_reads();
+                issue_d(e_next, h_next);
+            }
+        }
+        e = e_next;
+    }
+    small_store_sum<D, NW>(sm, acc, KR ? p.scale : 1.0f, true,
+                           (KR ? p.dK : p.dV) + ((int64_t)key * p.Hkv + g) * D + 4 * hh, wave, lane);
+}
+
+// The three kinds of workgroups, those with the longest walks first: a unit takes a dK wavefront about
+// 3 us, a dQ one 2.1, a dV one 1.8, of at most rows x heads per KV head and keys / 32 units (half of 1920
+// tokens, 6 / 2 heads, 90 and 60 units: 36 us with dQ ahead of dV, 33 behind; 128 of 4096 tokens, 2 / 2
+// heads, 4 and 128 units: 33 and 36).  Among equals the order is that of the causal walks' lengths.
+template <int D, int NW>
+__global__ void __launch_bounds__(64 * NW, 2)
+bwd_small_kernel(const SmallBwdArgs p) {
+    __shared__ SmallBwdLds<D, NW> sm;
+    const int n_kb = p.sh.S / kUnit * p.Hkv, n_rb = (p.sh.n_loc + kUnit - 1) / kUnit, n_q = n_rb * p.Hq;
+    const int units_k = n_rb * (p.Hq / p.Hkv), units_q = p.sh.S / kUnit;
+    const int first_q = 2 * units_q > 3 * units_k ? 0 : (7 * units_k > 8 * units_q ? 2 * n_kb : n_kb);
+    int wg = (int)blockIdx.x;
+    if (wg >= first_q && wg < first_q + n_q) {
+        small_dq<D, NW>(sm, p, wg - first_q);
+        return;
+    }
+    if (wg >= first_q) wg -= n_q;
+    if (wg < n_kb) small_dkv<D, NW, true>(sm, p, wg);
+    else small_dkv<D, NW, false>(sm, p, wg - n_kb);
+}
+
 // ---------------------------------------------------------------- host -------
 static SmallShare small_share(const AttnArgs& a, int32_t* err) {
     return SmallShare{a.bits, a.blocks, a.n_blocks, a.block, (int32_t)a.S, a.n_blocks * a.block, err};
@@ -482,6 +989,22 @@ int launch_fwd_small(const AttnArgs& a, void* o, float* lse, int32_t* err, hipSt
                        Hq_run, rep, a.Hq, a.Hkv, a.scale * kLog2e, (ushort_t*)o + qo,
                        lse + (int64_t)a.kv_begin * rep * n_loc);
     stage_end(MMATTN_STAGE_FWD, st);
+    MM_LAUNCH_CHECK();
+    return MMATTN_OK;
+}
+
+int launch_bwd_small(const AttnArgs& a, const void* o, const float* lse, const void* d_o, void* dq, void* dk, void* dv,
+                     int32_t* err, hipStream_t st) {
+    const int32_t n_loc = a.n_blocks * a.block;
+    const SmallBwdArgs p{(const ushort_t*)a.q, (const ushort_t*)a.k, (const ushort_t*)a.v, (const ushort_t*)o,
+                         (const ushort_t*)d_o, lse, small_share(a, err), a.Hq, a.Hkv, a.scale, a.scale * kLog2e,
+                         (ushort_t*)dq, (ushort_t*)dk, (ushort_t*)dv};
+    const dim3 grid((unsigned)(2 * (a.S / kUnit) * a.Hkv + (n_loc + kUnit - 1) / kUnit * a.Hq));
+    stage_begin(MMATTN_STAGE_DKV, st);
+    stage_begin(MMATTN_STAGE_DQ, st);
+    hipLaunchKernelGGL((a.D == 128 ? bwd_small_kernel<128, 8> : bwd_small_kernel<64, 8>), grid, dim3(512), 0, st, p);
+    stage_end(MMATTN_STAGE_DQ, st);
+    stage_end(MMATTN_STAGE_DKV, st);
     MM_LAUNCH_CHECK();
     return MMATTN_OK;
 }

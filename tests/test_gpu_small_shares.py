@@ -39,6 +39,8 @@ CASES = {
     "rows that see only their span": (wl.layout_random(204, S=896, n_samples=3, max_spans=6, noncausal_prob=0.7), spread(7, 6), 128, 2, 1, 128),
     "long list": (wl.Layout(4096, [(100, 700, 1)], [0, 4096]), [255, 17, 130, 40], 16, 32, 8, 128),
     "eight wavefronts, last size": (wl.layout_random(205, S=2048, n_samples=1), spread(16, 8), 128, 8, 2, 64),
+    "dQ ahead of dK and dV": (wl.layout_random(207, S=1920, n_samples=1, deny_prob=0.3), [3, 38], 48, 4, 4, 64),
+    "dQ behind dK and dV": (wl.layout_random(208, S=512, n_samples=2), spread(8, 7), 64, 6, 1, 128),
     "four wavefronts, first size": (wl.layout_random(206, S=2048, n_samples=1), spread(128, 65), 16, 8, 4, 128),
 }
 
@@ -67,6 +69,43 @@ def test_forward(name):
     assert rel_l2(bf16_to_f64(o), bf16_to_f64(o2)) < 1e-3
     fin = torch.isfinite(lse2)
     assert torch.equal(torch.isneginf(lse), ~fin) and float((lse - lse2)[fin].abs().max()) < 1e-4
+
+
+@pytest.mark.parametrize("name", [n for n in CASES if n != "more workgroups than CUs at 128 tokens"])
+def test_backward(name):
+    """dQ, dK, dV against the oracle (relative L2 1e-2, as for the general path); keys that no row of the
+    share sees get exactly zero.  The last two cases lie beyond the line and take the general path."""
+    lay, blocks, block, Hq, Hkv, D = CASES[name]
+    f, win = fields(lay), windows(lay)
+    t = make_tensors(210, len(blocks) * block, lay.S, Hq, Hkv, D)
+    bits, bl = gpu_bits(lay), torch.tensor(blocks, dtype=torch.int32, device=DEV)
+    o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, bl, block)
+    out = tuple(torch.full_like(t[n], 7.0) for n in ("q", "k", "v"))
+    mb.bwd(t["q"], t["k"], t["v"], bits, bl, block, o, lse, t["do"], out=out)
+    rows = oa.rows_of_blocks(blocks, block)
+    from oracle import mask as om
+    seen = om.visible(rows, np.arange(lay.S), f[0], f[1], f[2], f[3], f[4], win).any(axis=0)
+    rep = Hq // Hkv
+    for g in sorted({0, Hkv - 1}):
+        hs = slice(g * rep, (g + 1) * rep)
+        ref = oa.backward(f64(t["q_bits"])[:, hs], f64(t["k_bits"])[:, g:g + 1], f64(t["v_bits"])[:, g:g + 1],
+                          f64(t["do_bits"])[:, hs], rows, f[0], f[1], f[2], modality=f[3], attend=f[4], window=win)
+        for n, got, want in zip(("dq", "dk", "dv"), (out[0][:, hs], out[1][:, g:g + 1], out[2][:, g:g + 1]), ref):
+            x = bf16_to_f64(got)
+            assert np.isfinite(x).all() and rel_l2(x, want) < 1e-2, (n, g, rel_l2(x, want))
+    assert (bf16_to_f64(out[1])[~seen] == 0).all() and (bf16_to_f64(out[2])[~seen] == 0).all()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_backward_leaves_outputs_for_bad_blocks(D):
+    lay = wl.Layout(512, [(100, 60, 1)], [0, 300, 512])
+    t = make_tensors(211, 256, 512, 2, 1, D)
+    bits, bl = gpu_bits(lay), torch.tensor([1, 9, 0, 3], dtype=torch.int32, device=DEV)
+    o, lse = torch.zeros_like(t["q"]), torch.zeros((2, 256), dtype=torch.float32, device=DEV)
+    out = tuple(torch.full_like(t[n], 7.0) for n in ("q", "k", "v"))
+    ws = torch.zeros(mb.workspace_size(mb.OP_BWD, 512, 4, 64, 2, 1, D), dtype=torch.uint8, device=DEV)
+    mb.bwd(t["q"], t["k"], t["v"], bits, bl, 64, o, lse, t["do"], out=out, ws=ws)
+    assert all((x == 7.0).all() for x in out) and int(ws[:4].view(torch.int32)) != 0
 
 
 @pytest.mark.parametrize("D", [64, 128])
