@@ -9,13 +9,13 @@
 //            to 1024 blocks, else in LDS;
 //   phase 2  wavefront 0 runs the greedy loop over the ranks held SORTED by (load,
 //            rank), SLOTS per lane: a block goes to the first, whose grown key is
-//            re-inserted by one minimum and one maximum per key (see greedy_sorted);
+//            re-inserted by one median per key (see greedy_sorted);
 //   phase 3  per-rank CSR lists in ascending block index: every wavefront takes a
 //            stretch of blocks, finds equal ranks among 64 of them by ballots and
 //            counts with a histogram of its own.
 //
 // Bound by the latency of the loop, which takes the blocks one by one.  Measured, 8 ranks:
-// 512 blocks 126 -> 21 us, 1024 blocks 259 -> 38 us against a loop that found a
+// 512 blocks 126 -> 20 us, 1024 blocks 259 -> 33 us against a loop that found a
 // block's place by a ballot and scalar arithmetic, an order counted over all pairs
 // of blocks (34 us of the 259) and lists counted the same way.
 // Up to 64 blocks are the work of a single wavefront, which meets no other at barriers: 8
@@ -109,7 +109,8 @@ struct Key32 {
     __device__ static __forceinline__ uint32_t low(T k) { return k; }
     __device__ static __forceinline__ T step(uint64_t entry, int) { return (uint32_t)(entry >> 32); }
     __device__ static __forceinline__ T most(T a, T b) { return max(a, b); }
-    __device__ static __forceinline__ T least(T a, T b) { return min(a, b); }
+    // x, held between hi and the smaller lo (one v_med3_u32)
+    __device__ static __forceinline__ T between(T lo, T hi, T x) { return max(min(lo, hi), min(max(lo, hi), x)); }
     // the value of a lane in all lanes that hold keys
     template <int LANE>
     __device__ static __forceinline__ T everywhere(T v) {
@@ -148,7 +149,7 @@ struct Key52 {
         return (double)(entry >> kBalIndexBits << bits);
     }
     __device__ static __forceinline__ T most(T a, T b) { return fmax(a, b); }
-    __device__ static __forceinline__ T least(T a, T b) { return fmin(a, b); }
+    __device__ static __forceinline__ T between(T lo, T hi, T x) { return fmax(lo, fmin(hi, x)); }
     template <class F>
     __device__ static __forceinline__ T words(T v, F&& f) {
         const uint64_t b = __builtin_bit_cast(uint64_t, v);
@@ -165,14 +166,15 @@ struct Key52 {
 
 // The greedy loop.  Keys are sorted over (lane, slot).  A block goes to the first key's rank;
 // with x the first key less the workload, every place then holds max(next key, min(own key,
-// x)): the keys above x move down one place, x takes the place behind them.  One wavefront.
+// x)): the keys above x move down one place, x takes the place behind them.  The next key is at most
+// the own one, so that is the median of the three, one instruction.  One wavefront.
 // Every lane also holds the first key, `head`: the next one is max(second key, x).  Bound by
-// the chain from step to step and by the instructions that one wavefront can issue (one in
-// about five cycles), so the workloads come from LDS two to a read, kSteps steps ahead, and
+// the chain from step to step and by the instructions that one wavefront can issue, five a block,
+// so the workloads come from LDS two to a read, kSteps steps ahead, and
 // all else is left to the other wavefronts.  Measured per block: 185 ns with ballots and scalar
-// arithmetic; now 27 to 30 ns with at most 16 ranks, 35 ns with 64 (a crossing from vector to
-// scalar registers in every step), 46 ns with doubles (their minimum and maximum issue slowly),
-// 94 ns with 1024 ranks.
+// arithmetic; now 22 ns with at most 16 ranks (27 with a minimum and a maximum, each behind wait states
+// for its shift; 27 too with two blocks a step, thirteen instructions), 22 ns with 64 (35), 46 ns with
+// doubles (their minimum and maximum issue slowly), 63 ns with 1024 ranks (90).
 constexpr int kSteps = 8;
 template <class K, int SLOTS>
 __device__ __forceinline__ void greedy_sorted(uint64_t* entries, int32_t nB, int32_t P, int bits, int rebase_mask,
@@ -189,18 +191,11 @@ __device__ __forceinline__ void greedy_sorted(uint64_t* entries, int32_t nB, int
     T head = K::template everywhere<0>(key[0]);
     T second = K::template everywhere<1 / SLOTS>(key[1 % SLOTS]);
     uint64_t base = 0;
-    u64x2 ahead[kSteps / 2];
-    auto fetch = [&](int t) {
+    auto fetch = [&](u64x2 (&to)[kSteps / 2], int t) __attribute__((always_inline)) {
 #pragma unroll
-        for (int v = 0; v < kSteps / 2; ++v) ahead[v] = *(const u64x2*)&entries[t + 2 * v];
+        for (int v = 0; v < kSteps / 2; ++v) to[v] = *(const u64x2*)&entries[t + 2 * v];
     };
-    fetch(0);
-    // entries past the last block (up to a whole number of steps) are 0 and leave the keys as they are
-    for (int t = 0; t < nB; t += kSteps) {
-        T w[kSteps];
-#pragma unroll
-        for (int v = 0; v < kSteps; ++v) w[v] = K::step(ahead[v / 2][v % 2], bits);
-        if (t + kSteps < nB) fetch(t + kSteps);
+    auto steps = [&](const u64x2 (&from)[kSteps / 2], int t) __attribute__((always_inline)) {
         if (K::kRebase && (t & rebase_mask) == 0) {
             // the smallest load becomes the base
             const uint64_t least = K::value(head) >> bits;
@@ -215,17 +210,29 @@ __device__ __forceinline__ void greedy_sorted(uint64_t* entries, int32_t nB, int
 #pragma unroll
         for (int v = 0; v < kSteps; ++v) {
             got[v] = K::low(head);
-            const T x = head - w[v];
+            const T x = head - K::step(from[v / 2][v % 2], bits);
             head = K::most(second, x);
             const T above = K::above(key[0]);
 #pragma unroll
             for (int s = 0; s < SLOTS; ++s)
-                key[s] = K::most(s + 1 < SLOTS ? key[s + 1] : above, K::least(key[s], x));
+                key[s] = K::between(s + 1 < SLOTS ? key[s + 1] : above, key[s], x);
             second = K::template everywhere<1 / SLOTS>(key[1 % SLOTS]);
         }
         // (the same value from every lane)
 #pragma unroll
         for (int v = 0; v < kSteps; ++v) ((uint32_t*)entries)[2 * (t + v) + 1] = got[v];
+    };
+    // Entries past the last block (up to a whole number of steps) are 0 and leave the keys as they are.
+    // Two sets of registers take turns: moved from one to the other, the entries would cost an
+    // instruction per block.
+    u64x2 even[kSteps / 2], odd[kSteps / 2];
+    fetch(even, 0);
+    for (int t = 0; t < nB; t += 2 * kSteps) {
+        if (t + kSteps < nB) fetch(odd, t + kSteps);
+        steps(even, t);
+        if (t + kSteps >= nB) break;
+        if (t + 2 * kSteps < nB) fetch(even, t + 2 * kSteps);
+        steps(odd, t + kSteps);
     }
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s)
