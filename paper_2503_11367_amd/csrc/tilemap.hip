@@ -25,19 +25,27 @@ tile_map_kernel(const uint64_t* __restrict__ bits, const int32_t* __restrict__ b
     tile_map_body<CODE>(blockIdx.x, bits, blocks, block, n_seq_blocks, n_rows, jobs);
 }
 
-__global__ void __launch_bounds__(256)
-row_pairs_kernel(const uint32_t* __restrict__ cnt, int32_t nk, uint64_t* __restrict__ rowpairs) {
-    __shared__ uint64_t part[256];
-    const int64_t i = blockIdx.x;
+// A row per wavefront, 1024 counts of it in flight
+constexpr int kRowWaves = 4, kRowAhead = 16;
+__global__ void __launch_bounds__(kRowWaves * kWave)
+row_pairs_kernel(const uint32_t* __restrict__ cnt, int32_t nq, int32_t nk, uint64_t* __restrict__ rowpairs) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t i = (int64_t)blockIdx.x * kRowWaves + threadIdx.x / kWave;
+    if (i >= nq) return;
     uint64_t s = 0;
-    for (int j = threadIdx.x; j < nk; j += 256) s += cnt[i * nk + j];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) part[threadIdx.x] += part[threadIdx.x + off];
-        __syncthreads();
+    for (int j0 = 0; j0 < nk; j0 += kRowAhead * kWave) {
+        uint32_t c[kRowAhead];
+#pragma unroll
+        for (int u = 0; u < kRowAhead; ++u) {
+            const int j = j0 + u * kWave + lane;
+            c[u] = 0u;
+            if (j0 + u * kWave < nk && j < nk) c[u] = cnt[i * nk + j];
+        }
+#pragma unroll
+        for (int u = 0; u < kRowAhead; ++u) s += c[u];
     }
-    if (threadIdx.x == 0) rowpairs[i] = part[0];
+    for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if (lane == 0) rowpairs[i] = s;
 }
 
 int launch_tile_map(const uint64_t* d_bits, int64_t S, const int32_t* d_blocks, int32_t block,
@@ -48,15 +56,15 @@ int launch_tile_map(const uint64_t* d_bits, int64_t S, const int32_t* d_blocks, 
     jobs.j[0] = jobs.j[1] = tile_map_job(S, n_rows, tq, tk, d_cls, d_cnt);
     const bool runs = tile_map_by_runs(jobs);
     const auto kernel = S > kTmNarrow    ? tile_map_kernel<kTmWide>
-                        : tq <= kWave     ? (runs ? tile_map_kernel<kTmByRuns | kTmRows1> : tile_map_kernel<kTmRows1>)
-                        : tq <= 2 * kWave ? (runs ? tile_map_kernel<kTmByRuns | kTmRows2> : tile_map_kernel<kTmRows2>)
-                                          : (runs ? tile_map_kernel<kTmByRuns | kTmRows4> : tile_map_kernel<kTmRows4>);
+                        : tq <= kWave     ? (runs ? tile_map_kernel<kTmByRuns | kTmWhole | kTmRows1> : tile_map_kernel<kTmRows1>)
+                        : tq <= 2 * kWave ? (runs ? tile_map_kernel<kTmByRuns | kTmWhole | kTmRows2> : tile_map_kernel<kTmRows2>)
+                                          : (runs ? tile_map_kernel<kTmByRuns | kTmWhole | kTmRows4> : tile_map_kernel<kTmRows4>);
     hipLaunchKernelGGL(kernel, dim3(jobs.j[0].gx * jobs.j[0].gy), dim3(kTmThreads), 0, st, d_bits, d_blocks, block,
                        d_blocks ? S / block : (int64_t)0, n_rows, jobs);
     MM_LAUNCH_CHECK();
     if (d_rowpairs) {
-        hipLaunchKernelGGL(row_pairs_kernel, dim3((unsigned)jobs.j[0].nq), dim3(256), 0, st, d_cnt, jobs.j[0].nk,
-                           d_rowpairs);
+        hipLaunchKernelGGL(row_pairs_kernel, dim3((unsigned)((jobs.j[0].nq + kRowWaves - 1) / kRowWaves)),
+                           dim3(kRowWaves * kWave), 0, st, d_cnt, jobs.j[0].nq, jobs.j[0].nk, d_rowpairs);
         MM_LAUNCH_CHECK();
     }
     return MMATTN_OK;

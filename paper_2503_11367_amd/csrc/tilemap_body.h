@@ -3,6 +3,7 @@
 // they run side by side with that pass's other independent preparation work.
 #pragma once
 #include <algorithm>
+#include <type_traits>
 #include "common.h"
 
 namespace mm {
@@ -31,7 +32,8 @@ struct TileMapJobs { TileMapJob j[2]; };
 // runs.  A kernel for all of them needs 21 KiB more LDS and twice the code where neither is used:
 // small maps took 0.2 to 0.5 us longer (64 x 64 tiles of 64 x 64: 6.3 against 6.0 us).  kTmBeside:
 // other workgroups of the launch stream through memory, so that the map may not take much LDS.
-enum : int { kTmRows1 = 1, kTmRows2 = 2, kTmRows4 = 4, kTmWide = 8, kTmByRuns = 16, kTmBeside = 32 };
+// kTmWhole: the rows are the whole sequence, no list of blocks to look positions up in.
+enum : int { kTmRows1 = 1, kTmRows2 = 2, kTmRows4 = 4, kTmWide = 8, kTmByRuns = 16, kTmBeside = 32, kTmWhole = 64 };
 
 // A run: consecutive tokens of a tile that carry the same fields (x: the attend word of query
 // rows, the modality of keys) at consecutive positions.  A list of runs ends with an entry
@@ -223,8 +225,10 @@ __device__ __forceinline__ void tile_map_by_rows_any(const TileMapJob& J, const 
 // requested before the first is used), then each thread counts one tile pair.  Bound by the
 // latency of the words and the integer work per run pair; the group's shape trades words read
 // per pair, (gq + gk) / (gq gk) tiles, against workgroups in flight.  Measured per launch:
-// 1024 x 1024 tiles of 128 x 128 302 -> 25 us, 512 x 512 88 -> 13 us against counting every
-// row of a tile against every run of keys.  Where a group has fewer pairs than threads, tiles of
+// 1024 x 1024 tiles of 128 x 128 302 -> 19 us, 512 x 512 88 -> 10 us against counting every
+// row of a tile against every run of keys (25 and 13 without a way out for tiles of one run, and
+// with a branch and a look at the block list around every word; tiles of 512 x 512, one 64-word step
+// in flight instead of eight, 256 x 256 of them 19 -> 12 us).  Where a group has fewer pairs than threads, tiles of
 // more than kTmSplit runs have theirs shared out over several (256 x 256 tiles of 16 x 16 in
 // spans of 1 to 3 tokens 61 -> 24 us; tiles of few runs would pay 0.9 us for nothing).
 // Counted by rows all the same: tiles of more than kTmRuns runs, and q-tiles of more than most_q
@@ -247,15 +251,20 @@ __device__ __forceinline__ void tile_map_runs(const TileMapJob& J, const TmRows&
     __shared__ int32_t n_runs[2 * kTmGroup];
     __shared__ uint64_t left_s[kTmGroup * kTmGroup / kWave];     // pairs that the runs do not serve
 
-    // tile `slot` of the group (q-tiles first): its length (0: past the end of the map), and the
-    // position of its element e
+    // tile `slot` of the group (q-tiles first): its length (0: past the end of the map) and first row or key
     auto length_of = [&](int slot) -> int32_t {
         if (slot < gq) return i0 + slot < nq ? (int32_t)in.of_tile(tq, i0 + slot) : 0;
         return slot < gq + gk && j0 + slot - gq < nk ? tk : 0;
     };
-    auto element = [&](int slot, int32_t e) -> uint32_t {
-        return slot < gq ? (uint32_t)in.pos((int64_t)(i0 + slot) * tq + e)
-                         : (uint32_t)(j0 + slot - gq) * (uint32_t)tk + (uint32_t)e;
+    auto start_of = [&](int slot) -> uint32_t {
+        return slot < gq ? (uint32_t)(i0 + slot) * (uint32_t)tq : (uint32_t)(j0 + slot - gq) * (uint32_t)tk;
+    };
+    // position of element e of a tile (of its first one past the end, so that no load hangs on a branch).
+    // Called for all elements of a batch before the first word is requested: the block indices of a
+    // share are a load of their own.
+    auto position = [&](int slot, uint32_t start, int32_t len, int32_t e) -> uint32_t {
+        const uint32_t r = (len > 0 ? start : 0u) + (uint32_t)(e < len ? e : 0);
+        return (CODE & kTmWhole) || slot >= gq ? r : (uint32_t)in.pos((int64_t)r);
     };
     // 64 elements at0 .. of a tile (n of them valid) appended to its list of runs; (p_ss, p_x,
     // p_pos): the last element of the 64 before
@@ -280,6 +289,24 @@ __device__ __forceinline__ void tile_map_runs(const TileMapJob& J, const TmRows&
             if (count <= kTmRuns) runs[slot][count].at = (uint32_t)len;
         }
     };
+    // A tile, or some hundred tokens of a larger one, is usually one run: then no word differs from the first (equal
+    // words have equal fields) and positions are consecutive, one comparison per word, and all that
+    // is left is to see whether the run goes on.
+    auto one_run = [&](int slot, int32_t at0, int32_t n, uint64_t w0, uint32_t pos0, int32_t& count, uint32_t& p_ss,
+                       uint32_t& p_x, uint32_t& p_pos) {
+        const uint32_t ss = word_ss(w0), x = slot < gq ? word_att(w0) : word_mod(w0);
+        if (at0 == 0 || ss != p_ss || x != p_x || pos0 != p_pos + 1u) {
+            if (lane == 0 && count < kTmRuns) runs[slot][count] = TmRun{ss, x, pos0, (uint32_t)at0};
+            ++count;
+        }
+        p_ss = ss;
+        p_x = x;
+        p_pos = pos0 + (uint32_t)n - 1u;
+    };
+    auto first_word = [&](uint64_t w) -> uint64_t {
+        return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(w >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)w);
+    };
     if (max(tq, tk) <= 2 * kWave) {
         // tiles of one or two words per lane, the words of kTmAhead tiles in flight together
         for (int s0 = wave; s0 < gq + gk; s0 += kTmWaves * kTmAhead) {
@@ -289,16 +316,14 @@ __device__ __forceinline__ void tile_map_runs(const TileMapJob& J, const TmRows&
             for (int s = 0; s < kTmAhead; ++s) {
                 const int slot = s0 + kTmWaves * s;
                 const int32_t len = length_of(slot);
+                const uint32_t start = start_of(slot);
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    pos[s][c] = 0u;
-                    w[s][c] = 0u;
-                    if (c * kWave + lane < len) {
-                        pos[s][c] = element(slot, c * kWave + lane);
-                        w[s][c] = bits[pos[s][c]];
-                    }
-                }
+                for (int c = 0; c < 2; ++c) pos[s][c] = position(slot, start, len, c * kWave + lane);
             }
+#pragma unroll
+            for (int s = 0; s < kTmAhead; ++s)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) w[s][c] = bits[pos[s][c]];
 #pragma unroll
             for (int s = 0; s < kTmAhead; ++s) {
                 const int slot = s0 + kTmWaves * s;
@@ -306,23 +331,58 @@ __device__ __forceinline__ void tile_map_runs(const TileMapJob& J, const TmRows&
                 if (len == 0) continue;                      // wave-uniform
                 int32_t count = 0;
                 uint32_t p_ss = 0u, p_x = 0u, p_pos = 0u;
-                append(slot, 0, len, w[s][0], pos[s][0], count, p_ss, p_x, p_pos);
-                if (len > kWave) append(slot, kWave, len - kWave, w[s][1], pos[s][1], count, p_ss, p_x, p_pos);
+                const uint64_t w0 = first_word(w[s][0]);
+                const uint32_t pos0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos[s][0]);
+                bool same = (lane >= len || w[s][0] == w0) && (kWave + lane >= len || w[s][1] == w0);
+                if (!(CODE & kTmWhole))
+                    same = same && (lane >= len || pos[s][0] == pos0 + lane) &&
+                           (kWave + lane >= len || pos[s][1] == pos0 + kWave + lane);
+                if (__all(same)) {                           // wave-uniform
+                    one_run(slot, 0, len, w0, pos0, count, p_ss, p_x, p_pos);
+                } else {
+                    append(slot, 0, len, w[s][0], pos[s][0], count, p_ss, p_x, p_pos);
+                    if (len > kWave) append(slot, kWave, len - kWave, w[s][1], pos[s][1], count, p_ss, p_x, p_pos);
+                }
                 finish(slot, len, count);
             }
         }
     } else {
-        for (int slot = wave; slot < gq + gk; slot += kTmWaves) {
-            const int32_t len = length_of(slot);
-            if (len == 0) continue;
-            int32_t count = 0;
-            uint32_t p_ss = 0u, p_x = 0u, p_pos = 0u;
-            for (int32_t at = 0; at < len; at += kWave) {
-                const uint32_t pos = at + lane < len ? element(slot, at + lane) : 0u;
-                append(slot, at, len - at, at + lane < len ? bits[pos] : 0u, pos, count, p_ss, p_x, p_pos);
+        auto larger = [&](auto CH_) __attribute__((always_inline)) {
+            constexpr int CH = decltype(CH_)::value;         // times 64 words of a tile in flight together
+            for (int slot = wave; slot < gq + gk; slot += kTmWaves) {
+                const int32_t len = length_of(slot);
+                if (len == 0) continue;
+                const uint32_t start = start_of(slot);
+                int32_t count = 0;
+                uint32_t p_ss = 0u, p_x = 0u, p_pos = 0u;
+                for (int32_t at = 0; at < len; at += CH * kWave) {
+                    uint64_t w[CH];
+                    uint32_t pos[CH];
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) pos[c] = position(slot, start, len, at + c * kWave + lane);
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) w[c] = bits[pos[c]];
+                    const uint64_t w0 = first_word(w[0]);
+                    const uint32_t pos0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos[0]);
+                    bool same = true;
+#pragma unroll
+                    for (int c = 0; c < CH; ++c)
+                        same = same && (at + c * kWave + lane >= len ||
+                                        (w[c] == w0 && ((CODE & kTmWhole) || pos[c] == pos0 + c * kWave + lane)));
+                    if (__all(same)) {                           // wave-uniform
+                        one_run(slot, at, min(len - at, CH * kWave), w0, pos0, count, p_ss, p_x, p_pos);
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < CH; ++c)
+                            if (at + c * kWave < len)
+                                append(slot, at + c * kWave, len - at - c * kWave, w[c], pos[c], count, p_ss, p_x, p_pos);
+                    }
+                }
+                finish(slot, len, count);
             }
-            finish(slot, len, count);
-        }
+        };
+        if (max(tq, tk) <= 4 * kWave) larger(std::integral_constant<int, 4>{});
+        else larger(std::integral_constant<int, 8>{});
     }
     __syncthreads();
 

@@ -185,6 +185,19 @@ def test_tile_map_many_runs_in_large_maps(tile, kind):
     check_tile_map(lay, tile[0], tile[1], use_c=True)
 
 
+@pytest.mark.parametrize("tile", [(960, 16), (16, 960), (320, 48), (240, 240), (128, 96), (480, 32)])
+def test_tile_map_tiles_of_one_run_beside_mixed_ones(tile):
+    """Large maps of long runs whose ends lie one token before, at and behind multiples of 64, 256 and
+    512: tiles that are one run as a whole, step by step, and not at all."""
+    spans, pos = [], 100
+    for i, (gap, n) in enumerate([(28, 512), (1, 255), (64, 257), (511, 1), (130, 1024), (1, 63), (2, 4096), (300, 960), (65, 2047)]):
+        spans.append((pos + gap, n, 1 + i % 3))
+        pos += gap + n
+    lay = wl.Layout(30720, spans, [0, 12800, 30720], deny=[(i % 4 == 1) << 1 for i in range(len(spans))])
+    assert pos < 12800 and (30720 // tile[0]) * (30720 // tile[1]) > 4096
+    check_tile_map(lay, tile[0], tile[1], use_c=True)
+
+
 def test_tile_map_positions_beyond_30_bits():
     """A share's rows near the end of 2^30 + 2^20 tokens (the library's own map of a share; the
     public one would count all rows): positions are 64-bit there."""
