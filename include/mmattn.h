@@ -229,8 +229,11 @@ int mmattn_fwd_heads(const void* q_loc, const void* k, const void* v, const uint
  * each window of `heads_per_stage` KV heads, in order, the window's heads of
  * k_src, v_src are copied into k_stage, v_stage on `copy_stream` (a stand-in
  * for the arrival of the gathered heads) and `stream` waits for that window
- * only before running mmattn_fwd_heads on it, so the transfers of the later
- * windows overlap the attention of the earlier ones.
+ * only before attending its heads, so the transfers of the later windows overlap
+ * the attention of the earlier ones.  Consecutive windows that hold little data or
+ * little work between them (below 32 MiB of K and V, below 2048 query tiles times
+ * heads) travel and are attended together where k_src and v_src are memory of
+ * this GPU: their transfers take less time than hand-overs between the streams.
  *   k_src, v_src      device [S,Hkv,D], read on copy_stream once everything
  *                     enqueued on `stream` before this call has completed
  *   k_stage, v_stage  device [S,Hkv,D], overwritten with k_src, v_src (may be the
@@ -241,7 +244,7 @@ int mmattn_fwd_heads(const void* q_loc, const void* k, const void* v, const uint
  * its work reads or writes the caller's buffers.
  * When the call returns, all work has been enqueued; `stream` has been made to
  * wait for every copy, so later work on `stream` may reuse all buffers.
- * Creates and destroys up to Hkv/heads_per_stage + 2 HIP events (no device
+ * Creates and destroys at most Hkv/heads_per_stage + 2 HIP events (no device
  * memory).  Hkv % heads_per_stage == 0, at most MMATTN_MAX_STAGES windows. */
 #define MMATTN_MAX_STAGES 64
 int mmattn_fwd_staged(const void* q_loc, const void* k_src, const void* v_src,

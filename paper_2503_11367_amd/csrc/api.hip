@@ -1,6 +1,8 @@
 // C ABI of libmmattn: argument validation (host only, before any HIP call)
 // and dispatch to the kernels.  See include/mmattn.h for the contract.
+#include <algorithm>
 #include "common.h"
+#include "small.h"
 
 using namespace mm;
 
@@ -26,6 +28,35 @@ int check_attn(const void* q, const void* k, const void* v, const uint64_t* bits
         !aligned(blocks, 4))
         return MMATTN_ERR_SHAPE;
     return MMATTN_OK;
+}
+
+// Device memory of the current GPU, which its kernels may read whatever the peers' access is
+bool on_this_gpu(const void* p) {
+    hipPointerAttribute_t at;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();                  // it would be taken for a later launch's
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == dev && !at.isManaged;
+}
+
+// How many of the windows of KV heads the staged forward moves and attends at once: all of them
+// where the attention is a single small kernel (16 heads of 128 tokens by four 119 -> 40 us), else as
+// many as make kStageBytes of K and V and kStageTiles (128-row tile, query head) work items.  A
+// smaller transfer is over sooner (32 MiB in 13 us) than the hand-over to the attention and its
+// launches take, and an attention of fewer than four pairs of heads per CU leaves CUs idle at its end
+// or has its lists cut.  Measured, us, windows one by one / with half of either limit / so / all at
+// once: 8192 tokens, 32 / 8 heads by one 954 / 613 / 566 / 566; a rank of four of 32768, 32 / 8 by
+// four 2056 / 2055 / 1984 / 1983; a rank of eight of 65536, 64 / 8 by one 1547 / 1092 / 993 / 955;
+// of 131072, 32 / 8 by one 17392 / 15171 / 14832 / 14850, by four 14805 / 14897 / 14889 / 15022.
+constexpr int64_t kStageBytes = 32 << 20, kStageTiles = 2048;
+int stage_windows(const AttnArgs& all, int n_stage) {
+    if (all.n_blocks == 0 || small_fwd_wanted(all)) return n_stage;
+    const int64_t bytes = all.S * all.Hkv * all.D * 4;
+    const int64_t tiles = ((int64_t)all.n_blocks * all.block + 127) / 128 * all.Hq;
+    const int64_t parts = std::max<int64_t>(1, std::min(bytes / kStageBytes, tiles / kStageTiles));
+    return (int)((n_stage + parts - 1) / parts);
 }
 
 }  // namespace
@@ -193,9 +224,21 @@ int mmattn_fwd_staged(const void* q_loc, const void* k_src, const void* v_src, v
 
     hipStream_t cs = (hipStream_t)copy_stream, st = (hipStream_t)stream;
     const int n_stage = Hkv / heads_per_stage;
-    const size_t pitch = (size_t)Hkv * D * 2, width = (size_t)heads_per_stage * D * 2;
-    hipEvent_t ready = nullptr, behind = nullptr, arrived[MMATTN_MAX_STAGES] = {};
     if (n_stage > MMATTN_MAX_STAGES) return MMATTN_ERR_UNSUPPORTED;
+    hipEvent_t ready = nullptr, behind = nullptr, arrived[MMATTN_MAX_STAGES] = {};
+    // Memory of this GPU is moved by a kernel, several windows at a time where they are small; what
+    // lies elsewhere by the runtime, window by window.
+    const bool local = on_this_gpu(k_src) && on_this_gpu(v_src);
+    AttnArgs a{q_loc, k_stage, v_stage, bits, blocks, n_blocks, block, S, Hq, Hkv, D, scale, 0, Hkv, 1, 0};
+    const int at_once = local ? stage_windows(a, n_stage) : 1;
+    const int n_part = (n_stage + at_once - 1) / at_once;
+    auto part = [&](int i) {                                     // the heads of the i-th transfer
+        a.kv_begin = i * at_once * heads_per_stage;
+        a.kv_count = std::min(at_once * heads_per_stage, Hkv - a.kv_begin);
+    };
+    part(0);
+    const bool planned = n_blocks > 0 && !small_fwd_wanted(a);
+    a.norms_ready = local && planned;
     rc = MMATTN_OK;
     auto ok = [&](hipError_t e) { if (e != hipSuccess && rc == MMATTN_OK) rc = MMATTN_ERR_HIP; return e == hipSuccess; };
     // the copy stream starts once the inputs and the staging buffers are free on `stream`
@@ -203,38 +246,45 @@ int mmattn_fwd_staged(const void* q_loc, const void* k_src, const void* v_src, v
         ok(hipStreamWaitEvent(cs, ready, 0));
     // the plan reads bits and blocks and writes ws, which the caller may have left to earlier work
     // on the copy stream (recorded behind the wait, so that a capture of `stream` takes it in)
-    if (rc == MMATTN_OK && n_blocks > 0 &&
+    if (rc == MMATTN_OK && planned &&
         ok(hipEventCreateWithFlags(&behind, hipEventDisableTiming)) && ok(hipEventRecord(behind, cs)))
         ok(hipStreamWaitEvent(st, behind, 0));
-    for (int i = 0; i < n_stage && rc == MMATTN_OK; ++i) {
-        const size_t off = (size_t)i * width;
-        if (k_src != k_stage)                   // already in place: nothing to move
-            ok(hipMemcpy2DAsync((char*)k_stage + off, pitch, (const char*)k_src + off, pitch, width,
-                                (size_t)S, hipMemcpyDeviceToDevice, cs));
-        if (v_src != v_stage)
-            ok(hipMemcpy2DAsync((char*)v_stage + off, pitch, (const char*)v_src + off, pitch, width,
-                                (size_t)S, hipMemcpyDeviceToDevice, cs));
+    for (int i = 0; i < n_part && rc == MMATTN_OK; ++i) {
+        part(i);
+        if (local) {
+            rc = launch_stage(a, k_src, v_src, ws, cs);
+        } else {
+            const size_t pitch = (size_t)Hkv * D * 2, width = (size_t)a.kv_count * D * 2, off = (size_t)a.kv_begin * D * 2;
+            if (k_src != k_stage)               // already in place: nothing to move
+                ok(hipMemcpy2DAsync((char*)k_stage + off, pitch, (const char*)k_src + off, pitch, width,
+                                    (size_t)S, hipMemcpyDeviceToDevice, cs));
+            if (v_src != v_stage)
+                ok(hipMemcpy2DAsync((char*)v_stage + off, pitch, (const char*)v_src + off, pitch, width,
+                                    (size_t)S, hipMemcpyDeviceToDevice, cs));
+        }
         if (ok(hipEventCreateWithFlags(&arrived[i], hipEventDisableTiming)))
             ok(hipEventRecord(arrived[i], cs));
     }
-    // the plan needs neither keys nor values: it is built while the first window arrives (32768
+    // the plan needs neither keys nor values: it is built while the first heads arrive (32768
     // keys, two windows of four heads: 1999 -> 1993 us against building it behind the first wait)
-    AttnArgs a{q_loc, k_stage, v_stage, bits, blocks, n_blocks, block, S, Hq, Hkv, D, scale, 0, heads_per_stage, 1};
-    if (rc == MMATTN_OK && n_blocks > 0) rc = launch_fwd_plan(a, ws, st);
-    for (int i = 0; i < n_stage && rc == MMATTN_OK; ++i) {
+    if (rc == MMATTN_OK && planned) {
+        part(0);
+        rc = launch_fwd_plan(a, ws, st);
+    }
+    for (int i = 0; i < n_part && rc == MMATTN_OK; ++i) {
         if (!ok(hipStreamWaitEvent(st, arrived[i], 0))) break;
         if (n_blocks == 0) continue;
-        a.kv_begin = i * heads_per_stage;
-        rc = launch_fwd(a, o_loc, lse, ws, st);
+        part(i);
+        rc = planned ? launch_fwd(a, o_loc, lse, ws, st) : launch_fwd_small(a, o_loc, lse, (int32_t*)ws, st);
     }
     // on an error part-way, `stream` still has to wait for whatever the copy stream was given
     if (rc != MMATTN_OK)
-        for (int i = 0; i < n_stage; ++i)
+        for (int i = 0; i < n_part; ++i)
             if (arrived[i]) (void)hipStreamWaitEvent(st, arrived[i], 0);
     // destroying a recorded event is deferred by the runtime until it has completed
     if (ready) (void)hipEventDestroy(ready);
     if (behind) (void)hipEventDestroy(behind);
-    for (int i = 0; i < n_stage; ++i)
+    for (int i = 0; i < n_part; ++i)
         if (arrived[i]) (void)hipEventDestroy(arrived[i]);
     return rc;
 }

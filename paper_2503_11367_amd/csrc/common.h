@@ -157,6 +157,7 @@ struct AttnArgs {
     // forward only: the window of KV heads to run (with their query heads), and whether
     // the plan in the workspace is the one an earlier call built for the same share
     int32_t kv_begin, kv_count, plan_ready;
+    int32_t norms_ready;                  // with a plan: the window's key norms are in the workspace too
 };
 size_t fwd_workspace(int64_t S, int64_t n_loc, int32_t Hq, int32_t Hkv, int32_t D);
 size_t fwd_heads_workspace(int64_t S, int64_t n_loc, int32_t Hq, int32_t Hkv, int32_t D);
@@ -166,6 +167,9 @@ int launch_fwd(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st)
 int launch_fwd_whole(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st);
 // the plan alone, which needs neither q, k nor v; launch_fwd with plan_ready runs on it
 int launch_fwd_plan(const AttnArgs& a, void* ws, hipStream_t st);
+// the window's K and V move from k_src, v_src to a.k, a.v (where they are not there already);
+// with a.norms_ready its key norms go to the workspace on the way
+int launch_stage(const AttnArgs& a, const void* k_src, const void* v_src, void* ws, hipStream_t st);
 int launch_fwd_static(const AttnArgs& a, void* o, float* lse, hipStream_t st);
 int launch_zero_kv(void* dk, void* dv, size_t bytes_each, hipStream_t st);
 int launch_bwd(const AttnArgs& a, const void* o, const float* lse, const void* d_o,

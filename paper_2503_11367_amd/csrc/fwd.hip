@@ -51,10 +51,11 @@ constexpr int kNormChunks = 64;     // partial maxima of the squared key norms p
 // Largest squared key norm of every KV head, as kNormChunks partial maxima per head (no
 // atomics: the attention kernel takes the maximum of its head's partials).  One workgroup
 // of 256 threads per (chunk, head of the launch); a chunk is S / kNormChunks consecutive keys.
-template <int D>
+// With COPY the rows also go to `dst`, which lies as K does; without NORM that is all.
+template <int D, bool NORM = true, bool COPY = false>
 __device__ __forceinline__ void
 key_norm_body(int chunk, int g, const ushort_t* __restrict__ K, int64_t S, int32_t Hkv_s,
-              float* __restrict__ knorm) {
+              float* __restrict__ knorm, ushort_t* __restrict__ dst = nullptr) {
     constexpr int TPK = D / 8;                            // threads per key, 8 elements each
     constexpr int KPP = 256 / TPK;                        // keys per pass
     __shared__ float wmax[4];
@@ -66,11 +67,19 @@ key_norm_body(int chunk, int g, const ushort_t* __restrict__ K, int64_t S, int32
     float best = 0.f;
     for (int64_t k = kk; k < per; k += kAhead * KPP) {
         u32x4 raw[kAhead];
+        const int64_t at = ((k0 + k) * Hkv_s + g) * (int64_t)D + sub * 8;
+        const int64_t pass = (int64_t)KPP * Hkv_s * D;
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) {
             raw[i] = u32x4{0u, 0u, 0u, 0u};
-            if (k + i * KPP < per) raw[i] = *(const u32x4*)(K + ((k0 + k + i * KPP) * Hkv_s + g) * (int64_t)D + sub * 8);
+            if (k + i * KPP < per) raw[i] = *(const u32x4*)(K + at + i * pass);
         }
+        if constexpr (COPY) {
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+                if (k + i * KPP < per) *(u32x4*)(dst + at + i * pass) = raw[i];
+        }
+        if constexpr (!NORM) continue;
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) {
             const bf16x8 x = __builtin_bit_cast(bf16x8, raw[i]);
@@ -82,6 +91,7 @@ key_norm_body(int chunk, int g, const ushort_t* __restrict__ K, int64_t S, int32
             best = fmaxf(best, a);                        // a NaN norm is dropped here and caught by the row bound
         }
     }
+    if constexpr (!NORM) return;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) best = fmaxf(best, __shfl_xor(best, off));
     if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = best;
@@ -96,6 +106,28 @@ template <int D>
 __global__ void __launch_bounds__(256)
 key_norm_kernel(const ushort_t* __restrict__ K, int64_t S, int32_t Hkv_s, float* __restrict__ knorm) {
     key_norm_body<D>((int)blockIdx.x, (int)blockIdx.y, K, S, Hkv_s, knorm);
+}
+
+// One stage of the staged forward: K and V of some heads move to the buffers that the attention
+// reads, and the key norms are formed on the way.  Grid (kNormChunks, heads, 2): K first, then V;
+// a tensor that is in place already is not written, and without `knorm` there are no norms.
+// Bound by memory: 67 MB to and fro in 27 us.  Against two strided copies of the runtime and a
+// pass for the norms behind them, one of two windows: a rank of four of 32768 tokens, 32 / 8 heads
+// 2091 -> 2056 us; all heads at once 2005 -> 1972.
+template <int D>
+__global__ void __launch_bounds__(256)
+stage_kernel(const ushort_t* __restrict__ K, const ushort_t* __restrict__ V, ushort_t* __restrict__ k_to,
+             ushort_t* __restrict__ v_to, int64_t S, int32_t Hkv_s, float* __restrict__ knorm) {
+    const int chunk = (int)blockIdx.x, g = (int)blockIdx.y;
+    if (blockIdx.z == 1) {
+        if (v_to) key_norm_body<D, false, true>(chunk, g, V, S, Hkv_s, nullptr, v_to);
+    } else if (!k_to) {
+        if (knorm) key_norm_body<D, true, false>(chunk, g, K, S, Hkv_s, knorm);
+    } else if (knorm) {
+        key_norm_body<D, true, true>(chunk, g, K, S, Hkv_s, knorm, k_to);
+    } else {
+        key_norm_body<D, false, true>(chunk, g, K, S, Hkv_s, nullptr, k_to);
+    }
 }
 
 // Everything the forward prepares that depends on nothing but the caller's inputs, in one
@@ -990,6 +1022,20 @@ int launch_fwd_plan(const AttnArgs& a, void* ws, hipStream_t st) {
     return launch_fwd_prologue(a, fwd_scratch(a, ws), 0, st);
 }
 
+int launch_stage(const AttnArgs& a, const void* k_src, const void* v_src, void* ws, hipStream_t st) {
+    const int64_t first = (int64_t)a.kv_begin * a.D;
+    const bool move_k = k_src != a.k, move_v = v_src != a.v;
+    float* knorm = a.norms_ready ? fwd_scratch(a, ws).knorm : nullptr;
+    if (!move_k && !move_v && !knorm) return MMATTN_OK;
+    hipLaunchKernelGGL((a.D == 128 ? stage_kernel<128> : stage_kernel<64>),
+                       dim3(kNormChunks, (unsigned)a.kv_count, move_v ? 2 : 1), dim3(256), 0, st,
+                       (const ushort_t*)k_src + first, (const ushort_t*)v_src + first,
+                       move_k ? (ushort_t*)a.k + first : nullptr, move_v ? (ushort_t*)a.v + first : nullptr,
+                       a.S, a.Hkv, knorm);
+    MM_LAUNCH_CHECK();
+    return MMATTN_OK;
+}
+
 int launch_fwd(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st) {
     const int64_t n_loc = (int64_t)a.n_blocks * a.block;
     const FwdScratch s = fwd_scratch(a, ws);
@@ -1003,7 +1049,7 @@ int launch_fwd(const AttnArgs& a, void* o, float* lse, void* ws, hipStream_t st)
     if (!a.plan_ready) {
         const int rc = launch_fwd_prologue(a, s, a.kv_count, st);
         if (rc) return rc;
-    } else {
+    } else if (!a.norms_ready) {
         const ushort_t* kw = (const ushort_t*)a.k + (int64_t)a.kv_begin * a.D;
         const dim3 grid(kNormChunks, (unsigned)a.kv_count);
         if (a.D == 128)

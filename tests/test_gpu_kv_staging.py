@@ -116,6 +116,89 @@ def test_staged_in_place():
     assert torch.equal(t["k"], k0) and torch.equal(t["v"], v0)
 
 
+@pytest.mark.parametrize("S,Hq,Hkv,D,hps", [
+    (16384, 36, 9, 128, 1),      # 72 MiB, 4608 (tile, head) pairs: two transfers, of five heads and of four
+    (16384, 16, 16, 64, 4),      # 64 MiB, 2048 pairs: everything at once
+    (512, 16, 16, 128, 1),       # one kernel after one transfer
+])
+@pytest.mark.parametrize("in_place", ["neither", "k", "v"])
+def test_staged_windows_together(S, Hq, Hkv, D, hps, in_place):
+    """Windows that travel together, their last group smaller; K or V already in its place."""
+    lay = wl.layout_random(154, S=S, n_samples=3, max_spans=5, deny_prob=0.3)
+    nb = S // 128
+    blocks = np.random.default_rng(154).permutation(nb).tolist()
+    t = make_tensors(414, S, S, Hq, Hkv, D)
+    bits = gpu_bits(lay)
+    bl = torch.tensor(blocks, dtype=torch.int32, device=DEV)
+    ks = t["k"] if in_place == "k" else torch.full_like(t["k"], float("nan"))
+    vs = t["v"] if in_place == "v" else torch.full_like(t["v"], float("nan"))
+    k0, v0 = t["k"].clone(), t["v"].clone()
+    o, lse = mb.fwd_staged(t["q"], t["k"], t["v"], ks, vs, bits, bl, 128, hps, torch.cuda.Stream())
+    torch.cuda.synchronize()
+    assert torch.equal(ks, k0) and torch.equal(vs, v0)
+    f = fields(lay)
+    rows = oa.rows_of_blocks(blocks, 128)
+    sel = np.sort(np.random.default_rng(7).choice(S, size=96, replace=False))
+    Q, K, V = f64(t["q_bits"]), f64(t["k_bits"]), f64(t["v_bits"])
+    rep = Hq // Hkv
+    for g in sorted({0, 4, 5, Hkv - 1}):
+        h = g * rep + rep - 1
+        o_ref, lse_ref = oa.forward(Q[sel][:, h:h + 1], K[:, g:g + 1], V[:, g:g + 1], rows[sel], f[0], f[1], f[2],
+                                    modality=f[3], attend=f[4])
+        check(o[sel][:, h:h + 1], lse[h:h + 1][:, sel], o_ref, lse_ref)
+
+
+def test_staged_from_pinned_memory():
+    """Sources in pinned host memory take the runtime's copies, window by window."""
+    lay = wl.layout_random(155, S=1024, n_samples=2, max_spans=5)
+    Hq, Hkv, D, blocks = 8, 4, 128, [3, 14, 6, 9]
+    t = make_tensors(415, len(blocks) * 64, lay.S, Hq, Hkv, D)
+    bits = gpu_bits(lay)
+    bl = torch.tensor(blocks, dtype=torch.int32, device=DEV)
+    k_src, v_src = (torch.empty(t[x].shape, dtype=t[x].dtype, pin_memory=True) for x in "kv")
+    k_src.copy_(t["k"]); v_src.copy_(t["v"])
+    ks, vs = torch.full_like(t["k"], float("nan")), torch.full_like(t["v"], float("nan"))
+    o, lse = torch.empty_like(t["q"]), torch.empty(Hq, t["q"].shape[0], dtype=torch.float32, device=DEV)
+    ws = torch.empty(mb.workspace_size(mb.OP_FWD_HEADS, lay.S, len(blocks), 64, Hq, Hkv, D), dtype=torch.uint8, device=DEV)
+    copy = torch.cuda.Stream()
+    rc = mb.lib().mmattn_fwd_staged(t["q"].data_ptr(), k_src.data_ptr(), v_src.data_ptr(), ks.data_ptr(), vs.data_ptr(),
+                                    bits.data_ptr(), bl.data_ptr(), len(blocks), 64, lay.S, Hq, Hkv, D, D ** -0.5, mb.BF16, 2,
+                                    o.data_ptr(), lse.data_ptr(), ws.data_ptr(), ws.numel(), copy.cuda_stream,
+                                    torch.cuda.current_stream().cuda_stream)
+    assert rc == mb.OK
+    torch.cuda.synchronize()
+    assert torch.equal(ks, t["k"]) and torch.equal(vs, t["v"])
+    check(o, lse, *oracle_fwd(lay, blocks, 64, t, Hq, Hkv))
+
+
+@pytest.mark.parametrize("S,Hq,Hkv", [(512, 8, 4), (4096, 32, 8)])
+def test_staged_in_a_graph(S, Hq, Hkv):
+    """One captured call, replayed over new inputs with eager work in between."""
+    lay = wl.layout_random(156, S=S, n_samples=2, max_spans=4)
+    t = make_tensors(416, S, S, Hq, Hkv, 128)
+    bits = gpu_bits(lay)
+    bl = torch.arange(S // 64, dtype=torch.int32, device=DEV)
+    ks, vs = torch.empty_like(t["k"]), torch.empty_like(t["v"])
+    ws = torch.empty(mb.workspace_size(mb.OP_FWD_HEADS, S, S // 64, 64, Hq, Hkv, 128), dtype=torch.uint8, device=DEV)
+    out = (torch.empty_like(t["q"]), torch.empty(Hq, S, dtype=torch.float32, device=DEV))
+    copy = torch.cuda.Stream()
+    args = (t["q"], t["k"], t["v"], ks, vs, bits, bl, 64, 1, copy)
+    mb.fwd_staged(*args, out=out, ws=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        mb.fwd_staged(*args, out=out, ws=ws)
+    for _ in range(3):
+        t["k"].neg_(); t["v"].mul_(0.5)
+        ks.fill_(float("nan")); vs.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        o, lse = out[0].clone(), out[1].clone()
+        o2, lse2 = mb.fwd_staged(*args)
+        assert torch.equal(o, o2) and torch.equal(lse, lse2)
+
+
 def test_window_touches_only_its_heads():
     """Heads outside the window are neither read (NaN there is harmless) nor
     written (sentinel survives); windows in any order, plan reused."""
