@@ -8,14 +8,15 @@
 //            precede it, more by a bitonic sort of (W, index) keys, in registers up
 //            to 1024 blocks, else in LDS;
 //   phase 2  wavefront 0 runs the greedy loop over the ranks held SORTED by (load,
-//            rank), SLOTS per lane: a block goes to the first, whose grown key is
-//            re-inserted by one median per key (see greedy_sorted);
+//            rank): 8 to 64 ranks receive a block each at a time and are sorted again
+//            (see greedy_batches); else, SLOTS ranks per lane, a block goes to the first, whose
+//            grown key is re-inserted by one median per key (see greedy_sorted);
 //   phase 3  per-rank CSR lists in ascending block index: every wavefront takes a
 //            stretch of blocks, finds equal ranks among 64 of them by ballots and
 //            counts with a histogram of its own.
 //
-// Bound by the latency of the loop, which takes the blocks one by one.  Measured, 8 ranks:
-// 512 blocks 126 -> 20 us, 1024 blocks 259 -> 33 us against a loop that found a
+// Bound by the latency of the loop.  Measured, 8 ranks:
+// 512 blocks 126 -> 17 us, 1024 blocks 259 -> 28 us against a loop that found a
 // block's place by a ballot and scalar arithmetic, an order counted over all pairs
 // of blocks (34 us of the 259) and lists counted the same way.
 // Up to 64 blocks are the work of a single wavefront, which meets no other at barriers: 8
@@ -121,7 +122,7 @@ struct Key32 {
         return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130 /* wave_shl:1 */, 0xf, 0xf, true);
     }
 };
-// the same for at most 16 ranks: the first row of 16 lanes holds their keys, and there a
+// the same for a few ranks: the first row of 16 lanes holds their keys, and there a
 // lane's value reaches the others without a detour through a scalar register
 struct Key32Row : Key32 {
     static constexpr int kLanes = 16;
@@ -240,6 +241,155 @@ __device__ __forceinline__ void greedy_sorted(uint64_t* entries, int32_t nB, int
             const uint64_t v = K::value(key[s]);
             load[v & mask] = base + (v >> bits);
         }
+}
+
+// Keys into descending order over the first NL lanes, by merges that first compare mirrored places:
+// the lower place of a pair always keeps the larger key, and one median with all ones or with 0
+// takes it (two instructions and their wait states per step).
+struct LaneSort {
+    uint32_t keep[6];                                  // bit i of the lane clear: all ones, else 0
+    __device__ __forceinline__ explicit LaneSort(int lane) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) keep[i] = (lane >> i) & 1 ? 0u : ~0u;
+    }
+    template <int CTRL>
+    __device__ static __forceinline__ uint32_t dpp(uint32_t v) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+    }
+    // the key of lane ^ J
+    template <int J>
+    __device__ static __forceinline__ uint32_t across(uint32_t v) {
+        if constexpr (J == 1) return dpp<0xB1>(v);     // quad_perm 1,0,3,2
+        else if constexpr (J == 2) return dpp<0x4E>(v);   // quad_perm 2,3,0,1
+        else if constexpr (J == 3) return dpp<0x1B>(v);   // quad_perm 3,2,1,0
+        else if constexpr (J == 4) {                   // row_shl:4 into the even banks, row_shr:4 into the odd ones
+            const int up = __builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xf, 0x5, false);
+            return (uint32_t)__builtin_amdgcn_update_dpp(up, (int)v, 0x114, 0xf, 0xa, false);
+        }
+        else if constexpr (J == 7) return dpp<0x141>(v);  // row_half_mirror
+        else if constexpr (J == 8) return dpp<0x128>(v);  // row_ror:8
+        else if constexpr (J == 15) return dpp<0x140>(v); // row_mirror
+        else return (uint32_t)__shfl_xor((int)v, J);
+    }
+    template <int J, int BIT>
+    __device__ __forceinline__ uint32_t exchange(uint32_t v) const {
+        return Key32::between(v, across<J>(v), keep[BIT]);
+    }
+    template <int NL>
+    __device__ __forceinline__ uint32_t descending(uint32_t v) const {
+        if constexpr (NL >= 2) v = exchange<1, 0>(v);
+        if constexpr (NL >= 4) { v = exchange<3, 1>(v); v = exchange<1, 0>(v); }
+        if constexpr (NL >= 8) { v = exchange<7, 2>(v); v = exchange<2, 1>(v); v = exchange<1, 0>(v); }
+        if constexpr (NL >= 16) {
+            v = exchange<15, 3>(v); v = exchange<4, 2>(v); v = exchange<2, 1>(v); v = exchange<1, 0>(v);
+        }
+        if constexpr (NL >= 32) {
+            v = exchange<31, 4>(v); v = exchange<8, 3>(v); v = exchange<4, 2>(v); v = exchange<2, 1>(v);
+            v = exchange<1, 0>(v);
+        }
+        if constexpr (NL >= 64) {
+            v = exchange<63, 5>(v); v = exchange<16, 4>(v); v = exchange<8, 3>(v); v = exchange<4, 2>(v);
+            v = exchange<2, 1>(v); v = exchange<1, 0>(v);
+        }
+        return v;
+    }
+};
+
+// The greedy loop for up to NL ranks, one sorted key per lane, `width` blocks at a time (P at first).
+// Block i of a batch goes to the rank at place i if no rank served before it in the batch, with its
+// block added, comes before that rank: which holds where every grown key comes behind the last key that
+// the batch uses, as it does once the loads differ by less than a workload (all batches but a few
+// of a plan).  Then all keys grow at once and are sorted again.  Where it does not hold, a batch
+// serves the ranks that come before all grown keys; where these are less than kNarrow, kAlone
+// blocks are given out one by one.  After either, P at a time are tried again.
+// `apart`: blocks between two moves of the base (see greedy_sorted).  `spare`: two entries
+// that nobody reads, the first 0 in its high word.
+// A batch takes about 140 ns with 8 ranks, 190 with 16, 470 with 64, most of it a sort's chain of 6, 10
+// or 21 steps; one by one a block takes 22.  1024 blocks (whole kernel): 8 ranks 33 -> 28 us,
+// 16 ranks 33 -> 22, 64 ranks 33 -> 18; one block as large as a quarter of the rest 33 -> 32, 25,
+// 20.  With 6 ranks both take 33, with 4 batches take 36.  96 blocks of sizes between 2^7 and 2^20,
+// where half of the batches fail, 8.8 -> 9.0 us on 8 ranks, 9.8 on 16.
+constexpr int kBatchRanks = 8, kNarrow = 4, kAlone = 64;
+template <int NL>
+__device__ __forceinline__ void greedy_batches(uint64_t* entries, int32_t nB, int32_t P, int bits, int apart,
+                                               int spare, int lane, uint64_t* __restrict__ load) {
+    const LaneSort sort(lane);
+    uint32_t* const high = (uint32_t*)entries + 1;
+    uint32_t key = lane < P ? Key32::of((uint32_t)lane) : 0u;
+    uint64_t base = 0;
+    auto lane_key = [](uint32_t v, int l) __attribute__((always_inline)) {
+        return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+    };
+    auto move_base = [&]() __attribute__((always_inline)) {
+        const uint32_t least = (uint32_t)(Key32::value(lane_key(key, 0)) >> bits);
+        base += least;
+        key += key != 0u ? least << bits : 0u;
+    };
+    int t = 0, width = P, hold = 0;
+    while (t < nB) {
+        width = min(width, nB - t);
+        // a lane past the width reads a 0 and writes where nobody reads
+        const bool in = lane < width;
+        int from = in ? 2 * (t + lane) : 2 * spare, to = in ? from : 2 * spare + 2;
+        const int by = in ? 2 * width : 0;
+        const uint32_t passes = lane < width - 1 ? 0u : ~0u;
+        uint32_t w = high[from], front = 0;
+        bool whole = true;
+        for (;;) {
+            move_base();
+            const int upto = min(nB, t + max(apart, width));
+            do {
+                from += by;
+                const uint32_t w_next = high[from];    // (zeros follow the last block)
+                const uint32_t grown = key - w;
+                const uint32_t last = lane_key(key, width - 1);
+                uint32_t sorted = sort.descending<NL>(grown);
+                asm volatile("" : "+v"(sorted));       // beside the test, not behind its branch
+                whole = !__any(grown >= (last | passes));
+                if (__builtin_expect(!whole, 0)) {
+                    front = lane_key(sorted, 0);
+                    break;
+                }
+                high[to] = key;
+                to += by;
+                key = sorted;
+                w = w_next;
+                t += width;
+            } while (t + width <= upto);
+            // (after some stretches of less than the whole width that may do again)
+            if (!whole || t + width > nB || (width < P && --hold < 0)) break;
+        }
+        if (whole) {
+            width = P;
+            continue;
+        }
+        // the keys before all grown ones may be served at once
+        const int n = __popcll(__ballot(key > front));
+        hold = 2 * n >= P ? 4 : 0;
+        width = n;
+        if (n >= kNarrow) continue;
+        width = P;
+        for (int c = 0; c < kAlone && t < nB; c += kSteps, t += kSteps) {
+            move_base();
+            uint32_t head = lane_key(key, 0), second = lane_key(key, 1), got[kSteps], wl[kSteps];
+#pragma unroll
+            for (int v = 0; v < kSteps; ++v) wl[v] = high[2 * (t + v)];
+#pragma unroll
+            for (int v = 0; v < kSteps; ++v) {
+                got[v] = head;
+                const uint32_t x = head - wl[v];
+                head = max(second, x);
+                key = Key32::between(Key32::above(key), key, x);
+                second = lane_key(key, 1);
+            }
+#pragma unroll
+            for (int v = 0; v < kSteps; ++v) high[2 * (t + v)] = got[v];
+        }
+    }
+    if (lane < P) {
+        const uint64_t v = Key32::value(key);
+        load[v & ((1u << bits) - 1u)] = base + (v >> bits);
+    }
 }
 
 // the value of lane `u`, wave-uniform
@@ -461,7 +611,9 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
     constexpr bool kOne = kWaves == 1;                 // at most kBalCounted blocks
     constexpr int kLds = kOne ? 4 * kWave : MMATTN_MAX_BLOCKS;
     constexpr int kRobAt = kOne ? 2 * kWave : kBalRobAt, kHistAt = kOne ? 3 * kWave : kBalHistAt;
-    __shared__ __attribute__((aligned(16))) uint64_t lds[kLds];
+    // past the keys: zeros that a batch may read ahead and kSteps entries that steps may write
+    constexpr int kPast = kWave + kSteps, kSpare = kLds + kPast;
+    __shared__ __attribute__((aligned(16))) uint64_t lds[kSpare + 2];
     __shared__ uint64_t sum_s[kWaves], max_s[kWaves];
     __shared__ int32_t scan_s[kWaves];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -478,6 +630,8 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
     uint64_t sum = 0, most = 0;
     int n2 = 2 * kWave;
     while (n2 < nB) n2 <<= 1;
+    for (int i = tid; i < kPast; i += THREADS) keys[n2 + i] = 0;
+    if (tid == 0) keys[kSpare] = 0;
     for (int b = tid; b < n2; b += THREADS) {
         const uint64_t w = b < nB ? W[b] : 0;
         sum += w;
@@ -548,13 +702,19 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
         if (wave == 0) {
             // one move of the base per 64 blocks where 32 bits allow it
             const int rebase_mask = fits32_for(64) ? 63 : kSteps - 1;
-            if (SLOTS == 1 && fits32 && P <= Key32Row::kLanes) {
-                if (lane < Key32Row::kLanes)
-                    greedy_sorted<Key32Row, SLOTS>(keys, nB, P, bits, rebase_mask, lane, load);
-            } else if (fits32) {
-                greedy_sorted<Key32, SLOTS>(keys, nB, P, bits, rebase_mask, lane, load);
-            } else {
+            const int apart = rebase_mask + 1;
+            if (!fits32) {
                 greedy_sorted<Key52, SLOTS>(keys, nB, P, bits, rebase_mask, lane, load);
+            } else if constexpr (SLOTS > 1) {
+                greedy_sorted<Key32, SLOTS>(keys, nB, P, bits, rebase_mask, lane, load);
+            } else if (P >= kBatchRanks) {
+                const int apart = rebase_mask + 1;
+                if (P <= 8) greedy_batches<8>(keys, nB, P, bits, apart, kSpare, lane, load);
+                else if (P <= 16) greedy_batches<16>(keys, nB, P, bits, apart, kSpare, lane, load);
+                else if (P <= 32) greedy_batches<32>(keys, nB, P, bits, apart, kSpare, lane, load);
+                else greedy_batches<64>(keys, nB, P, bits, apart, kSpare, lane, load);
+            } else if (lane < Key32Row::kLanes) {
+                greedy_sorted<Key32Row, SLOTS>(keys, nB, P, bits, rebase_mask, lane, load);
             }
         }
         __syncthreads();

@@ -343,6 +343,23 @@ def test_balance_few_blocks(nB):
     check_balance([0] * nB, max(1, nB // 2))
 
 
+@pytest.mark.parametrize("P", [2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64])
+@pytest.mark.parametrize("nB", [66, 129, 200, 512, 1024])
+def test_balance_batches(nB, P):
+    """Blocks given out P at a time: every number of lanes that a sort covers and its edges, last
+    batches of any length, and batches that go one by one: a block as large as all others, groups of
+    unlike sizes, ties, blocks without work; keys that need their base moved every 8 blocks."""
+    rng = np.random.default_rng(100 * nB + P)
+    ramp = np.arange(nB, 0, -1) * 16384
+    giant = ramp.copy(); giant[0] = ramp.sum()
+    bits = max(1, (P - 1).bit_length())
+    for W in (ramp, giant, np.where(np.arange(nB) % 3 == 0, 10 ** 6, 7), np.full(nB, 12345),
+              rng.integers(0, 4, size=nB), 1 + rng.integers(0, 2 ** 20, size=nB) // (1 + rng.integers(0, 999, size=nB)),
+              rng.integers(0, (2 ** (32 - bits) - 2) // (2 + 7 // P), size=nB)):
+        check_balance(rng.permutation(W).tolist(), P)
+
+
+
 @pytest.mark.parametrize("c", [1, 2, 3, 4, 5])
 def test_balance_workloads_end_to_end(c):
     """encode -> tile map -> balance, all on the GPU, against the oracle chain."""
