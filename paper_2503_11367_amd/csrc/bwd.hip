@@ -1236,15 +1236,29 @@ struct BwdLayout {
 
 // Split the query heads of a (k-tile, KV head) unit over several workgroups only
 // when the units alone cannot fill the chip a few times over (256 resident
-// workgroups).
-static KvChunking kv_chunking(int32_t nk_b, int32_t Hq, int32_t Hkv) {
+// workgroups).  Lists too short for slices (kFewRowTiles) are split less: each chunk's workgroup
+// stores and the reduction reads back 256 KiB of fp32 partial sums at head_dim 128, as long as
+// seven of its steps (64 rows of a head) take.  One and a quarter workgroups per CU are enough
+// there, or hardly one of no more than 32 steps; at head_dim 64, where both a step and the partial sums
+// are half as long and three workgroups share a CU, twice that, of half the steps.  Measured,
+// whole calls, us, 1024 workgroups / so: 256 rows, 5888 keys, 32 / 4 heads 200 / 157, 24 / 8
+// heads 172 / 123; 128 rows, 8192 keys, 32 / 4 heads 148 / 105, 16384 keys, 12 / 3 heads
+// 166 / 96; 768 rows, 5888 packed keys, 64 / 16 heads 281 / 216; head_dim 64, 128 rows, 8192 keys,
+// 64 / 8 heads 137 / 114, 640 rows, 512 units 179 / 179.  Over 214 such shares 14 % less on the mean at
+// head_dim 128, 5 % at 64, none more than 3 % more.  Longer lists keep 1024: half of that is 2 %
+// less on the mean, but 8 % more where few of the lists are long.
+constexpr int32_t kFewRowTiles = 16;
+static KvChunking kv_chunking(int32_t nk_b, int32_t nq_b, int32_t Hq, int32_t Hkv, int32_t D) {
     const int64_t units = (int64_t)nk_b * Hkv;
     const int32_t rep = Hq / Hkv;
-    int32_t cmax = 1;                  // smallest divisor of rep that yields >= 1024 workgroups, else rep
+    const bool brief = nq_b < kFewRowTiles;
+    const int64_t enough = !brief ? 1024 : D == 128 ? 320 : 640;
+    const int32_t steps = D == 128 ? 32 : 16;
+    int32_t cmax = 1;                  // smallest divisor of rep that yields enough workgroups, else rep
     for (int32_t c = 1; c <= rep; ++c) {
         if (rep % c) continue;
         cmax = c;
-        if (units * c >= 1024) break;
+        if (units * c >= enough || (brief && units * c >= 224 && rep / c * nq_b <= steps)) break;
     }
     return KvChunking{cmax, rep / cmax};
 }
@@ -1257,7 +1271,7 @@ static BwdLayout bwd_layout(int64_t S, int64_t n_loc, int32_t n_blocks, int32_t 
     L.nq_b = (int32_t)((n_loc + kKvBM - 1) / kKvBM);
     L.nk_b = (int32_t)(S / kKvBN);
     L.n_pad = (int64_t)L.nq_a * kDqBM;
-    L.ch = kv_chunking(L.nk_b, Hq, Hkv);
+    L.ch = kv_chunking(L.nk_b, L.nq_b, Hq, Hkv, D);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes, 256); return o; };
     L.err = take(256);
@@ -1277,7 +1291,7 @@ static BwdLayout bwd_layout(int64_t S, int64_t n_loc, int32_t n_blocks, int32_t 
     L.korder = take((size_t)L.nk_b * 4);
     // list slices of the key-outer pass: none for short lists; else as many extra slices as
     // bring the launch to about 2048 workgroups, at most 256
-    L.n_extra = L.nq_b >= 16 ? std::min(256, 2048 / (Hkv * L.ch.cmax)) : 0;
+    L.n_extra = L.nq_b >= kFewRowTiles ? std::min(256, 2048 / (Hkv * L.ch.cmax)) : 0;
     L.slicing = take(kSliceInts * 4);
     L.pbase = take((size_t)L.nk_b * 4);
     L.extra = take((size_t)std::max(L.n_extra, 1) * 8);

@@ -153,6 +153,20 @@ def test_random_layouts(seed, D):
     run_case(lay, blocks, block, Hq=4, Hkv=2, D=D, seed=20 + seed)
 
 
+@pytest.mark.parametrize("S,block,n,Hq,Hkv,D", [
+    (1792, 16, 8, 64, 16, 128),      # 224 (key tile, KV head) units, 8 steps each: heads together
+    (1664, 16, 13, 64, 16, 128),     # 208: two workgroups for a unit's four heads
+    (2560, 80, 7, 32, 16, 128),      # 320, a last row tile of 48: heads together
+    (2560, 80, 8, 32, 16, 64),       # the same at head_dim 64: two workgroups
+    (1920, 240, 4, 24, 8, 64),       # 15 row tiles, the most of a short list; three workgroups
+])
+def test_short_lists_head_chunks(S, block, n, Hq, Hkv, D):
+    """Few rows against many keys: how many workgroups share a unit's query heads."""
+    lay = wl.layout_random(75, S=S, n_samples=2, max_spans=4, deny_prob=0.3)
+    blocks = np.random.default_rng(75).choice(S // block, size=n, replace=False).tolist()
+    run_case(lay, blocks, block, Hq, Hkv, D, seed=76)
+
+
 @pytest.mark.parametrize("block", [48, 80, 240])
 def test_block_size_not_a_power_of_two(block):
     """Blocks of 48, 80 and 240 tokens (multiples of 16 that divide S = 1920): the
