@@ -44,7 +44,7 @@ bool on_this_gpu(const void* p) {
 // How many of the windows of KV heads the staged forward moves and attends at once: all of them
 // where the attention is a single small kernel (16 heads of 128 tokens by four 119 -> 40 us), else as
 // many as make kStageBytes of K and V and kStageTiles (128-row tile, query head) work items.  A
-// smaller transfer is over sooner (32 MiB in 13 us) than the hand-over to the attention and its
+// smaller transfer is over sooner (32 MiB in 11 us) than the hand-over to the attention and its
 // launches take, and an attention of fewer than four pairs of heads per CU leaves CUs idle at its end
 // or has its lists cut.  Measured, us, windows one by one / with half of either limit / so / all at
 // once: 8192 tokens, 32 / 8 heads by one 954 / 613 / 566 / 566; a rank of four of 32768, 32 / 8 by

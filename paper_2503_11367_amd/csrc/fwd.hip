@@ -111,7 +111,7 @@ key_norm_kernel(const ushort_t* __restrict__ K, int64_t S, int32_t Hkv_s, float*
 // One stage of the staged forward: K and V of some heads move to the buffers that the attention
 // reads, and the key norms are formed on the way.  Grid (kNormChunks, heads, 2): K first, then V;
 // a tensor that is in place already is not written, and without `knorm` there are no norms.
-// Bound by memory: 67 MB to and fro in 27 us.  Against two strided copies of the runtime and a
+// Bound by memory: 134 MB read and as much written in 46 us, 5.9 TB/s.  Against two strided copies of the runtime and a
 // pass for the norms behind them, one of two windows: a rank of four of 32768 tokens, 32 / 8 heads
 // 2091 -> 2056 us; all heads at once 2005 -> 1972.
 template <int D>

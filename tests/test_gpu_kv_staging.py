@@ -121,7 +121,7 @@ def test_staged_in_place():
     (16384, 16, 16, 64, 4),      # 64 MiB, 2048 pairs: everything at once
     (512, 16, 16, 128, 1),       # one kernel after one transfer
 ])
-@pytest.mark.parametrize("in_place", ["neither", "k", "v"])
+@pytest.mark.parametrize("in_place", ["neither", "k", "v", "both"])
 def test_staged_windows_together(S, Hq, Hkv, D, hps, in_place):
     """Windows that travel together, their last group smaller; K or V already in its place."""
     lay = wl.layout_random(154, S=S, n_samples=3, max_spans=5, deny_prob=0.3)
@@ -130,8 +130,8 @@ def test_staged_windows_together(S, Hq, Hkv, D, hps, in_place):
     t = make_tensors(414, S, S, Hq, Hkv, D)
     bits = gpu_bits(lay)
     bl = torch.tensor(blocks, dtype=torch.int32, device=DEV)
-    ks = t["k"] if in_place == "k" else torch.full_like(t["k"], float("nan"))
-    vs = t["v"] if in_place == "v" else torch.full_like(t["v"], float("nan"))
+    ks = t["k"] if in_place in ("k", "both") else torch.full_like(t["k"], float("nan"))
+    vs = t["v"] if in_place in ("v", "both") else torch.full_like(t["v"], float("nan"))
     k0, v0 = t["k"].clone(), t["v"].clone()
     o, lse = mb.fwd_staged(t["q"], t["k"], t["v"], ks, vs, bits, bl, 128, hps, torch.cuda.Stream())
     torch.cuda.synchronize()
