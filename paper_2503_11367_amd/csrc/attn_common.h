@@ -169,6 +169,11 @@ __device__ __forceinline__ void wait_vmcnt() {
 // the probabilities are taken relative to before the shift follows it; inside
 // this band probabilities stay within 2^+-kShiftSlack, harmless in fp32/bf16
 constexpr float kShiftSlack = 64.0f;
+// exponent of a partial sum of probabilities relative to `shift`: a sum is between 2^-64 and 2^64 (times
+// the number of keys), so that shifts alone do not tell which of two partial sums counts
+__device__ __forceinline__ float sum_exponent(float shift, float sum) {
+    return shift + (float)__builtin_amdgcn_frexp_expf(sum);
+}
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;

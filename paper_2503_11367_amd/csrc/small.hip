@@ -503,10 +503,14 @@ fwd_small_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
         sm.ml[wave][li][1] = l_run;
     }
     __syncthreads();
+    // Relative to the largest sum, not to the largest shift: a wavefront whose shift stayed at 0 may hold
+    // sums of 2^-64 beside others of 2^64 at a shift of -128, whose weight against 0 would be flushed.  A
+    // whole number, so that shifts of 0 are weighted exactly.
     float m = -INFINITY, den = 0.f, wt[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w)
-        if (sm.ml[w][li][1] != 0.f) m = fmaxf(m, sm.ml[w][li][0]);
+        if (sm.ml[w][li][1] != 0.f) m = fmaxf(m, sum_exponent(sm.ml[w][li][0], sm.ml[w][li][1]));
+    m = __builtin_rintf(m);
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         const float l = sm.ml[w][li][1];

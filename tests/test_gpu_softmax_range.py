@@ -162,3 +162,40 @@ def test_offsets_inside_the_untracked_band():
     whole(222, 5, prepare=down, lse_far=25.0)
     whole(223, 11, prepare=both, lse_far=25.0)
     check(LAY_SPLIT(), list(range(0, 32, 3)), 128, 4, 2, 128, seed=224, prepare=both, lse_far=25.0)
+
+
+# Scores in base-2 units that depend on the key alone: the mass lies at kNear (reached from the shift's
+# start at 0, where it stays) and kLate; a partial sum that begins at kEarly moves its shift there and
+# keeps it, for kLate is less than 64 away, so that it holds sums of 2^63.
+kNear, kEarly, kLate = -62.0, -129.5, -66.25
+
+
+def far_apart(t, D, of_key):
+    """Every score with key j as near to of_key[j] as bf16 keys come; the shifts move as above."""
+    q0 = 128.0 if D == 128 else 64.0
+    unit = q0 / np.sqrt(D) * 1.4426950408889634
+    t["q_bits"] = np.zeros_like(t["q_bits"])
+    set_feature(t, "q", q0)
+    k0 = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits((of_key / unit).astype(np.float32)))
+    set_feature(t, "k", k0)
+    near, early, late = (float(x) * unit for x in (k0[of_key == kNear][0], k0[of_key == kEarly][0], k0[of_key == kLate][0]))
+    assert -64 < near < -61 and early < -127 and 60 < late - early < 64 and late > near - 5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S", [256, 512])
+def test_wavefronts_whose_shifts_end_far_apart(S, D):
+    """The small forward's wavefronts walk units of 32 keys, every fourth (256 keys) or eighth each.  The
+    first stays at shift 0 with sums of 2^-57, the others, with a tenth or more of the mass, hold sums of 2^69
+    at a shift of -129.5: their weight against shift 0 is below the smallest normal number."""
+    n = S // 64                                              # wavefronts
+    unit = np.arange(S) // 32
+    of_key = np.where(unit % n == 0, kNear, np.where(unit < n, kEarly, kLate))
+    lay = wl.Layout(S, [(0, S, 1)], [0, S])
+    t = make_tensors(231, 64, S, 2, 1, D)
+    far_apart(t, D, of_key)
+    o, lse = mb.fwd(t["q"], t["k"], t["v"], gpu_bits(lay), torch.tensor([1], dtype=torch.int32, device=DEV), 64)
+    f = fields(lay)
+    o_ref, lse_ref = oa.forward(f64(t["q_bits"]), f64(t["k_bits"]), f64(t["v_bits"]), oa.rows_of_blocks([1], 64), f[0], f[1], f[2])
+    err = max_abs(bf16_to_f64(o), o_ref), rel_l2(bf16_to_f64(o), o_ref), max_abs(lse.cpu().numpy().astype(np.float64), lse_ref)
+    assert err[0] < TOL_MAX and err[1] < TOL_L2 and err[2] < TOL_LSE, err
