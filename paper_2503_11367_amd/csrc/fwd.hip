@@ -809,7 +809,8 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
 // Aggregation of the slices of split q-tiles (paper section 3.2.2: partial results of
 // the sub-blocks are combined by one more kernel): with shift m_c, row sum l_c and
 // unnormalised output o_c per slice, O = sum_c o_c 2^(m_c - m) / sum_c l_c 2^(m_c - m)
-// for m = max m_c.  One thread per (row, head, 4 head-dim values).
+// for m = the largest exponent of an l_c 2^(m_c), a whole number (m = max m_c would flush the weight of a
+// slice with l_c = 2^63 at -129 beside one of 2^-62 at 0).  One thread per (row, head, 4 head-dim values).
 __global__ void __launch_bounds__(256)
 fwd_combine_kernel(TilePlan plan, FwdSplit split, int64_t n_loc, int32_t Hq, int32_t Hq_s, int32_t D,
                    const int32_t* __restrict__ err, const float* __restrict__ Opart,
@@ -845,8 +846,9 @@ fwd_combine_kernel(TilePlan plan, FwdSplit split, int64_t n_loc, int32_t Hq, int
         fetch_ml(c0, ml);
 #pragma unroll
         for (int u = 0; u < kBatch; ++u)
-            if (ml[u][1] > 0.f) m = fmaxf(m, ml[u][0]);
+            if (ml[u][1] > 0.f) m = fmaxf(m, sum_exponent(ml[u][0], ml[u][1]));
     }
+    m = __builtin_rintf(m);
     floatx4 num = {0.f, 0.f, 0.f, 0.f};
     float den = 0.f;
     for (int c0 = 0; c0 < nchunk; c0 += kBatch) {

@@ -199,3 +199,25 @@ def test_wavefronts_whose_shifts_end_far_apart(S, D):
     o_ref, lse_ref = oa.forward(f64(t["q_bits"]), f64(t["k_bits"]), f64(t["v_bits"]), oa.rows_of_blocks([1], 64), f[0], f[1], f[2])
     err = max_abs(bf16_to_f64(o), o_ref), rel_l2(bf16_to_f64(o), o_ref), max_abs(lse.cpu().numpy().astype(np.float64), lse_ref)
     assert err[0] < TOL_MAX and err[1] < TOL_L2 and err[2] < TOL_LSE, err
+
+
+@pytest.mark.parametrize("S", [4096, 8192])
+@pytest.mark.parametrize("D", [64, 128])
+def test_slices_whose_shifts_end_far_apart(S, D):
+    """The same in the list slices of the general path (mmattn_fwd_heads takes it at any size): the keys of
+    the first eight tiles lie near, of the others two tiles early and two late in turn, so that a slice of
+    any length that begins with an early tile keeps its shift."""
+    tile = np.arange(S) // 64
+    of_key = np.where(tile < 8, kNear, np.where(tile // 2 % 2 == 0, kEarly, kLate))
+    lay = wl.Layout(S, [(0, S, 1)], [0, S])
+    blocks = [1, 3, 4]
+    t = make_tensors(232, 384, S, 2, 1, D)
+    far_apart(t, D, of_key)
+    bits, bl = gpu_bits(lay), torch.tensor(blocks, dtype=torch.int32, device=DEV)
+    ws = torch.empty(mb.workspace_size(mb.OP_FWD_HEADS, S, 3, 128, 2, 1, D), dtype=torch.uint8, device=DEV)
+    o, lse = torch.empty_like(t["q"]), torch.empty((2, 384), dtype=torch.float32, device=DEV)
+    mb.fwd_heads(t["q"], t["k"], t["v"], bits, bl, 128, 0, 1, False, (o, lse), ws)
+    f = fields(lay)
+    o_ref, lse_ref = oa.forward(f64(t["q_bits"]), f64(t["k_bits"]), f64(t["v_bits"]), oa.rows_of_blocks(blocks, 128), f[0], f[1], f[2])
+    err = max_abs(bf16_to_f64(o), o_ref), rel_l2(bf16_to_f64(o), o_ref), max_abs(lse.cpu().numpy().astype(np.float64), lse_ref)
+    assert err[0] < TOL_MAX and err[1] < TOL_L2 and err[2] < TOL_LSE, err
