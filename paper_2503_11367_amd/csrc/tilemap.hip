@@ -55,10 +55,17 @@ int launch_tile_map(const uint64_t* d_bits, int64_t S, const int32_t* d_blocks, 
     TileMapJobs jobs;
     jobs.j[0] = jobs.j[1] = tile_map_job(S, n_rows, tq, tk, d_cls, d_cnt);
     const bool runs = tile_map_by_runs(jobs);
-    const auto kernel = S > kTmNarrow    ? tile_map_kernel<kTmWide>
-                        : tq <= kWave     ? (runs ? tile_map_kernel<kTmByRuns | kTmWhole | kTmRows1> : tile_map_kernel<kTmRows1>)
-                        : tq <= 2 * kWave ? (runs ? tile_map_kernel<kTmByRuns | kTmWhole | kTmRows2> : tile_map_kernel<kTmRows2>)
-                                          : (runs ? tile_map_kernel<kTmByRuns | kTmWhole | kTmRows4> : tile_map_kernel<kTmRows4>);
+    // (kTmWhole: not with a list of blocks)
+    auto for_rows = [&](auto ROWS_) {
+        constexpr int ROWS = decltype(ROWS_)::value;
+        return !runs      ? tile_map_kernel<ROWS>
+               : d_blocks ? tile_map_kernel<kTmByRuns | ROWS>
+                          : tile_map_kernel<kTmByRuns | kTmWhole | ROWS>;
+    };
+    const auto kernel = S > kTmNarrow     ? tile_map_kernel<kTmWide>
+                        : tq <= kWave     ? for_rows(std::integral_constant<int, kTmRows1>{})
+                        : tq <= 2 * kWave ? for_rows(std::integral_constant<int, kTmRows2>{})
+                                          : for_rows(std::integral_constant<int, kTmRows4>{});
     hipLaunchKernelGGL(kernel, dim3(jobs.j[0].gx * jobs.j[0].gy), dim3(kTmThreads), 0, st, d_bits, d_blocks, block,
                        d_blocks ? S / block : (int64_t)0, n_rows, jobs);
     MM_LAUNCH_CHECK();

@@ -233,6 +233,37 @@ def test_tile_map_positions_beyond_30_bits():
         assert (k[:-1] == (0 if before[r].sum() == 0 else 1 if before[r].sum() == n * tk else 2)).all()
 
 
+@pytest.mark.parametrize("tq,tk", [(16, 16), (96, 32), (256, 16)])
+def test_tile_map_of_a_share(tq, tk):
+    """The library's own entry with a list of blocks, on maps large enough for tiles cut into runs
+    (more than 4096 pairs, more than 16384 of 64 x 64): q-tiles across blocks in any order."""
+    import ctypes
+    from oracle import mask as om
+    S, block = 8192, 48 if tq == 96 else 16
+    S -= S % (block * 128)
+    lay = wl.layout_random(95, S=S, n_samples=3, max_spans=6, deny_prob=0.4)
+    blocks = np.random.default_rng(95).permutation(S // block)[: (S // block) * 3 // 4].astype(np.int32)
+    rows = (blocks[:, None].astype(np.int64) * block + np.arange(block)).reshape(-1)
+    n_q, n_k = -(-rows.size // tq), S // tk
+    assert n_q * n_k * -(-tq // 64) * -(-tk // 64) > 16384
+    cls = torch.full((n_q, n_k), 9, dtype=torch.uint8, device=DEV)
+    cnt = torch.full((n_q, n_k), -1, dtype=torch.int32, device=DEV)
+    f = mb.lib()._ZN2mm15launch_tile_mapEPKmlPKiiliiPhPjPmP12ihipStream_t
+    f.restype = ctypes.c_int
+    vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+    f.argtypes = [vp, i64, vp, i32, i64, i32, i32, vp, vp, vp, vp]
+    bits, bl = gpu_bits(lay), torch.from_numpy(blocks).to(DEV)
+    assert f(bits.data_ptr(), S, bl.data_ptr(), block, rows.size, tq, tk, cls.data_ptr(), cnt.data_ptr(), 0,
+             torch.cuda.current_stream().cuda_stream) == 0
+    fl = fields(lay)
+    got, kind = cnt.cpu().numpy().view(np.uint32), cls.cpu().numpy()
+    for i in range(n_q):
+        r = rows[i * tq:(i + 1) * tq]
+        want = om.visible(r, np.arange(S), fl[0], fl[1], fl[2], fl[3], fl[4]).reshape(r.size, n_k, tk).sum(axis=(0, 2))
+        assert np.array_equal(got[i], want), i
+        assert np.array_equal(kind[i], np.where(want == 0, 0, np.where(want == r.size * tk, 1, 2))), i
+
+
 def layouts_window():
     """Look-back windows: attention sinks plus a sliding window (the lambda
     pattern of section 5.5) in one sample and packed, window shorter and longer
