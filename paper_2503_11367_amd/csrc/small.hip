@@ -101,20 +101,19 @@ __device__ __forceinline__ uint32_t unit_class(bool any, bool all) {
 }
 
 // The active ones of `n` units into lds.list, by all wavefronts; returns how many.  A lane has a unit;
-// sees(unit, run, any, all) compares it with the workgroup's own tokens.
+// sees(unit, run, any, all) compares it with the workgroup's own tokens, which it reads from the
+// other lanes: all of them stay active (those past the end compare the last unit).
 template <int NW, class F>
 __device__ __forceinline__ int small_list(SmallPlanLds& lds, int n, int wave, int lane, F&& sees) {
     __syncthreads();
     int count = 0;
     for (int u0 = 0; u0 < n; u0 += kWave) {
-        const int u = u0 + lane;
-        uint32_t c = MMATTN_TILE_EMPTY;
-        if (u < n) {
-            const SmallRun r = lds.run[u];
-            bool any = false, all = true;
-            sees(u, r, any, all);
-            c = r.x & kSmallMixed ? r.x & 3u : unit_class(any, all);
-        }
+        const int u = min(u0 + lane, n - 1);
+        const SmallRun r = lds.run[u];
+        bool any = false, all = true;
+        sees(u, r, any, all);
+        uint32_t c = r.x & kSmallMixed ? r.x & 3u : unit_class(any, all);
+        if (u0 + lane >= n) c = MMATTN_TILE_EMPTY;
         const uint64_t m = __ballot(c != MMATTN_TILE_EMPTY);
         const int at = count + __popcll(m & ((1ull << lane) - 1));
         if (c != MMATTN_TILE_EMPTY && at % NW == wave)

@@ -30,6 +30,7 @@ def spread(n, take, seed=0):
 # (layout, blocks, block, Hq, Hkv, D)
 CASES = {
     "one block of 16 rows": (wl.Layout(128, [(20, 50, 1)], [0, 128]), [5], 16, 1, 1, 64),
+    "four units, runs in lanes beyond them": (wl.Layout(128, [(10, 6, 1), (40, 9, 2), (88, 25, 1)], [0, 70, 128]), [6, 1, 3, 7, 0, 5], 16, 2, 1, 64),
     "all of 128 tokens": (wl.Layout(128, [], [0, 100, 128]), [0], 128, 3, 1, 128),
     "more workgroups than CUs at 128 tokens": (wl.Layout(128, [], [0, 128]), [1, 0], 64, 96, 12, 64),
     "units of two runs": (wl.layout_random(201, S=640, n_samples=2, max_spans=4), spread(40, 23), 16, 4, 2, 128),
