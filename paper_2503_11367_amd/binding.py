@@ -124,10 +124,9 @@ def _span_array(spans, flags) -> ctypes.Array:
     arr = (Span * max(n, 1))()
     fl = [0] * n if flags is None else flags
     try:
-        if len(fl) >= n:
-            flat = [x for (st, ln, mod), f in zip(spans, fl) for x in (st, ln, mod, f)]
-            struct.pack_into("qqii" * n, arr, 0, *flat)
-            return arr
+        flat = [x for i, (st, ln, mod) in enumerate(spans) for x in (st, ln, mod, fl[i])]
+        struct.pack_into("qqii" * n, arr, 0, *flat)
+        return arr
     except (struct.error, TypeError):
         pass
     for i, (st, ln, mod) in enumerate(spans):

@@ -188,3 +188,29 @@ def test_current_stream_without_the_raw_handle(monkeypatch):
     monkeypatch.setattr(mb.torch.cuda, "is_initialized", lambda: False)
     assert mb._stream(None) == 77
     assert mb._stream(Stream) == 77 and mb._stream(5) == 5
+
+
+def test_span_list_packing():
+    """mask_encode's span list as one by one: lists longer than one packing call, values that need
+    converting or wrapping, flags in whatever answers flags[i]."""
+    import numpy as np
+    rng = np.random.default_rng(3)
+
+    def plain(spans, flags):
+        arr = (mb.Span * max(len(spans), 1))()
+        for i, (st, ln, mod) in enumerate(spans):
+            arr[i] = mb.Span(int(st), int(ln), int(mod), int(flags[i]) if flags is not None else 0)
+        return bytes(arr)
+
+    for n in (0, 1, 255, 256, 257, 1000):
+        spans = [tuple(int(x) for x in rng.integers(0, 1 << 31, 3)) for _ in range(n)]
+        flags = [int(x) for x in rng.integers(-(1 << 31), 1 << 31, n)]
+        for f in (None, flags, tuple(flags), np.array(flags), dict(enumerate(flags)), flags + [7]):
+            assert bytes(mb._span_array(spans, f)) == plain(spans, f), (n, type(f))
+        for odd in ((1.9, 2, 1), (np.int64(5), True, 2), ("7", 8, 1), (1, 2, 1 << 33), (0, 5, 1)):
+            assert bytes(mb._span_array(spans + [odd], None)) == plain(spans + [odd], None), odd
+        big = flags + [0x80000001]
+        assert bytes(mb._span_array(spans + [(1, 2, 1)], big)) == plain(spans + [(1, 2, 1)], big)
+    for bad in ([1], 5):
+        with pytest.raises((IndexError, TypeError)):
+            mb._span_array([(0, 1, 1), (4, 1, 1)], bad)
