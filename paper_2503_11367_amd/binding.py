@@ -117,15 +117,21 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
 
 
+# spans per packing call: Python keeps the compiled formats of the last hundred lengths, 128 bytes per span
+_SPANS_PACKED = 256
+
+
 def _span_array(spans, flags) -> ctypes.Array:
-    """The C array of a span list.  One packing call for all integers that fit (24 spans 17 -> 5 us,
+    """The C array of a span list.  Packed together where all integers fit (24 spans 17 -> 5 us,
     which the GPU would wait for); values that need converting or wrapping go one by one."""
     n = len(spans)
     arr = (Span * max(n, 1))()
     fl = [0] * n if flags is None else flags
     try:
         flat = [x for i, (st, ln, mod) in enumerate(spans) for x in (st, ln, mod, fl[i])]
-        struct.pack_into("qqii" * n, arr, 0, *flat)
+        for i in range(0, n, _SPANS_PACKED):
+            m = min(n - i, _SPANS_PACKED)
+            struct.pack_into("qqii" * m, arr, i * ctypes.sizeof(Span), *flat[4 * i:4 * (i + m)])
         return arr
     except (struct.error, TypeError):
         pass

@@ -214,3 +214,17 @@ def test_span_list_packing():
     for bad in ([1], 5):
         with pytest.raises((IndexError, TypeError)):
             mb._span_array([(0, 1, 1), (4, 1, 1)], bad)
+
+
+def test_span_list_packing_keeps_nothing_of_long_lists():
+    """Long lists of many different lengths: a compiled format of each would stay in the process (5 MB
+    for 40000 spans).  Formats of at most 256 spans, 100 of them: below 4 MB."""
+    import tracemalloc
+    tracemalloc.start()
+    try:
+        before = tracemalloc.get_traced_memory()[0]
+        for n in range(40000, 40010):
+            mb._span_array([(1, 2, 1)] * n, None)
+        assert tracemalloc.get_traced_memory()[0] - before < 4 << 20
+    finally:
+        tracemalloc.stop()
