@@ -43,6 +43,17 @@ def make_tensors(seed, n_loc, S, Hq, Hkv, D):
     return out
 
 
+def spy_workspace(op, S, n_blocks, block, Hq, Hkv, D):
+    """A workspace that tells afterwards which path an attention call took (general_path)."""
+    return torch.full((mb.workspace_size(op, S, n_blocks, block, Hq, Hkv, D),), 0xA5, dtype=torch.uint8, device=DEV)
+
+
+def general_path(ws):
+    """Whether the call left its checked block list behind the status block, as the general path does; the
+    single-launch kernels for small shares write nothing but the status."""
+    return bool((ws[256:260] != 0xA5).any())
+
+
 def f64(bits_u16):
     return wl.bf16_bits_to_f32(bits_u16).astype(np.float64)
 

@@ -12,27 +12,31 @@ from oracle import tilemap as ot
 from paper_2503_11367_amd import binding as mb
 from paper_2503_11367_amd import workloads as wl
 
-from gpu_util import (DEV, bf16_to_f64, f64, fields, gpu_bits, make_tensors, max_abs, rel_l2, windows)
+from gpu_util import (DEV, bf16_to_f64, f64, fields, general_path, gpu_bits, make_tensors, max_abs, rel_l2,
+                      spy_workspace, windows)
 
 pytestmark = pytest.mark.gpu
 
 TOL = 1e-2
 
 
-def gpu_fwd_bwd(lay, blocks, block, t):
+def gpu_fwd_bwd(lay, blocks, block, t, ws=None):
     bits = gpu_bits(lay)
     bl = torch.tensor(blocks, dtype=torch.int32, device=DEV)
     o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, bl, block)
-    dq, dk, dv = mb.bwd(t["q"], t["k"], t["v"], bits, bl, block, o, lse, t["do"])
+    dq, dk, dv = mb.bwd(t["q"], t["k"], t["v"], bits, bl, block, o, lse, t["do"], ws=ws)
     torch.cuda.synchronize()
     return o, lse, dq, dk, dv
 
 
-def run_case(lay, blocks, block, Hq, Hkv, D, seed):
+def run_case(lay, blocks, block, Hq, Hkv, D, seed, general=None):
+    """general: whether the backward is meant to take the general path (None: either)."""
     f = fields(lay)
     n_loc = len(blocks) * block
     t = make_tensors(seed, n_loc, lay.S, Hq, Hkv, D)
-    o, lse, dq, dk, dv = gpu_fwd_bwd(lay, blocks, block, t)
+    ws = spy_workspace(mb.OP_BWD, lay.S, len(blocks), block, Hq, Hkv, D)
+    o, lse, dq, dk, dv = gpu_fwd_bwd(lay, blocks, block, t, ws)
+    assert general is None or general_path(ws) == general
     rows = oa.rows_of_blocks(blocks, block)
     Q, K, V, dO = f64(t["q_bits"]), f64(t["k_bits"]), f64(t["v_bits"]), f64(t["do_bits"])
     dq_ref, dk_ref, dv_ref = oa.backward(Q, K, V, dO, rows, f[0], f[1], f[2], modality=f[3], attend=f[4],
@@ -70,10 +74,31 @@ def test_long_key_lists_cut_into_slices():
     """Sinks that every later row attends make one k-tile's list of query tiles
     far longer than the others: the key-outer pass cuts long lists into slices
     (separate workgroups, partial sums added in a fixed order).  Here the sink
-    tile has 64 entries and is cut into 8 slices, the band tiles into 2."""
-    run_case(wl.layout_lambda([4096], 32, 512), list(range(32)), 128, Hq=1, Hkv=1, D=64, seed=98)
+    tile has 66 entries and is cut into 9 slices, the band tiles into 2."""
+    run_case(wl.layout_lambda([4224], 32, 512), list(range(33)), 128, Hq=1, Hkv=1, D=64, seed=98, general=True)
     # a share that is not the whole sequence, two heads per group
-    run_case(wl.layout_lambda([2048, 2048], 8, 200), list(range(3, 32)), 128, Hq=2, Hkv=1, D=128, seed=99)
+    run_case(wl.layout_lambda([2048, 2048], 8, 200), list(range(3, 32)), 128, Hq=2, Hkv=1, D=128, seed=99, general=True)
+    # the same sinks in the single-launch kernel
+    run_case(wl.layout_lambda([4096], 32, 512), list(range(32)), 128, Hq=1, Hkv=1, D=64, seed=98, general=False)
+
+
+@pytest.mark.parametrize("kind", ["short spans", "windowed spans", "lambda", "shared question", "denied", "block causal"])
+def test_general_path_masks(kind):
+    """The mask families of the tests around this one beyond the single-launch kernel's limit: more than
+    4096 tokens, shares of a few hundred rows in blocks of 16 to 240 in any order."""
+    lay, block, n, Hq, Hkv, D = {
+        "short spans": (wl.layout_short_spans(19, 4224), 48, 9, 2, 1, 128),
+        "windowed spans": (wl.layout_random(72, S=4224, n_samples=2, max_spans=6), 128, 4, 4, 2, 64),
+        "lambda": (wl.layout_lambda([1700, 2524], 16, 256), 16, 30, 3, 1, 128),
+        "shared question": (wl.layout_shared_question(600, [530, 664, 857, 700], n_tail=873), 128, 4, 2, 2, 128),
+        "denied": (wl.layout_random(73, S=5760, n_samples=2, max_spans=6, noncausal_prob=0.2, deny_prob=0.8), 240, 2, 2, 1, 64),
+        "block causal": (wl.layout_block_causal(4224, 96), 64, 7, 2, 2, 64)}[kind]
+    if kind == "windowed spans":
+        lay.window = [37 * (j + 1) for j in range(len(lay.spans))]
+    nb = lay.S // block
+    blocks = np.random.default_rng(74).permutation(nb)[: n - 1].tolist() + [nb - 1]
+    blocks = list(dict.fromkeys(blocks))
+    run_case(lay, blocks, block, Hq, Hkv, D, seed=75, general=True)
 
 
 def test_lambda_8k_sampled():
@@ -161,10 +186,10 @@ def test_random_layouts(seed, D):
     (1920, 240, 4, 24, 8, 64),       # 15 row tiles, the most of a short list; three workgroups
 ])
 def test_short_lists_head_chunks(S, block, n, Hq, Hkv, D):
-    """Few rows against many keys: how many workgroups share a unit's query heads."""
+    """Few rows against many keys: how many workgroups share a unit's query heads (general path)."""
     lay = wl.layout_random(75, S=S, n_samples=2, max_spans=4, deny_prob=0.3)
     blocks = np.random.default_rng(75).choice(S // block, size=n, replace=False).tolist()
-    run_case(lay, blocks, block, Hq, Hkv, D, seed=76)
+    run_case(lay, blocks, block, Hq, Hkv, D, seed=76, general=True)
 
 
 @pytest.mark.parametrize("block", [48, 80, 240])
@@ -382,13 +407,15 @@ def test_workload4_sampled():
         key_range_check(w, blocks, t, outs, g, k0, k0 + 128, max_rows=1536)
 
 
-def test_row_that_sees_no_key():
+@pytest.mark.parametrize("S", [512, 4224])
+def test_row_that_sees_no_key(S):
     """Hand-built mask words (the encoder never produces such a token): one
     token without the causal bit and outside every span sees nothing, not even
     itself.  Forward: O = 0, LSE = -inf; backward: dQ = 0 for that row, finite
-    dK / dV that match the oracle."""
+    dK / dV that match the oracle.  The share's rows are the first 512 tokens; at 4224 tokens
+    both directions take the general path."""
     from oracle import mask as om
-    S, block, Hq, Hkv, D = 512, 64, 4, 2, 128
+    block, Hq, Hkv, D = 64, 4, 2, 128
     lay = wl.Layout(S, [(100, 150, 1)], [0, 300, S])
     sample, span, causal, modality, attend = fields(lay)
     blind = [77, 301, 448]                 # text tokens: span id 0
@@ -396,15 +423,17 @@ def test_row_that_sees_no_key():
     causal[blind] = 0
     words = om.encode(sample, span, causal, modality, attend)
     bits = torch.from_numpy(words.view(np.int64)).to(DEV)
-    blocks = list(range(S // block))
+    blocks = list(range(512 // block))
     bl = torch.tensor(blocks, dtype=torch.int32, device=DEV)
-    t = make_tensors(123, S, S, Hq, Hkv, D)
-    o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, bl, block)
-    dq, dk, dv = mb.bwd(t["q"], t["k"], t["v"], bits, bl, block, o, lse, t["do"])
+    t = make_tensors(123, 512, S, Hq, Hkv, D)
+    ws = [spy_workspace(op, S, len(blocks), block, Hq, Hkv, D) for op in (mb.OP_FWD, mb.OP_BWD)]
+    o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, bl, block, ws=ws[0])
+    dq, dk, dv = mb.bwd(t["q"], t["k"], t["v"], bits, bl, block, o, lse, t["do"], ws=ws[1])
     torch.cuda.synchronize()
+    assert [general_path(w) for w in ws] == [S > 512] * 2
     assert (o[blind] == 0).all() and torch.isneginf(lse[:, blind]).all()
     assert (dq[blind] == 0).all()
-    rows = np.arange(S)
+    rows = np.arange(512)
     Q, K, V, dO = f64(t["q_bits"]), f64(t["k_bits"]), f64(t["v_bits"]), f64(t["do_bits"])
     o_ref, lse_ref = oa.forward(Q, K, V, rows, sample, span, causal, modality=modality, attend=attend)
     dq_ref, dk_ref, dv_ref = oa.backward(Q, K, V, dO, rows, sample, span, causal, modality=modality,
@@ -419,15 +448,17 @@ def test_row_that_sees_no_key():
         assert rel_l2(gg, ref) < TOL, (name, rel_l2(gg, ref))
 
 
-def test_bad_block_index_leaves_outputs_untouched():
+@pytest.mark.parametrize("S", [512, 4224])
+def test_bad_block_index_leaves_outputs_untouched(S):
     """A block index outside [0, S/block) raises the status word (first int32 of
-    the workspace); dq, dk, dv keep what they held."""
-    lay = wl.Layout(512, [(100, 200, 1)], [0, 512])
+    the workspace); dq, dk, dv keep what they held.  At 4224 tokens the general path."""
+    lay = wl.Layout(S, [(100, 200, 1)], [0, S])
     t = make_tensors(6, 128, lay.S, 2, 1, 64)
     bits = gpu_bits(lay)
     o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, torch.tensor([1, 2], dtype=torch.int32, device=DEV), 64)
-    ws = torch.zeros(mb.workspace_size(mb.OP_BWD, lay.S, 2, 64, 2, 1, 64), dtype=torch.uint8, device=DEV)
-    for bad in ([1, 8], [-1, 2]):
+    ws = spy_workspace(mb.OP_BWD, S, 2, 64, 2, 1, 64)
+    ws[:256] = 0
+    for bad in ([1, S // 64], [-1, 2]):
         dq = torch.full_like(t["q"], 5.0)
         dk = torch.full_like(t["k"], 3.0)
         dv = torch.full_like(t["v"], -2.0)
@@ -439,4 +470,5 @@ def test_bad_block_index_leaves_outputs_untouched():
     dq, dk, dv = mb.bwd(t["q"], t["k"], t["v"], bits, torch.tensor([1, 2], dtype=torch.int32, device=DEV), 64,
                         o, lse, t["do"], ws=ws)
     torch.cuda.synchronize()
+    assert general_path(ws) == (S > 512)
     assert int(ws[:4].view(torch.int32)[0]) == 0 and torch.isfinite(dq.float()).all()

@@ -19,43 +19,58 @@ from oracle import tilemap as ot
 from paper_2503_11367_amd import binding as mb
 from paper_2503_11367_amd import workloads as wl
 
-from gpu_util import (DEV, bf16_to_f64, f64, fields, gpu_bits, make_tensors, max_abs, rel_l2, windows)
+from gpu_util import (DEV, bf16_to_f64, f64, fields, general_path, gpu_bits, make_tensors, max_abs, rel_l2,
+                      spy_workspace, windows)
 
 pytestmark = pytest.mark.gpu
 
 TOL_MAX, TOL_L2, TOL_LSE = 2e-2, 5e-3, 4.5e-3
 
 
+def both_paths(t, bits, bl, block, scale=None):
+    """(O, LSE) of mmattn_fwd and, where the single-launch kernel takes the share, of mmattn_fwd_heads
+    on all heads, which takes the general path at any size."""
+    (n_loc, Hq, D), (S, Hkv, _) = t["q"].shape, t["k"].shape
+    ws = spy_workspace(mb.OP_FWD, S, bl.numel(), block, Hq, Hkv, D)
+    out = [mb.fwd(t["q"], t["k"], t["v"], bits, bl, block, scale=scale, ws=ws)]
+    if not general_path(ws):
+        ws = spy_workspace(mb.OP_FWD_HEADS, S, bl.numel(), block, Hq, Hkv, D)
+        o, lse = torch.full_like(t["q"], 7.0), torch.full((Hq, n_loc), 7.0, dtype=torch.float32, device=DEV)
+        out.append(mb.fwd_heads(t["q"], t["k"], t["v"], bits, bl, block, 0, Hkv, False, (o, lse), ws, scale=scale))
+        assert general_path(ws)
+    return out
+
+
 def run_case(lay, blocks, block, Hq, Hkv, D, seed, heads=None, rows_sample=None):
-    """GPU forward on the share `blocks`; oracle on all of it, or on sampled
-    local rows / a subset of heads."""
+    """GPU forward on the share `blocks`, by both paths where there are two; oracle on
+    all of it, or on sampled local rows / a subset of heads."""
     f = fields(lay)
     n_loc = len(blocks) * block
     t = make_tensors(seed, n_loc, lay.S, Hq, Hkv, D)
     bits = gpu_bits(lay)
     bl = torch.tensor(blocks, dtype=torch.int32, device=DEV)
-    o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, bl, block)
-    torch.cuda.synchronize()
+    results = both_paths(t, bits, bl, block)
     rows = oa.rows_of_blocks(blocks, block)
     sel = np.arange(n_loc) if rows_sample is None else rows_sample
     hs = list(range(Hq)) if heads is None else heads
     rep = Hq // Hkv
-    o_gpu = bf16_to_f64(o)[sel][:, hs]
-    lse_gpu = lse.cpu().numpy().astype(np.float64)[hs][:, sel]
     Q, K, V = f64(t["q_bits"]), f64(t["k_bits"]), f64(t["v_bits"])
-    o_ref = np.zeros_like(o_gpu)
-    lse_ref = np.zeros_like(lse_gpu)
+    o_ref = np.zeros((len(sel), len(hs), D))
+    lse_ref = np.zeros((len(hs), len(sel)))
     for j, h in enumerate(hs):
         g = h // rep
         oo, ll = oa.forward(Q[sel][:, h:h + 1], K[:, g:g + 1], V[:, g:g + 1], rows[sel], f[0], f[1], f[2],
                             modality=f[3], attend=f[4], window=windows(lay))
         o_ref[:, j] = oo[:, 0]
         lse_ref[j] = ll[0]
-    assert np.isfinite(o_gpu).all()
-    assert max_abs(o_gpu, o_ref) < TOL_MAX, max_abs(o_gpu, o_ref)
-    assert rel_l2(o_gpu, o_ref) < TOL_L2, rel_l2(o_gpu, o_ref)
-    assert max_abs(lse_gpu, lse_ref) < TOL_LSE, max_abs(lse_gpu, lse_ref)
-    return o, lse, t
+    for o, lse in results:
+        o_gpu = bf16_to_f64(o)[sel][:, hs]
+        lse_gpu = lse.cpu().numpy().astype(np.float64)[hs][:, sel]
+        assert np.isfinite(o_gpu).all()
+        assert max_abs(o_gpu, o_ref) < TOL_MAX, max_abs(o_gpu, o_ref)
+        assert rel_l2(o_gpu, o_ref) < TOL_L2, rel_l2(o_gpu, o_ref)
+        assert max_abs(lse_gpu, lse_ref) < TOL_LSE, max_abs(lse_gpu, lse_ref)
+    return (*results[0], t)
 
 
 @pytest.mark.parametrize("Hq,Hkv,D", [(1, 1, 128), (3, 1, 128), (2, 1, 64), (1, 1, 64)])
@@ -70,10 +85,12 @@ def test_one_head_per_workgroup_list_lengths(Hq, Hkv, D, sharp):
     Q, K, V = f64(t["q_bits"]), f64(t["k_bits"]), f64(t["v_bits"])
     scale = sharp / np.sqrt(D)
     for b in range(16):
-        o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, torch.tensor([b], dtype=torch.int32, device=DEV), 64, scale=scale)
+        results = both_paths(t, bits, torch.tensor([b], dtype=torch.int32, device=DEV), 64, scale=scale)
+        assert len(results) == 2
         oo, ll = oa.forward(Q, K, V, oa.rows_of_blocks([b], 64), f[0], f[1], f[2], modality=f[3], attend=f[4], scale=scale)
-        assert max_abs(bf16_to_f64(o), oo) < TOL_MAX and rel_l2(bf16_to_f64(o), oo) < TOL_L2, b
-        assert max_abs(lse.cpu().numpy().astype(np.float64), ll) < TOL_LSE, b
+        for o, lse in results:
+            assert max_abs(bf16_to_f64(o), oo) < TOL_MAX and rel_l2(bf16_to_f64(o), oo) < TOL_L2, b
+            assert max_abs(lse.cpu().numpy().astype(np.float64), ll) < TOL_LSE, b
 
 
 def test_one_head_per_workgroup_long_lists():
@@ -205,7 +222,8 @@ def test_block_size_not_a_power_of_two(block):
 def test_few_work_items_split_into_list_slices():
     """Shares with few (q-tile, head) work items cut every q-tile's k-tile list
     into slices run by separate workgroups and aggregate the partial results:
-    4096 keys, 11 q-tiles of 4 heads -> up to 16 slices, ragged at the diagonal."""
+    4096 keys, 11 q-tiles of 4 heads -> up to 16 slices, ragged at the diagonal (the first share
+    by mmattn_fwd_heads: mmattn_fwd gives it to the single-launch kernel)."""
     lay = wl.layout_random(91, S=4096, n_samples=2, noncausal_prob=0.0)
     run_case(lay, list(range(0, 32, 3)), 128, Hq=4, Hkv=2, D=128, seed=51)
     run_case(lay, [31, 2, 17], 128, Hq=2, Hkv=2, D=64, seed=52)
@@ -250,25 +268,29 @@ def test_zero_q_reads_back_the_mask():
     vv[np.arange(S), 0, 64 + np.arange(S) // 16] = 1.0
     v = torch.from_numpy(vv).to(DEV).to(torch.bfloat16)
     bl = torch.arange(S // 16, dtype=torch.int32, device=DEV)
-    o, lse = mb.fwd(q, k, v, gpu_bits(lay), bl, 16)
+    results = both_paths({"q": q, "k": k, "v": v}, gpu_bits(lay), bl, 16)
     from oracle import mask as om
     vis = om.visible(np.arange(S), np.arange(S), f[0], f[1], f[2]).astype(np.float64)
     ref = (vis @ vv[:, 0].astype(np.float64)) / vis.sum(axis=1, keepdims=True)
-    assert max_abs(bf16_to_f64(o)[:, 0], ref) < 6e-3
-    assert max_abs(lse.cpu().numpy()[0].astype(np.float64), np.log(vis.sum(axis=1))) < 1e-4
+    for o, lse in results:
+        assert max_abs(bf16_to_f64(o)[:, 0], ref) < 6e-3
+        assert max_abs(lse.cpu().numpy()[0].astype(np.float64), np.log(vis.sum(axis=1))) < 1e-4
 
 
 def test_bad_block_index_is_contained():
     """An out-of-range block index must not fault: the kernels exit and leave
-    the output untouched."""
-    lay = wl.Layout(512, [], [0, 512])
-    t = make_tensors(3, 256, 512, 2, 1, 128)
-    bl = torch.tensor([1, 9], dtype=torch.int32, device=DEV)
-    o = torch.full((256, 2, 128), 7.0, dtype=torch.bfloat16, device=DEV)
-    lse = torch.full((2, 256), 7.0, dtype=torch.float32, device=DEV)
-    mb.fwd(t["q"], t["k"], t["v"], gpu_bits(lay), bl, 128, out=(o, lse))
-    torch.cuda.synchronize()
-    assert (o.float() == 7.0).all() and (lse == 7.0).all()
+    the output untouched.  At 4224 tokens the general path (also with its lists cut)."""
+    for S, bad in ((512, 9), (4224, 33)):
+        lay = wl.Layout(S, [], [0, S])
+        t = make_tensors(3, 256, S, 2, 1, 128)
+        bl = torch.tensor([1, bad], dtype=torch.int32, device=DEV)
+        o = torch.full((256, 2, 128), 7.0, dtype=torch.bfloat16, device=DEV)
+        lse = torch.full((2, 256), 7.0, dtype=torch.float32, device=DEV)
+        ws = spy_workspace(mb.OP_FWD, S, 2, 128, 2, 1, 128)
+        mb.fwd(t["q"], t["k"], t["v"], gpu_bits(lay), bl, 128, out=(o, lse), ws=ws)
+        torch.cuda.synchronize()
+        assert general_path(ws) == (S > 512)
+        assert (o.float() == 7.0).all() and (lse == 7.0).all()
 
 
 def test_workload2_full_sequence():

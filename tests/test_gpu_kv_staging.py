@@ -10,7 +10,8 @@ from paper_2503_11367_amd import binding as mb
 from paper_2503_11367_amd import staging
 from paper_2503_11367_amd import workloads as wl
 
-from gpu_util import (DEV, bf16_to_f64, f64, fields, gpu_bits, make_tensors, max_abs, rel_l2)
+from gpu_util import (DEV, bf16_to_f64, f64, fields, general_path, gpu_bits, make_tensors, max_abs, rel_l2,
+                      spy_workspace)
 
 pytestmark = pytest.mark.gpu
 
@@ -148,9 +149,11 @@ def test_staged_windows_together(S, Hq, Hkv, D, hps, in_place):
         check(o[sel][:, h:h + 1], lse[h:h + 1][:, sel], o_ref, lse_ref)
 
 
-def test_staged_from_pinned_memory():
-    """Sources in pinned host memory take the runtime's copies, window by window."""
-    lay = wl.layout_random(155, S=1024, n_samples=2, max_spans=5)
+@pytest.mark.parametrize("S", [1024, 4224])
+def test_staged_from_pinned_memory(S):
+    """Sources in pinned host memory take the runtime's copies, window by window; at 4224 tokens on the
+    general path, which forms the key norms of each window behind its arrival."""
+    lay = wl.layout_random(155, S=S, n_samples=2, max_spans=5)
     Hq, Hkv, D, blocks = 8, 4, 128, [3, 14, 6, 9]
     t = make_tensors(415, len(blocks) * 64, lay.S, Hq, Hkv, D)
     bits = gpu_bits(lay)
@@ -159,7 +162,7 @@ def test_staged_from_pinned_memory():
     k_src.copy_(t["k"]); v_src.copy_(t["v"])
     ks, vs = torch.full_like(t["k"], float("nan")), torch.full_like(t["v"], float("nan"))
     o, lse = torch.empty_like(t["q"]), torch.empty(Hq, t["q"].shape[0], dtype=torch.float32, device=DEV)
-    ws = torch.empty(mb.workspace_size(mb.OP_FWD_HEADS, lay.S, len(blocks), 64, Hq, Hkv, D), dtype=torch.uint8, device=DEV)
+    ws = spy_workspace(mb.OP_FWD_HEADS, lay.S, len(blocks), 64, Hq, Hkv, D)
     copy = torch.cuda.Stream()
     rc = mb.lib().mmattn_fwd_staged(t["q"].data_ptr(), k_src.data_ptr(), v_src.data_ptr(), ks.data_ptr(), vs.data_ptr(),
                                     bits.data_ptr(), bl.data_ptr(), len(blocks), 64, lay.S, Hq, Hkv, D, D ** -0.5, mb.BF16, 2,
@@ -167,6 +170,7 @@ def test_staged_from_pinned_memory():
                                     torch.cuda.current_stream().cuda_stream)
     assert rc == mb.OK
     torch.cuda.synchronize()
+    assert general_path(ws) == (S > 1024)
     assert torch.equal(ks, t["k"]) and torch.equal(vs, t["v"])
     check(o, lse, *oracle_fwd(lay, blocks, 64, t, Hq, Hkv))
 
@@ -232,7 +236,8 @@ def test_window_touches_only_its_heads():
 def test_windows_share_a_plan_across_kernels(order):
     """4096 rows of 64 / 8 heads: windows of four KV heads put pairs of heads into a workgroup and
     walk whole lists, windows of one and two run single heads and cut them; each reuses the plan
-    that another left, whatever slice length that chose.  `staged`: two windows of four."""
+    that another left, whatever slice length that chose.  `staged`: two windows of four in
+    mmattn_fwd_staged, where 16 MiB of keys and values travel and are attended together."""
     Hq, Hkv, D, S = 64, 8, 128, 4096
     lay = wl.layout_packed(153, S=S, n_samples=4, span_lo=40, span_hi=300)
     blocks = np.random.default_rng(153).permutation(S // 64).tolist()

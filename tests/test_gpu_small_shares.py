@@ -12,7 +12,8 @@ from oracle import attention as oa
 from paper_2503_11367_amd import binding as mb
 from paper_2503_11367_amd import workloads as wl
 
-from gpu_util import DEV, bf16_to_f64, f64, fields, gpu_bits, make_tensors, max_abs, rel_l2, windows
+from gpu_util import (DEV, bf16_to_f64, f64, fields, general_path, gpu_bits, make_tensors, max_abs, rel_l2,
+                      spy_workspace, windows)
 
 pytestmark = pytest.mark.gpu
 
@@ -45,6 +46,9 @@ CASES = {
     "four wavefronts, first size": (wl.layout_random(206, S=2048, n_samples=1), spread(128, 65), 16, 8, 4, 128),
 }
 
+# beyond the backward's 768 workgroups: the general path
+GENERAL_BWD = {"long list", "four wavefronts, first size"}
+
 
 @pytest.mark.parametrize("name", CASES)
 def test_forward(name):
@@ -54,7 +58,9 @@ def test_forward(name):
     t = make_tensors(200, n_loc, lay.S, Hq, Hkv, D)
     bits, bl = gpu_bits(lay), torch.tensor(blocks, dtype=torch.int32, device=DEV)
     o, lse = torch.full_like(t["q"], 7.0), torch.full((Hq, n_loc), 7.0, dtype=torch.float32, device=DEV)
-    mb.fwd(t["q"], t["k"], t["v"], bits, bl, block, out=(o, lse))
+    ws = spy_workspace(mb.OP_FWD, lay.S, len(blocks), block, Hq, Hkv, D)
+    mb.fwd(t["q"], t["k"], t["v"], bits, bl, block, out=(o, lse), ws=ws)
+    assert not general_path(ws)
     heads = sorted({0, Hq // 2, Hq - 1})
     for h in heads:
         g = h // (Hq // Hkv)
@@ -64,9 +70,10 @@ def test_forward(name):
         assert max_abs(got, oo) < 2e-2 and rel_l2(got, oo) < 5e-3, h
         fin = np.isfinite(ll)
         assert np.array_equal(np.isneginf(l), ~fin) and max_abs(l[fin], ll[fin]) < 4.5e-3, h
-    ws = torch.empty(mb.workspace_size(mb.OP_FWD_HEADS, lay.S, len(blocks), block, Hq, Hkv, D), dtype=torch.uint8, device=DEV)
+    ws = spy_workspace(mb.OP_FWD_HEADS, lay.S, len(blocks), block, Hq, Hkv, D)
     o2, lse2 = torch.full_like(o, 3.0), torch.full_like(lse, 3.0)
     mb.fwd_heads(t["q"], t["k"], t["v"], bits, bl, block, 0, Hkv, False, (o2, lse2), ws)
+    assert general_path(ws)
     assert rel_l2(bf16_to_f64(o), bf16_to_f64(o2)) < 1e-3
     fin = torch.isfinite(lse2)
     assert torch.equal(torch.isneginf(lse), ~fin) and float((lse - lse2)[fin].abs().max()) < 1e-4
@@ -75,14 +82,16 @@ def test_forward(name):
 @pytest.mark.parametrize("name", [n for n in CASES if n != "more workgroups than CUs at 128 tokens"])
 def test_backward(name):
     """dQ, dK, dV against the oracle (relative L2 1e-2, as for the general path); keys that no row of the
-    share sees get exactly zero.  The last two cases lie beyond the line and take the general path."""
+    share sees get exactly zero.  The cases of GENERAL_BWD lie beyond the line and take the general path."""
     lay, blocks, block, Hq, Hkv, D = CASES[name]
     f, win = fields(lay), windows(lay)
     t = make_tensors(210, len(blocks) * block, lay.S, Hq, Hkv, D)
     bits, bl = gpu_bits(lay), torch.tensor(blocks, dtype=torch.int32, device=DEV)
     o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, bl, block)
     out = tuple(torch.full_like(t[n], 7.0) for n in ("q", "k", "v"))
-    mb.bwd(t["q"], t["k"], t["v"], bits, bl, block, o, lse, t["do"], out=out)
+    ws = spy_workspace(mb.OP_BWD, lay.S, len(blocks), block, Hq, Hkv, D)
+    mb.bwd(t["q"], t["k"], t["v"], bits, bl, block, o, lse, t["do"], out=out, ws=ws)
+    assert general_path(ws) == (name in GENERAL_BWD)
     rows = oa.rows_of_blocks(blocks, block)
     from oracle import mask as om
     seen = om.visible(rows, np.arange(lay.S), f[0], f[1], f[2], f[3], f[4], win).any(axis=0)
@@ -104,9 +113,10 @@ def test_backward_leaves_outputs_for_bad_blocks(D):
     bits, bl = gpu_bits(lay), torch.tensor([1, 9, 0, 3], dtype=torch.int32, device=DEV)
     o, lse = torch.zeros_like(t["q"]), torch.zeros((2, 256), dtype=torch.float32, device=DEV)
     out = tuple(torch.full_like(t[n], 7.0) for n in ("q", "k", "v"))
-    ws = torch.zeros(mb.workspace_size(mb.OP_BWD, 512, 4, 64, 2, 1, D), dtype=torch.uint8, device=DEV)
+    ws = spy_workspace(mb.OP_BWD, 512, 4, 64, 2, 1, D)
+    ws[:256] = 0
     mb.bwd(t["q"], t["k"], t["v"], bits, bl, 64, o, lse, t["do"], out=out, ws=ws)
-    assert all((x == 7.0).all() for x in out) and int(ws[:4].view(torch.int32)) != 0
+    assert all((x == 7.0).all() for x in out) and int(ws[:4].view(torch.int32)) != 0 and not general_path(ws)
 
 
 @pytest.mark.parametrize("D", [64, 128])

@@ -3,7 +3,8 @@ them in.  The forward takes its probabilities relative to a per-row shift that
 starts at 0 and follows the running maximum only when the two drift far apart
 (section 3.2.2's online softmax, with a lazy shift); these cases make the shift
 move, up and down, inside one workgroup and across the list slices whose
-partial results are aggregated afterwards, and feed the backward an LSE far
+partial results are aggregated afterwards (and the wavefronts of the small
+kernels), and feed the backward an LSE far
 from 0.  Same tolerances as everywhere: O max-abs 2e-2 and relative L2 5e-3,
 LSE 4.5e-3 absolute, gradients relative L2 1e-2."""
 import numpy as np
@@ -14,7 +15,8 @@ from oracle import attention as oa
 from paper_2503_11367_amd import binding as mb
 from paper_2503_11367_amd import workloads as wl
 
-from gpu_util import DEV, bf16_to_f64, f64, fields, gpu_bits, make_tensors, max_abs, rel_l2
+from gpu_util import (DEV, bf16_to_f64, f64, fields, general_path, gpu_bits, make_tensors, max_abs, rel_l2,
+                      spy_workspace)
 
 pytestmark = pytest.mark.gpu
 
@@ -34,9 +36,11 @@ def set_feature(t, name, value):
     t[name] = mb.bf16_from_bits(b, DEV)
 
 
-def check(lay, blocks, block, Hq, Hkv, D, seed, scale=None, prepare=None, lse_far=None, group=None):
+def check(lay, blocks, block, Hq, Hkv, D, seed, scale=None, prepare=None, lse_far=None, group=None,
+          general=(True, True)):
     """GPU forward and backward on all heads; the oracle on all of them, or (group
-    given) on the query heads of that KV head, which gives complete dK / dV for it."""
+    given) on the query heads of that KV head, which gives complete dK / dV for it.
+    general: whether the forward, the backward are meant to take the general path."""
     f = fields(lay)
     n_loc = len(blocks) * block
     t = make_tensors(seed, n_loc, lay.S, Hq, Hkv, D)
@@ -45,9 +49,11 @@ def check(lay, blocks, block, Hq, Hkv, D, seed, scale=None, prepare=None, lse_fa
         prepare(t, rows)
     bits = gpu_bits(lay)
     bl = torch.tensor(blocks, dtype=torch.int32, device=DEV)
-    o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, bl, block, scale=scale)
-    dq, dk, dv = mb.bwd(t["q"], t["k"], t["v"], bits, bl, block, o, lse, t["do"], scale=scale)
+    ws = [spy_workspace(op, lay.S, len(blocks), block, Hq, Hkv, D) for op in (mb.OP_FWD, mb.OP_BWD)]
+    o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, bl, block, scale=scale, ws=ws[0])
+    dq, dk, dv = mb.bwd(t["q"], t["k"], t["v"], bits, bl, block, o, lse, t["do"], scale=scale, ws=ws[1])
     torch.cuda.synchronize()
+    assert tuple(map(general_path, ws)) == general
     rep = Hq // Hkv
     hs = slice(0, Hq) if group is None else slice(group * rep, (group + 1) * rep)
     gs = slice(0, Hkv) if group is None else slice(group, group + 1)
@@ -76,7 +82,15 @@ def whole(seed, group, **kw):
                  seed=seed, group=group, **kw)
 
 
-LAY_SPLIT = lambda: wl.layout_random(91, S=4096, n_samples=2)          # few work items: lists cut into slices
+def split(blocks, Hq, Hkv, D, seed, general, **kw):
+    """Few work items: at 4224 tokens every list is cut into slices, aggregated by the combine kernel (and
+    the backward is the general one); at 4096 `general` of forward and backward (else the small kernels,
+    whose wavefronts merge their sums the same way)."""
+    check(wl.layout_random(91, S=4224, n_samples=2), blocks, 128, Hq, Hkv, D, seed=seed, **kw)
+    check(wl.layout_random(91, S=4096, n_samples=2), blocks, 128, Hq, Hkv, D, seed=seed, general=general, **kw)
+
+
+SMALL = (False, False)
 
 
 @pytest.mark.parametrize("factor", [4.0, 16.0])
@@ -86,9 +100,8 @@ def test_large_softmax_scale(factor):
     with and without list slices, both head dims."""
     whole(201, 3, scale=factor / np.sqrt(128.0),
           lse_far=40.0 if factor == 16.0 else None)
-    # 11 q-tiles x 2 head pairs: every list cut into slices, aggregated by the combine kernel
-    check(LAY_SPLIT(), list(range(0, 32, 3)), 128, 4, 2, 128, seed=202, scale=factor / np.sqrt(128.0))
-    check(LAY_SPLIT(), [31, 2, 17], 128, 2, 2, 64, seed=203, scale=factor / 8.0)
+    split(list(range(0, 32, 3)), 4, 2, 128, 202, SMALL, scale=factor / np.sqrt(128.0))
+    split([31, 2, 17], 2, 2, 64, 203, (True, False), scale=factor / 8.0)
 
 
 def test_all_scores_far_above_zero():
@@ -102,7 +115,7 @@ def test_all_scores_far_above_zero():
         set_feature(t, "q", 128.0)
         set_feature(t, "k", 8.0)
     whole(204, 6, prepare=prep, lse_far=85.0)
-    check(LAY_SPLIT(), list(range(0, 32, 3)), 128, 4, 2, 128, seed=205, prepare=prep, lse_far=85.0)
+    split(list(range(0, 32, 3)), 4, 2, 128, 205, SMALL, prepare=prep, lse_far=85.0)
 
 
 def test_scores_far_below_zero_then_far_above():
@@ -115,10 +128,10 @@ def test_scores_far_below_zero_then_far_above():
         set_feature(t, "q", 128.0)
         set_feature(t, "k", np.where(np.arange(t["k_bits"].shape[0]) < 1024, -8.0, 8.0))
     whole(206, 9, prepare=prep, lse_far=85.0)
-    check(LAY_SPLIT(), list(range(0, 32, 3)), 128, 4, 2, 128, seed=207, prepare=prep, lse_far=85.0)
-    check(LAY_SPLIT(), list(range(32)), 128, 2, 1, 64, seed=208,
+    split(list(range(0, 32, 3)), 4, 2, 128, 207, SMALL, prepare=prep, lse_far=85.0)
+    split(list(range(32)), 2, 1, 64, 208, (False, True),
           prepare=lambda t, rows: (set_feature(t, "q", 64.0),
-                                   set_feature(t, "k", np.where(np.arange(4096) % 1024 < 512, -8.0, 8.0))))
+                                   set_feature(t, "k", np.where(np.arange(t["k_bits"].shape[0]) % 1024 < 512, -8.0, 8.0))))
 
 
 def test_scores_far_above_zero_then_far_below():
@@ -128,7 +141,7 @@ def test_scores_far_above_zero_then_far_below():
         set_feature(t, "q", 128.0)
         set_feature(t, "k", np.where(np.arange(t["k_bits"].shape[0]) < 1024, 8.0, -8.0))
     whole(209, 12, prepare=prep, lse_far=85.0)
-    check(LAY_SPLIT(), list(range(0, 32, 3)), 128, 4, 2, 128, seed=210, prepare=prep)
+    split(list(range(0, 32, 3)), 4, 2, 128, 210, SMALL, prepare=prep)
 
 
 def test_per_row_offsets():
@@ -140,7 +153,7 @@ def test_per_row_offsets():
         set_feature(t, "q", ((np.arange(n) * 7) % 81 - 40).astype(np.float32) * 4.0)
         set_feature(t, "k", 8.0)
     whole(211, 15, prepare=prep, lse_far=100.0)
-    check(LAY_SPLIT(), [30, 1, 12, 7], 128, 2, 2, 64, seed=212, prepare=prep)
+    split([30, 1, 12, 7], 2, 2, 64, 212, (True, False), prepare=prep)
 
 
 def test_offsets_inside_the_untracked_band():
@@ -161,7 +174,7 @@ def test_offsets_inside_the_untracked_band():
     whole(221, 2, prepare=up, lse_far=25.0)
     whole(222, 5, prepare=down, lse_far=25.0)
     whole(223, 11, prepare=both, lse_far=25.0)
-    check(LAY_SPLIT(), list(range(0, 32, 3)), 128, 4, 2, 128, seed=224, prepare=both, lse_far=25.0)
+    split(list(range(0, 32, 3)), 4, 2, 128, 224, SMALL, prepare=both, lse_far=25.0)
 
 
 # Scores in base-2 units that depend on the key alone: the mass lies at kNear (reached from the shift's

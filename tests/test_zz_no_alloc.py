@@ -31,14 +31,18 @@ def test_too_large_share_is_rejected_on_the_host():
 def test_two_calls_in_a_row_match_the_workspace_entry_point():
     import torch
     from paper_2503_11367_amd import workloads as wl
-    from gpu_util import DEV, gpu_bits, make_tensors
+    from gpu_util import DEV, general_path, gpu_bits, make_tensors, spy_workspace
 
     cases = [
         # 16 q-tiles x 32 head pairs: lists not cut, the scratch holds the plan only
         (wl.layout_random(30, S=2048, n_samples=1, max_spans=3), list(range(16)), 128, 64, 16, 128, 300),
-        # few work items: every q-tile's list may be cut into slices, 8 MiB of partial results in the scratch
-        (wl.layout_random(31, S=1024, n_samples=2, max_spans=5), list(range(8)), 128, 4, 2, 128, 301),
+        # few work items: every q-tile's list may be cut into slices, 26 MiB of partial results at most
+        # (beyond 4096 tokens: the single-launch kernel for small shares leaves no plan and no partial results)
+        (wl.layout_random(31, S=4224, n_samples=2, max_spans=5), list(range(0, 31, 6)), 128, 4, 2, 128, 301),
         # smaller share, other head shape, unsorted block list; its slices land on the leftovers
+        (wl.layout_random(32, S=4224, n_samples=1, max_spans=3), [5, 31, 16], 128, 2, 1, 64, 302),
+        # the single-launch kernel, which finds both calls' leftovers
+        (wl.layout_random(31, S=1024, n_samples=2, max_spans=5), list(range(8)), 128, 4, 2, 128, 301),
         (wl.layout_random(32, S=1024, n_samples=1, max_spans=3), [5, 1, 6], 128, 2, 1, 64, 302),
     ]
     results = []
@@ -49,7 +53,9 @@ def test_two_calls_in_a_row_match_the_workspace_entry_point():
         bl = torch.tensor(blocks, dtype=torch.int32, device=DEV)
         need = mb.workspace_size(mb.OP_FWD, lay.S, len(blocks), block, Hq, Hkv, D)
         assert need <= mb.STATIC_SCRATCH_BYTES
-        ref = mb.fwd(t["q"], t["k"], t["v"], bits, bl, block)
+        ws = spy_workspace(mb.OP_FWD, lay.S, len(blocks), block, Hq, Hkv, D)
+        ref = mb.fwd(t["q"], t["k"], t["v"], bits, bl, block, ws=ws)
+        assert general_path(ws) == (lay.S > 1024) and (lay.S < 4224 or need > 3 << 20)
         out = (torch.full_like(t["q"], float("nan")),
                torch.full((Hq, n_loc), float("nan"), dtype=torch.float32, device=DEV))
         results.append((t, bits, bl, block, ref, out))
@@ -63,18 +69,22 @@ def test_two_calls_in_a_row_match_the_workspace_entry_point():
 
 
 @pytest.mark.gpu
-def test_share_without_partial_results_fits_whatever_its_heads():
-    """512 keys, 64 heads: no list is cut, so the scratch holds the plan only."""
+@pytest.mark.parametrize("Hq", [64, 72])
+def test_share_without_partial_results_fits_whatever_its_heads(Hq):
+    """512 keys: no list is cut, so the scratch holds the plan only.  64 heads go to the single-launch
+    kernel, 72 would be 1152 workgroups of it and take the general path."""
     import torch
     from paper_2503_11367_amd import workloads as wl
-    from gpu_util import DEV, gpu_bits, make_tensors
+    from gpu_util import DEV, general_path, gpu_bits, make_tensors, spy_workspace
 
     lay = wl.layout_random(33, S=512, n_samples=2, max_spans=4)
-    t = make_tensors(303, 512, 512, 64, 8, 128)
+    t = make_tensors(303, 512, 512, Hq, 8, 128)
     bits, bl = gpu_bits(lay), torch.arange(4, dtype=torch.int32, device=DEV)
-    assert mb.workspace_size(mb.OP_FWD, 512, 4, 128, 64, 8, 128) < 1 << 16
-    ref = mb.fwd(t["q"], t["k"], t["v"], bits, bl, 128)
-    out = torch.full_like(t["q"], float("nan")), torch.full((64, 512), float("nan"), dtype=torch.float32, device=DEV)
+    ws = spy_workspace(mb.OP_FWD, 512, 4, 128, Hq, 8, 128)
+    assert ws.numel() < 1 << 16
+    ref = mb.fwd(t["q"], t["k"], t["v"], bits, bl, 128, ws=ws)
+    assert general_path(ws) == (Hq == 72)
+    out = torch.full_like(t["q"], float("nan")), torch.full((Hq, 512), float("nan"), dtype=torch.float32, device=DEV)
     mb.fwd_static(t["q"], t["k"], t["v"], bits, bl, 128, out)
     torch.cuda.synchronize()
     assert torch.equal(out[0], ref[0]) and torch.equal(out[1], ref[1])
