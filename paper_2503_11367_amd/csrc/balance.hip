@@ -702,7 +702,6 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
         if (wave == 0) {
             // one move of the base per 64 blocks where 32 bits allow it
             const int rebase_mask = fits32_for(64) ? 63 : kSteps - 1;
-            const int apart = rebase_mask + 1;
             if (!fits32) {
                 greedy_sorted<Key52, SLOTS>(keys, nB, P, bits, rebase_mask, lane, load);
             } else if constexpr (SLOTS > 1) {

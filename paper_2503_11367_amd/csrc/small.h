@@ -4,12 +4,11 @@
 
 namespace mm {
 
-constexpr int kSmallUnits = 512;       // most 32-token units of the sequence and of the share (LDS lists)
-constexpr int kSmallBlocks = 512;      // most blocks of the share (LDS)
+// most 32-token units of the sequence, and of the share, which is no longer; most blocks of it (of at
+// least 16 tokens): what the kernels' lists in LDS hold
+constexpr int kSmallUnits = 128, kSmallBlocks = 2 * kSmallUnits;
 
-inline bool small_fits(const AttnArgs& a) {
-    return a.S <= 32 * kSmallUnits && (int64_t)a.n_blocks * a.block <= 32 * kSmallUnits && a.n_blocks <= kSmallBlocks;
-}
+inline bool small_fits(const AttnArgs& a) { return a.S <= 32 * kSmallUnits; }
 inline int64_t small_row_units(const AttnArgs& a) { return ((int64_t)a.n_blocks * a.block + 31) / 32; }
 inline int64_t small_fwd_wgs(const AttnArgs& a) { return small_row_units(a) * (a.Hq / a.Hkv) * a.kv_count; }
 
@@ -20,7 +19,7 @@ inline int64_t small_fwd_wgs(const AttnArgs& a) { return small_row_units(a) * (a
 // 2048 tokens, 1024 rows 45 us here, 53 there at head_dim 128, 30 and 32 at 64; 2048 rows, 128 and 70).
 inline bool small_fwd_wanted(const AttnArgs& a) {
     const int64_t wgs = small_fwd_wgs(a);
-    return small_fits(a) && a.S <= 4096 && wgs <= 1024 && wgs * a.S <= (1 << 21) && (a.S <= 2048 || wgs * 64 >= a.S);
+    return small_fits(a) && wgs <= 1024 && wgs * a.S <= (1 << 21) && (a.S <= 2048 || wgs * 64 >= a.S);
 }
 // Workgroups of four wavefronts, of which two or three share a CU, where the chip has no room for
 // all of eight at once (2048 tokens, 1024 rows, 16 / 4 heads, 512 workgroups: 19.6 us with four, 27 with
@@ -34,7 +33,7 @@ inline bool small_fwd_four(const AttnArgs& a) { return small_fwd_wgs(a) > 256 ||
 // 8 / 1 heads, sinks and a window, 64 units per wavefront: 161 and 107 us).
 inline bool small_bwd_wanted(const AttnArgs& a) {
     const int64_t rows = small_row_units(a), wgs = 2 * (a.S / 32) * a.Hkv + rows * a.Hq;
-    return small_fits(a) && a.S <= 4096 && wgs <= 768 && rows * (a.Hq / a.Hkv) <= 192;
+    return small_fits(a) && wgs <= 768 && rows * (a.Hq / a.Hkv) <= 192;
 }
 
 // `err`: the call's status word and its spare words (kFlagInts)
