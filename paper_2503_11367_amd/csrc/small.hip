@@ -359,7 +359,7 @@ template <int D, int NW>
 struct SmallFwdLds {
     alignas(1024) unsigned char ring[NW][2 * SmallTile<D>::kBytes];    // K, V; then the wavefront's O
     alignas(256) uint64_t kw[NW][kUnit];
-    float ml[NW][kUnit][2];
+    floatx4 ml[NW][kUnit];                                             // shift, sum, exponent of the sum
     SmallPlanLds plan;
 };
 
@@ -498,23 +498,25 @@ fwd_small_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
         *(floatx4*)(sm.ring[wave] + q * 1024 + lane * 16) =
             floatx4{o[q / 4][(q & 3) * 4], o[q / 4][(q & 3) * 4 + 1], o[q / 4][(q & 3) * 4 + 2], o[q / 4][(q & 3) * 4 + 3]};
     if (hh == 0) {
-        sm.ml[wave][li][0] = m_run;
-        sm.ml[wave][li][1] = l_run;
+        const float at = l_run != 0.f ? sum_exponent(m_run, l_run) : -INFINITY;
+        sm.ml[wave][li] = floatx4{m_run, l_run, at, 0.f};
     }
     __syncthreads();
     // Relative to the largest sum, not to the largest shift: a wavefront whose shift stayed at 0 may hold
     // sums of 2^-64 beside others of 2^64 at a shift of -128, whose weight against 0 would be flushed.  A
     // whole number, so that shifts of 0 are weighted exactly.
     float m = -INFINITY, den = 0.f, wt[NW];
+    floatx4 ml[NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w)
-        if (sm.ml[w][li][1] != 0.f) m = fmaxf(m, sum_exponent(sm.ml[w][li][0], sm.ml[w][li][1]));
+    for (int w = 0; w < NW; ++w) {
+        ml[w] = sm.ml[w][li];
+        m = fmaxf(m, ml[w][2]);
+    }
     m = __builtin_rintf(m);
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        const float l = sm.ml[w][li][1];
-        wt[w] = l != 0.f ? __builtin_amdgcn_exp2f(sm.ml[w][li][0] - m) : 0.f;
-        den += l != 0.f ? l * wt[w] : 0.f;
+        wt[w] = ml[w][1] != 0.f ? __builtin_amdgcn_exp2f(ml[w][0] - m) : 0.f;
+        den += ml[w][1] * wt[w];
     }
     if (!row_ok) return;
     const float inv = den > 0.f ? 1.f / den : 0.f;
