@@ -225,8 +225,8 @@ __device__ __forceinline__ void tile_map_by_rows_any(const TileMapJob& J, const 
 // requested before the first is used), then each thread counts one tile pair.  Bound by the
 // latency of the words and the integer work per run pair; the group's shape trades words read
 // per pair, (gq + gk) / (gq gk) tiles, against workgroups in flight.  Measured per launch:
-// 1024 x 1024 tiles of 128 x 128 302 -> 19 us, 512 x 512 88 -> 10 us against counting every
-// row of a tile against every run of keys (25 and 13 without a way out for tiles of one run, and
+// 1024 x 1024 tiles of 128 x 128 302 -> 21 us, 512 x 512 88 -> 12 us against counting every
+// row of a tile against every run of keys (back to back 19 and 10; 25 and 13 without a way out for tiles of one run, and
 // with a branch and a look at the block list around every word; tiles of 512 x 512, one 64-word step
 // in flight instead of eight, 256 x 256 of them 19 -> 12 us).  Where a group has fewer pairs than threads, tiles of
 // more than kTmSplit runs have theirs shared out over several (256 x 256 tiles of 16 x 16 in
