@@ -32,6 +32,12 @@ __device__ __forceinline__ floatx16 mfma32(bf16x8 a, bf16x8 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// C[16x16] += A[16x32] * B[32x16]: lane l holds row / column l%16 of A / B, k = 8*(l/16) .. +7, and of C
+// column l%16, rows 4*(l/16) .. +3
+__device__ __forceinline__ floatx4 mfma16(bf16x8 a, bf16x8 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 // row of a 32x32 C tile held in register r by a lane of half hh
 __device__ __forceinline__ int c_row(int r, int hh) { return 8 * (r >> 2) + 4 * hh + (r & 3); }
 

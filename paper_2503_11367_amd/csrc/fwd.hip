@@ -88,7 +88,7 @@ key_norm_body(int chunk, int g, const ushort_t* __restrict__ K, int64_t S, int32
             for (int u = 0; u < 8; ++u) a += (float)x[u] * (float)x[u];
 #pragma unroll
             for (int off = TPK / 2; off > 0; off >>= 1) a += __shfl_xor(a, off);
-            best = fmaxf(best, a);                        // a NaN norm is dropped here and caught by the row bound
+            best = fmaxf(best, a == a ? a : INFINITY);    // a NaN counts as infinite: no row is bounded then
         }
     }
     if constexpr (!NORM) return;
@@ -311,6 +311,23 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
     float m_run = 0.f, m_true = -INFINITY, l_run = 0.f;   // shift, running maximum (log2 units), row sum
+    // Row sums of a wavefront that does not track the maximum: two 16x16x32 products per half tile
+    // instead of eight two-element dot products per lane, for what the loop issues beside its
+    // 32x32x16 products is what it is bound by.  Read as the B operand of the small product, a
+    // fragment of P^T of 32 queries holds query l%16 in the lanes of even l/16 and query 16 + l%16
+    // in those of odd l/16; l_sel has ones where its row's parity picks the one or the other, so
+    // that register 0 of l_acc is the sum of query l%16 and register 1 that of query 16 + l%16.
+    // A zero times a probability must be zero: scores of these wavefronts are bounded and their
+    // probabilities finite.  Measured, 8192 tokens, 32 / 8 heads: 511 -> 500 us; a rank of four of
+    // 32768 tokens 1887 -> 1843; 32768 tokens, window of 4096, 16 heads of 64: 545 -> 529.
+    floatx4 l_acc = {0.f, 0.f, 0.f, 0.f};
+    bf16x8 l_sel;
+    {
+        const int sr = lane & 3;
+        const __bf16 one = (__bf16)(sr < 2 && ((lane >> 4) & 1) == sr ? 1.0f : 0.0f);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) l_sel[u] = one;
+    }
 
     // ---- tile transfers: which global chunk lands at this lane's LDS slot --------
     uint32_t gk[NI], gv[NI];              // byte offsets inside a tile of K / V
@@ -515,6 +532,7 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
         constexpr int PPS = EPS / 2;       // probability pairs exponentiated per S slot
         constexpr int MPS = 16 / NDB;      // scores scaled per early / folded into the maximum per late PV slot
         constexpr int DPS = 8 / NDB;       // row-sum updates per late PV slot
+        constexpr int NS = NDS + 2 * NDB;  // slots
         bf16x8 vf[NKF], pf0, pf1;
         float ef[16];                      // exp2 of the current scores
         uint32_t pw[8];                    // the same as bf16 pairs, in score-register order
@@ -523,7 +541,7 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
         // them the compiler gathers the slices where their results are consumed.
         MM_SLOT_END();
 #pragma unroll
-        for (int t = 0; t < NDS + 2 * NDB; ++t) {
+        for (int t = 0; t < NS; ++t) {
             // ---- matrix instruction and the fragment request that refills its operand ----
             if (t < NDS) {
                 if (t == 0) {
@@ -562,7 +580,19 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
                     ef[r] = __builtin_amdgcn_exp2f(s_cur[r]);
                     asm volatile("" : "+v"(ef[r]));
                 }
-            } else if (t < NDS + NDB) {
+            }
+            if constexpr (!TRACK) {
+                // the row sums, by two small products (see l_sel), and the finished scores become
+                // exponents of 2, from the slot after their last product to the end
+                if (t == NDS + NDB) l_acc = mfma16(l_sel, pf0, l_acc);
+                if (t == NS - 1) l_acc = mfma16(l_sel, pf1, l_acc);
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (NDS + 1 + r * (2 * NDB - 1) / 16 == t) {
+                        s_next[r] *= scale_log2;
+                        asm volatile("" : "+v"(s_next[r]));
+                    }
+            } else if (t >= NDS && t < NDS + NDB) {
                 // the finished scores become exponents of 2
 #pragma unroll
                 for (int u = 0; u < MPS; ++u) {
@@ -570,7 +600,7 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
                     s_next[r] *= scale_log2;
                     asm volatile("" : "+v"(s_next[r]));
                 }
-            } else {
+            } else if (t >= NDS + NDB) {
                 // row sums of the bf16-rounded probabilities (what the PV product sees)
 #pragma unroll
                 for (int u = 0; u < DPS; ++u) {
@@ -578,15 +608,13 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
                     l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[pr]),
                                                             bf16x2{(__bf16)1.0f, (__bf16)1.0f}, l_run, false);
                 }
-                if (TRACK) {
 #pragma unroll
-                    for (int u = 0; u < MPS; ++u) m_loc = fmaxf(m_loc, s_next[(t - NDS - NDB) * MPS + u]);
-                    asm volatile("" : "+v"(m_loc));
-                }
+                for (int u = 0; u < MPS; ++u) m_loc = fmaxf(m_loc, s_next[(t - NDS - NDB) * MPS + u]);
+                asm volatile("" : "+v"(m_loc));
                 asm volatile("" : "+v"(l_run));
             }
             MM_SLOT_END();
-            if (t == NDS + NDB - 1) mask_scores(e_next, kw_next, kb_next, s_next);
+            if (t == (TRACK ? NDS + NDB - 1 : NS - 1)) mask_scores(e_next, kw_next, kb_next, s_next);
         }
         if (TRACK && live_next) new_max(pair_max(m_loc), s_next);   // past the last tile the scores are stale data
     };
@@ -768,7 +796,7 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
     }
 #undef MM_SLOT_END
     // ---- epilogue -----------------------------------------------------------------
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    const float l_tot = tracked ? l_run + __shfl_xor(l_run, 32) : (lane & 16) ? l_acc[1] : l_acc[0];
     if (!row_ok) return;
     if (nchunk > 1) {
         // partial result of this slice: unnormalised O^T, the shift and the row sum

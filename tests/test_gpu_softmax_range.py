@@ -234,3 +234,27 @@ def test_slices_whose_shifts_end_far_apart(S, D):
     o_ref, lse_ref = oa.forward(f64(t["q_bits"]), f64(t["k_bits"]), f64(t["v_bits"]), oa.rows_of_blocks(blocks, 128), f[0], f[1], f[2])
     err = max_abs(bf16_to_f64(o), o_ref), rel_l2(bf16_to_f64(o), o_ref), max_abs(lse.cpu().numpy().astype(np.float64), lse_ref)
     assert err[0] < TOL_MAX and err[1] < TOL_L2 and err[2] < TOL_LSE, err
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,value", [(2, 1, 64, "nan"), (2, 1, 64, "inf"), (3, 1, 128, "nan"), (32, 8, 128, "nan"),
+                                            (32, 8, 128, "-inf")])
+def test_rows_do_not_mix_where_a_key_is_not_finite(Hq, Hkv, D, value):
+    """Two queries share the products that sum their rows: a key that is not a number, or infinite, must
+    reach no row but those that see it; the results of the others are those of the same call without it
+    to rounding.  Rows that see a NaN are NaN where lists stay whole (the aggregation leaves out a slice
+    whose sum is not a number)."""
+    lay = wl.Layout(4608, [(640, 100, 1)], [0, 1500, 4608])
+    t = make_tensors(231, 4608, 4608, Hq, Hkv, D)
+    bits, bl = gpu_bits(lay), torch.arange(36, dtype=torch.int32, device=DEV)
+    clean = mb.fwd(t["q"], t["k"], t["v"], bits, bl, 128)
+    t["k"][1410] = float(value)                      # of the first sample: rows 1410..1499 see it
+    ws = spy_workspace(mb.OP_FWD, 4608, 36, 128, Hq, Hkv, D)
+    o, lse = mb.fwd(t["q"], t["k"], t["v"], bits, bl, 128, ws=ws)
+    assert general_path(ws)
+    sees = torch.zeros(4608, dtype=torch.bool, device=DEV)
+    sees[1410:1500] = True
+    if value == "nan" and Hq == 32:
+        assert torch.isnan(o[sees]).all()
+    # tracked or not, a row's probabilities are the same; its row sum is taken in another order
+    assert rel_l2(bf16_to_f64(o[~sees]), bf16_to_f64(clean[0][~sees])) < 2 ** -9
+    assert float((lse[:, ~sees] - clean[1][:, ~sees]).abs().max()) < 1e-5
