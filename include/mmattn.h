@@ -153,6 +153,22 @@ int mmattn_balance(const uint64_t* d_W, int32_t nB, int32_t P,
                    int32_t* d_rank_of_block, uint64_t* d_load,
                    int32_t* d_rank_off, int32_t* d_rank_blocks, void* stream);
 
+/* mmattn_balance, and the loads and list offsets on the host as well: the call
+ * returns when h_load [P] and h_rank_off [P+1] hold them (the rest of the
+ * kernel may still run; work that follows on `stream` waits for it as ever).
+ *   box        pinned host memory that the GPU can write (hipHostMalloc),
+ *              MMATTN_BALANCE_BOX(P) bytes, 8-byte aligned, used by one call at a
+ *              time
+ *   ticket     differs from that of every earlier call with the same box, and
+ *              from what fresh memory holds (count from 1 in cleared memory)
+ * Not for streams under capture (MMATTN_ERR_UNSUPPORTED, nothing launched). */
+#define MMATTN_BALANCE_BOX(P) (8 * (3 * (size_t)(P)))
+int mmattn_balance_read(const uint64_t* d_W, int32_t nB, int32_t P,
+                        int32_t* d_rank_of_block, uint64_t* d_load,
+                        int32_t* d_rank_off, int32_t* d_rank_blocks,
+                        void* box, size_t box_bytes, uint32_t ticket,
+                        uint64_t* h_load, int32_t* h_rank_off, void* stream);
+
 /* Section 4.3 / 4.2: attention forward for one rank's query blocks against
  * all S keys/values under the bitfield mask; fully masked tiles are skipped.
  *   q_loc,k,v,bits,blocks  device inputs (layouts above); blocks[n_blocks]

@@ -9,6 +9,7 @@ from __future__ import annotations
 import ctypes
 import os
 import struct
+import threading
 from typing import Optional, Sequence, Tuple
 
 import numpy as np
@@ -62,6 +63,9 @@ def lib() -> ctypes.CDLL:
         L.mmattn_tile_map.argtypes = [_vp, _i64, _i32, _i32, _vp, _vp, _vp, _vp]
         L.mmattn_balance.restype = ctypes.c_int
         L.mmattn_balance.argtypes = [_vp, _i32, _i32, _vp, _vp, _vp, _vp, _vp]
+        L.mmattn_balance_read.restype = ctypes.c_int
+        L.mmattn_balance_read.argtypes = [_vp, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _sz, ctypes.c_uint32,
+                                          _vp, _vp, _vp]
         L.mmattn_fwd.restype = ctypes.c_int
         L.mmattn_fwd.argtypes = [_vp, _vp, _vp, _vp, _vp, _i32, _i32, _i64, _i32, _i32, _i32, _f32,
                                  ctypes.c_int, _vp, _vp, _vp, _sz, _vp]
@@ -175,26 +179,47 @@ def tile_map(bits: torch.Tensor, tq: int, tk: int, stream=None, want_cls=True, w
     return cls, cnt, rp
 
 
+MAX_RANKS = 1024
+_boxes = threading.local()       # a thread's box per GPU that the balancer leaves loads and offsets in
+
+
+def _balance_box(index: int) -> list:
+    """[pinned words, last ticket] of this thread for GPU `index`; a call is over before the next one
+    of its thread, so that one is enough."""
+    if not hasattr(_boxes, "of"):
+        _boxes.of = {}
+    box = _boxes.of.get(index)
+    if box is None or box[1] == 0xFFFFFFFF:      # (a used-up box starts again as a new one)
+        box = _boxes.of[index] = [torch.zeros(3 * MAX_RANKS, dtype=torch.int64, pin_memory=True), 0]
+    return box
+
+
 def balance(W: torch.Tensor, P: int, stream=None, host: bool = False):
     """mmattn_balance -> (rank_of_block int32[nB], load int64[P], rank_off
-    int32[P+1], rank_blocks int32[nB]).  load and rank_off share one
-    allocation; with host=True two more items follow, their host copies
-    (uint64 / int32 numpy arrays) fetched with a single device-to-host copy."""
+    int32[P+1], rank_blocks int32[nB]).  With host=True two more items follow,
+    load and rank_off on the host (uint64 / int32 numpy arrays), which the
+    kernel itself sends there: not for a stream under capture."""
     nB = W.numel()
     dev = W.device
     Pn = max(P, 1)
     rob = torch.empty(nB, dtype=torch.int32, device=dev)
-    both = torch.empty(8 * Pn + 4 * (Pn + 1), dtype=torch.uint8, device=dev)
-    load = both[:8 * Pn].view(torch.int64)
-    off = both[8 * Pn:].view(torch.int32)
+    load = torch.empty(Pn, dtype=torch.int64, device=dev)
+    off = torch.empty(Pn + 1, dtype=torch.int32, device=dev)
     blocks = torch.empty(nB, dtype=torch.int32, device=dev)
-    rc = lib().mmattn_balance(_ptr(W), nB, P, _ptr(rob), _ptr(load), _ptr(off), _ptr(blocks),
-                              _stream(stream))
-    _check("mmattn_balance", rc)
     if not host:
+        rc = lib().mmattn_balance(_ptr(W), nB, P, _ptr(rob), _ptr(load), _ptr(off), _ptr(blocks),
+                                  _stream(stream))
+        _check("mmattn_balance", rc)
         return rob, load, off, blocks
-    h = both.cpu().numpy()
-    return rob, load, off, blocks, h[:8 * Pn].view("<u8"), h[8 * Pn:].view("<i4")
+    here = (ctypes.c_uint64 * (Pn + Pn // 2 + 1))()
+    box = _balance_box(dev.index)
+    box[1] += 1
+    rc = lib().mmattn_balance_read(_ptr(W), nB, P, _ptr(rob), _ptr(load), _ptr(off), _ptr(blocks),
+                                   box[0].data_ptr(), 24 * MAX_RANKS, box[1], ctypes.addressof(here),
+                                   ctypes.addressof(here) + 8 * Pn, _stream(stream))
+    _check("mmattn_balance", rc)
+    return (rob, load, off, blocks, np.frombuffer(here, "<u8", Pn),
+            np.frombuffer(here, "<i4", Pn + 1, 8 * Pn))
 
 
 def fwd(q_loc: torch.Tensor, k: torch.Tensor, v: torch.Tensor, bits: torch.Tensor,

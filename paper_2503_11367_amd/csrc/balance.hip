@@ -41,6 +41,22 @@ constexpr int kBalLdsRob = 8192;
 constexpr int kBalRobAt = kBalLdsRob, kBalHistAt = kBalLdsRob + 4096;
 static_assert((MMATTN_MAX_BLOCKS - kBalHistAt) * 8 >= kBalThreads / kWave * MMATTN_MAX_RANKS * 2, "histograms fit");
 
+// The loads and offsets for a host that waits for them: words of 32 bits of data and the call's
+// ticket, three per rank (load, low and high; end of its list).  A word is stored as a whole, so that
+// the ticket says for each by itself that it has arrived: no order between stores is needed, nor a
+// release, whose write-back of the L2 takes as long as a launch.
+__device__ __forceinline__ void tell(const BalanceBox& host, int32_t at, uint32_t v) {
+    __hip_atomic_store(host.box + at, ((uint64_t)host.ticket << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void tell_load(const BalanceBox& host, int32_t r, uint64_t v) {
+    if (!host.box) return;
+    tell(host, 3 * r, (uint32_t)v);
+    tell(host, 3 * r + 1, (uint32_t)(v >> 32));
+}
+__device__ __forceinline__ void tell_end(const BalanceBox& host, int32_t r, int32_t end) {
+    if (host.box) tell(host, 3 * r + 2, (uint32_t)end);
+}
+
 struct MinKey { uint64_t load; uint32_t rank; };
 
 __device__ __forceinline__ bool key_less(const MinKey& a, const MinKey& b) {
@@ -416,8 +432,10 @@ struct Ballots {
         else if (lane == at) { lo = (uint32_t)grown; hi = (uint32_t)(grown >> 32); rk = g; }
         return g;
     }
+    __device__ __forceinline__ int32_t rank() const { return (int32_t)rk; }
+    __device__ __forceinline__ uint64_t load_of() const { return ((uint64_t)hi << 32) | lo; }
     __device__ __forceinline__ void loads(int32_t P, int lane, uint64_t* __restrict__ load) const {
-        if (lane < P) load[rk] = ((uint64_t)hi << 32) | lo;
+        if (lane < P) load[rk] = load_of();
     }
 };
 
@@ -426,7 +444,7 @@ struct Ballots {
 // all go to the first rank that the others leave.
 __device__ void few_blocks(const uint64_t* __restrict__ W, int32_t nB, int32_t P, int lane,
                            int32_t* __restrict__ rank_of_block, uint64_t* __restrict__ load,
-                           int32_t* __restrict__ rank_off, int32_t* __restrict__ rank_blocks) {
+                           int32_t* __restrict__ rank_off, int32_t* __restrict__ rank_blocks, const BalanceBox& host) {
     const uint64_t w = lane < nB ? W[lane] : 0;
     int pos = lane < nB ? 0 : lane;                    // place in the visiting order
     for (int c = 0; c < nB; ++c) {
@@ -440,7 +458,10 @@ __device__ void few_blocks(const uint64_t* __restrict__ W, int32_t nB, int32_t P
     int g = 0;
     if (nB <= P) {
         g = min(pos, (int)__popcll(__ballot(w != 0)));
-        for (int r = lane; r < P; r += kWave) load[r] = r < nB ? w_at : 0;
+        for (int r = lane; r < P; r += kWave) {
+            load[r] = r < nB ? w_at : 0;
+            tell_load(host, r, r < nB ? w_at : 0);
+        }
     } else {
         const int b_at = __builtin_amdgcn_ds_permute(pos * 4, lane);
         Ballots ranks(P, lane);
@@ -449,6 +470,7 @@ __device__ void few_blocks(const uint64_t* __restrict__ W, int32_t nB, int32_t P
             if (lane == __builtin_amdgcn_readlane(b_at, t)) g = got;
         }
         ranks.loads(P, lane, load);
+        if (lane < P) tell_load(host, ranks.rank(), ranks.load_of());
     }
     int before = 0, upto = 0;                          // list entries ahead of this block; of ranks <= lane
     for (int c = 0; c < nB; ++c) {
@@ -460,7 +482,10 @@ __device__ void few_blocks(const uint64_t* __restrict__ W, int32_t nB, int32_t P
         rank_of_block[lane] = g;
         rank_blocks[before] = lane;
     }
-    for (int r = lane; r < P; r += kWave) rank_off[r + 1] = r < kWave ? upto : nB;
+    for (int r = lane; r < P; r += kWave) {
+        rank_off[r + 1] = r < kWave ? upto : nB;
+        tell_end(host, r, r < kWave ? upto : nB);
+    }
     if (lane == 0) rank_off[0] = 0;
 }
 
@@ -606,7 +631,7 @@ template <int SLOTS, int THREADS>
 __global__ void __launch_bounds__(THREADS)
 balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
                int32_t* __restrict__ rank_of_block, uint64_t* __restrict__ load,
-               int32_t* __restrict__ rank_off, int32_t* __restrict__ rank_blocks) {
+               int32_t* __restrict__ rank_off, int32_t* __restrict__ rank_blocks, const BalanceBox host) {
     constexpr int kWaves = THREADS / kWave;
     constexpr bool kOne = kWaves == 1;                 // at most kBalCounted blocks
     constexpr int kLds = kOne ? 4 * kWave : MMATTN_MAX_BLOCKS;
@@ -623,7 +648,7 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
     uint16_t* hist = (uint16_t*)(lds + kHistAt);    // [wave][rank]
 
     if (kOne && P > 1 && (nB <= P || nB <= kBalFew)) {
-        few_blocks(W, nB, P, lane, rank_of_block, load, rank_off, rank_blocks);
+        few_blocks(W, nB, P, lane, rank_of_block, load, rank_off, rank_blocks, host);
         return;
     }
     // sum and largest workload; small ones go to LDS as sort keys on the way
@@ -653,6 +678,8 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
             load[0] = sum;
             rank_off[0] = 0;
             rank_off[1] = nB;
+            tell_load(host, 0, sum);
+            tell_end(host, 0, nB);
         }
         return;
     }
@@ -725,7 +752,7 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
             if (rob_lds) rob[b] = (uint16_t)g;
         }
     } else if (kOne) {
-        few_blocks(W, nB, P, lane, rank_of_block, load, rank_off, rank_blocks);
+        few_blocks(W, nB, P, lane, rank_of_block, load, rank_off, rank_blocks, host);
         return;
     } else {
         int32_t* order = rank_blocks;                  // until phase 3 overwrites it
@@ -756,6 +783,7 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
         }
     }
     __syncthreads();
+    const uint64_t my_load = host.box && tid < P ? load[tid] : 0;
 
     // phase 3.  Wavefront `wave` takes blocks first .. last-1
     const int per = ((nB + THREADS - 1) / THREADS) * kWave;
@@ -806,6 +834,8 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
     }
     if (tid < P) {
         rank_off[tid + 1] = inc;
+        tell_load(host, tid, my_load);
+        tell_end(host, tid, inc);
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) hist[w * P + tid] = (uint16_t)(inc - total + before[w]);
     }
@@ -822,20 +852,21 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
 }
 
 int launch_balance(const uint64_t* d_W, int32_t nB, int32_t P, int32_t* d_rank_of_block,
-                   uint64_t* d_load, int32_t* d_rank_off, int32_t* d_rank_blocks, hipStream_t st) {
+                   uint64_t* d_load, int32_t* d_rank_off, int32_t* d_rank_blocks, const BalanceBox& host,
+                   hipStream_t st) {
     // registers per lane for the rank loads: the smallest instantiation that holds P ranks
     if (nB <= kBalCounted)
         hipLaunchKernelGGL((balance_kernel<1, kWave>), dim3(1), dim3(kWave), 0, st, d_W, nB, P,
-                           d_rank_of_block, d_load, d_rank_off, d_rank_blocks);
+                           d_rank_of_block, d_load, d_rank_off, d_rank_blocks, host);
     else if (P <= kWave)
         hipLaunchKernelGGL((balance_kernel<1, kBalThreads>), dim3(1), dim3(kBalThreads), 0, st, d_W, nB, P,
-                           d_rank_of_block, d_load, d_rank_off, d_rank_blocks);
+                           d_rank_of_block, d_load, d_rank_off, d_rank_blocks, host);
     else if (P <= 4 * kWave)
         hipLaunchKernelGGL((balance_kernel<4, kBalThreads>), dim3(1), dim3(kBalThreads), 0, st, d_W, nB, P,
-                           d_rank_of_block, d_load, d_rank_off, d_rank_blocks);
+                           d_rank_of_block, d_load, d_rank_off, d_rank_blocks, host);
     else
         hipLaunchKernelGGL((balance_kernel<kBalSlots, kBalThreads>), dim3(1), dim3(kBalThreads), 0, st, d_W, nB, P,
-                           d_rank_of_block, d_load, d_rank_off, d_rank_blocks);
+                           d_rank_of_block, d_load, d_rank_off, d_rank_blocks, host);
     MM_LAUNCH_CHECK();
     return MMATTN_OK;
 }

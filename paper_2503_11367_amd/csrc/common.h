@@ -133,8 +133,14 @@ int launch_encode(const mmattn_span* spans, int32_t n_spans, const int64_t* samp
 int launch_tile_map(const uint64_t* d_bits, int64_t S, const int32_t* d_blocks, int32_t block,
                     int64_t n_rows, int32_t tq, int32_t tk, uint8_t* d_cls, uint32_t* d_cnt,
                     uint64_t* d_rowpairs, hipStream_t st);
+// Host memory that the balancer writes the loads and offsets to as well (box: none)
+struct BalanceBox {
+    uint64_t* box;
+    uint32_t ticket;
+};
 int launch_balance(const uint64_t* d_W, int32_t nB, int32_t P, int32_t* d_rank_of_block,
-                   uint64_t* d_load, int32_t* d_rank_off, int32_t* d_rank_blocks, hipStream_t st);
+                   uint64_t* d_load, int32_t* d_rank_off, int32_t* d_rank_blocks, const BalanceBox& host,
+                   hipStream_t st);
 
 // optional per-stage event pairs (measurement aid, see mmattn_stage_events)
 struct StageEvents { hipEvent_t start, stop; };

@@ -228,3 +228,13 @@ def test_span_list_packing_keeps_nothing_of_long_lists():
         assert tracemalloc.get_traced_memory()[0] - before < 4 << 20
     finally:
         tracemalloc.stop()
+
+
+def test_balance_read_validation():
+    f = mb.lib().mmattn_balance_read
+    ok = dict(W=FAKE, nB=8, P=2, rob=FAKE, load=FAKE, off=FAKE, blocks=FAKE, box=FAKE, size=48, ticket=1, h=FAKE, ho=FAKE,
+              st=0)
+    rc = lambda **k: f(*dict(ok, **k).values())                                 # noqa: E731
+    assert all(rc(**{n: 0}) == -1 for n in ("W", "rob", "load", "off", "blocks", "box", "h", "ho"))
+    assert rc(nB=0) == -2 and rc(P=0) == -2 and rc(nB=1 << 20) == -3 and rc(P=5000) == -3
+    assert rc(box=FAKE + 4) == -2 and rc(size=47) == -4

@@ -1,5 +1,7 @@
 """GPU parity, integer stages: mask encode, tile map, balancer -- bit-exact
 against the oracle (through the C ABI)."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -442,3 +444,40 @@ def test_plan_chain_random_shapes(batch):
         assert np.array_equal(rob.cpu().numpy(), r2[0]), what
         assert np.array_equal(load.cpu().numpy().view(np.uint64), r2[1]), what
         assert np.array_equal(off.cpu().numpy(), r2[2]) and np.array_equal(rb.cpu().numpy(), r2[3]), what
+
+
+@pytest.mark.parametrize("nB,P", [(1, 1), (500, 1), (1, 5), (8, 3), (40, 40), (40, 1024), (64, 7), (65, 64), (700, 8),
+                                  (1025, 5), (3000, 300), (16384, 1024)])
+def test_balance_on_the_host(nB, P):
+    """The loads and offsets that the kernel sends to the host are those that it leaves on the GPU, on
+    every way through it (workloads of any size among them), call after call."""
+    rng = np.random.default_rng(nB + P)
+    for hi in (2, 2 ** 20, 2 ** 40, 2 ** 60 // nB):
+        Wt = torch.from_numpy(rng.integers(0, hi, size=nB)).to(DEV)
+        _, load, off, _, load_h, off_h = mb.balance(Wt, P, host=True)
+        assert load_h.dtype == np.uint64 and off_h.dtype == np.int32 and off_h[0] == 0 and off_h[-1] == nB
+        assert np.array_equal(load.cpu().numpy().view(np.uint64), load_h) and np.array_equal(off.cpu().numpy(), off_h)
+
+
+def test_balance_on_the_host_from_threads():
+    """Threads with streams of their own, each with its own box."""
+    W = [torch.from_numpy(np.random.default_rng(i).integers(0, 2 ** 20, size=300 + 100 * i)).to(DEV) for i in range(4)]
+    want = [ob.lpt(w.cpu().numpy().view(np.uint64).tolist(), 8) for w in W]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for _ in range(20):
+                got = mb.balance(W[i], 8, host=True)
+                if not (np.array_equal(got[4], want[i][1]) and np.array_equal(got[5], want[i][2])):
+                    wrong.append(i)
+            stream.synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
