@@ -318,8 +318,9 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
     // in those of odd l/16; l_sel has ones where its row's parity picks the one or the other, so
     // that register 0 of l_acc is the sum of query l%16 and register 1 that of query 16 + l%16.
     // A zero times a probability must be zero: scores of these wavefronts are bounded and their
-    // probabilities finite.  Measured, 8192 tokens, 32 / 8 heads: 511 -> 500 us; a rank of four of
-    // 32768 tokens 1887 -> 1843; 32768 tokens, window of 4096, 16 heads of 64: 545 -> 529.
+    // probabilities finite.  With the scaling of the scores spread as it is below, measured: 8192
+    // tokens, 32 / 8 heads 519 -> 502 us; a rank of four of 32768 tokens 1922 -> 1864; 32768 tokens,
+    // window of 4096, 16 heads of 64 555 -> 537.
     floatx4 l_acc = {0.f, 0.f, 0.f, 0.f};
     bf16x8 l_sel;
     {
@@ -583,12 +584,13 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
             }
             if constexpr (!TRACK) {
                 // the row sums, by two small products (see l_sel), and the finished scores become
-                // exponents of 2, from the slot after their last product to the end
-                if (t == NDS + NDB) l_acc = mfma16(l_sel, pf0, l_acc);
+                // exponents of 2, spread over all slots that are left (the scale is positive: masked
+                // ones may wait for it at -inf)
+                if (t == NDS + NDB - 1) l_acc = mfma16(l_sel, pf0, l_acc);
                 if (t == NS - 1) l_acc = mfma16(l_sel, pf1, l_acc);
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    if (NDS + 1 + r * (2 * NDB - 1) / 16 == t) {
+                    if (NDS + r * (2 * NDB) / 16 == t) {
                         s_next[r] *= scale_log2;
                         asm volatile("" : "+v"(s_next[r]));
                     }
@@ -614,7 +616,7 @@ fwd_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
                 asm volatile("" : "+v"(l_run));
             }
             MM_SLOT_END();
-            if (t == (TRACK ? NDS + NDB - 1 : NS - 1)) mask_scores(e_next, kw_next, kb_next, s_next);
+            if (t == NDS + NDB - 1) mask_scores(e_next, kw_next, kb_next, s_next);
         }
         if (TRACK && live_next) new_max(pair_max(m_loc), s_next);   // past the last tile the scores are stale data
     };
