@@ -1,6 +1,7 @@
 // C ABI of libmmattn: argument validation (host only, before any HIP call)
 // and dispatch to the kernels.  See include/mmattn.h for the contract.
 #include <algorithm>
+#include <chrono>
 #include "common.h"
 #include "small.h"
 
@@ -67,8 +68,11 @@ int check_balance(const void* d_W, int32_t nB, int32_t P, const void* d_rank_of_
     return MMATTN_OK;
 }
 
-// looks at a word of the balancer's between two looks at its stream (some 100 us)
-constexpr uint32_t kSpinsPerQuery = 4096;
+// How long a host looks for the balancer's words by itself, and how often at the clock meanwhile: longer
+// than plans take, shorter than a step that may be queued ahead of one.  (Not at the stream: a query
+// makes the queue report, 13 us of a plan of 1738 blocks over 100 ranks.)
+constexpr std::chrono::milliseconds kSpinFor{2};
+constexpr uint32_t kSpinsPerLook = 256;
 
 }  // namespace
 
@@ -185,9 +189,10 @@ int mmattn_balance_read(const uint64_t* d_W, int32_t nB, int32_t P, int32_t* d_r
     rc = launch_balance(d_W, nB, P, d_rank_of_block, d_load, d_rank_off, d_rank_blocks,
                         BalanceBox{(uint64_t*)box, ticket}, st);
     if (rc != MMATTN_OK) return rc;
-    // word by word; a stream that has finished, or failed, ends the wait for one that does not come
+    // word by word; after a while by the runtime's own wait, which also ends where the GPU failed
     const int n = 3 * P;
     const uint64_t* words = (const uint64_t*)box;
+    const auto began = std::chrono::steady_clock::now();
     bool finished = false;
     h_rank_off[0] = 0;
     for (int i = 0; i < n; ++i) {
@@ -195,15 +200,13 @@ int mmattn_balance_read(const uint64_t* d_W, int32_t nB, int32_t P, int32_t* d_r
         for (uint32_t spins = 1; (uint32_t)((w = __atomic_load_n(words + i, __ATOMIC_RELAXED)) >> 32) != ticket; ++spins) {
             if (finished) return MMATTN_ERR_HIP;
             __builtin_ia32_pause();
-            if (spins % kSpinsPerQuery) continue;
-            const hipError_t e = hipStreamQuery(st);
-            if (e != hipSuccess && e != hipErrorNotReady) return MMATTN_ERR_HIP;
-            finished = e == hipSuccess;
+            if (spins % kSpinsPerLook || std::chrono::steady_clock::now() - began < kSpinFor) continue;
+            MM_HIP_TRY(hipStreamSynchronize(st));
+            finished = true;
         }
-        const int r = i / 3;
-        if (i % 3 == 0) h_load[r] = (uint32_t)w;
-        else if (i % 3 == 1) h_load[r] |= (w & 0xFFFFFFFFull) << 32;
-        else h_rank_off[r + 1] = (int32_t)(uint32_t)w;
+        if (i < P) h_load[i] = (uint32_t)w;
+        else if (i < 2 * P) h_load[i - P] |= (w & 0xFFFFFFFFull) << 32;
+        else h_rank_off[i - 2 * P + 1] = (int32_t)(uint32_t)w;
     }
     return MMATTN_OK;
 }

@@ -42,19 +42,20 @@ constexpr int kBalRobAt = kBalLdsRob, kBalHistAt = kBalLdsRob + 4096;
 static_assert((MMATTN_MAX_BLOCKS - kBalHistAt) * 8 >= kBalThreads / kWave * MMATTN_MAX_RANKS * 2, "histograms fit");
 
 // The loads and offsets for a host that waits for them: words of 32 bits of data and the call's
-// ticket, three per rank (load, low and high; end of its list).  A word is stored as a whole, so that
+// ticket, P each of the loads' low and high halves and of the ends of the lists (neighbouring lanes
+// store neighbouring words: one by one over the link, those of 100 ranks took 13 us).  A word is stored as a whole, so that
 // the ticket says for each by itself that it has arrived: no order between stores is needed, nor a
 // release, whose write-back of the L2 takes as long as a launch.
 __device__ __forceinline__ void tell(const BalanceBox& host, int32_t at, uint32_t v) {
     __hip_atomic_store(host.box + at, ((uint64_t)host.ticket << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-__device__ __forceinline__ void tell_load(const BalanceBox& host, int32_t r, uint64_t v) {
+__device__ __forceinline__ void tell_load(const BalanceBox& host, int32_t P, int32_t r, uint64_t v) {
     if (!host.box) return;
-    tell(host, 3 * r, (uint32_t)v);
-    tell(host, 3 * r + 1, (uint32_t)(v >> 32));
+    tell(host, r, (uint32_t)v);
+    tell(host, P + r, (uint32_t)(v >> 32));
 }
-__device__ __forceinline__ void tell_end(const BalanceBox& host, int32_t r, int32_t end) {
-    if (host.box) tell(host, 3 * r + 2, (uint32_t)end);
+__device__ __forceinline__ void tell_end(const BalanceBox& host, int32_t P, int32_t r, int32_t end) {
+    if (host.box) tell(host, 2 * P + r, (uint32_t)end);
 }
 
 struct MinKey { uint64_t load; uint32_t rank; };
@@ -460,7 +461,7 @@ __device__ void few_blocks(const uint64_t* __restrict__ W, int32_t nB, int32_t P
         g = min(pos, (int)__popcll(__ballot(w != 0)));
         for (int r = lane; r < P; r += kWave) {
             load[r] = r < nB ? w_at : 0;
-            tell_load(host, r, r < nB ? w_at : 0);
+            tell_load(host, P, r, r < nB ? w_at : 0);
         }
     } else {
         const int b_at = __builtin_amdgcn_ds_permute(pos * 4, lane);
@@ -470,7 +471,7 @@ __device__ void few_blocks(const uint64_t* __restrict__ W, int32_t nB, int32_t P
             if (lane == __builtin_amdgcn_readlane(b_at, t)) g = got;
         }
         ranks.loads(P, lane, load);
-        if (lane < P) tell_load(host, ranks.rank(), ranks.load_of());
+        if (lane < P) tell_load(host, P, ranks.rank(), ranks.load_of());
     }
     int before = 0, upto = 0;                          // list entries ahead of this block; of ranks <= lane
     for (int c = 0; c < nB; ++c) {
@@ -484,7 +485,7 @@ __device__ void few_blocks(const uint64_t* __restrict__ W, int32_t nB, int32_t P
     }
     for (int r = lane; r < P; r += kWave) {
         rank_off[r + 1] = r < kWave ? upto : nB;
-        tell_end(host, r, r < kWave ? upto : nB);
+        tell_end(host, P, r, r < kWave ? upto : nB);
     }
     if (lane == 0) rank_off[0] = 0;
 }
@@ -678,8 +679,8 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
             load[0] = sum;
             rank_off[0] = 0;
             rank_off[1] = nB;
-            tell_load(host, 0, sum);
-            tell_end(host, 0, nB);
+            tell_load(host, P, 0, sum);
+            tell_end(host, P, 0, nB);
         }
         return;
     }
@@ -834,8 +835,8 @@ balance_kernel(const uint64_t* __restrict__ W, int32_t nB, int32_t P,
     }
     if (tid < P) {
         rank_off[tid + 1] = inc;
-        tell_load(host, tid, my_load);
-        tell_end(host, tid, inc);
+        tell_load(host, P, tid, my_load);
+        tell_end(host, P, tid, inc);
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) hist[w * P + tid] = (uint16_t)(inc - total + before[w]);
     }
