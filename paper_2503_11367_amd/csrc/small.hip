@@ -20,8 +20,8 @@
 // per wavefront, about 1 us each; on larger shares by the transfers, for 32 rows of one head use a
 // unit where the general path's 128 or 256 do (waiting: 57 % of the wavefronts' cycles at 512 tokens, 68 % in the
 // backward; 54 and 52 % at 1920, 18 and 22 % more for a turn to issue; no LDS bank conflicts).  Measured,
-// whole calls back to back: 512 tokens, one head, 128 rows 16.9 -> 7.7 us forward, 27.9 -> 8.9 us backward; 1920
-// tokens, 960 rows, 6 / 2 heads (head_dim 128) 32 -> 15 and 74 -> 33 us; 4096 tokens, 1024 rows, 8 / 2 heads
+// whole calls back to back: 512 tokens, one head, 128 rows 16.9 -> 7.0 us forward, 27.9 -> 7.1 us backward; 1920
+// tokens, 960 rows, 6 / 2 heads (head_dim 128) 32 -> 14 and 74 -> 27 us; 4096 tokens, 1024 rows, 8 / 2 heads
 // 44 -> 24 and 93 -> 61 us (128), 27 -> 14 and 69 -> 47 us (64).  In a sweep of 2000 shapes the calls that come
 // here (up to 4096 tokens) take about half of the general path's time on the mean; the slowest is 3 % behind.
 #include "attn_common.h"
@@ -66,7 +66,8 @@ struct SmallShare {
     }
 };
 
-// Block list into LDS; false when an entry is out of range (workgroup-uniform)
+// Block list into LDS; false when an entry is out of range (workgroup-uniform).  What the wavefronts
+// have fetched into LDS before is there for all of them behind it.
 template <int NT>
 __device__ __forceinline__ bool small_check(const SmallShare& sh, int32_t* blk) {
     const int32_t n_seq = sh.S / sh.block;
@@ -79,6 +80,7 @@ __device__ __forceinline__ bool small_check(const SmallShare& sh, int32_t* blk) 
         }
         blk[i] = b;
     }
+    wait_landed<0>();
     bad = __syncthreads_or(bad);
     if (blockIdx.x == 0 && threadIdx.x < kFlagInts) sh.err[threadIdx.x] = threadIdx.x == 0 ? bad : 0;
     return !bad;
@@ -303,6 +305,20 @@ struct SmallTile {
         T::src_of(4 * i + (lane >> 4), lane & 15, r, c);
         return (uint32_t)(min(r, last) * row_stride + c * 16);
     }
+    // The workgroup's own 32 rows into a tile that all its wavefronts read their fragments from, a share of the
+    // transfers each.  As fragments from memory, by every wavefront for itself, an instruction took 32
+    // pieces of 32 bytes, which the L1 cache serves one by one: until the list is checked, a dQ workgroup of
+    // 1920 tokens, 6 heads took 6.6 us so and takes 1.7 now (Q, dO, O), a forward one 2.7 and 1.5, a dK
+    // one 5.0 and 0.9.
+    template <int NW>
+    __device__ static __forceinline__ void fetch_own(const ushort_t* rows, int64_t row_stride, int last, uint32_t tile,
+                                                     int wave, int lane) {
+#pragma unroll
+        for (int i0 = 0; i0 < NI; i0 += NW) {
+            const int i = i0 + wave;
+            if (i < NI) dma16(rows, source(lane, i, row_stride, last), tile + i * 1024);
+        }
+    }
     __device__ __forceinline__ bf16x8 read_row(uint32_t tile, int ds) const {
         return __builtin_bit_cast(bf16x8, *(lds_u4)(uintptr_t)(tile + row[ds]));
     }
@@ -381,19 +397,14 @@ fwd_small_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
     const int row = rb * kUnit + li;
     const bool row_ok = row < sh.n_loc;
 
-    bf16x8 qf[NDS];
+    const uint32_t q_tile = lds_addr_of(sm.ring[0]);
+    Tile::template fetch_own<NW>(Q + ((int64_t)rb * kUnit * Hq_s + h) * D, (int64_t)Hq_s * D * 2,
+                                 min(kUnit, sh.n_loc - rb * kUnit) - 1, q_tile, wave, lane);
     uint64_t first[kSmallAhead];
 #pragma unroll
     for (int a = 0; a < kSmallAhead; ++a) {
         first[a] = 0;
         if ((wave + a * NW) * kWave < sh.S) first[a] = sh.bits[(wave + a * NW) * kWave + lane];
-    }
-#pragma unroll
-    for (int ds = 0; ds < NDS; ++ds) qf[ds] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-    if (row_ok) {
-        const ushort_t* qp = Q + ((int64_t)row * Hq_s + h) * D + hh * 8;
-#pragma unroll
-        for (int ds = 0; ds < NDS; ++ds) qf[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + ds * 16));
     }
     if (!small_check<64 * NW>(sh, sm.plan.blk)) return;
     int32_t q_pos = 0;
@@ -406,6 +417,13 @@ fwd_small_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
     }
     Tile t;
     t.init(lane, (int64_t)Hkv_s * D * 2);
+    bf16x8 qf[NDS];                                            // (read before the barriers of the list, behind which
+#pragma unroll                                                 // the ring is the wavefronts' own)
+    for (int ds = 0; ds < NDS; ++ds) qf[ds] = t.read_row(q_tile, ds);
+    if (!row_ok) {
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) qf[ds] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+    }
     const int n = small_keys_of_rows<NW>(sh, sm.plan, first, row_ok, q_ss, q_att, q_pos, wave, lane);
 
     const uint32_t k_tile = lds_addr_of(sm.ring[wave]), v_tile = k_tile + Tile::kBytes, kw = lds_addr_of(sm.kw[wave]);
@@ -610,36 +628,26 @@ __device__ __forceinline__ void small_dq(SmallBwdLds<D, NW>& sm, const SmallBwdA
     const int row = rb * kUnit + li;
     const bool row_ok = row < sh.n_loc;
 
+    const uint32_t own = lds_addr_of(sm.ring[0]);              // Q, dO, O
+    {
+        const int64_t off = ((int64_t)rb * kUnit * p.Hq + h) * D, row_bytes = (int64_t)p.Hq * D * 2;
+        const int last = min(kUnit, sh.n_loc - rb * kUnit) - 1;
+        static_assert(NW >= 2, "two rings hold three tiles");
+        Tile::template fetch_own<NW>(p.Q + off, row_bytes, last, own, wave, lane);
+        Tile::template fetch_own<NW>(p.dO + off, row_bytes, last, own + Tile::kBytes, wave, lane);
+        Tile::template fetch_own<NW>(p.O + off, row_bytes, last, own + 2 * Tile::kBytes, wave, lane);
+    }
     uint64_t first[kSmallAhead];
 #pragma unroll
     for (int a = 0; a < kSmallAhead; ++a) {
         first[a] = 0;
         if ((wave + a * NW) * kWave < sh.S) first[a] = sh.bits[(wave + a * NW) * kWave + lane];
     }
-    bf16x8 qf[NDS], dof[NDS];
-    float lse2 = INFINITY, delta = 0.f;                        // +inf: every probability is 0
-#pragma unroll
-    for (int ds = 0; ds < NDS; ++ds) {
-        qf[ds] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-        dof[ds] = qf[ds];
-    }
+    float lse2 = INFINITY;                                     // every probability is 0
     if (row_ok) {
-        const int64_t off = ((int64_t)row * p.Hq + h) * D + hh * 8;
-        bf16x8 of[NDS];
-#pragma unroll
-        for (int ds = 0; ds < NDS; ++ds) {
-            qf[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(p.Q + off + ds * 16));
-            dof[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(p.dO + off + ds * 16));
-            of[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(p.O + off + ds * 16));
-        }
         const float l2 = p.lse[(int64_t)h * sh.n_loc + row] * kLog2e;
         lse2 = l2 == -INFINITY ? INFINITY : l2;                // a row that sees no key
-#pragma unroll
-        for (int ds = 0; ds < NDS; ++ds)
-#pragma unroll
-            for (int u = 0; u < 8; ++u) delta += (float)of[ds][u] * (float)dof[ds][u];
     }
-    delta += __shfl_xor(delta, 32);
     if (!small_check<64 * NW>(sh, sm.plan.blk)) return;
     int32_t q_pos = 0;
     uint32_t q_ss = 0, q_att = 0;
@@ -651,6 +659,25 @@ __device__ __forceinline__ void small_dq(SmallBwdLds<D, NW>& sm, const SmallBwdA
     }
     Tile t;
     t.init(lane, (int64_t)p.Hkv * D * 2);
+    bf16x8 qf[NDS], dof[NDS];                                  // (read before the barriers of the list, behind which
+    float delta = 0.f;                                         // the ring is the wavefronts' own)
+#pragma unroll
+    for (int ds = 0; ds < NDS; ++ds) {
+        qf[ds] = t.read_row(own, ds);
+        dof[ds] = t.read_row(own + Tile::kBytes, ds);
+    }
+#pragma unroll
+    for (int ds = 0; ds < NDS; ++ds) {
+        const bf16x8 of = t.read_row(own + 2 * Tile::kBytes, ds);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) delta += (float)of[u] * (float)dof[ds][u];
+    }
+    if (!row_ok) {
+        delta = 0.f;
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) qf[ds] = dof[ds] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+    }
+    delta += __shfl_xor(delta, 32);
     const int n = small_keys_of_rows<NW>(sh, sm.plan, first, row_ok, q_ss, q_att, q_pos, wave, lane);
 
     const uint32_t k_tile = lds_addr_of(sm.ring[wave]), v_tile = k_tile + Tile::kBytes, kw = lds_addr_of(sm.kw[wave]);
@@ -739,27 +766,33 @@ __device__ __forceinline__ void small_dkv(SmallBwdLds<D, NW>& sm, const SmallBwd
     const int rep = p.Hq / p.Hkv, kb = wg / p.Hkv, g = wg % p.Hkv;
     const int key = kb * kUnit + li;
 
-    // resident operands: the keys for S, in dK the values for dP.  (Both in registers, dK at D = 128
-    // would spill: there the keys are read from LDS, a fragment per product.)
-    bf16x8 res[NDS];
     const uint64_t k_word = sh.bits[key];
+    const uint32_t own = lds_addr_of(sm.ring[0]);              // K; V
     {
-        const int64_t off = ((int64_t)key * p.Hkv + g) * D + hh * 8;
-#pragma unroll
-        for (int ds = 0; ds < NDS; ++ds)
-            res[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)((KR ? p.V : p.K) + off + ds * 16));
-        static_assert(NDS <= NW, "a fragment per wavefront");
-        if (KR && wave < NDS)
-            *(u32x4*)(sm.key_frags[wave] + lane * 16) = *(const u32x4*)(p.K + off + wave * 16);
+        const int64_t off = ((int64_t)kb * kUnit * p.Hkv + g) * D, row_bytes = (int64_t)p.Hkv * D * 2;
+        Tile::template fetch_own<NW>(p.K + off, row_bytes, kUnit - 1, own, wave, lane);
+        if (KR) Tile::template fetch_own<NW>(p.V + off, row_bytes, kUnit - 1, own + Tile::kBytes, wave, lane);
     }
     if (!small_check<64 * NW>(sh, sm.plan.blk)) return;
+    Tile t;
+    const int64_t row_bytes = (int64_t)p.Hq * D * 2;
+    t.init(lane, row_bytes);
+    // Resident operands: the keys for S, in dK the values for dP.  (Both in registers, dK at D = 128
+    // would spill: there the keys are read from LDS, a fragment per product.)  They leave the ring before the
+    // barriers of the list, behind which it is the wavefronts' own.
+    bf16x8 res[NDS];
+#pragma unroll
+    for (int ds = 0; ds < NDS; ++ds) res[ds] = t.read_row(KR ? own + Tile::kBytes : own, ds);
+    static_assert(NDS <= NW, "a fragment per wavefront");
+    if (KR) {
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds)
+            if (wave == ds) *(u32x4*)(sm.key_frags[ds] + lane * 16) = __builtin_bit_cast(u32x4, t.read_row(own, ds));
+    }
     const uint32_t k_ss = word_ss(k_word), k_mod = word_mod(k_word);
     const int n_list = small_rows_of_keys<NW>(sh, sm.plan, k_ss, k_mod, key, wave, lane);
     const int n = n_list * rep;                                // item: (head of the group, entry of the list)
 
-    Tile t;
-    const int64_t row_bytes = (int64_t)p.Hq * D * 2;
-    t.init(lane, row_bytes);
     const uint32_t q_tile = lds_addr_of(sm.ring[wave]), d_tile = q_tile + Tile::kBytes, lse_at = lds_addr_of(sm.lse[wave]);
     const int n_units = (sh.n_loc + kUnit - 1) / kUnit, last_row = (sh.n_loc - 1) % kUnit;
 
