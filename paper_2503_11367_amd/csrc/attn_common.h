@@ -171,6 +171,32 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// A wavefront's 32 rows of a tensor into a tile of its own in LDS, to be read as operand fragments there.
+// As fragments from memory an instruction takes 32 pieces of 32 bytes, which the L1 cache serves one by
+// one; whole rows go by lines.  Rows `first` .. first + 31 from the base that fetch is given, those past
+// `last` as that one (its data in their place).
+template <class Tile, int D>
+struct OwnRows {
+    static constexpr int NI = 32 * D * 2 / 1024;          // 1 KiB transfers
+    uint32_t off[NI];
+    __device__ __forceinline__ void init(int lane, int32_t first, int32_t last, uint32_t row_bytes) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            int r, c;
+            Tile::src_of(4 * i + (lane >> 4), lane & 15, r, c);
+            off[i] = (uint32_t)min(first + r, last) * row_bytes + (uint32_t)c * 16u;
+        }
+    }
+    __device__ __forceinline__ void fetch(const void* base_uniform, uint32_t lds_addr) const {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) dma16(base_uniform, off[i], lds_addr + i * 1024);
+    }
+};
+// the wavefront's own transfers have landed; its own LDS reads are done (a transfer may overwrite what
+// they read).  Nothing that reads LDS moves across.
+__device__ __forceinline__ void own_rows_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void own_rows_read() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 // how far (in powers of two) the running row maximum may drift from the shift that
 // the probabilities are taken relative to before the shift follows it; inside
 // this band probabilities stay within 2^+-kShiftSlack, harmless in fp32/bf16

@@ -840,7 +840,7 @@ dq_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
     const int h = h0 + wave / 4, w4 = wave & 3;
     const int li = lane & 31, hh = lane >> 5;
 
-    const int64_t row = (int64_t)qt * kDqBM + w4 * 32 + li;     // < n_pad
+    const int64_t row = (int64_t)qt * kDqBM + w4 * 32 + li;     // < n_pad, below 2^23
     const bool row_ok = row < n_loc;
     int64_t q_pos = 0;
     uint32_t q_ss = 0, q_causal = 0;
@@ -856,44 +856,92 @@ dq_kernel(const ushort_t* __restrict__ Q, const ushort_t* __restrict__ K,
         my_lse2 = l2 == -INFINITY ? INFINITY : l2;
         my_delta = ld_g[((int64_t)h * 2 + 1) * n_pad + row];
     }
-    bf16x8 qf[NDS], dof[NDS];
-#pragma unroll
-    for (int ds = 0; ds < NDS; ++ds) {
-        qf[ds] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-        dof[ds] = qf[ds];
-    }
-    if (row_ok) {
-        q_pos = row_pos(blocks, block, row);
-        const uint64_t w = bits[q_pos];
-        q_ss = word_ss(w);
-        q_causal = word_att(w);
-        const int64_t off = (row * Hq + h) * (int64_t)D + hh * 8;
-#pragma unroll
-        for (int ds = 0; ds < NDS; ++ds) {
-            qf[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(Q + off + ds * 16));
-            dof[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(dO + off + ds * 16));
-        }
-        if (own_delta) {
-            const float l2 = lse[(int64_t)h * n_loc + row] * kLog2e;
-            my_lse2 = l2 == -INFINITY ? INFINITY : l2;
-            bf16x8 of[NDS];
-#pragma unroll
-            for (int ds = 0; ds < NDS; ++ds)
-                of[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(O + off + ds * 16));
-#pragma unroll
-            for (int ds = 0; ds < NDS; ++ds)
-#pragma unroll
-                for (int u = 0; u < 8; ++u) my_delta += (float)of[ds][u] * (float)dof[ds][u];
-        }
-    }
-    if (own_delta) my_delta += __shfl_xor(my_delta, 32);
     // entries past the list's length, inside the q-tile's row of the list array, are read
     // but never used
     uint32_t list_chunk = chunk * csz + lane < plan.nk ? klist[lane] : 0u;
-
+    if (row_ok) {
+        q_pos = row_pos(blocks, block, row);
+        if (own_delta) {
+            const float l2 = lse[(int64_t)h * n_loc + row] * kLog2e;
+            my_lse2 = l2 == -INFINITY ? INFINITY : l2;
+        }
+    }
+    // (where lists are cut, workgroups without a slice leave before they fetch rows)
     const int nchunk = max(1, (kc_total + csz - 1) / csz);
-    if (chunk >= nchunk) return;          // workgroup-uniform
+    if (split.cmax > 1 && chunk >= nchunk) return;      // workgroup-uniform
     const int n_active = max(0, min(kc_total - chunk * csz, csz));
+
+    bf16x8 qf[NDS], dof[NDS];
+    auto row_word = [&]() {
+        if (!row_ok) return;
+        const uint64_t w = bits[q_pos];
+        q_ss = word_ss(w);
+        q_causal = word_att(w);
+    };
+    auto no_row = [&]() {
+        if (row_ok) return;
+        if (own_delta) my_delta = 0.f;
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) qf[ds] = dof[ds] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+    };
+    auto add_delta = [&](bf16x8 of, int ds) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) my_delta += (float)of[u] * (float)dof[ds][u];
+    };
+    if constexpr (D == 128) {
+        // Q and dO, then O in the place of Q, by way of a part of the rings for each wavefront, which
+        // are free until all of them have read theirs.  Fetched as fragments, 24 instructions of 32 pieces
+        // of 32 bytes each, they took 6 to 7 us of a workgroup's time (16 heads of 6272 tokens: of 47 us).
+        // Whole backward: 7168 tokens, 2048 rows, 16 / 8 heads 166 -> 160 us, 57984 tokens, 3648 rows, 16 / 2
+        // heads 476 -> 449, 21120 tokens, 8 / 4 heads 598 -> 582; 8192 tokens, 32 / 8 heads 1772 -> 1767.
+        // Rows of 64 are half the pieces and no faster so (32768 tokens, 16 heads, window 1991 / 2006 us).
+        const uint32_t own = lds_addr_of(sm.k[0]) + wave * (64 * RB);
+        static_assert(NW * 64 * RB <= 2 * NST * kStageBytes, "two tensors of every wavefront's rows fit the rings");
+        OwnRows<KT, D> rows;
+        const int64_t tile_off = ((int64_t)qt * kDqBM * Hq + h) * D;
+        rows.init(lane, w4 * 32, (int32_t)min(n_loc - 1 - (int64_t)qt * kDqBM, (int64_t)kDqBM - 1), (uint32_t)Hq * RB);
+        rows.fetch(Q + tile_off, own);
+        rows.fetch(dO + tile_off, own + 32 * RB);
+        row_word();
+        RowFragAddr<KT, D> fr;
+        fr.init(lane);
+        auto frag = [&](int part, int ds) __attribute__((always_inline)) -> bf16x8 {
+            return __builtin_bit_cast(bf16x8, *(lds_u4)(uintptr_t)(own + (uint32_t)(part * 32 * RB + fr.off[ds])));
+        };
+        own_rows_landed();
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) qf[ds] = frag(0, ds);
+        own_rows_read();
+        if (own_delta) rows.fetch(O + tile_off, own);
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) dof[ds] = frag(1, ds);
+        if (own_delta) {
+            own_rows_landed();
+#pragma unroll
+            for (int ds = 0; ds < NDS; ++ds) add_delta(frag(0, ds), ds);
+        }
+        no_row();
+        __syncthreads();
+    } else {
+        row_word();
+        if (row_ok) {
+            const int64_t off = (row * Hq + h) * (int64_t)D + hh * 8;
+#pragma unroll
+            for (int ds = 0; ds < NDS; ++ds) {
+                qf[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(Q + off + ds * 16));
+                dof[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(dO + off + ds * 16));
+            }
+            if (own_delta) {
+                bf16x8 of[NDS];
+#pragma unroll
+                for (int ds = 0; ds < NDS; ++ds) of[ds] = __builtin_bit_cast(bf16x8, *(const u32x4*)(O + off + ds * 16));
+#pragma unroll
+                for (int ds = 0; ds < NDS; ++ds) add_delta(of[ds], ds);
+            }
+        }
+        no_row();
+    }
+    if (own_delta) my_delta += __shfl_xor(my_delta, 32);
 
     floatx16 dq[NDB];
 #pragma unroll

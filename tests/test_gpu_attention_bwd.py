@@ -192,6 +192,15 @@ def test_short_lists_head_chunks(S, block, n, Hq, Hkv, D):
     run_case(lay, blocks, block, Hq, Hkv, D, seed=76, general=True)
 
 
+@pytest.mark.parametrize("n", [1, 2, 9, 11, 14])
+def test_last_row_tile_of_few_wavefronts(n):
+    """Row tiles that end within the first, second or fourth wavefront's rows (16, 32, 16, 48 and 96 of 128): the
+    others have none and fetch the last one in their place (general path)."""
+    lay = wl.layout_random(77, S=1280, n_samples=2, max_spans=4, deny_prob=0.3)
+    blocks = np.random.default_rng(n).choice(lay.S // 16, size=n, replace=False).tolist()
+    run_case(lay, blocks, 16, Hq=16, Hkv=16, D=128, seed=78 + n, general=True)
+
+
 @pytest.mark.parametrize("block", [48, 80, 240])
 def test_block_size_not_a_power_of_two(block):
     """Blocks of 48, 80 and 240 tokens (multiples of 16 that divide S = 1920): the
