@@ -198,7 +198,7 @@ def test_last_row_tile_of_few_wavefronts(n):
     others have none and fetch the last one in their place (general path)."""
     lay = wl.layout_random(77, S=1280, n_samples=2, max_spans=4, deny_prob=0.3)
     blocks = np.random.default_rng(n).choice(lay.S // 16, size=n, replace=False).tolist()
-    run_case(lay, blocks, 16, Hq=16, Hkv=16, D=128, seed=78 + n, general=True)
+    run_case(lay, blocks, 16, Hq=32, Hkv=32, D=128, seed=78 + n, general=True)
 
 
 @pytest.mark.parametrize("block", [48, 80, 240])

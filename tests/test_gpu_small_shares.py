@@ -44,10 +44,14 @@ CASES = {
     "dQ ahead of dK and dV": (wl.layout_random(207, S=1920, n_samples=1, deny_prob=0.3), [3, 38], 48, 4, 4, 64),
     "dQ behind dK and dV": (wl.layout_random(208, S=512, n_samples=2), spread(8, 7), 64, 6, 1, 128),
     "four wavefronts, first size": (wl.layout_random(206, S=2048, n_samples=1), spread(128, 65), 16, 8, 4, 128),
+    "six rounds of the backward": (wl.layout_random(209, S=1536, n_samples=2, deny_prob=0.3), spread(12, 6), 128, 32, 8, 128),
+    "28 units per wavefront": (wl.layout_random(212, S=1024, n_samples=1), spread(16, 16), 64, 7, 1, 64),
+    "most workgroups of 64 wide heads": (wl.layout_random(210, S=1024, n_samples=2, noncausal_prob=0.2), spread(16, 16), 64, 64, 16, 64),
+    "many keys of 128 wide heads": (wl.layout_random(211, S=2560, n_samples=3, max_spans=4), spread(20, 20), 128, 12, 4, 128),
 }
 
-# beyond the backward's 768 workgroups: the general path
-GENERAL_BWD = {"long list", "four wavefronts, first size"}
+# beyond the backward's 768 workgroups (1536 up to 1536 tokens): the general path
+GENERAL_BWD = {"long list", "four wavefronts, first size", "most workgroups of 64 wide heads", "many keys of 128 wide heads"}
 
 
 @pytest.mark.parametrize("name", CASES)
