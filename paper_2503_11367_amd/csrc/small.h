@@ -31,17 +31,17 @@ inline bool small_fwd_wanted(const AttnArgs& a) {
 inline bool small_fwd_four(const AttnArgs& a) { return small_fwd_wgs(a) > 256 || a.S <= 256; }
 
 // Backward (workgroups: 32 keys of a KV head for dK, as many for dV, 32 rows of a head for dQ): up to
-// six rounds of one workgroup per CU, three beyond 1536 tokens, where walks are longer and a causal mask has
-// the two paths level, and no dK / dV workgroup with more than 28 units per
+// six rounds of one workgroup per CU, beyond 1536 tokens, where walks are longer and a causal mask has
+// the two paths level sooner, three, or five at head_dim 64; and no dK / dV workgroup with more than 28 units per
 // wavefront.  Beyond, the general path, whose tiles are shared by 128 keys, is level or ahead.  Here / there, us,
 // up to 1536 tokens: 1280 tokens, 12 / 4 heads (800 workgroups) 49 / 90, 768 tokens, 32 / 8 heads (1152) 53 / 74, 1024
 // tokens, 32 / 8 heads (1536) 85 / 115; head_dim 64, 512 tokens, 64 / 16 heads (1536) 60 / 66; beyond, 1280 tokens,
 // 16 / 16 heads (1920) 90 / 84, 1024 tokens, 64 / 16 heads of 64 (3072) 137 / 117.  Longer: 3584 tokens, 2 / 1
-// heads of 64 (448, 28 units) 36 / 61; beyond, 2048 tokens, 512 rows, 32 / 8 heads (1536) 98 / 98, 4096 tokens, 6 / 2
+// heads of 64 (448, 28 units) 36 / 61, 3072 tokens, 1536 rows, 4 / 4 heads of 64 (960) 42 / 62; beyond, 2048 tokens, 512 rows, 32 / 8 heads (1536) 98 / 98, 4096 tokens, 6 / 2
 // heads (1280, 48 units) 202 / 198.
 inline bool small_bwd_wanted(const AttnArgs& a) {
     const int64_t rows = small_row_units(a), wgs = 2 * (a.S / 32) * a.Hkv + rows * a.Hq;
-    return small_fits(a) && wgs <= (a.S <= 1536 ? 1536 : 768) && rows * (a.Hq / a.Hkv) <= 224;
+    return small_fits(a) && wgs <= (a.S <= 1536 ? 1536 : a.D == 64 ? 1280 : 768) && rows * (a.Hq / a.Hkv) <= 224;
 }
 
 // `err`: the call's status word and its spare words (kFlagInts)

@@ -47,10 +47,11 @@ CASES = {
     "six rounds of the backward": (wl.layout_random(209, S=1536, n_samples=2, deny_prob=0.3), spread(12, 6), 128, 32, 8, 128),
     "28 units per wavefront": (wl.layout_random(212, S=1024, n_samples=1), spread(16, 16), 64, 7, 1, 64),
     "most workgroups of 64 wide heads": (wl.layout_random(210, S=1024, n_samples=2, noncausal_prob=0.2), spread(16, 16), 64, 64, 16, 64),
+    "five rounds of 64 wide heads": (wl.layout_random(213, S=2560, n_samples=2, max_spans=4), spread(20, 20), 128, 5, 5, 64),
     "many keys of 128 wide heads": (wl.layout_random(211, S=2560, n_samples=3, max_spans=4), spread(20, 20), 128, 12, 4, 128),
 }
 
-# beyond the backward's 768 workgroups (1536 up to 1536 tokens): the general path
+# beyond the backward's 768 workgroups (1280 of 64 wide heads, 1536 up to 1536 tokens): the general path
 GENERAL_BWD = {"long list", "four wavefronts, first size", "most workgroups of 64 wide heads", "many keys of 128 wide heads"}
 
 
