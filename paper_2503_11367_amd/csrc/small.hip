@@ -18,8 +18,8 @@
 //
 // Bound by latency: block list, mask words, first tiles, one after the other, then a unit or two
 // per wavefront, about 1 us each; on larger shares by the transfers, for 32 rows of one head use a
-// unit where the general path's 128 or 256 do (waiting: 57 % of the wavefronts' cycles at 512 tokens, 68 % in the
-// backward; 54 and 52 % at 1920, 18 and 22 % more for a turn to issue; no LDS bank conflicts).  Measured,
+// unit where the general path's 128 or 256 do (waiting: 53 % of the wavefronts' cycles at 512 tokens, 64 % in the
+// backward; 53 and 51 % at 1920, 17 % more for a turn to issue; no LDS bank conflicts).  Measured,
 // whole calls back to back: 512 tokens, one head, 128 rows 16.9 -> 7.0 us forward, 27.9 -> 7.1 us backward; 1920
 // tokens, 960 rows, 6 / 2 heads (head_dim 128) 32 -> 14 and 74 -> 27 us; 4096 tokens, 1024 rows, 8 / 2 heads
 // 44 -> 24 and 93 -> 61 us (128), 27 -> 14 and 69 -> 47 us (64).  In a sweep of 2000 shapes the calls that come
